@@ -72,10 +72,10 @@ typedef struct {
                              of its lanes are done, 1..64 (default 32) */
     int32_t chunk;        /* segments a wave claims per global atomic, 64..2^20
                              (default: about eight chunks per resident wave, 64..4096) */
-    int32_t stack_depth;  /* traversal-stack entries per lane of the main pass, kept in LDS
-                             (default 20 on the four-way walk, 17 for its boolean and counting
-                             walks, 32 on the binary walk); a walk that needs more is finished
-                             by the deep pass, whose stack continues in device memory.  A smaller
+    int32_t stack_depth;  /* traversal-stack entries per lane kept in LDS (default 18 on the four-way
+                             walk, 17 for its boolean and counting walks, 32 on the binary walk); a
+                             walk that needs more continues in device memory (four-way: its older
+                             entries move there; binary: the deep pass walks it again).  A smaller
                              value raises occupancy. 1..255 */
     int32_t branching;    /* 4 (default): traverse the four-way view of the binary tree of
                              Section 3.1 (every node with its grandchildren as children, child
@@ -178,8 +178,8 @@ rsi_status rsi_query(rsi_handle h, const float *S, const float *E, int64_t n_r,
  *   mode  nonzero mask of RSI_BOOL, RSI_FIRST_HIT, RSI_COUNT (RSI_ALL_HITS
  *         needs memory that grows with the crossings and is rejected)
  *   S, E, n_r, out as for rsi_query (only the arrays of `mode` are used)
- * The array holds the deep pass's stack (its size depends on block_size and
- * the stack options; about 16 MB at the defaults on 256 CUs) and a queue
+ * The array holds the stacks' device-memory part (at most 16 MB, by the
+ * bound on the tree height) and a queue
  * of one entry per segment; a query with more segments than the queue
  * holds (about 4.3 million at the defaults) runs as consecutive parts of
  * that many segments each, with the same kernels and results as rsi_query.
@@ -189,9 +189,7 @@ rsi_status rsi_query(rsi_handle h, const float *S, const float *E, int64_t n_r,
  * one GPU (other streams, other handles, other threads) race and must be
  * ordered by the caller.  Its contents need no clearing between calls.
  * Errors: as rsi_query, plus RSI_E_INVALID when the current device is not
- * the handle's, for a batch handle, or when the options' deep-pass stack
- * leaves no room in the array (a block_size of 256 with the deepest stack
- * bound comes close; use a smaller block_size or rsi_query). */
+ * the handle's, or for a batch handle. */
 rsi_status rsi_query_noalloc(rsi_handle h, const float *S, const float *E, int64_t n_r, uint32_t mode,
                              const rsi_outputs *out, void *stream);
 
@@ -257,7 +255,7 @@ rsi_status rsi_spill_read(rsi_handle h, int32_t *seg, int64_t *offset, int32_t *
  *   stack_dropped       the deep pass dropped a stack entry (damaged tree)
  *   overflow_full       the last all-hits query's pool or arena was too small
  *   deep_segments       segments of the last query whose stack outgrew its
- *                       LDS part and were walked by the deep pass
+ *                       LDS part and continued in device memory
  *   overflow_segments   all hits: segments with more crossings than slots
  *   overflow_crossings  all hits: pool entries they needed (their crossings)
  *   arena_records       all hits: crossings past the slots

@@ -52,7 +52,8 @@ void free_handle_memory(rsi_bvh *h)
                     h->retry_q, h->retry_stack, h->arena, h->T, h->V_all, h->src_V, h->src_T, h->cent, h->keys,
                     h->order, h->nodes, h->tris, h->arrive, h->heights, h->climb, h->split_prefix, h->scalars,
                     h->counters, h->ovf_seg, h->ovf_cnt, h->ovf_list, h->ovf_off, h->ovf_part, h->pool_ids, h->pool_ts, h->tri_off,
-                    h->vert_off, h->mesh_bounds, h->mesh_height, h->mesh_root, h->mesh_entry};
+                    h->vert_off, h->mesh_bounds, h->mesh_height, h->mesh_root, h->mesh_entry,
+                    h->mesh_scale};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     rsi::BatchTables *tabs[] = {&h->bt, &h->bt_graph};
@@ -168,7 +169,7 @@ rsi_status alloc_handle(int32_t M, const int64_t *n_v, const int64_t *n_t, const
     if (e == hipSuccess) e = dalloc(&h->rank, n);
     if (e == hipSuccess) e = dalloc(&h->nodes, n);
     if (e == hipSuccess && h->width == 4) e = dalloc(&h->nodes4, n);
-    if (e == hipSuccess) e = dalloc(&h->tris, n);
+    if (e == hipSuccess) e = dalloc(&h->tris, n + 1);
     if (e == hipSuccess) e = dalloc(&h->arrive, n);
     if (e == hipSuccess) e = dalloc(&h->heights, 2 * n);
     if (e == hipSuccess) e = dalloc(&h->climb, 11 * n);
@@ -181,6 +182,7 @@ rsi_status alloc_handle(int32_t M, const int64_t *n_v, const int64_t *n_t, const
     if (e == hipSuccess) e = dalloc(&h->mesh_height, M);
     if (e == hipSuccess) e = dalloc(&h->mesh_root, M);
     if (e == hipSuccess) e = dalloc(&h->mesh_entry, M);
+    if (e == hipSuccess) e = dalloc(&h->mesh_scale, M);
     if (e == hipSuccess && batch) e = alloc_tables(h->bt, M);
     if (e == hipSuccess && batch) e = alloc_tables(h->bt_graph, M);
     if (e == hipSuccess)
@@ -605,7 +607,7 @@ rsi_status rsi_query_stats(rsi_handle h, rsi_stats *out)
     out->build_inconsistent = (c[rsi::kBadIndex] & 2) ? 1 : 0;
     out->walk_cut = c[rsi::kWalkCut] != 0;
     out->stack_dropped = c[rsi::kStackDropped] != 0;
-    out->deep_segments = c[rsi::kRetryN];
+    out->deep_segments = (int64_t)c[rsi::kRetryN] + c[rsi::kSpilled];
     out->overflow_segments = c[rsi::kOvfUsed];
     out->overflow_crossings = u64(rsi::kOvfTotalLo, rsi::kOvfTotalHi);
     out->arena_records = c[rsi::kArenaUsed];

@@ -65,6 +65,7 @@ struct BuildArgs {
     int32_t *bounds;       // [6M] ordered-int centroid bounds per mesh
     int32_t *mesh_height;  // [M]
     int32_t *mesh_root;    // [M]
+    float *mesh_scale;     // [M]
     int32_t *scalars;
     int32_t leaf_size;
 };
@@ -111,6 +112,11 @@ __global__ void k_init(BuildArgs a)
         }
         a.mesh_height[i] = 0;
         a.mesh_root[i] = 0;
+        a.mesh_scale[i] = 0.0f;
+    }
+    if (i == 0) {  // the record that unused four-way slots name: no segment crosses it
+        const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        a.tris[a.n_t].a = a.tris[a.n_t].b = a.tris[a.n_t].c = z;
     }
     if (i == 0) a.scalars[kBadIndex] = 0;
     if (i < a.n_t) a.arrive[i] = 0;
@@ -275,6 +281,10 @@ __device__ inline void write_entry(const BuildArgs &a, int32_t m, int32_t lo, in
     e->aux[1] = hi;
     a.mesh_height[m] = c.h;
     a.mesh_root[m] = c.ref;
+    float s = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s = fmaxf(s, fabsf(c.box[k]));
+    a.mesh_scale[m] = s;
 }
 
 constexpr int kClimbWords = 11;
@@ -505,14 +515,14 @@ __global__ __launch_bounds__(256) void k_lbvh_global(BuildArgs a)
 // Every record is rewritten, including ones no traversal reaches (inside
 // collapsed leaves), so references are range-checked before use.
 //
-// Grid step per axis: the smallest power of two 2^e with 255 * 2^e >= the
-// box extent (with a 2^-40 relative margin over the FP64 extent); planes are
-// placed in FP64, where the offset from the corner carries at most 2^-45
-// steps of rounding error, and rounded outward with a 2^-40-step margin, so
-// corner + q * step bounds the exact plane on the safe side.
+// Grid step per axis: the smallest power of two 2^e with 254.5 * 2^e >= the
+// box extent; planes are placed in FP64, where the offset from the corner
+// carries at most 2^-45 steps of rounding error, and rounded outward with a
+// margin of kQuantMargin steps (the box test relies on it), so corner +
+// q * step bounds the exact plane on the safe side.
 __device__ inline int quant_exponent(double ext)
 {
-    const double x = ext * (1.0 + 0x1p-40) / 255.0;
+    const double x = ext * (1.0 + 0x1p-40) / 254.5;
     if (!(x > 0x1p-126)) return -126;
     int k = 0;
     const double m = frexp(x, &k);  // x = m 2^k, m in [0.5, 1)
@@ -523,13 +533,13 @@ __device__ inline int quant_exponent(double ext)
 // `inv_step` is 1 / step, a power of two, so the scaling is exact
 __device__ inline uint32_t quant_down(double off, double inv_step)
 {
-    const double q = floor(off * inv_step - 0x1p-40);
+    const double q = floor(off * inv_step - kQuantMargin);
     return (uint32_t)fmin(fmax(q, 0.0), 255.0);
 }
 
 __device__ inline uint32_t quant_up(double off, double inv_step)
 {
-    const double q = ceil(off * inv_step + 0x1p-40);
+    const double q = ceil(off * inv_step + kQuantMargin);
     return (uint32_t)fmin(fmax(q, 0.0), 255.0);
 }
 
@@ -583,7 +593,7 @@ __global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, i
     for (int a = 0; a < 3; ++a) {
         uint32_t ql = 0, qh = 0;
         for (int s = 0; s < 4; ++s) {
-            uint32_t l = 255u, h = 0u;  // unused slot: never read (kEmptySlot)
+            uint32_t l = 255u, h = 0u;  // unused slot: an empty box
             if (s < k) {
                 l = quant_down((double)box[s][a] - (double)lo[a], inv_step[a]);
                 h = quant_up((double)box[s][3 + a] - (double)lo[a], inv_step[a]);
@@ -594,7 +604,7 @@ __global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, i
         w.lo[a] = ql;
         w.hi[a] = qh;
     }
-    for (int s = 0; s < 4; ++s) w.ref[s] = s < k ? ref[s] : kEmptySlot;
+    for (int s = 0; s < 4; ++s) w.ref[s] = s < k ? ref[s] : leaf_ref((int32_t)n, 1);
     out[j] = w;
 }
 
@@ -620,6 +630,7 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     a.bounds = h->mesh_bounds;
     a.mesh_height = h->mesh_height;
     a.mesh_root = h->mesh_root;
+    a.mesh_scale = h->mesh_scale;
     a.scalars = h->scalars;
     a.leaf_size = h->leaf_size;
     return a;
@@ -666,7 +677,8 @@ hipError_t launch_gather(rsi_bvh *h, hipStream_t s)
 
 hipError_t launch_widen(rsi_bvh *h, hipStream_t s)
 {
-    if (h->width != 4 || h->n_t == 0 || !h->nodes4) {
+    // (the four-way walk addresses records by 32-bit byte offsets: 2^26 of them)
+    if (h->width != 4 || h->n_t == 0 || h->n_t > (int64_t(1) << 26) || !h->nodes4) {
         h->width_built = 2;
         return hipSuccess;
     }

@@ -12,26 +12,26 @@
 // avoids.
 //
 // A lane walks the tree from the entry node with a stack laid out
-// [depth][lane] in LDS so a wave's pushes and pops hit distinct banks.  The
-// main pass keeps the whole stack in LDS (20 entries per lane on the
-// four-way walk, 17 when it holds the top copy below; 32 on the binary
-// walk); a walk that would push past it stops, queues its segment, and a
-// deep pass (a small grid whose stacks continue in device memory up to a
-// bound on the tree height) walks those segments again from the root.  No
-// tree height is needed on the host, so builds, rebuilds and queries are
-// enqueued without waiting for the device.
+// [depth][lane] in LDS so a wave's pushes and pops hit distinct banks (18
+// entries per lane on the four-way walk, 17 when it holds the top copy
+// below; 32 on the binary walk).  On the four-way walk the LDS part is a
+// window on the stack's top whose older entries move to device memory when
+// it is full.  On the binary walk a push past it stops the walk and queues
+// its segment, and a deep pass (a small grid whose stacks continue in device
+// memory up to a bound on the tree height) walks those segments again from
+// the root.  No tree height is needed on the host, so builds, rebuilds and
+// queries are enqueued without waiting for the device.
 // Each node step loads one 64-byte record; the boolean and counting walks of
 // a single mesh read the records of the top three four-way levels from a
 // per-workgroup copy in LDS instead.
 // The default four-way walk (Node4) tests the segment against the four
-// quantised boxes of the node's grandchildren, keeps the touched leaf
-// children as pending, descends into the nearest touched internal child and
-// pushes the others; the binary walk (Node, branching 2) tests the two exact
-// child boxes, keeps walking past one pending leaf and descends into the
-// nearer touched child.  Pending leaves are tested once few lanes can still
-// take a node step, so the triangle test runs with most lanes active.  The
-// paper's bounded candidate list with resume (Section 3.2) is therefore not
-// needed: candidates are tested soon after they are found.
+// quantised boxes of the node's grandchildren and pushes the touched
+// children, nodes and leaves alike; the binary walk (Node, branching 2)
+// tests the two exact child boxes, keeps walking past one pending leaf and
+// descends into the nearer touched child.  Leaves are tested once few lanes
+// can still take a node step, so the triangle test runs with most lanes
+// active.  The paper's bounded candidate list with resume (Section 3.2) is
+// therefore not needed: candidates are tested soon after they are found.
 //
 // Modes
 //   bool only   stop at the first crossing (any-hit, Section 3.2)
@@ -93,10 +93,12 @@ struct QArgs {
     unsigned long long *ovf_part;  // all hits: per-part count sums of the pool-offset scan
     int32_t *scalars;
     Counters *counters;
-    int32_t depth;       // stack entries per lane: the LDS part (main pass) or the height bound (deep pass)
-    int32_t lds_depth;   // of which the first lds_depth live in LDS, the rest in gstack (deep pass)
-    int32_t *gstack;     // deep pass: [(depth - lds_depth) x threads of the grid], laid out [entry][thread]
+    int32_t depth;       // stack entries per lane: the bound on any tree (binary main pass: the LDS part)
+    int32_t lds_depth;   // entries per lane kept in LDS
+    int32_t *gstack;     // stack entries past the LDS part, laid out [entry][column]: four-way walk n_cols
+                         // columns of `depth` entries; binary deep pass a column per thread
     int64_t gstack_cap;  // entries in gstack
+    int32_t n_cols;
     int32_t *retry_q;    // work items whose stack outgrew the main pass's LDS part
     int64_t retry_cap;
     int32_t max_steps;   // node records: a walk of a valid tree visits each at most once
@@ -106,6 +108,7 @@ struct QArgs {
     // batched queries: work item k belongs to mesh m with bt.seg_off[m] <= k < bt.seg_off[m+1]
     int32_t M;
     const int32_t *mesh_entry;
+    const float *mesh_scale;  // per mesh: the largest |coordinate| of its box
     BatchTables bt;
 };
 
@@ -156,7 +159,7 @@ constexpr int32_t kTopRef = 0x40000000;
 // LDS entries the copy takes from the stack cost more than it saves.
 constexpr bool top_copy(uint32_t mode) { return !(mode & (M_ALL | M_FIRST)); }
 
-__device__ inline bool inner_ref(int32_t r) { return r >= 0 && r != kEmptySlot; }
+__device__ inline bool inner_ref(int32_t r) { return r >= 0; }
 __device__ inline int32_t ref_at(const int4 &c, int k) { return k == 0 ? c.x : (k == 1 ? c.y : (k == 2 ? c.z : c.w)); }
 
 // Lane l < kTopNodes of the block's first wave fills slot l of the copy:
@@ -229,8 +232,7 @@ struct Lane {
     int32_t e;         // all hits: overflow-table entry, -1 while count <= K
     int32_t item;      // work item (a segment, or a (mesh, segment) pair of a batch)
     int32_t seg_i;     // segment index (within its mesh for batched queries; below 2^30)
-    const float *sp;   // this segment's start and end (3 floats each)
-    const float *ep;
+    float tiny;        // four-way walk: smallest |direction component| whose reciprocal is used as it is
     int32_t mesh;      // batched queries: the segment's mesh
     int32_t hp0, hp1, hp2, hp3;  // all hits, capacity <= 4: the hit positions found so far
     bool found;
@@ -366,157 +368,122 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Leaf phase of the four-way walk.  A lane holds up to four pending leaves
-// (one per child slot of its last node); tested by their owners, a phase
-// would take as many rounds as the busiest lane has leaves, with few lanes
-// busy in each.  Instead the wave's pending (lane, leaf) pairs are gathered,
-// slot by slot, into a queue of 64 in LDS and each lane tests one pair per
-// round against the owner's segment (read from the owner's registers); the
-// owners then take the outcomes back.  Pairs past the 64th wait for the next
-// round.  The outcome of a leaf is the set of its triangles crossed (a bit
-// mask) and, for the first hit, its best crossing in (t, id) order: the
-// owner's results are the same as from testing its leaves itself, in any
-// order.  The plain boolean query needs one bit per leaf and takes it from
-// a ballot; the other modes get the outcome back through the queue entry.
+// Leaf phase of the four-way walk: every lane whose stack has a leaf on top
+// (cur < 0).  Such a lane often has further leaves right below; tested by
+// their owners, a phase would take as many rounds as the busiest lane has
+// leaves, with few lanes busy in each.  Instead the wave's (lane, leaf)
+// pairs are drained from the stacks, up to four per lane, into a queue of 64
+// in LDS and each lane tests one pair against the owner's segment (read from
+// the owner's registers); the owners then take the outcomes back.  The
+// outcome of a leaf is the set of its triangles crossed (a bit mask) and,
+// for the first hit, its best crossing in (t, id) order: the owner's results
+// are the same as from testing its leaves itself, in any order.  The plain
+// boolean query needs one bit per lane (a flag in the queue entry of the
+// owner's number); the other modes get the outcome back through the queue
+// entry of the pair.
 template <uint32_t MODE>
 using LeafEnt = typename std::conditional<MODE == M_BOOL, int2, int4>::type;
 
-template <uint32_t MODE, bool BATCH, bool COUNT>
-__device__ inline void leaf_phase4(const QArgs &a, Lane &L, int32_t &leaf0, int32_t &leaf1, int32_t &leaf2,
-                                   int32_t &leaf3, int32_t &node, uint32_t &tests, volatile int32_t *wst,
+template <uint32_t MODE, bool COUNT, typename Pop>
+__device__ inline void leaf_phase4(const QArgs &a, Lane &L, int32_t &cur, Pop pop, uint32_t &tests,
                                    LeafEnt<MODE> *q, uint32_t &w_rounds, unsigned long long &w_lanes)
 {
     const int32_t lane = (int32_t)__lane_id();
-    for (;;) {
-        const uint64_t b0 = ballot(leaf0 != 0), b1 = ballot(leaf1 != 0);
-        const uint64_t b2 = ballot(leaf2 != 0), b3 = ballot(leaf3 != 0);
-        const int32_t c0 = (int32_t)__popcll(b0), c1 = (int32_t)__popcll(b1);
-        const int32_t c2 = (int32_t)__popcll(b2), c3 = (int32_t)__popcll(b3);
-        const int32_t total = c0 + c1 + c2 + c3;
-        if (total == 0) break;
-        const int32_t p0 = (int32_t)lanes_below(b0);
-        const int32_t p1 = c0 + (int32_t)lanes_below(b1);
-        const int32_t p2 = c0 + c1 + (int32_t)lanes_below(b2);
-        const int32_t p3 = c0 + c1 + c2 + (int32_t)lanes_below(b3);
-        const bool in0 = leaf0 != 0 && p0 < 64, in1 = leaf1 != 0 && p1 < 64;
-        const bool in2 = leaf2 != 0 && p2 < 64, in3 = leaf3 != 0 && p3 < 64;
-        auto put = [&](bool in, int32_t p, int32_t ref) {
-            if (!in) return;
+    uint64_t m = ballot(cur < 0);
+    int32_t total = 0;
+    uint32_t mine = 0;    // this lane's queue places, one per byte, the last in the low byte
+    int32_t n_mine = 0;
+    for (int r = 0; r < 4 && m != 0 && total < 64; ++r) {
+        const int32_t p = total + (int32_t)lanes_below(m);
+        if (cur < 0 && p < 64) {
             LeafEnt<MODE> e;
-            e.x = ref;
+            e.x = cur;
             e.y = lane;
             q[p] = e;
-        };
-        put(in0, p0, leaf0);
-        put(in1, p1, leaf1);
-        put(in2, p2, leaf2);
-        put(in3, p3, leaf3);
-        wave_lds_sync();
-        const int32_t n = total < 64 ? total : 64;
-        const bool mine = lane < n;
-        int2 ent = make_int2(0, lane);
-        if (mine) {
-            const LeafEnt<MODE> e = q[lane];
-            ent = make_int2(e.x, e.y);
+            mine = (mine << 8) | (uint32_t)p;
+            ++n_mine;
+            cur = pop();
         }
-        wave_lds_sync();
-        if (COUNT) {
-            ++w_rounds;
-            w_lanes += (unsigned long long)n;
-        }
-        // the owner's segment and t limit
-        const int32_t own = ent.y;
-        Seg s;
-        s.ox = __shfl(L.seg.ox, own, 64);
-        s.oy = __shfl(L.seg.oy, own, 64);
-        s.oz = __shfl(L.seg.oz, own, 64);
-        s.dx = __shfl(L.seg.dx, own, 64);
-        s.dy = __shfl(L.seg.dy, own, 64);
-        s.dz = __shfl(L.seg.dz, own, 64);
-        s.ix = s.iy = s.iz = 0.0f;
-        float lim = (MODE & M_FULL) || MODE == M_BOOL ? 1.0f : __shfl(L.tlim, own, 64);
-        uint32_t mask = 0;
-        float bt = INFINITY;
-        int32_t bid = 0x7FFFFFFF, bpos = -1;
-        if (mine) {
-            const int32_t first = leaf_first(ent.x);
-            const int32_t cnt = leaf_count(ent.x);
-            for (int32_t k = 0; k < cnt; ++k) {
-                const int32_t pos = first + k;
-                float v[9];
-                int32_t id;
-                tri_load(a.tris, pos, v, id);
-                if (COUNT) ++tests;
-                const MTHit h = mt_test(s, v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], lim);
-                if (!h.hit) continue;
-                mask |= 1u << k;
-                if (MODE == M_BOOL) break;
-                if (MODE & M_FIRST) {
-                    const float t = h.tn / h.det;
-                    if (t < bt || (t == bt && id < bid)) {
-                        bt = t;
-                        bid = id;
-                        bpos = pos;
-                        if (!(MODE & M_FULL)) lim = fminf(1.0f, t * (1.0f + 0x1p-20f));
-                    }
+        total += (int32_t)__popcll(m);
+        m = ballot(cur < 0);
+    }
+    wave_lds_sync();
+    const int32_t n = total < 64 ? total : 64;
+    const bool test = lane < n;
+    int2 ent = make_int2(0, lane);
+    if (test) {
+        const LeafEnt<MODE> e = q[lane];
+        ent = make_int2(e.x, e.y);
+    }
+    wave_lds_sync();
+    if constexpr (MODE == M_BOOL) q[lane].x = 0;  // the owners' flags
+    if (COUNT) {
+        ++w_rounds;
+        w_lanes += (unsigned long long)n;
+    }
+    // the owner's segment and t limit
+    const int32_t own = ent.y;
+    Seg s;
+    s.ox = __shfl(L.seg.ox, own, 64);
+    s.oy = __shfl(L.seg.oy, own, 64);
+    s.oz = __shfl(L.seg.oz, own, 64);
+    s.dx = __shfl(L.seg.dx, own, 64);
+    s.dy = __shfl(L.seg.dy, own, 64);
+    s.dz = __shfl(L.seg.dz, own, 64);
+    s.ix = s.iy = s.iz = 0.0f;
+    float lim = (MODE & M_FULL) || MODE == M_BOOL ? 1.0f : __shfl(L.tlim, own, 64);
+    uint32_t mask = 0;
+    float bt = INFINITY;
+    int32_t bid = 0x7FFFFFFF, bpos = -1;
+    if (test) {
+        const int32_t first = leaf_first(ent.x);
+        const int32_t cnt = leaf_count(ent.x);
+        for (int32_t k = 0; k < cnt; ++k) {
+            const int32_t pos = first + k;
+            float v[9];
+            int32_t id;
+            tri_load(a.tris, pos, v, id);
+            if (COUNT) ++tests;
+            const MTHit h = mt_test(s, v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], lim);
+            if (!h.hit) continue;
+            mask |= 1u << k;
+            if (MODE == M_BOOL) break;
+            if (MODE & M_FIRST) {
+                const float t = h.tn / h.det;
+                if (t < bt || (t == bt && id < bid)) {
+                    bt = t;
+                    bid = id;
+                    bpos = pos;
+                    if (!(MODE & M_FULL)) lim = fminf(1.0f, t * (1.0f + 0x1p-20f));
                 }
             }
         }
-        // outcomes back to the owners
-        if constexpr (MODE == M_BOOL) {
-            const uint64_t H = ballot(mask != 0);
-            const bool hit = (in0 && ((H >> p0) & 1)) || (in1 && ((H >> p1) & 1)) || (in2 && ((H >> p2) & 1)) ||
-                             (in3 && ((H >> p3) & 1));
-            if (hit) {
-                L.found = true;
-                leaf0 = leaf1 = leaf2 = leaf3 = 0;
-                node = -1;
-            }
-        } else {
-            // each lane's outcome replaces the entry it tested
-            q[lane] = make_int4((int32_t)mask, __float_as_int(bt), bid, bpos);
-            wave_lds_sync();
-            // the owner's outcomes; all hits: then its crossings, one per
-            // iteration (the recording code appears once)
-            uint32_t m0 = 0, m1 = 0, m2 = 0, m3 = 0;
-            auto back = [&](bool in, int32_t p, uint32_t &m) {
-                if (!in) return;
-                const int4 r = q[p];
-                m = (uint32_t)r.x;
-                if (m == 0) return;
-                L.found = true;
-                if (MODE & M_FIRST) take_first<MODE>(L, __int_as_float(r.y), r.z, r.w);
-                if ((MODE & M_COUNT) && !(MODE & M_ALL)) L.count += (int32_t)__popc(m);
-            };
-            back(in0, p0, m0);
-            back(in1, p1, m1);
-            back(in2, p2, m2);
-            back(in3, p3, m3);
-            wave_lds_sync();
-            if constexpr ((MODE & M_ALL) != 0) {
-                while ((m0 | m1 | m2 | m3) != 0) {
-                    int32_t pos;
-                    if (m0) {
-                        pos = leaf_first(leaf0) + (int32_t)__builtin_ctz(m0);
-                        m0 &= m0 - 1;
-                    } else if (m1) {
-                        pos = leaf_first(leaf1) + (int32_t)__builtin_ctz(m1);
-                        m1 &= m1 - 1;
-                    } else if (m2) {
-                        pos = leaf_first(leaf2) + (int32_t)__builtin_ctz(m2);
-                        m2 &= m2 - 1;
-                    } else {
-                        pos = leaf_first(leaf3) + (int32_t)__builtin_ctz(m3);
-                        m3 &= m3 - 1;
-                    }
-                    take_crossing<MODE, BATCH>(a, L, pos, wst);
+    }
+    // outcomes back to the owners
+    if constexpr (MODE == M_BOOL) {
+        if (mask) q[own].x = 1;
+        wave_lds_sync();
+        if (q[lane].x) {
+            L.found = true;
+            cur = kDone;
+        }
+        wave_lds_sync();
+    } else {
+        // each lane's outcome replaces the entry it tested
+        q[lane] = make_int4((int32_t)mask, __float_as_int(bt), bid, bpos);
+        wave_lds_sync();
+        for (int r = 0; r < 4; ++r) {
+            if (ballot(n_mine > r) == 0) break;
+            if (n_mine > r) {
+                const int4 e = q[(mine >> (8 * r)) & 63u];
+                if (e.x) {
+                    L.found = true;
+                    if constexpr ((MODE & M_FIRST) != 0) take_first<MODE>(L, __int_as_float(e.y), e.z, e.w);
+                    if constexpr ((MODE & M_COUNT) != 0) L.count += (int32_t)__popc((uint32_t)e.x);
                 }
             }
         }
-        if (in0) leaf0 = 0;
-        if (in1) leaf1 = 0;
-        if (in2) leaf2 = 0;
-        if (in3) leaf3 = 0;
+        wave_lds_sync();
     }
 }
 
@@ -595,64 +562,502 @@ __device__ inline void finish(const QArgs &a, const Lane &L)
     }
 }
 
-// RETRY: the deep pass.  Work items come from the retry queue (its length
-// is read on the device), and the stack continues past its LDS part into
-// device memory up to a bound on the tree height, so it never outgrows it
-// in a valid tree.  WIDE: walk the four-way view (Node4 records) instead of
-// the binary nodes; leaves and triangles are the same, so are the results.
-// The all-hits variants are held to six waves per SIMD (80 VGPRs): without
-// the bound the compiler gives them 94 and five waves.
-template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH, bool WIDE>
+// Work claiming, shared by both walks.  The main pass's items are cut into
+// eight contiguous ranges, one per XCD, each with its own counter on its own
+// 128-byte line; a wave takes chunks from its XCD's range first, then from
+// the others in turn.  A single counter line shared by all XCDs serialises
+// the claims in the memory fabric (measured: 0.83 against 0.69 ms for the
+// 10M-segment boolean query); with the ranges each XCD also walks its own
+// part of spatially ordered items.  The deep pass has one range.  Every
+// field is wave-uniform; items number below 2^30 (checked at the boundary),
+// so the arithmetic is 32-bit.
+struct Claim {
+    int32_t n_items;
+    int32_t range, ranges_left;
+    int32_t next, end;  // the wave's claimed, not yet handed out items
+    bool exhausted;     // every range's counter has passed its last item
+};
+
+template <bool RETRY>
+__device__ inline Claim claim_init(const QArgs &a)
+{
+    Claim c;
+    c.n_items = (int32_t)a.n_items;
+    if (RETRY) {
+        const int32_t q = a.scalars[kRetryN];
+        c.n_items = q < (int32_t)a.retry_cap ? q : (int32_t)a.retry_cap;
+    }
+    c.range = RETRY ? 0 : xcd_id();
+    c.ranges_left = RETRY ? 1 : kXcds;
+    c.next = c.end = 0;
+    c.exhausted = false;
+    return c;
+}
+
+// Hand each lane with `idle` the next unclaimed item (-1: none); a new chunk
+// is claimed from a range counter with one atomic.
+template <bool RETRY>
+__device__ inline int32_t claim_items(const QArgs &a, Claim &c, bool idle_lane)
+{
+    constexpr int kRanges = RETRY ? 1 : kXcds;
+    int32_t *const work = &a.scalars[RETRY ? kWorkRetry : kWorkXcd];
+    const uint64_t idle = ballot(idle_lane);
+    const int32_t n_idle = (int32_t)__popcll(idle);
+    const int32_t rank = (int32_t)lanes_below(idle);
+    int32_t k = -1;
+    const int32_t avail = c.end - c.next;
+    const int32_t used = avail < n_idle ? avail : n_idle;
+    if (rank < used) k = c.next + rank;
+    c.next += used;
+    if (used < n_idle && !c.exhausted) {
+        const int leader = __builtin_ctzll(idle);
+        for (;;) {
+            const int32_t lo = (int32_t)((int64_t)c.n_items * c.range / kRanges);
+            const int32_t hi = (int32_t)((int64_t)c.n_items * (c.range + 1) / kRanges);
+            int32_t base = 0;
+            if ((int)__lane_id() == leader) base = atomicAdd(work + kWorkStride * c.range, a.chunk);
+            base = __builtin_amdgcn_readfirstlane(__shfl(base, leader, 64));
+            if (base < hi - lo) {
+                c.next = lo + base;
+                c.end = hi - c.next > a.chunk ? c.next + a.chunk : hi;
+                const int32_t room = c.end - c.next;
+                const int32_t more = n_idle - used < room ? n_idle - used : room;
+                if (rank >= used && rank - used < more) k = c.next + (rank - used);
+                c.next += more;
+                break;
+            }
+            // this range is used up: the next one
+            if (--c.ranges_left == 0) {
+                c.exhausted = true;
+                break;
+            }
+            c.range = c.range + 1 == kRanges ? 0 : c.range + 1;
+        }
+    }
+    return idle_lane ? k : -1;
+}
+
+// Start of a segment: its ends, and the lane's results cleared.  Returns the
+// entry node of its mesh (< 0: an empty mesh).  The reciprocals of the
+// direction are the caller's.
+template <bool RETRY, bool BATCH>
+__device__ inline int32_t start_item(const QArgs &a, Lane &L, int32_t k)
+{
+    const int32_t it = RETRY ? a.retry_q[k] : k;
+    int32_t i = it;
+    int32_t entry = a.entry;
+    const float *sp, *ep;
+    if (BATCH) {
+        const int32_t m = mesh_of(a.bt.seg_off, a.M, it);
+        i = (int32_t)(it - a.bt.seg_off[m]);
+        L.mesh = m;
+        sp = a.bt.S[m] + 3 * (int64_t)i;
+        ep = a.bt.E[m] + 3 * (int64_t)i;
+        entry = a.mesh_entry[m];
+    } else {
+        L.mesh = 0;
+        sp = a.S + 3 * (int64_t)i;
+        ep = a.E + 3 * (int64_t)i;
+    }
+    L.item = it;
+    L.seg_i = i;
+    L.seg.ox = ld_nt(sp);
+    L.seg.oy = ld_nt(sp + 1);
+    L.seg.oz = ld_nt(sp + 2);
+    L.seg.dx = ld_nt(ep) - L.seg.ox;
+    L.seg.dy = ld_nt(ep + 1) - L.seg.oy;
+    L.seg.dz = ld_nt(ep + 2) - L.seg.oz;
+    L.tlim = 1.0f;
+    L.best_t = INFINITY;
+    L.best_id = 0x7FFFFFFF;
+    L.best_pos = -1;
+    L.count = 0;
+    L.e = -1;
+    L.found = false;
+    L.retry = false;
+    return entry;
+}
+
+// Work counters of the counting variants.
+struct Tally {
+    uint32_t visits, boxes, tests, segs;
+    uint32_t w_loops, w_steps, w_leaf, w_refill, w_lrounds;     // wave-uniform
+    unsigned long long w_blocked, w_waiting, w_llanes;          // wave-uniform
+};
+
+__device__ inline void tally_out(const QArgs &a, const Tally &c)
+{
+    wave_add_u64(&a.counters->node_visits, c.visits);
+    wave_add_u64(&a.counters->box_tests, c.boxes);
+    wave_add_u64(&a.counters->tri_tests, c.tests);
+    wave_add_u64(&a.counters->segments, c.segs);
+    if (__lane_id() == 0) {
+        atomicAdd(&a.counters->wave_loops, (unsigned long long)c.w_loops);
+        atomicAdd(&a.counters->wave_node_steps, (unsigned long long)c.w_steps);
+        atomicAdd(&a.counters->wave_leaf_phases, (unsigned long long)c.w_leaf);
+        atomicAdd(&a.counters->wave_refills, (unsigned long long)c.w_refill);
+        atomicAdd(&a.counters->lanes_blocked, c.w_blocked);
+        atomicAdd(&a.counters->lanes_waiting, c.w_waiting);
+        atomicAdd(&a.counters->wave_leaf_rounds, (unsigned long long)c.w_lrounds);
+        atomicAdd(&a.counters->leaf_lanes, c.w_llanes);
+    }
+}
+
+// All hits, every lane of the wave here at its end: void the unused rest of
+// the wave's blocks (the offset scan and k_spill_finish skip an entry whose
+// count is negative, k_spill_place a record without entry).
+__device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
+{
+    const int32_t lane = (int32_t)__lane_id();
+    for (int32_t j = wst[0] + lane; j < wst[1]; j += 64) void_slot<0>(a, j);
+    for (int32_t j = wst[2] + lane; j < wst[3]; j += 64) void_slot<1>(a, j);
+}
+
+// The four-way walk (Node4 records), the default.
+//
+// One stack per lane holds both kinds of references: a node step pushes
+// every child whose box the segment touches and takes the top entry as the
+// next one (`cur`), an internal node or a leaf; a lane with a leaf on top
+// waits for the wave's leaf phase.  Slot 0 of every stack holds kDone, so a
+// pop needs no check for the end.  The step is what bounds the walk (VALU
+// issue 0.99 on the 29,768-triangle mesh with 10M segments), so it is kept
+// short: about 100 VALU instructions per step, against 148 when leaves were
+// kept in registers, the nearest child was picked in every mode and the
+// plane margins were formed per plane.  Only the first-hit walk still picks
+// the nearest child (pruning pays for it); for the other modes the build
+// orders the children.
+//
+// The stack's LDS part is a window on its top.  A push that finds it full
+// moves the older half of the window to a column in device memory (claimed
+// at the lane's first such push, kept for the launch) and a lane that runs
+// out of entries takes the newest ones back.  Walks that outgrow the LDS
+// part are few (2 to 6 segments of 4M to 10M on the 499,280-triangle sphere),
+// but finishing them in a pass of their own cost 150 to 275 us per query: a
+// few lanes walking alone from the root.  Only a lane that finds every
+// column taken still leaves its segment to that pass (RETRY: work items come
+// from the retry queue, whose length is read on the device, and every lane
+// has a column).
+template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_ALL) ? 6 : 1))) void k_query(QArgs a)
 {
-    constexpr bool HYB = RETRY;
     // the deep pass is launched after every main pass; with nothing queued
     // (the usual case) every workgroup leaves before touching memory
     if (RETRY && a.scalars[kRetryN] == 0) return;
     extern __shared__ int32_t lds_dyn[];
-    int32_t *const lds_stack = lds_dyn;
-    constexpr bool TOP = WIDE && !BATCH && top_copy(MODE);
+    constexpr bool TOP = !BATCH && top_copy(MODE);
+    constexpr bool NEAREST = (MODE & M_FIRST) && !(MODE & M_FULL);
     __shared__ uint4 top4[TOP ? 4 * kTopNodes : 4];
     if constexpr (TOP) {
         if (threadIdx.x < 64) load_top(a.nodes4, a.entry, top4, threadIdx.x);
         __syncthreads();
     }
-    int32_t *const stk = lds_stack + threadIdx.x;
-    const int stride = blockDim.x;
-    // work claiming: the main pass's items are cut into eight contiguous
-    // ranges, one per XCD, each with its own counter on its own 128-byte
-    // line; a wave takes chunks from its XCD's range first, then from the
-    // others in turn.  A single counter line shared by all XCDs serialises
-    // the claims in the memory fabric (measured: 0.83 against 0.69 ms for
-    // the 10M-segment boolean query); with the ranges each XCD also walks
-    // its own part of spatially ordered items.  The deep pass has one range.
-    constexpr int kRanges = RETRY ? 1 : kXcds;
-    int32_t *const work = &a.scalars[RETRY ? kWorkRetry : kWorkXcd];
-    int range = RETRY ? 0 : xcd_id();  // wave-uniform
-    int ranges_left = kRanges;
-    // stack entry k >= lds_depth lives at gstack[(k - lds_depth) * gstride + gtid]
-    const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // each wave's stack slots [lds_depth + 1][64], then (all hits aside) each wave's leaf queue
+    const int wave = (int)(threadIdx.x >> 6);
+    const int wave_ints = 64 * (a.lds_depth + 1);
+    int32_t *const stk = lds_dyn + wave * wave_ints + (int)__lane_id();
+    LeafEnt<MODE> *const leafq =
+        reinterpret_cast<LeafEnt<MODE> *>(lds_dyn + (blockDim.x >> 6) * wave_ints) + 64 * wave;
+    *stk = kDone;
+    int32_t *sp = stk;                                // the top entry's slot
+    int32_t *const sp_last = stk + 64 * a.lds_depth;  // the last slot in LDS
+    // the column: (number + 1) above bit 10 (0: none), bit 9 set once this
+    // segment has used it, entries in it below (at most 274)
+    int32_t col = RETRY ? (int32_t)(blockIdx.x * blockDim.x + threadIdx.x + 1) << 10 : 0;
+    // all hits: the wave's blocks of overflow-table entries and arena
+    // records, (next, end) each, none held at first
+    __shared__ int32_t wave_blocks[(MODE & M_ALL) ? 4 * kWavesPerBlock : 1];
+    volatile int32_t *const wst = wave_blocks + ((MODE & M_ALL) ? 4 * wave : 0);
+    if ((MODE & M_ALL) && __lane_id() == 0) {
+        wst[0] = wst[1] = 0;
+        wst[2] = wst[3] = 0;
+    }
 
     // a lane's state starts defined: the leaf phase reads any lane's segment
     // and t limit with shuffles, including lanes that never take an item
     Lane L = {};
     L.tlim = 1.0f;
-    L.retry = false;
     L.e = -1;
-    // all hits: the wave's blocks of overflow-table entries and arena
-    // records, (next, end) each, none held at first
+    int32_t item = -1;    // >= 0 owned work item; -1 idle; -2 no work left
+    int32_t cur = kDone;  // next entry: >= 0 a node, < 0 a leaf, kDone none
+    // bound on a walk (a damaged tree can give wrong answers, never a hang):
+    // each lane counts the node records it visits for its current segment; a
+    // walk of a valid tree visits every record at most once, so a count past
+    // the number of records can only come from a damaged tree.  Lanes check
+    // their count every 64 node-step rounds of the wave (behind a
+    // wave-uniform branch); a lane past the bound stops its walk and flags it.
+    int32_t wround = 0;  // wave-uniform
+    int32_t vis = 0;
+    Tally tl = {};
+    Claim cl = claim_init<RETRY>(a);
+    const float k_rel = kPlaneRel, k_start = kStartShift;
+
+    auto pop = [&]() -> int32_t {
+        const int32_t r = *sp;
+        sp -= 64;
+        return r;
+    };
+    // make room in a full window; false when no column is left
+    auto spill = [&]() -> bool {
+        if (col < 1024) {
+            const int32_t c = atomicAdd(&a.scalars[kStackCol], 1);
+            if (c >= a.n_cols) return false;
+            col = (c + 1) << 10;
+        }
+        if (!(col & 512)) {
+            col |= 512;
+            if (!RETRY) atomicAdd(&a.scalars[kSpilled], 1);
+        }
+        const int32_t n = (int32_t)(sp - stk) >> 6, k = (n + 1) >> 1;
+        const int32_t have = col & 511;
+        int32_t *g = a.gstack + ((col >> 10) - 1);
+        if (have + k > a.depth) {  // deeper than any valid tree: the entries are dropped and flagged
+            atomicOr(&a.scalars[kStackDropped], 1);
+        } else {
+            for (int32_t i = 0; i < k; ++i) g[(int64_t)(have + i) * a.n_cols] = stk[64 * (1 + i)];
+            col += k;
+        }
+        for (int32_t i = 1; i <= n - k; ++i) stk[64 * i] = stk[64 * (i + k)];
+        sp -= 64 * k;
+        return true;
+    };
+
+    for (;;) {
+        // ---- lanes whose walk is over write their results and take a new
+        // work item, batched: only once `refill` lanes are waiting (or no
+        // lane can make progress), so the epilogue and the segment set-up run
+        // with many lanes at once.
+        if (COUNT) ++tl.w_loops;
+        if (ballot(cur == kDone && (col & 511) != 0) != 0) {
+            // lanes out of entries with some in their column: the newest
+            // half window comes back
+            if (cur == kDone && (col & 511) != 0) {
+                const int32_t have = col & 511, half = (a.lds_depth + 1) >> 1;
+                const int32_t k = have < half ? have : half;
+                const int32_t *g = a.gstack + ((col >> 10) - 1);
+                for (int32_t i = 0; i < k; ++i) stk[64 * (1 + i)] = g[(int64_t)(have - k + i) * a.n_cols];
+                col -= k;
+                sp = stk + 64 * k;
+                cur = pop();
+            }
+        }
+        const bool done = item >= 0 && cur == kDone;
+        const uint64_t waiting = ballot(done || item == -1);
+        if (waiting != 0 && ((int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
+            if (COUNT) ++tl.w_refill;
+            if (done) {
+                finish<MODE, RETRY, BATCH>(a, L);
+                item = -1;
+            }
+            const int32_t k = claim_items<RETRY>(a, cl, item == -1);
+            if (item == -1) {
+                if (k >= 0) {
+                    item = k;
+                    const int32_t entry = start_item<RETRY, BATCH>(a, L, k);
+                    // |coordinate| bound of the mesh's box: with the
+                    // origin's it bounds every plane offset of this walk
+                    const float scale = a.mesh_scale[BATCH ? L.mesh : 0];
+                    L.tiny = box_tiny(L.seg, scale);
+                    box_rcp(L.seg, 1.0f, L.tiny);
+                    cur = entry < 0 ? kDone : (TOP ? kTopRef : entry);
+                    sp = stk;
+                    col &= ~1023;
+                    vis = 0;
+                    if (COUNT && !RETRY) ++tl.segs;
+                } else if (cl.exhausted) {
+                    item = -2;
+                }
+            }
+        }
+        if (ballot(item >= 0) == 0) break;
+
+        // ---- node steps for every lane with a node on top.  Steps repeat
+        // without the refill and leaf-phase checks while at least `defer`
+        // lanes step; pending leaves are tested after the first step made by
+        // fewer lanes.
+        uint64_t w;
+        do {
+            const bool want = (uint32_t)cur < (uint32_t)kDone;
+            w = ballot(want);
+            if (w == 0) break;
+            if (COUNT) {
+                ++tl.w_steps;
+                const uint64_t leaf = ballot(cur < 0);
+                tl.w_blocked += (unsigned long long)__popcll(leaf);
+                tl.w_waiting += (unsigned long long)(64 - __popcll(leaf | w));
+            }
+            if (want) {
+                ++vis;
+                uint4 P, Q, R;
+                int4 C;
+                if (TOP && cur >= kTopRef) {
+                    const uint4 *t = top4 + 4 * (cur - kTopRef);
+                    P = t[0];
+                    Q = t[1];
+                    R = t[2];
+                    const uint4 c = t[3];
+                    C = make_int4((int32_t)c.x, (int32_t)c.y, (int32_t)c.z, (int32_t)c.w);
+                } else {
+                    // n_t <= 2^26 in this walk, so a record's offset fits 32 bits
+                    const char *rec = reinterpret_cast<const char *>(a.nodes4) + ((uint32_t)cur << 6);
+                    const uint4 *q = reinterpret_cast<const uint4 *>(rec);
+                    P = q[0];
+                    Q = q[1];
+                    R = q[2];
+                    C = reinterpret_cast<const int4 *>(rec)[3];
+                }
+                // plane q of an axis lies at parameter fma(q, a, b); b is
+                // moved down for the plane the segment meets first (the lower
+                // one for a non-negative direction component) and up for the
+                // other one (see qslab_hit)
+                const float sx = __uint_as_float(R.z), sy = __uint_as_float(R.w), sz = __uint_as_float(P.w);
+                const float ax = sx * L.seg.ix, ay = sy * L.seg.iy, az = sz * L.seg.iz;
+                const float bx = fmaf(__uint_as_float(P.x) - L.seg.ox, L.seg.ix, k_start);
+                const float by = fmaf(__uint_as_float(P.y) - L.seg.oy, L.seg.iy, k_start);
+                const float bz = fmaf(__uint_as_float(P.z) - L.seg.oz, L.seg.iz, k_start);
+                const float bnx = fmaf(-fabsf(bx), k_rel, bx), bfx = fmaf(fabsf(bx), k_rel, bx);
+                const float bny = fmaf(-fabsf(by), k_rel, by), bfy = fmaf(fabsf(by), k_rel, by);
+                const float bnz = fmaf(-fabsf(bz), k_rel, bz), bfz = fmaf(fabsf(bz), k_rel, bz);
+                const bool px = L.seg.ix >= 0.0f, py = L.seg.iy >= 0.0f, pz = L.seg.iz >= 0.0f;
+                // child c: lower planes in byte c of Q.x, Q.y, Q.z, upper
+                // planes in byte c of Q.w, R.x, R.y
+                const uint32_t nqx = px ? Q.x : Q.w, fqx = px ? Q.w : Q.x;
+                const uint32_t nqy = py ? Q.y : R.x, fqy = py ? R.x : Q.y;
+                const uint32_t nqz = pz ? Q.z : R.y, fqz = pz ? R.y : Q.z;
+                auto qb = [](uint32_t v, int c) { return (float)((v >> (8 * c)) & 0xFFu); };
+                auto test = [&](int c, float &t) {
+                    return qslab_hit(ax, ay, az, bnx, bny, bnz, bfx, bfy, bfz, qb(nqx, c), qb(nqy, c), qb(nqz, c),
+                                     qb(fqx, c), qb(fqy, c), qb(fqz, c), t);
+                };
+                float t0, t1, t2, t3;
+                bool h0 = test(0, t0), h1 = test(1, t1), h2 = test(2, t2), h3 = test(3, t3);
+                if (COUNT) {
+                    const int32_t none = leaf_ref(a.n_tris, 1);
+                    ++tl.visits;
+                    tl.boxes += (C.x != none) + (C.y != none) + (C.z != none) + (C.w != none);
+                }
+                int32_t near = kDone;
+                if constexpr (NEAREST) {
+                    // the nearest touched child next; the others are pushed
+                    const bool n1 = h1 && !(h0 && t0 <= t1);
+                    const float m1 = n1 ? t1 : (h0 ? t0 : INFINITY);
+                    const bool n2 = h2 && t2 < m1;
+                    const float m2 = n2 ? t2 : m1;
+                    const bool n3 = h3 && t3 < m2;
+                    near = n3 ? C.w : (n2 ? C.z : (n1 ? C.y : (h0 ? C.x : kDone)));
+                    h3 = h3 && !n3;
+                    h2 = h2 && (n3 || !n2);
+                    h1 = h1 && (n3 || n2 || !n1);
+                    h0 = h0 && (n3 || n2 || n1);
+                }
+                if (sp + 4 * 64 <= sp_last) {
+                    // room for four: every child is written above the top
+                    // and the top moves past the touched ones only
+                    sp[64] = C.x;
+                    sp += h0 ? 64 : 0;
+                    sp[64] = C.y;
+                    sp += h1 ? 64 : 0;
+                    sp[64] = C.z;
+                    sp += h2 ? 64 : 0;
+                    sp[64] = C.w;
+                    sp += h3 ? 64 : 0;
+                    if (!NEAREST || near == kDone) {
+                        cur = *sp;
+                        sp -= 64;
+                    } else {
+                        cur = near;
+                    }
+                } else {
+                    // a full window: the last touched child stays in a
+                    // register, the others are pushed one by one
+                    int32_t top = near;
+                    auto put = [&](bool h, int32_t child) {
+                        if (!h) return;
+                        const int32_t e = NEAREST ? child : top;
+                        if (!NEAREST) top = child;
+                        if (e == kDone) return;
+                        if (sp == sp_last && !spill()) {
+                            L.retry = true;
+                            return;
+                        }
+                        sp += 64;
+                        *sp = e;
+                    };
+                    put(h0, C.x);
+                    put(h1, C.y);
+                    put(h2, C.z);
+                    put(h3, C.w);
+                    cur = top != kDone ? top : pop();
+                    if (L.retry) {  // no column left: the deep pass walks this segment again
+                        cur = kDone;
+                        col &= ~511;
+                    }
+                }
+            }
+            if (__builtin_expect((++wround & 63) == 0, 0)) {
+                if (vis > a.max_steps) {
+                    cur = kDone;
+                    col &= ~511;
+                    atomicOr(&a.scalars[kWalkCut], 1);
+                }
+            }
+        } while ((int)__popcll(w) >= a.defer);
+
+        // ---- test pending leaves once few lanes can still step
+        if (ballot(cur < 0) != 0) {
+            if (COUNT) ++tl.w_leaf;
+            const float before = L.tlim;
+            if constexpr ((MODE & M_ALL) != 0) {
+                // all hits: the top leaf of each lane per round (gathered,
+                // the 29,768-triangle mesh's query is 3% faster and the
+                // 499,280-triangle sphere's 10% slower: 3.30 against 2.97 ms)
+                uint64_t m;
+                while ((m = ballot(cur < 0)) != 0) {
+                    if (COUNT) {
+                        ++tl.w_lrounds;
+                        tl.w_llanes += (unsigned long long)__popcll(m);
+                    }
+                    if (cur < 0) {
+                        visit_leaf<MODE, BATCH, COUNT>(a, L, cur, tl.tests, wst);
+                        cur = pop();
+                    }
+                }
+            } else {
+                leaf_phase4<MODE, COUNT>(a, L, cur, pop, tl.tests, leafq, tl.w_lrounds, tl.w_llanes);
+            }
+            if (MODE == M_BOOL && L.found) col &= ~511;  // the walk is over
+            // a nearer hit shortens the segment for the boxes
+            if (NEAREST && L.tlim != before) box_rcp(L.seg, L.tlim * (1.0f + 0x1p-20f), L.tiny);
+        }
+    }
+    if constexpr ((MODE & M_ALL) != 0) void_blocks(a, wst);
+    if (COUNT) tally_out(a, tl);
+}
+
+// The walk of the binary tree itself (branching 2, and meshes past 2^26
+// triangles).  RETRY as for k_query.  The all-hits variants are held to six
+// waves per SIMD (80 VGPRs): without the bound the compiler gives them 94
+// and five waves.
+template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_ALL) ? 6 : 1))) void k_query_binary(
+    QArgs a)
+{
+    constexpr bool HYB = RETRY;
+    if (RETRY && a.scalars[kRetryN] == 0) return;
+    extern __shared__ int32_t lds_dyn[];
+    int32_t *const stk = lds_dyn + threadIdx.x;
+    const int stride = blockDim.x;
+    // stack entry k >= lds_depth lives at gstack[(k - lds_depth) * gstride + gtid]
+    const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     __shared__ int32_t wave_blocks[(MODE & M_ALL) ? 4 * kWavesPerBlock : 1];
-    // four-way walk: the wave's leaf queue, past the stack's LDS part
-    LeafEnt<MODE> *const leafq =
-        reinterpret_cast<LeafEnt<MODE> *>(lds_dyn + (size_t)a.lds_depth * blockDim.x) + 64 * (threadIdx.x >> 6);
     volatile int32_t *const wst = wave_blocks + ((MODE & M_ALL) ? 4 * (threadIdx.x >> 6) : 0);
     if ((MODE & M_ALL) && __lane_id() == 0) {
         wst[0] = wst[1] = 0;
         wst[2] = wst[3] = 0;
     }
-    // work items number below 2^30 (checked at the boundary), so item and
-    // chunk arithmetic is 32-bit; the chunk bounds are wave-uniform
+    Lane L = {};
+    L.tlim = 1.0f;
+    L.e = -1;
     int32_t item = -1;   // >= 0 owned work item; -1 idle; -2 no work left
     int32_t node = -1;   // next node to visit; < 0: none
     // stack pointer kept as an element offset into the [depth][lane] LDS
@@ -664,115 +1069,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
     int32_t *const stk_end = stk + a.depth * stride;
     const int32_t depth_off = a.depth * stride;
     const int32_t lds_off = a.lds_depth * stride;
-    // pending leaf references (leaf refs are negative; 0 = none): filled in
-    // order in the binary walk, by child slot in the four-way walk
-    int32_t leaf0 = 0, leaf1 = 0, leaf2 = 0, leaf3 = 0;
-    // bound on a walk (a damaged tree can give wrong answers, never a hang):
-    // each lane counts the node records it visits for its current segment; a
-    // walk of a valid tree visits every record at most once, so a count past
-    // the number of records can only come from a damaged tree.  Lanes check
-    // their count every 64 node-step rounds of the wave (behind a
-    // wave-uniform branch); a lane past the bound stops its walk and flags it.
-    int32_t wround = 0;      // wave-uniform
+    // pending leaf references (leaf refs are negative; 0 = none), filled in order
+    int32_t leaf0 = 0, leaf1 = 0, leaf2 = 0;
+    int32_t wround = 0;  // the walk bound, as in k_query
     int32_t vis = 0;
-    uint32_t visits = 0, boxes = 0, tests = 0, segs = 0;
-    uint32_t w_loops = 0, w_steps = 0, w_leaf = 0, w_refill = 0;  // wave-uniform
-    unsigned long long w_blocked = 0, w_waiting = 0;               // wave-uniform
-    uint32_t w_lrounds = 0;                                        // wave-uniform
-    unsigned long long w_llanes = 0;                               // wave-uniform
-    int32_t chunk_next = 0, chunk_end = 0;  // the wave's claimed, not yet handed out items
-    int32_t n_items = (int32_t)a.n_items;
-    if (RETRY) {
-        const int32_t q = a.scalars[kRetryN];
-        n_items = q < (int32_t)a.retry_cap ? q : (int32_t)a.retry_cap;
-    }
-    bool exhausted = false;                 // every range's counter has passed its last item
+    Tally tl = {};
+    Claim cl = claim_init<RETRY>(a);
 
     for (;;) {
-        // ---- lanes whose walk is over write their results and take a new
-        // work item, batched: only once `refill` lanes are waiting (or no
-        // lane can make progress), so the epilogue and the segment set-up run
-        // with many lanes at once.  Items come from the wave's chunk; a new
-        // chunk is claimed from a range counter with one atomic.
-        if (COUNT) ++w_loops;
-        const bool done = item >= 0 && node < 0 && (WIDE ? (leaf0 | leaf1 | leaf2 | leaf3) == 0 : leaf0 == 0);
+        if (COUNT) ++tl.w_loops;
+        const bool done = item >= 0 && node < 0 && leaf0 == 0;
         const uint64_t waiting = ballot(done || item == -1);
-        if (waiting != 0 &&
-            ((int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
-            if (COUNT) ++w_refill;
+        if (waiting != 0 && ((int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
+            if (COUNT) ++tl.w_refill;
             if (done) {
                 finish<MODE, RETRY, BATCH>(a, L);
                 item = -1;
             }
-            const uint64_t idle = ballot(item == -1);
-            const int32_t n_idle = (int32_t)__popcll(idle);
-            const int32_t rank = (int32_t)lanes_below(idle);
-            int32_t k = -1;
-            const int32_t avail = chunk_end - chunk_next;
-            const int32_t used = avail < n_idle ? avail : n_idle;
-            if (rank < used) k = chunk_next + rank;
-            chunk_next += used;
-            if (used < n_idle && !exhausted) {
-                const int leader = __builtin_ctzll(idle);
-                for (;;) {
-                    const int32_t lo = (int32_t)((int64_t)n_items * range / kRanges);
-                    const int32_t hi = (int32_t)((int64_t)n_items * (range + 1) / kRanges);
-                    int32_t base = 0;
-                    if ((int)__lane_id() == leader) base = atomicAdd(work + kWorkStride * range, a.chunk);
-                    base = __builtin_amdgcn_readfirstlane(__shfl(base, leader, 64));
-                    if (base < hi - lo) {
-                        chunk_next = lo + base;
-                        chunk_end = hi - chunk_next > a.chunk ? chunk_next + a.chunk : hi;
-                        const int32_t room = chunk_end - chunk_next;
-                        const int32_t more = n_idle - used < room ? n_idle - used : room;
-                        if (rank >= used && rank - used < more) k = chunk_next + (rank - used);
-                        chunk_next += more;
-                        break;
-                    }
-                    // this range is used up: the next one
-                    if (--ranges_left == 0) {
-                        exhausted = true;
-                        break;
-                    }
-                    range = range + 1 == kRanges ? 0 : range + 1;
-                }
-            }
+            const int32_t k = claim_items<RETRY>(a, cl, item == -1);
             if (item == -1) {
                 if (k >= 0) {
                     item = k;
-                    const int32_t it = RETRY ? a.retry_q[k] : k;
-                    int32_t i = it;
-                    int32_t entry = (TOP && a.entry >= 0) ? kTopRef : a.entry;
-                    if (BATCH) {
-                        const int32_t m = mesh_of(a.bt.seg_off, a.M, it);
-                        i = (int32_t)(it - a.bt.seg_off[m]);
-                        L.mesh = m;
-                        L.sp = a.bt.S[m] + 3 * (int64_t)i;
-                        L.ep = a.bt.E[m] + 3 * (int64_t)i;
-                        entry = a.mesh_entry[m];
-                    } else {
-                        L.mesh = 0;
-                        L.sp = a.S + 3 * (int64_t)i;
-                        L.ep = a.E + 3 * (int64_t)i;
-                    }
-                    L.item = it;
-                    L.seg_i = i;
-                    L.seg = make_seg(ld_nt(L.sp), ld_nt(L.sp + 1), ld_nt(L.sp + 2), ld_nt(L.ep), ld_nt(L.ep + 1),
-                                     ld_nt(L.ep + 2));
-                    L.tlim = 1.0f;
-                    L.best_t = INFINITY;
-                    L.best_id = 0x7FFFFFFF;
-                    L.best_pos = -1;
-                    L.count = 0;
-                    L.e = -1;
-                    L.found = false;
-                    L.retry = false;
-                    node = entry;  // < 0 for an empty mesh: the segment misses
+                    node = start_item<RETRY, BATCH>(a, L, k);  // < 0 for an empty mesh: the segment misses
+                    L.seg.ix = guarded_rcp(L.seg.dx);
+                    L.seg.iy = guarded_rcp(L.seg.dy);
+                    L.seg.iz = guarded_rcp(L.seg.dz);
                     sp = 0;
                     sptr = stk;
                     vis = 0;
-                    if (COUNT && !RETRY) ++segs;
-                } else if (exhausted) {
+                    if (COUNT && !RETRY) ++tl.segs;
+                } else if (cl.exhausted) {
                     item = -2;
                 }
             }
@@ -828,161 +1154,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
         // Steps repeat without the refill and leaf-phase checks while at
         // least `defer` lanes step; pending leaves are tested after the first
         // step made by fewer lanes.
-        auto can_step = [&]() {
-            return node >= 0 && (WIDE ? (leaf0 | leaf1 | leaf2 | leaf3) == 0 : leaf1 == 0);
-        };
         uint64_t w;
         do {
-            const bool want = can_step();
+            const bool want = node >= 0 && leaf1 == 0;
             // the two conditions' masks, each straight from its compare
-            w = ballot(node >= 0) & ballot(WIDE ? (leaf0 | leaf1 | leaf2 | leaf3) == 0 : leaf1 == 0);
+            w = ballot(node >= 0) & ballot(leaf1 == 0);
             if (w == 0) break;
             if (COUNT) {
-                ++w_steps;
+                ++tl.w_steps;
                 const uint64_t has_node = ballot(node >= 0);
-                w_blocked += (unsigned long long)__popcll(has_node & ~w);
-                w_waiting += (unsigned long long)(64 - __popcll(has_node));
+                tl.w_blocked += (unsigned long long)__popcll(has_node & ~w);
+                tl.w_waiting += (unsigned long long)(64 - __popcll(has_node));
             }
-            if constexpr (WIDE) {
-              if (want) {
-                ++vis;
-                uint4 P, Q, R;
-                int4 C;
-                if (TOP && node >= kTopRef) {
-                    const uint4 *t = top4 + 4 * (node - kTopRef);
-                    P = t[0];
-                    Q = t[1];
-                    R = t[2];
-                    const uint4 c = t[3];
-                    C = make_int4((int32_t)c.x, (int32_t)c.y, (int32_t)c.z, (int32_t)c.w);
-                } else {
-                    const uint4 *q = reinterpret_cast<const uint4 *>(a.nodes4 + node);
-                    P = q[0];
-                    Q = q[1];
-                    R = q[2];
-                    C = reinterpret_cast<const int4 *>(a.nodes4 + node)[3];
-                }
-                const float lim = ((MODE & M_FIRST) && !(MODE & M_FULL) ? L.tlim : 1.0f) * (1.0f + 0x1p-20f);
-                // grid steps, the corner's offset from the segment origin and
-                // the margin that makes the plane evaluation conservative
-                const float sx = __uint_as_float(R.z), sy = __uint_as_float(R.w), sz = __uint_as_float(P.w);
-                const float Dx = __uint_as_float(P.x) - L.seg.ox;
-                const float Dy = __uint_as_float(P.y) - L.seg.oy;
-                const float Dz = __uint_as_float(P.z) - L.seg.oz;
-                // per axis the plane met first: the lower one for a
-                // non-negative direction component; the margin moves it
-                // toward the segment origin and the other plane away
-                const bool px = L.seg.ix >= 0.0f, py = L.seg.iy >= 0.0f, pz = L.seg.iz >= 0.0f;
-                const float mx = fmaf(255.0f, sx, fabsf(Dx)) * (px ? 0x1p-19f : -0x1p-19f);
-                const float my = fmaf(255.0f, sy, fabsf(Dy)) * (py ? 0x1p-19f : -0x1p-19f);
-                const float mz = fmaf(255.0f, sz, fabsf(Dz)) * (pz ? 0x1p-19f : -0x1p-19f);
-                // plane q of an axis lies at parameter fma(q, a, b)
-                const float ax = sx * L.seg.ix, ay = sy * L.seg.iy, az = sz * L.seg.iz;
-                const float bnx = (Dx - mx) * L.seg.ix, bny = (Dy - my) * L.seg.iy, bnz = (Dz - mz) * L.seg.iz;
-                const float bfx = (Dx + mx) * L.seg.ix, bfy = (Dy + my) * L.seg.iy, bfz = (Dz + mz) * L.seg.iz;
-                // child c: lower planes in byte c of Q.x, Q.y, Q.z, upper
-                // planes in byte c of Q.w, R.x, R.y
-                const uint32_t nqx = px ? Q.x : Q.w, fqx = px ? Q.w : Q.x;
-                const uint32_t nqy = py ? Q.y : R.x, fqy = py ? R.x : Q.y;
-                const uint32_t nqz = pz ? Q.z : R.y, fqz = pz ? R.y : Q.z;
-                auto qb = [](uint32_t v, int c) { return (float)((v >> (8 * c)) & 0xFFu); };
-                auto test = [&](int c, float &t) {
-                    return qslab_hit(ax, ay, az, bnx, bny, bnz, bfx, bfy, bfz, qb(nqx, c), qb(nqy, c), qb(nqz, c),
-                                     qb(fqx, c), qb(fqy, c), qb(fqz, c), lim, t);
-                };
-                float t0, t1, t2, t3;
-                const bool h0 = test(0, t0) && C.x != kEmptySlot;
-                const bool h1 = test(1, t1) && C.y != kEmptySlot;
-                const bool h2 = test(2, t2) && C.z != kEmptySlot;
-                const bool h3 = test(3, t3) && C.w != kEmptySlot;
-                if (COUNT) {
-                    ++visits;
-                    boxes += (C.x != kEmptySlot) + (C.y != kEmptySlot) + (C.z != kEmptySlot) + (C.w != kEmptySlot);
-                }
-                leaf0 = (h0 && C.x < 0) ? C.x : 0;
-                leaf1 = (h1 && C.y < 0) ? C.y : 0;
-                leaf2 = (h2 && C.z < 0) ? C.z : 0;
-                leaf3 = (h3 && C.w < 0) ? C.w : 0;
-                const bool g0 = h0 && C.x >= 0, g1 = h1 && C.y >= 0, g2 = h2 && C.z >= 0, g3 = h3 && C.w >= 0;
-                // descend into the nearest internal child that was hit; push the others
-                float bt = INFINITY;
-                int32_t near = -1;
-                if (g0) { bt = t0; near = C.x; }
-                if (g1 && t1 < bt) { bt = t1; near = C.y; }
-                if (g2 && t2 < bt) { bt = t2; near = C.z; }
-                if (g3 && t3 < bt) { bt = t3; near = C.w; }
-                const bool p0 = g0 && C.x != near, p1 = g1 && C.y != near;
-                const bool p2 = g2 && C.z != near, p3 = g3 && C.w != near;
-                // at most three pushes (the nearest child is taken, not
-                // pushed): with room for three more entries in LDS every
-                // child is written at the top and the top advances past the
-                // pushed ones only (a write past them lands in a free slot)
-                bool room;
-                if constexpr (HYB) room = sp + 3 * stride < lds_off;
-                else room = sptr + 3 * stride < stk_end;
-                if (room && HYB) {
-                    stk[sp] = C.x;
-                    sp += p0 ? stride : 0;
-                    stk[sp] = C.y;
-                    sp += p1 ? stride : 0;
-                    stk[sp] = C.z;
-                    sp += p2 ? stride : 0;
-                    stk[sp] = C.w;
-                    sp += p3 ? stride : 0;
-                } else if (room) {
-                    *sptr = C.x;
-                    sptr += p0 ? stride : 0;
-                    *sptr = C.y;
-                    sptr += p1 ? stride : 0;
-                    *sptr = C.z;
-                    sptr += p2 ? stride : 0;
-                    *sptr = C.w;
-                    sptr += p3 ? stride : 0;
-                } else {
-                    push(p0, C.x);
-                    push(p1, C.y);
-                    push(p2, C.z);
-                    push(p3, C.w);
-                }
-                node = near >= 0 ? near : pop();
-                if (!RETRY && L.retry) {
-                    // the stack is full: stop here, the deep pass takes over
-                    node = -1;
-                    leaf0 = leaf1 = leaf2 = leaf3 = 0;
-                }
-              }
-            } else if (want) {
+            if (want) {
                 ++vis;
                 const float4 *q = reinterpret_cast<const float4 *>(a.nodes + node);
                 const float4 q0 = q[0], q1 = q[1], q2 = q[2];
                 const int4 q3 = reinterpret_cast<const int4 *>(a.nodes + node)[3];
                 const float lim = (MODE & M_FIRST) && !(MODE & M_FULL) ? L.tlim : 1.0f;
-                float tl, tr;
-                const bool hl = slab_hit(L.seg, q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, lim, tl);
+                float tl_, tr;
+                const bool hl = slab_hit(L.seg, q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, lim, tl_);
                 const bool hr = slab_hit(L.seg, q1.z, q1.w, q2.x, q2.y, q2.z, q2.w, lim, tr);
                 if (COUNT) {
-                    ++visits;
-                    boxes += 2;
+                    ++tl.visits;
+                    tl.boxes += 2;
                 }
-                const int32_t cl = q3.x, cr = q3.y;
+                const int32_t cl_ = q3.x, cr = q3.y;
                 // add the hit leaf children to the pending list, kept in
                 // ascending order: references are negative and 0 marks a free
                 // slot, so the pending entries come first (at most one is
                 // pending here, so three slots suffice); the order in which a
                 // lane tests its leaves changes no result
-                const int32_t n0 = (hl && cl < 0) ? cl : 0;
+                const int32_t n0 = (hl && cl_ < 0) ? cl_ : 0;
                 const int32_t n1 = (hr && cr < 0) ? cr : 0;
                 const int32_t lo01 = min(n0, n1), hi01 = max(n0, n1);
                 leaf2 = max(leaf0, hi01);
                 leaf1 = max(min(leaf0, hi01), lo01);
                 leaf0 = min(leaf0, lo01);
-                const bool gl = hl && cl >= 0;
+                const bool gl = hl && cl_ >= 0;
                 const bool gr = hr && cr >= 0;
                 // descend into the nearer internal child that was hit; push the
                 // other one when both were
-                const bool take_l = gl && (!gr || tl <= tr);
-                push(gl && gr, take_l ? cr : cl);
-                node = (gl || gr) ? (take_l ? cl : cr) : pop();
+                const bool take_l = gl && (!gr || tl_ <= tr);
+                push(gl && gr, take_l ? cr : cl_);
+                node = (gl || gr) ? (take_l ? cl_ : cr) : pop();
                 if (!RETRY && L.retry) {
                     node = -1;
                     leaf0 = leaf1 = leaf2 = 0;
@@ -997,42 +1212,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
         } while ((int)__popcll(w) >= a.defer);
 
         // ---- test pending leaves once few lanes can still step
-        const uint64_t pend = ballot(WIDE ? (leaf0 | leaf1 | leaf2 | leaf3) != 0 : leaf0 != 0);
-        if (pend != 0) {
-            if (COUNT) ++w_leaf;
-            if constexpr (WIDE && !(MODE & M_ALL)) {
-                leaf_phase4<MODE, BATCH, COUNT>(a, L, leaf0, leaf1, leaf2, leaf3, node, tests, wst, leafq,
-                                                w_lrounds, w_llanes);
-            } else if constexpr (WIDE) {
-                // all hits: one pending leaf per lane and round, the first
-                // occupied slot (the gathered phase needs more registers
-                // than these variants have)
-                do {
-                    const int32_t cur = leaf0 ? leaf0 : (leaf1 ? leaf1 : (leaf2 ? leaf2 : leaf3));
-                    if (COUNT) {
-                        ++w_lrounds;
-                        w_llanes += (unsigned long long)__popcll(ballot(cur != 0));
-                    }
-                    if (cur != 0) {
-                        visit_leaf<MODE, BATCH, COUNT>(a, L, cur, tests, wst);
-                        if (leaf0 == cur) {
-                            leaf0 = 0;
-                        } else if (leaf1 == cur) {
-                            leaf1 = 0;
-                        } else if (leaf2 == cur) {
-                            leaf2 = 0;
-                        } else {
-                            leaf3 = 0;
-                        }
-                    }
-                } while (ballot((leaf0 | leaf1 | leaf2 | leaf3) != 0) != 0);
-            } else do {
+        if (ballot(leaf0 != 0) != 0) {
+            if (COUNT) ++tl.w_leaf;
+            do {
                 if (COUNT) {
-                    ++w_lrounds;
-                    w_llanes += (unsigned long long)__popcll(ballot(leaf0 != 0));
+                    ++tl.w_lrounds;
+                    tl.w_llanes += (unsigned long long)__popcll(ballot(leaf0 != 0));
                 }
                 if (leaf0 != 0) {
-                    const bool stop = visit_leaf<MODE, BATCH, COUNT>(a, L, leaf0, tests, wst);
+                    const bool stop = visit_leaf<MODE, BATCH, COUNT>(a, L, leaf0, tl.tests, wst);
                     leaf0 = stop ? 0 : leaf1;
                     leaf1 = stop ? 0 : leaf2;
                     leaf2 = 0;
@@ -1040,32 +1228,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
                 }
             } while (ballot(leaf0 != 0) != 0);
         }
-
     }
-    if constexpr ((MODE & M_ALL) != 0) {
-        // every lane of the wave is here: void the unused rest of the wave's
-        // blocks (the offset scan and k_spill_finish skip an entry whose
-        // count is negative, k_spill_place a record without entry)
-        const int32_t lane = (int32_t)__lane_id();
-        for (int32_t j = wst[0] + lane; j < wst[1]; j += 64) void_slot<0>(a, j);
-        for (int32_t j = wst[2] + lane; j < wst[3]; j += 64) void_slot<1>(a, j);
-    }
-    if (COUNT) {
-        wave_add_u64(&a.counters->node_visits, visits);
-        wave_add_u64(&a.counters->box_tests, boxes);
-        wave_add_u64(&a.counters->tri_tests, tests);
-        wave_add_u64(&a.counters->segments, segs);
-        if (__lane_id() == 0) {
-            atomicAdd(&a.counters->wave_loops, (unsigned long long)w_loops);
-            atomicAdd(&a.counters->wave_node_steps, (unsigned long long)w_steps);
-            atomicAdd(&a.counters->wave_leaf_phases, (unsigned long long)w_leaf);
-            atomicAdd(&a.counters->wave_refills, (unsigned long long)w_refill);
-            atomicAdd(&a.counters->lanes_blocked, w_blocked);
-            atomicAdd(&a.counters->lanes_waiting, w_waiting);
-            atomicAdd(&a.counters->wave_leaf_rounds, (unsigned long long)w_lrounds);
-            atomicAdd(&a.counters->leaf_lanes, w_llanes);
-        }
-    }
+    if constexpr ((MODE & M_ALL) != 0) void_blocks(a, wst);
+    if (COUNT) tally_out(a, tl);
 }
 
 // Segment and output arrays of work item `it` (a segment of a single mesh,
@@ -1731,7 +1896,7 @@ __global__ void k_parity(const int32_t *__restrict__ count, int64_t n, uint8_t *
 // so they describe every part.
 __global__ void k_reset(int32_t *scalars, Counters *c, int keep)
 {
-    const int32_t zero[] = {kWorkRetry, kRetryN,  kOvfSegs, kOvfTotalLo, kOvfTotalHi,   kArenaLo, kArenaHi,
+    const int32_t zero[] = {kWorkRetry, kRetryN,  kStackCol, kSpilled, kOvfSegs, kOvfTotalLo, kOvfTotalHi,   kArenaLo, kArenaHi,
                             kOvfFull,   kOvfUsed, kArenaUsed, kRetryLost, kStackDropped, kWalkCut};
     for (int r = 0; r < kXcds; ++r) scalars[kWorkXcd + kWorkStride * r] = 0;
     const int n = (int)(sizeof(zero) / sizeof(zero[0])) - (keep ? 3 : 0);
@@ -1827,9 +1992,11 @@ hipError_t launch_refine_first(const QArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// Grid of the deep pass: a few workgroups per CU (the queue is short); its
-// device-memory stack holds one column per thread of this grid.
-constexpr int kRetryBlocksPerCU = 1;
+// Columns of the stacks' device-memory part, and with it the most threads of
+// the deep pass (about one workgroup per CU: the queue is short).  At the
+// deepest stack bound they take 16 MB, which leaves rsi_query_noalloc's fixed
+// array room for a queue of 4.3 million segments.
+constexpr int kStackCols = 28672;
 
 int device_cus()
 {
@@ -1842,13 +2009,14 @@ int device_cus()
 template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH, bool WIDE>
 hipError_t launch_kernel(const QArgs &a, int block, size_t lds, hipStream_t s)
 {
-    auto kern = k_query<MODE, RETRY, COUNT, BATCH, WIDE>;
+    auto kern = WIDE ? k_query<MODE, RETRY, COUNT, BATCH> : k_query_binary<MODE, RETRY, COUNT, BATCH>;
     int64_t grid;
     QArgs b = a;
     if (RETRY) {
-        grid = (int64_t)kRetryBlocksPerCU * device_cus();
-        if (a.lds_depth < a.depth && (a.gstack == nullptr || grid * block * (int64_t)(a.depth - a.lds_depth) >
-                                                                 a.gstack_cap))
+        grid = device_cus();
+        if (grid > kStackCols / block) grid = kStackCols / block;  // block <= 256: at least 112
+        if (a.lds_depth < a.depth &&
+            (a.gstack == nullptr || grid * block * (int64_t)(a.depth - a.lds_depth) > a.gstack_cap))
             return hipErrorInvalidValue;
         b.chunk = 64;
     } else {
@@ -1909,13 +2077,14 @@ hipError_t dispatch(uint32_t mode, const QArgs &a, const QArgs &d, int block, si
     }
 }
 
-// Dynamic LDS of a query launch: the stack's LDS part, then in the
-// four-way walk (all-hits modes aside) each wave's leaf queue (64 entries).
+// Dynamic LDS of a query launch: the stack's LDS part; in the four-way walk
+// with one more slot per lane (the end marker), then (all-hits modes aside)
+// each wave's leaf queue (64 entries).
 size_t query_lds(int block, int depth, int width, uint32_t mode)
 {
-    const size_t ent = mode == M_BOOL ? sizeof(int2) : sizeof(int4);
-    const bool queue = width == 4 && !(mode & M_ALL);
-    return (size_t)block * depth * sizeof(int32_t) + (queue ? (size_t)(block / 64) * 64 * ent : 0);
+    if (width != 4) return (size_t)block * depth * sizeof(int32_t);
+    const size_t ent = (mode & M_ALL) ? 0 : mode == M_BOOL ? sizeof(int2) : sizeof(int4);
+    return (size_t)block * ((depth + 1) * sizeof(int32_t) + ent);
 }
 
 // Largest multiple of 64 not above `want` (and at most 256, the kernels'
@@ -1937,14 +2106,14 @@ int stack_need(int height, int width)
 }
 
 // LDS stack entries per lane of the main pass: the `stack_depth` option, or
-// 20 on the four-way walk (17 when the walk also holds the 1,344-byte copy
+// 18 on the four-way walk (17 when the walk also holds the 1,344-byte copy
 // of the top records), 32 on the binary walk; never more than the bound.
 int lds_part(const rsi_bvh *h, bool top)
 {
     const int width = h->width_built;
     const int bound = stack_need(h->height_bound, width);
     int cap = h->stack_cap;
-    if (cap <= 0) cap = width == 4 ? (top ? 17 : 20) : 32;
+    if (cap <= 0) cap = width == 4 ? (top ? 17 : 18) : 32;
     return cap < bound ? cap : bound;
 }
 
@@ -1974,6 +2143,7 @@ QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, con
     a.lds_depth = 0;
     a.gstack = h->retry_stack;
     a.gstack_cap = h->retry_stack_cap;
+    a.n_cols = 0;
     a.retry_q = h->retry_q;
     a.retry_cap = h->retry_cap;
     a.max_steps = (int32_t)(h->n_t > 0 ? h->n_t : 1);
@@ -1982,20 +2152,25 @@ QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, con
     a.chunk = h->chunk;
     a.M = h->M;
     a.mesh_entry = h->mesh_entry;
+    a.mesh_scale = h->mesh_scale;
     a.bt = h->bt;
     return a;
 }
 
-// Arguments of the two passes: the main pass keeps its whole stack (ld
-// entries) in LDS; the deep pass has the same LDS part and continues in
-// device memory up to the height bound.
+// Arguments of the two passes, with ld stack entries per lane in LDS.  In
+// the four-way walk both passes continue in device memory up to the height
+// bound; in the binary walk the main pass has its LDS part only.
 void pass_args(const rsi_bvh *h, QArgs &main, QArgs &deep, int ld)
 {
-    main.depth = main.lds_depth = ld;
+    const int need = stack_need(h->height_bound, h->width_built);
+    main.lds_depth = ld;
+    main.depth = h->width_built == 4 ? (need > ld ? need : ld) : ld;
+    if (h->width_built == 4) {
+        const int64_t cols = main.gstack ? main.gstack_cap / main.depth : 0;
+        main.n_cols = (int32_t)(cols < kStackCols ? cols : kStackCols);
+    }
     deep = main;
-    deep.depth = stack_need(h->height_bound, h->width_built);
-    deep.lds_depth = ld;
-    if (deep.depth < ld) deep.depth = ld;
+    deep.depth = need > ld ? need : ld;
 }
 
 hipError_t launch_all_hits_tail(const QArgs &a, bool batch, hipStream_t s)
@@ -2030,9 +2205,8 @@ hipError_t launch_all_hits_tail(const QArgs &a, bool batch, hipStream_t s)
 int64_t deep_stack_entries(const rsi_bvh *h, uint32_t mode)
 {
     const int ld = lds_part(h, h->width_built == 4 && top_copy(mode));
-    const int block = fit_block(h->block_size, ld, h->width_built, mode);
     const int need = stack_need(h->height_bound, h->width_built);
-    return need > ld ? (int64_t)kRetryBlocksPerCU * device_cus() * block * (need - ld) : 0;
+    return (int64_t)kStackCols * (need > ld ? need : ld);
 }
 
 hipError_t launch_query(rsi_bvh *h, const float *S, const float *E, int64_t n_r, uint32_t mode,
@@ -2121,15 +2295,9 @@ hipError_t ensure_query_memory(rsi_bvh *h, int64_t n, bool all_hits)
         if (e == hipSuccess) cap = want;
     };
     grow(&h->retry_q, h->retry_cap, n, sizeof(int32_t));
-    // deep-pass stack: every thread of its grid, entries past the LDS part
-    {
-        const int width = h->width_built;
-        const int ld_min = lds_part(h, width == 4);  // the smaller LDS part: the longer tail
-        const int need = stack_need(h->height_bound, width);
-        const int64_t want =
-            need > ld_min ? (int64_t)kRetryBlocksPerCU * device_cus() * h->block_size * (need - ld_min) : 1;
-        grow(&h->retry_stack, h->retry_stack_cap, want, sizeof(int32_t));
-    }
+    // the stacks' device-memory part
+    grow(&h->retry_stack, h->retry_stack_cap, (int64_t)kStackCols * stack_need(h->height_bound, h->width_built),
+         sizeof(int32_t));
     if (all_hits) {
         // waves that can hold a block of entries and one of records at
         // once: every resident wave of the main pass (at most 32 per CU,

@@ -42,13 +42,16 @@ static_assert(sizeof(Node) == 64, "Node must be 64 bytes");
 //                steps spanning n's box on that axis
 //   lo[a]        byte c: child c's lower plane on axis a in grid steps,
 //                rounded down;  hi[a] likewise for the upper plane, rounded
-//                up -- every quantised box contains its exact child box
-//   ref[c]       child reference, kEmptySlot for an unused slot
+//                up, each at least kQuantMargin steps outside the child's
+//                box except a lower plane at 0, the exact corner
+//   ref[c]       child reference; an unused slot (planes 255 and 0, so its
+//                box is empty) names the leaf at position n_t, a record of
+//                zeros that no segment crosses
 //
 // With exact boxes the four-way record would need 128 bytes; 64 bytes halve
 // the vector-cache lookups per visited box, which bound the binary walk.  Any finite
 // box is representable.
-constexpr int32_t kEmptySlot = 0x7FFFFFFF;
+constexpr int32_t kDone = 0x7FFFFFFF;  // the four-way walk's end-of-stack mark; no reference has this value
 struct alignas(64) Node4 {
     float ox, oy, oz, sz;
     uint32_t lo[3];
@@ -138,39 +141,72 @@ __device__ inline bool slab_hit(const Seg &s, float lx, float ly, float lz,
     return n <= f * (1.0f + 0x1p-20f);
 }
 
-// Conservative segment / quantised-box test for the four-way view.  Per
-// node and axis the caller forms D = corner - o, the margin
-// eps = (255 step + |D|) 2^-19 and the parameter of grid plane q
-// as one fused multiply-add, fma(q, a, b), with a = step * (1/d) and
-// b = (D -+ eps) * (1/d): the lower sign for the plane the segment meets
-// first on that axis (the lower plane when the direction component is
-// non-negative -- 1/d keeps the sign of d, zero included), the upper sign
-// for the other one; qn and qf are those planes' quantised values as floats.
-// step is a power of two, so a is exact (barring underflow, i.e. |d| near
-// the FP32 range).  The roundings of D, of D -+ eps, of b and of the fma, and
-// the reciprocal's own error (within 1 ulp), add up to at most
-// 6 * 2^-24 (|D| + 255 step) in plane-offset units, under a fifth of eps: a
-// first plane's parameter never exceeds, and an other plane's never falls
-// below, that of the exact quantised plane, so the tested box contains the
-// quantised box, which contains the child box.  No per-axis min/max is
-// needed, and no further slack on the far side.  A product that leaves the
-// FP32 range makes the parameter an infinity with the sign of the exact
-// one, which then lies far outside [0, 1], or NaN (an exactly zero offset
-// with d near zero), which fmaxf / fminf skip with the bounds 0 and tmax_s
-// still in place, so such a plane never rejects a box that the exact test
-// accepts.  `tmax_s` is the segment's upper parameter with the slack that
-// covers the FP32 error of a first-hit bound.
+// Conservative segment / quantised-box test of the four-way walk.  With o
+// the segment's start, id the guarded reciprocal of its direction (box_rcp)
+// and D = corner - o, the caller forms per node and axis
+//   a  = step id,   b = fma(D, id, kStartShift),   bn = b - |b| kPlaneRel,
+//   bf = b + |b| kPlaneRel,
+// and grid plane q lies at parameter fma(q, a, bn) when it is the plane the
+// segment meets first on that axis (the lower plane for a non-negative
+// direction component) and at fma(q, a, bf) when it is the other one; qn and
+// qf are those planes' quantised values as floats.  Parameters are shifted
+// by kStartShift: the segment spans [2^-21, 1 + 2^-21].  Both sides are
+// clamped to [0, 1] (a modifier of the max3 / min3, so the limits cost no
+// instruction) and the test is near < far.
+//
+// Why it never rejects a touched box.  id is within 1 ulp, step is a power
+// of two: the roundings of D, id, b, bn / bf and the fma add up to at most
+// 2^-21.4 |b| + 2^-22.4 q |a|.  The margin is 2^-19 |b|, and for every plane
+// with q > 0 also 2^-10 |a| (k_widen places planes at least 2^-10 steps
+// outside the child's box; a lower plane at q = 0 is the exact corner, and
+// its parameter has no term in q).  So each parameter is strictly on the
+// safe side of the exact one, by enough that (i) a box met at t <= 1 has
+// near < 1: there q |a| + |b| >= 1, hence a margin of at least 2^-19 (2^-19 |b|
+// + 2^-10 |a|, q <= 255) minus the shift 2^-21 and the roundings; (ii) a box
+// left at t >= 0 has far >= 2^-21 minus roundings relative to it, so far > 0,
+// also when the start lies exactly on its face (b = 2^-21 then); (iii) in
+// between, near <= exact near <= exact far <= far with a strict step on each
+// side.  Boxes past either end clamp to near = far and are rejected.
+// box_rcp keeps every product finite, so no NaN arises from finite input.
+constexpr float kPlaneRel = 0x1p-19f;
+constexpr float kStartShift = 0x1p-21f;
+constexpr double kQuantMargin = 0x1p-10;  // grid steps between a child's box and its planes
+
 __device__ inline bool qslab_hit(float ax, float ay, float az, float bnx, float bny, float bnz, float bfx,
                                  float bfy, float bfz, float qnx, float qny, float qnz, float qfx, float qfy,
-                                 float qfz, float tmax_s, float &tnear)
+                                 float qfz, float &tnear)
 {
     const float nx = fmaf(qnx, ax, bnx), fx = fmaf(qfx, ax, bfx);
     const float ny = fmaf(qny, ay, bny), fy = fmaf(qfy, ay, bfy);
     const float nz = fmaf(qnz, az, bnz), fz = fmaf(qfz, az, bfz);
-    const float n = fmaxf(fmaxf(nx, ny), fmaxf(nz, 0.0f));
-    const float f = fminf(fminf(fx, fy), fminf(fz, tmax_s));
+    const float n = __builtin_amdgcn_fmed3f(fmaxf(fmaxf(nx, ny), nz), 0.0f, 1.0f);
+    const float f = __builtin_amdgcn_fmed3f(fminf(fminf(fx, fy), fz), 0.0f, 1.0f);
     tnear = n;
-    return n <= f;
+    return n < f;
+}
+
+// Smallest |direction component| the four-way walk inverts as it is: with
+// `scale` the largest |coordinate| of the mesh's box, every plane offset from
+// the segment's start is at most R = scale + |o|, and a component below
+// R 2^-125 is replaced by that value (with its sign), so offset times
+// reciprocal stays below 2^126.  The replacement keeps the box decision
+// exact while every nonzero plane offset is at least R 2^-125: its
+// parameter then lies outside [0, 1] on the same side as the exact one.
+__device__ inline float box_tiny(const Seg &s, float scale)
+{
+    const float R = scale + fmaxf(fmaxf(fabsf(s.ox), fabsf(s.oy)), fabsf(s.oz));
+    return fmaf(R, 0x1p-125f, 0x1p-126f);
+}
+
+// Reciprocal direction for the four-way walk, with the segment cut at tlim
+// (parameters are then fractions of the cut segment, so the box test's
+// limits stay 0 and 1).
+__device__ inline void box_rcp(Seg &s, float tlim, float tiny)
+{
+    const float c = fmaxf(tlim, 0x1p-40f);
+    s.ix = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(s.dx) * c, tiny), s.dx));
+    s.iy = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(s.dy) * c, tiny), s.dy));
+    s.iz = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(s.dz) * c, tiny), s.dz));
 }
 
 // Moller-Trumbore segment / triangle test in FP32, division-free decision

@@ -27,6 +27,8 @@ enum Scalar {
     kOvfFull = 26,     // the overflow table, arena or pool was too small: lists incomplete
     kOvfUsed = 27,     // all hits: overflow-table entries in use (segments with more crossings than slots)
     kArenaUsed = 28,   // all hits: arena records placed into the pool (crossings past the slots)
+    kStackCol = 14,    // columns of the stacks' device-memory part claimed by the query's lanes
+    kSpilled = 15,     // segments whose stack continued in such a column
     kOvfValid = 29,    // all hits: overflow-table entries that are not void (listed in table order)
     kWorkXcd = 32,     // 8 counters, kWorkStride ints (128 bytes) apart: items claimed from each
                        // eighth of the main query pass's items
@@ -98,6 +100,7 @@ struct rsi_bvh {
     int32_t *mesh_height = nullptr;  // [M]
     int32_t *mesh_root = nullptr;    // [M]
     int32_t *mesh_entry = nullptr;   // [M] entry node per mesh, -1 for an empty mesh
+    float *mesh_scale = nullptr;     // [M] largest |coordinate| of each mesh's box
 
     // geometry and tree (device)
     int32_t *T = nullptr;          // index triplets with global vertex indices [n_t*3]
@@ -109,7 +112,7 @@ struct rsi_bvh {
     uint32_t *order = nullptr;     // original triangle per sorted position [n_t]
     int32_t *rank = nullptr;       // sorted position of each triangle (inverse of order) [n_t]
     rsi::Node *nodes = nullptr;    // [max(n_t, 1)]; each mesh's last record is its entry node
-    rsi::Tri *tris = nullptr;      // [n_t] in sorted order
+    rsi::Tri *tris = nullptr;      // [n_t + 1] in sorted order, then a record of zeros (unused four-way slots name it)
     int32_t *arrive = nullptr;     // arrival counters [n_t]
     int32_t *heights = nullptr;    // child heights [2*n_t]
     int32_t *climb = nullptr;      // climbs handed from the local to the global build pass [11*n_t]

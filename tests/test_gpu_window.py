@@ -1,0 +1,35 @@
+"""The four-way walk's stack window: entries past the LDS part move to device
+memory in halves and come back.  Window sizes from one entry to past the
+deepest stack, in every mode, must give the default's answers bit for bit
+(which the parity tests hold to the oracle)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2209_02878_amd import rsi
+from paper_2209_02878_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a, dtype=torch.float32):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype).contiguous()
+
+
+@pytest.mark.parametrize("depth", [1, 3, 5, 6, 9, 255])
+def test_window_sizes_keep_answers(depth):
+    V, T = wl.noisy_sphere(30, 4, 0.3)
+    S, E = wl.segments_in_box(np.random.default_rng(9), V.min(0), V.max(0), 20_011, scale=1.5)
+    V, T, S, E = _t(V), _t(T, torch.int32), _t(S), _t(E)
+    base, small = rsi.Mesh(V, T), rsi.Mesh(V, T, stack_depth=depth)
+    for mode in ("bool", "first", "count", "all", "first|count", "all|first|bool"):
+        want, got = base.query(S, E, mode, capacity=2), small.query(S, E, mode, capacity=2)
+        st = small.stats()
+        assert st["stack_dropped"] == 0 and st["walk_cut"] == 0
+        assert (st["deep_segments"] > 0) == (depth < 255), mode
+        for k in want:
+            if k != "spill":
+                assert torch.equal(want[k], got[k]), (mode, k)
+    base.close()
+    small.close()
