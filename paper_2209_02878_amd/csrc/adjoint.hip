@@ -389,10 +389,15 @@ hipError_t launch_first_hit_adjoint(rsi_bvh *h, const float *V, const float *S, 
             if ((e = grow(&h->inc_vals, cv, n_inc)) != hipSuccess) return e;
             h->inc_cap = n_inc;
         }
+        uint64_t *ksrc = nullptr;
+        uint32_t *vsrc = nullptr;
+        const int bits = bits_for(h->n_v);
+        e = sort_source(h->inc_keys, h->inc_vals, n_inc, bits, h->seg_sort, nullptr, 1, &ksrc, &vsrc);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_adj_incidence, dim3((unsigned)((n_inc + 255) / 256)), dim3(256), 0, s, h->T, h->n_t,
-                           h->rank, h->n_v, h->inc_keys, h->inc_vals);
+                           h->rank, h->n_v, ksrc, vsrc);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        e = radix_sort_pairs(h->inc_keys, h->inc_vals, n_inc, bits_for(h->n_v), h->seg_sort, s);
+        e = radix_sort_pairs(h->inc_keys, h->inc_vals, n_inc, bits, h->seg_sort, s);
         if (e != hipSuccess) return e;
         // first table entry of every vertex (CSR starts; an invalid index sorts last, at n_v)
         if ((e = grow(&h->inc_first, h->inc_first_cap, h->n_v + 2)) != hipSuccess) return e;

@@ -187,6 +187,8 @@ __device__ inline uint64_t spread3(uint32_t v)
     return x;
 }
 
+constexpr int kCodeBits = 63;
+
 __device__ inline uint32_t quantise21(float c, float lo, float ext)
 {
     // floor((c - lo) / ext * 2^21), clamped to [0, 2^21 - 1]; a flat axis maps to 0
@@ -696,10 +698,13 @@ hipError_t launch_build(rsi_bvh *h, const float *V, hipStream_t s)
     hipLaunchKernelGGL(k_init, dim3(init_grid(a)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_centroids, dim3((unsigned)((n + kCentBlock - 1) / kCentBlock)), dim3(kCentBlock), 0, s,
                        a);
-    hipLaunchKernelGGL(k_morton, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
+    const int64_t *mesh_off = h->M > 1 ? h->tri_off : nullptr;
+    BuildArgs km = a;  // the codes go where the sort wants its input
+    hipError_t e = sort_source(h->keys, h->order, n, kCodeBits, h->sort, mesh_off, h->M, &km.keys, &km.order);
     if (e != hipSuccess) return e;
-    e = radix_sort_pairs(h->keys, h->order, n, 63, h->sort, s, h->M > 1 ? h->tri_off : nullptr, h->M);
+    hipLaunchKernelGGL(k_morton, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, km);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    e = radix_sort_pairs(h->keys, h->order, n, kCodeBits, h->sort, s, mesh_off, h->M);
     if (e != hipSuccess) return e;
     e = run_hierarchy(a, s);
     if (e != hipSuccess) return e;

@@ -14,6 +14,8 @@
 namespace rsi {
 namespace {
 
+constexpr int kSegKeyBits = 33;
+
 __global__ void k_seg_bounds_init(int32_t *b)
 {
     if (threadIdx.x < 3) b[threadIdx.x] = 0x7FFFFFFF;      // ordered min
@@ -116,6 +118,10 @@ hipError_t launch_segment_order(rsi_bvh *h, const float *S, const float *E, int6
             return e;
         h->seg_key_cap = n;
     }
+    uint32_t *vals = reinterpret_cast<uint32_t *>(order), *vsrc = nullptr;
+    uint64_t *ksrc = nullptr;
+    if ((e = sort_source(h->seg_keys, vals, n, kSegKeyBits, h->seg_sort, nullptr, 1, &ksrc, &vsrc)) != hipSuccess)
+        return e;
     int32_t *b = h->scalars + kSegBounds;
     hipLaunchKernelGGL(k_seg_bounds_init, dim3(1), dim3(64), 0, s, b);
     int dev = 0, n_cu = 0;
@@ -124,10 +130,10 @@ hipError_t launch_segment_order(rsi_bvh *h, const float *S, const float *E, int6
     int64_t blocks = (n + 255) / 256;
     if (blocks > 4 * (int64_t)n_cu) blocks = 4 * (int64_t)n_cu;
     hipLaunchKernelGGL(k_seg_bounds, dim3((unsigned)blocks), dim3(256), 0, s, S, E, n, b);
-    hipLaunchKernelGGL(k_seg_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, E, n, b, h->seg_keys,
-                       reinterpret_cast<uint32_t *>(order));
+    hipLaunchKernelGGL(k_seg_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, E, n, b, ksrc,
+                       vsrc);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return radix_sort_pairs(h->seg_keys, reinterpret_cast<uint32_t *>(order), n, 33, h->seg_sort, s);
+    return radix_sort_pairs(h->seg_keys, vals, n, kSegKeyBits, h->seg_sort, s);
 }
 
 hipError_t launch_gather_segments(rsi_bvh *h, const float *S, const float *E, const int32_t *order, int64_t n,

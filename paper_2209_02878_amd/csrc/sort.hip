@@ -1,17 +1,19 @@
-// sort.hip -- stable LSD radix sort of (uint64 key, uint32 value) pairs,
-// 8-bit digits, LDS-staged (the Morton-code sorting step timed in the paper's
-// Table 2, which there ran on the host).
+// sort.hip -- stable radix sort of (uint64 key, uint32 value) pairs (the
+// Morton-code sorting step timed in the paper's Table 2, which there ran on
+// the host): stable passes on the top 8-bit digits until the groups of equal
+// prefixes are small, then one pass that orders each group by counting
+// (k_finish; plan_sort says how many passes).
 //
-// One pass per digit:
+// One digit pass:
 //   k_hist     per-tile digit histogram in LDS -> hist[digit][tile]
-//   k_scan     one workgroup turns hist into exclusive global offsets
-//              (digit-major, so the offset of (digit, tile) is the count of
-//              all smaller digits plus this digit in earlier tiles)
+//   k_scan     one workgroup per digit turns its row of hist into the count
+//              of that digit in earlier tiles, and its sum
 //   k_scatter  per tile: stable rank of every element among equal digits
 //              via wave64 ballots, reorder the tile in LDS by digit, then
 //              write each digit run to its global offset (contiguous runs)
-// With at most 64 tiles (inputs up to 128k elements, where the passes are
-// latency bound) every scatter workgroup derives its own offsets from the
+// With at most 16 tiles (inputs up to 32k elements, where the passes are
+// latency bound; at 49 tiles a fused pass took 19 us, the three launches 17)
+// every scatter workgroup derives its own offsets from the
 // raw histograms (no k_scan) and also counts the next pass's digits of the
 // elements it writes, per destination tile, so only the first pass needs
 // k_hist: one launch per pass.  Three histogram buffers rotate: pass p reads
@@ -35,7 +37,7 @@ using rank::scan256;
 using rank::rank_tile;
 constexpr int kItems = 8;                // elements per thread in large sorts
 constexpr int kTile = kThreads * kItems;
-constexpr int kFusedTiles = 64;  // up to this many tiles each workgroup scans the histograms itself
+constexpr int kFusedTiles = 16;  // up to this many tiles each workgroup scans the histograms itself
 
 // Digit of an element for one pass: 8 bits of the key, or (for batches)
 // 8 bits of the mesh that the element's value (a triangle index) belongs to.
@@ -72,90 +74,52 @@ __global__ __launch_bounds__(kThreads) void k_hist(const uint64_t *__restrict__ 
     hist[(int64_t)tid * ntiles + blockIdx.x] = h[tid];
 }
 
-// Exclusive scan of n counts in place by one workgroup of 1024 threads:
-// each thread sums a contiguous chunk, the chunk sums are scanned in LDS,
-// then each thread rewrites its chunk.
-__global__ __launch_bounds__(1024) void k_scan(uint32_t *__restrict__ a, int64_t n)
+// Exclusive scan of every digit's counts over the tiles, in place, one
+// workgroup per digit; total[d] gets the digit's sum (k_scatter turns the
+// sums into the digits' offsets).  One launch; a scan of the whole table
+// (block sums, their scan, a second sweep) took three, 16 us a pass.
+__global__ __launch_bounds__(kThreads) void k_scan(uint32_t *__restrict__ hist, int ntiles,
+                                                   uint32_t *__restrict__ total)
 {
-    __shared__ uint32_t part[1024];
-    const int tid = threadIdx.x;
-    const int64_t chunk = (n + 1023) / 1024;
-    const int64_t lo = tid * chunk;
-    const int64_t hi = lo + chunk < n ? lo + chunk : n;
-    uint32_t sum = 0;
-    for (int64_t i = lo; i < hi; ++i) sum += a[i];
-    part[tid] = sum;
-    __syncthreads();
-    // Hillis-Steele inclusive scan over 1024 partial sums
-    for (int off = 1; off < 1024; off <<= 1) {
-        uint32_t v = tid >= off ? part[tid - off] : 0u;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    uint32_t run = tid ? part[tid - 1] : 0u;
-    for (int64_t i = lo; i < hi; ++i) {
-        uint32_t v = a[i];
-        a[i] = run;
-        run += v;
-    }
-}
-
-// Large tables (many tiles): a three-launch scan.  k_part_sums reduces
-// blocks of kScanChunk counts, k_scan scans those sums (one workgroup), and
-// k_part_apply rescans each block from its offset.
-constexpr int kScanChunk = 4096;
-
-__global__ __launch_bounds__(256) void k_part_sums(const uint32_t *__restrict__ a, int64_t n,
-                                                   uint32_t *__restrict__ part)
-{
-    __shared__ uint32_t ws[4];
-    const int64_t base = (int64_t)blockIdx.x * kScanChunk;
-    uint32_t s = 0;
-    for (int k = threadIdx.x; k < kScanChunk; k += 256) {
-        const int64_t i = base + k;
-        if (i < n) s += a[i];
-    }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (__lane_id() == 0) ws[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
-}
-
-__global__ __launch_bounds__(256) void k_part_apply(uint32_t *__restrict__ a, int64_t n,
-                                                    const uint32_t *__restrict__ part)
-{
-    // each thread owns 16 consecutive counts of the block's 4096
-    __shared__ uint32_t ts[256];
-    const int64_t base = (int64_t)blockIdx.x * kScanChunk + threadIdx.x * 16;
-    uint32_t v[16];
-    uint32_t s = 0;
+    __shared__ uint32_t ws[kWaves];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    uint32_t *const row = hist + (int64_t)blockIdx.x * ntiles;
+    uint32_t base = 0;
+    for (int c0 = 0; c0 < ntiles; c0 += 4 * kThreads) {
+        // four consecutive counts per thread
+        const int i = c0 + 4 * tid;
+        uint32_t v[4];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        v[k] = base + k < n ? a[base + k] : 0u;
-        s += v[k];
-    }
-    ts[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t x = (int)threadIdx.x >= off ? ts[threadIdx.x - off] : 0u;
+        for (int k = 0; k < 4; ++k) v[k] = i + k < ntiles ? row[i + k] : 0u;
+        const uint32_t s = v[0] + v[1] + v[2] + v[3];
+        uint32_t incl = s;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t u = __shfl_up(incl, off, 64);
+            if ((int)__lane_id() >= off) incl += u;
+        }
+        if (__lane_id() == 63) ws[wave] = incl;
         __syncthreads();
-        ts[threadIdx.x] += x;
+        uint32_t run = base + incl - s;
+        for (int w = 0; w < kWaves; ++w) {
+            run += w < wave ? ws[w] : 0u;
+            base += ws[w];
+        }
         __syncthreads();
-    }
-    uint32_t run = part[blockIdx.x] + ts[threadIdx.x] - s;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        if (base + k < n) a[base + k] = run;
-        run += v[k];
+        for (int k = 0; k < 4; ++k) {
+            if (i + k < ntiles) row[i + k] = run;
+            run += v[k];
+        }
     }
+    if (tid == 0) total[blockIdx.x] = base;
 }
 
 // FUSED: `offs` holds the raw per-tile histograms and each workgroup forms
 // its own global digit offsets (few tiles: this saves the separate scan
 // launch); it then also adds the next pass's digit counts of the elements it
 // writes into `hnext` (per destination tile) and clears `hclear`.  Otherwise
-// `offs` is the scanned table.
+// `offs` holds each digit's counts scanned over the tiles, and the digits'
+// sums behind them.
 template <bool FUSED, int IPT>
 __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict__ kin,
                                                       const uint32_t *__restrict__ vin,
@@ -205,8 +169,12 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict
         __syncthreads();
         gbase[tid] += before;
     } else {
-        gbase[tid] = offs[(int64_t)tid * ntiles + blockIdx.x];
+        const uint32_t before = offs[(int64_t)tid * ntiles + blockIdx.x];
+        start[tid] = offs[(int64_t)kRadix * ntiles + tid];
         __syncthreads();
+        scan256(start, gbase);
+        __syncthreads();
+        gbase[tid] += before;
     }
 
     // per round: the lanes of this wave holding the same digit (8 ballots);
@@ -270,132 +238,50 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict
     }
 }
 
-// A bucket of at most IPT * kThreads elements: all low passes in LDS.
-template <int IPT>
-__device__ inline void sort_bucket_lds(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
-                                       uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, uint32_t b0,
-                                       uint32_t bn, int nlow, uint32_t *wcnt, uint32_t *run, uint32_t *start,
-                                       uint64_t *skey, uint32_t *sval)
-{
-    const int tid = threadIdx.x;
-    uint64_t key[IPT];
-    uint32_t val[IPT], dig[IPT], pos[IPT];
-    bool valid[IPT];
-#pragma unroll
-    for (int r = 0; r < IPT; ++r) {
-        const uint32_t i = (uint32_t)(r * kThreads + tid);
-        valid[r] = i < bn;
-        key[r] = valid[r] ? kin[b0 + i] : 0ull;
-        val[r] = valid[r] ? vin[b0 + i] : 0u;
-    }
-    for (int p = 0; p < nlow; ++p) {
-#pragma unroll
-        for (int r = 0; r < IPT; ++r) dig[r] = valid[r] ? (uint32_t)(key[r] >> (8 * p)) & (kRadix - 1) : 0u;
-        rank_tile<IPT>(dig, valid, pos, wcnt, run, start);
-#pragma unroll
-        for (int r = 0; r < IPT; ++r)
-            if (valid[r]) {
-                skey[pos[r]] = key[r];
-                sval[pos[r]] = val[r];
-            }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < IPT; ++r)
-            if (valid[r]) {
-                key[r] = skey[r * kThreads + tid];
-                val[r] = sval[r * kThreads + tid];
-            }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < IPT; ++r)
-        if (valid[r]) {
-            kout[b0 + r * kThreads + tid] = key[r];
-            vout[b0 + r * kThreads + tid] = val[r];
-        }
-}
+// A group too large for the window below: the stable passes over its `low`
+// low key bits in device memory by one workgroup, one histogram sweep and
+// one tile-by-tile scatter sweep per pass, alternating between the range in
+// kin and in kout (the result ends in kout).
+constexpr int kLargeItems = 4;
 
-// A small bucket (at most 2 * kThreads keys, all with the same top digit):
-// every key's place is the number of keys below it, equal keys counted by
-// their index, i.e. the place of a stable sort by the whole key, which is
-// what the low passes compute; the keys are read from LDS by all threads at
-// the same index (broadcast).  About bn compares per thread instead of
-// nlow stable ranking rounds.
-__device__ inline void sort_bucket_count(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
-                                         uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, uint32_t b0,
-                                         uint32_t bn, uint64_t *skey)
+__device__ inline void sort_group_global(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
+                                         uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t b0,
+                                         int64_t bn, int low, uint32_t *wcnt, uint32_t *run, uint32_t *start,
+                                         uint32_t *gcount, uint32_t *gbase)
 {
     const int tid = threadIdx.x;
-    uint64_t key[2];
-    uint32_t val[2], below[2] = {0u, 0u};
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const uint32_t i = (uint32_t)(r * kThreads + tid);
-        key[r] = i < bn ? kin[b0 + i] : ~0ull;
-        val[r] = i < bn ? vin[b0 + i] : 0u;
-        if (i < bn) skey[i] = key[r];
-    }
-    __syncthreads();
-    for (uint32_t j = 0; j < bn; ++j) {
-        const uint64_t kj = skey[j];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const uint32_t i = (uint32_t)(r * kThreads + tid);
-            below[r] += (kj < key[r] || (kj == key[r] && j < i)) ? 1u : 0u;
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const uint32_t i = (uint32_t)(r * kThreads + tid);
-        if (i < bn) {
-            kout[b0 + below[r]] = key[r];
-            vout[b0 + below[r]] = val[r];
-        }
-    }
-}
-
-// A larger bucket: the same stable low passes over its range in device
-// memory, one histogram sweep and one tile-by-tile scatter sweep per pass,
-// alternating between the range in kin and in kout (the result ends in kout).
-__device__ inline void sort_bucket_global(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
-                                          uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, uint32_t b0,
-                                          uint32_t bn, int nlow, uint32_t *wcnt, uint32_t *run, uint32_t *start,
-                                          uint32_t *gcount, uint32_t *gbase)
-{
-    const int tid = threadIdx.x;
-    uint64_t *ks = kin, *kd = kout;
-    uint32_t *vs = vin, *vd = vout;
-    for (int p = 0; p < nlow; ++p) {
-        const int shift = 8 * p;
+    uint64_t *ks = kin + b0, *kd = kout + b0;
+    uint32_t *vs = vin + b0, *vd = vout + b0;
+    for (int shift = 0; shift < low; shift += 8) {
+        const uint32_t mask = low - shift < 8 ? (1u << (low - shift)) - 1u : kRadix - 1u;
         gcount[tid] = 0;
         __syncthreads();
-        for (uint32_t i = tid; i < bn; i += kThreads)
-            atomicAdd(&gcount[(uint32_t)(ks[b0 + i] >> shift) & (kRadix - 1)], 1u);
+        for (int64_t i = tid; i < bn; i += kThreads) atomicAdd(&gcount[(uint32_t)(ks[i] >> shift) & mask], 1u);
         __syncthreads();
-        // a digit that every element of the bucket shares changes no order
-        if (gcount[(uint32_t)(ks[b0] >> shift) & (kRadix - 1)] == bn) {
+        // a digit that every element of the group shares changes no order
+        if (gcount[(uint32_t)(ks[0] >> shift) & mask] == (uint32_t)bn) {
             __syncthreads();
             continue;
         }
         scan256(gcount, gbase);
         __syncthreads();
-        for (uint32_t c0 = 0; c0 < bn; c0 += kTile) {
-            uint64_t key[kItems];
-            uint32_t val[kItems], dig[kItems], pos[kItems];
-            bool valid[kItems];
+        for (int64_t c0 = 0; c0 < bn; c0 += kThreads * kLargeItems) {
+            uint64_t key[kLargeItems];
+            uint32_t val[kLargeItems], dig[kLargeItems], pos[kLargeItems];
+            bool valid[kLargeItems];
 #pragma unroll
-            for (int r = 0; r < kItems; ++r) {
-                const uint32_t i = c0 + (uint32_t)(r * kThreads + tid);
+            for (int r = 0; r < kLargeItems; ++r) {
+                const int64_t i = c0 + r * kThreads + tid;
                 valid[r] = i < bn;
-                key[r] = valid[r] ? ks[b0 + i] : 0ull;
-                val[r] = valid[r] ? vs[b0 + i] : 0u;
-                dig[r] = valid[r] ? (uint32_t)(key[r] >> shift) & (kRadix - 1) : 0u;
+                key[r] = valid[r] ? ks[i] : 0ull;
+                val[r] = valid[r] ? vs[i] : 0u;
+                dig[r] = valid[r] ? (uint32_t)(key[r] >> shift) & mask : 0u;
             }
-            rank_tile<kItems>(dig, valid, pos, wcnt, run, start);
+            rank_tile<kLargeItems>(dig, valid, pos, wcnt, run, start);
 #pragma unroll
-            for (int r = 0; r < kItems; ++r)
+            for (int r = 0; r < kLargeItems; ++r)
                 if (valid[r]) {
-                    const uint32_t dst = b0 + gbase[dig[r]] + (pos[r] - start[dig[r]]);
+                    const int64_t dst = (int64_t)gbase[dig[r]] + (pos[r] - start[dig[r]]);
                     kd[dst] = key[r];
                     vd[dst] = val[r];
                 }
@@ -406,68 +292,129 @@ __device__ inline void sort_bucket_global(uint64_t *__restrict__ kin, uint32_t *
         uint64_t *tk = ks; ks = kd; kd = tk;
         uint32_t *tv = vs; vs = vd; vd = tv;
     }
-    if (ks != kout) {  // an even number of passes left the result in kin's range
-        for (uint32_t i = tid; i < bn; i += kThreads) {
-            kout[b0 + i] = ks[b0 + i];
-            vout[b0 + i] = vs[b0 + i];
+    if (ks != kout + b0) {  // an even number of passes left the result in kin's range
+        for (int64_t i = tid; i < bn; i += kThreads) {
+            kout[b0 + i] = ks[i];
+            vout[b0 + i] = vs[i];
         }
     }
 }
 
-// One workgroup per top-digit bucket.  kin/vin hold the elements grouped
-// by their top digit (stable); `hist` holds that digit's per-tile counts
-// (digit-major), raw or (`scanned`) as the exclusive scan of the whole
-// table, whose entry (d, tile 0) is bucket d's offset.  Each bucket is
-// sorted by its `nlow` lower digits and written to the same offsets in
-// kout/vout: in LDS up to kBucketLds elements, else over device memory.
-constexpr int kBucketLds = 16 * kThreads;
-
-__global__ __launch_bounds__(kThreads) void k_bucket_sort(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
-                                                          uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
-                                                          const uint32_t *__restrict__ hist, int ntiles, int64_t n,
-                                                          int scanned, int nlow)
+// The last pass of a key sort: kin/vin are in stable order of key >> low
+// (within each mesh's range of positions); each group of equal prefixes is
+// put in key order into kout/vout.  The passes before it have made the
+// groups small (tens of keys), so a key's place is found by counting: its
+// group's start plus the keys of the group below it, equal keys by position,
+// which is the place a stable sort by the whole key gives it.  A workgroup
+// takes TILE consecutive keys, with HALO more on either side in LDS: a group
+// of up to HALO keys is then seen whole by every tile it touches.  A larger
+// one (visible extent above HALO, which every tile it touches finds alike)
+// is left to the workgroup whose tile holds its first key.  (Its passes
+// permute the group's range of kin while other tiles may still load it as
+// their halo: those only compare its prefixes, which are all the same.)
+//
+// Counting replaces sorting each top-8-bit bucket in one workgroup, which at
+// 499,280 keys took 189 us and at 4M 1,187 us (a 16,000-key bucket streamed
+// through one workgroup).
+//
+// The window's keys lie in LDS shifted up by 12 bits (their prefixes, equal
+// within a group, may fall off) with their window position below, so keys
+// are distinct and one 64-bit compare counts equal keys by position; PACKED
+// false (low > 52) compares key and position.  The first keys of the groups
+// are one bit each.
+template <int TILE, int HALO, bool PACKED>
+__global__ __launch_bounds__(kThreads) void k_finish(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
+                                                     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
+                                                     int64_t n, int low, const int64_t *__restrict__ off, int32_t M)
 {
-    __shared__ uint32_t wcnt[16 * kWaves * kRadix];
-    __shared__ uint32_t run[kRadix], start[kRadix], gcount[kRadix], gbase[kRadix];
-    __shared__ uint64_t skey[kBucketLds];
-    __shared__ uint32_t sval[kBucketLds];
+    constexpr int kWin = TILE + 2 * HALO;
+    static_assert(kWin <= 4096 && kWin % 64 == 0, "window positions take 12 bits, group starts whole words");
+    constexpr int kWork = kLargeItems * kWaves * kRadix + 4 * kRadix;  // words of the large-group passes
+    __shared__ union {
+        uint64_t key[kWin];
+        uint32_t work[kWork];
+    } sh;
+    __shared__ uint64_t head[kWin / 64];        // bit j of word w: window position 64 w + j starts a group
+    __shared__ int64_t large[TILE / HALO + 1];  // first keys of large groups: more than HALO keys apart
+    __shared__ int n_large;
     const int tid = threadIdx.x;
-    uint32_t b0, bn;
-    if (scanned) {
-        const int d = blockIdx.x;
-        b0 = hist[(int64_t)d * ntiles];
-        const uint32_t end = d + 1 < kRadix ? hist[(int64_t)(d + 1) * ntiles] : (uint32_t)n;
-        bn = end - b0;
-    } else {
-        // bucket sizes and offsets: digit tid's total over the tiles, scanned
-        uint32_t tot = 0;
-        for (int b = 0; b < ntiles; ++b) tot += hist[(int64_t)tid * ntiles + b];
-        gcount[tid] = tot;
-        __syncthreads();
-        scan256(gcount, gbase);
-        __syncthreads();
-        b0 = gbase[blockIdx.x];
-        bn = gcount[blockIdx.x];
-        __syncthreads();
+    const int64_t t0 = (int64_t)blockIdx.x * TILE;
+    const int64_t w0 = t0 - HALO > 0 ? t0 - HALO : 0;
+    const int nw = (int)((t0 + TILE + HALO < n ? t0 + TILE + HALO : n) - w0);
+    if (tid == 0) n_large = 0;
+    // all loads first: one memory latency for the whole window
+    constexpr int kPer = kWin / kThreads;
+    static_assert(kWin % kThreads == 0, "whole rounds");
+    uint64_t win[kPer], prev[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int p = r * kThreads + tid;
+        win[r] = p < nw ? kin[w0 + p] : 0ull;
+        prev[r] = p > 0 && p < nw && __lane_id() == 0 ? kin[w0 + p - 1] : 0ull;
     }
-    if (bn == 0) return;
-    if (bn <= 2u * kThreads)
-        sort_bucket_count(kin, vin, kout, vout, b0, bn, skey);
-    else if (bn <= (uint32_t)kTile)
-        sort_bucket_lds<kItems>(kin, vin, kout, vout, b0, bn, nlow, wcnt, run, start, skey, sval);
-    else if (bn <= (uint32_t)kBucketLds)
-        sort_bucket_lds<16>(kin, vin, kout, vout, b0, bn, nlow, wcnt, run, start, skey, sval);
-    else
-        sort_bucket_global(kin, vin, kout, vout, b0, bn, nlow, wcnt, run, start, gcount, gbase);
-}
-
-__global__ void k_copy_pairs(const uint64_t *__restrict__ ks, const uint32_t *__restrict__ vs,
-                             uint64_t *__restrict__ kd, uint32_t *__restrict__ vd, int64_t n)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        kd[i] = ks[i];
-        vd[i] = vs[i];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int p = r * kThreads + tid;
+        const uint64_t k = win[r];
+        uint64_t before = __shfl_up(k, 1, 64);
+        if (__lane_id() == 0) before = prev[r];
+        // a position past the last key starts a group (of nothing), and so
+        // does the window's first
+        bool first = p == 0 || p >= nw || (before >> low) != (k >> low);
+        if (off && !first) first = off[mesh_of(off, M, w0 + p)] == w0 + p;
+        sh.key[p] = PACKED ? (k << 12) | (uint64_t)p : k;
+        const uint64_t m = __ballot(first);
+        if (__lane_id() == 0) head[p >> 6] = m;
+    }
+    __syncthreads();
+    for (int q = tid; q < TILE; q += kThreads) {
+        const int64_t i = t0 + q;
+        if (i >= n) break;
+        const int me = (int)(i - w0);
+        // the group's visible extent [b, e): the last start up to me, the
+        // first one after it (or the window's end)
+        int w = me >> 6;
+        uint64_t m = head[w] & (~0ull >> (63 - (me & 63)));
+        while (m == 0) m = head[--w];  // bit 0 of word 0 is set
+        const int b = 64 * w + 63 - __clzll((long long)m);
+        w = (me + 1) >> 6;
+        m = w < kWin / 64 ? head[w] & (~0ull << ((me + 1) & 63)) : 0;
+        while (m == 0 && ++w < kWin / 64) m = head[w];
+        const int e = m ? 64 * w + __builtin_ctzll(m) : kWin;
+        if (e - b > HALO) {
+            // (an extent cut by the window starts before the tile)
+            if (me == b) large[atomicAdd(&n_large, 1)] = i;
+            continue;
+        }
+        const uint64_t k = sh.key[me];
+        int below = 0;
+#pragma unroll 4
+        for (int j = b; j < e; ++j) {
+            const uint64_t kj = sh.key[j];
+            below += (PACKED ? kj < k : kj < k || (kj == k && j < me)) ? 1 : 0;
+        }
+        const int64_t dst = w0 + b + below;
+        kout[dst] = PACKED ? kin[i] : k;
+        vout[dst] = vin[i];
+    }
+    __syncthreads();
+    const int nl = n_large;
+    for (int g = 0; g < nl; ++g) {
+        const int64_t b0 = large[g];
+        // the group's end: the first later key with another prefix, or its mesh's last
+        int64_t lo = b0 + 1, hi = n;
+        if (off) hi = off[mesh_of(off, M, b0) + 1];
+        const uint64_t pre = kin[b0] >> low;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((kin[mid] >> low) <= pre) lo = mid + 1;
+            else hi = mid;
+        }
+        uint32_t *w = sh.work;
+        sort_group_global(kin, vin, kout, vout, b0, lo - b0, low, w, w + kLargeItems * kWaves * kRadix,
+                          w + kLargeItems * kWaves * kRadix + kRadix, w + kLargeItems * kWaves * kRadix + 2 * kRadix,
+                          w + kLargeItems * kWaves * kRadix + 3 * kRadix);
+        __syncthreads();
     }
 }
 
@@ -487,10 +434,8 @@ hipError_t ensure_sort_scratch(SortScratch &sc, int64_t n)
         sc.cap = n;
     }
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    // fused path: three rotating histograms; else one table plus the
-    // partial sums of the three-launch scan
-    const int64_t hn = (ntiles <= kFusedTiles ? 3 * kFusedTiles * kRadix
-                                                  : ntiles * kRadix + (ntiles * kRadix + kScanChunk - 1) / kScanChunk);
+    // fused path: three rotating histograms; else one table and the digits' sums
+    const int64_t hn = ntiles <= kFusedTiles ? 3 * kFusedTiles * kRadix : (ntiles + 1) * kRadix;
     if (hn > sc.hist_cap) {
         if (sc.hist) (void)hipFree(sc.hist);
         sc.hist = nullptr;
@@ -530,24 +475,63 @@ void fused_passes(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_
     }
 }
 
-// Exclusive scan of a digit-major histogram table in place: one workgroup
-// for small tables, else block sums, their scan and a rescan of each block.
-static void scan_table(uint32_t *hist, int64_t hsz, hipStream_t s)
+// The passes of a sort.  Key sorts (first_bit 0): `prefix` stable passes on
+// the top 8-bit digits, so that the groups of equal prefixes hold tens of
+// keys, then k_finish over the `low` other bits, however many they are.  The
+// number of passes goes by n (by n per mesh in a batch, whose groups lie
+// inside a mesh) alone: none while one group may hold every key (k_finish
+// alone), one while 256 groups keep the count loop short, two up to 2^20
+// keys, else three.  Measured: 29,768 triangles, k_finish 18 us after one
+// pass and 6 us after two (a pass: 9 us); 4M segments, 189 us after two (the
+// densest groups pass 512 keys) and 32 us after three (a pass: 55 us).  Keys
+// of no more bits than that, and passes that start above bit 0 (which leave
+// the lower bits unsorted), run as digit passes only.  With mesh_off (M > 1)
+// the mesh id's digits follow the key's, so each mesh's elements end up
+// contiguous, and k_finish works inside each mesh's range.
+struct SortPlan {
+    Digit pass[16];
+    int np = 0;
+    int low = 0;   // key bits left to k_finish (0: none)
+    int moves = 0; // times the pairs change buffers
+};
+
+constexpr int64_t kOneGroup = 256;
+constexpr int64_t kOnePass = 16384;
+constexpr int64_t kTwoPasses = int64_t(1) << 20;
+
+static SortPlan plan_sort(int64_t n, int key_bits, int first_bit, const int64_t *mesh_off, int32_t M)
 {
-    if (hsz <= 4 * kScanChunk) {
-        hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, hist, hsz);
-    } else {
-        const int64_t nparts = (hsz + kScanChunk - 1) / kScanChunk;
-        uint32_t *part = hist + hsz;
-        hipLaunchKernelGGL(k_part_sums, dim3((unsigned)nparts), dim3(256), 0, s, hist, hsz, part);
-        hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, part, nparts);
-        hipLaunchKernelGGL(k_part_apply, dim3((unsigned)nparts), dim3(256), 0, s, hist, hsz, part);
+    SortPlan p;
+    int from = first_bit;
+    const bool batch = mesh_off && M > 1;
+    if (first_bit == 0) {
+        const int64_t per = batch ? n / M : n;
+        const int prefix = n <= kOneGroup ? 0 : n <= kOnePass ? 1 : per <= kTwoPasses ? 2 : 3;
+        if (8 * prefix < key_bits) p.low = from = key_bits - 8 * prefix;
     }
+    for (int b = from; b < key_bits; b += 8) p.pass[p.np++] = Digit{nullptr, 0, b};
+    if (batch) {
+        p.pass[p.np++] = Digit{mesh_off, M, 0};
+        if (M > 256) p.pass[p.np++] = Digit{mesh_off, M, 8};
+    }
+    p.moves = p.np + (p.low ? 1 : 0);
+    return p;
 }
 
-// Inputs up to kRadix * kBucketLarge keys take the bucket sort (an average
-// bucket of at most kBucketLarge keys per workgroup).
-constexpr uint32_t kBucketLarge = 16384;
+hipError_t sort_source(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, SortScratch &sc,
+                       const int64_t *mesh_off, int32_t M, uint64_t **ksrc, uint32_t **vsrc)
+{
+    *ksrc = keys;
+    *vsrc = vals;
+    if (n <= 1 || key_bits <= 0) return hipSuccess;
+    const hipError_t e = ensure_sort_scratch(sc, n);
+    if (e != hipSuccess) return e;
+    if (plan_sort(n, key_bits, 0, mesh_off, M).moves & 1) {
+        *ksrc = sc.keys_alt;
+        *vsrc = sc.vals_alt;
+    }
+    return hipSuccess;
+}
 
 hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, SortScratch &sc,
                             hipStream_t s, const int64_t *mesh_off, int32_t M, int first_bit, uint64_t **kres,
@@ -559,82 +543,49 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
     hipError_t e = ensure_sort_scratch(sc, n);
     if (e != hipSuccess) return e;
     const int ntiles = (int)((n + kTile - 1) / kTile);
-    // key digits first, then (batches) the mesh id as the most significant
-    // digits, so each mesh's elements end up contiguous in key order
-    Digit passes[16];
-    int np = 0;
-    for (int b = first_bit; b < key_bits; b += 8) passes[np++] = Digit{nullptr, 0, b};
-    if (mesh_off && M > 1) {
-        passes[np++] = Digit{mesh_off, M, 0};
-        if (M > 256) passes[np++] = Digit{mesh_off, M, 8};
-    }
+    const SortPlan p = plan_sort(n, key_bits, first_bit, mesh_off, M);
     uint64_t *ka = keys, *kb = sc.keys_alt;
     uint32_t *va = vals, *vb = sc.vals_alt;
-    const int64_t hsz = (int64_t)ntiles * kRadix;
-    // Key digits by buckets: one stable pass on the top 8 bits groups the
-    // elements into 256 buckets, then one workgroup per bucket sorts it by
-    // the lower digits (k_bucket_sort), so three or four launches replace
-    // one or more per digit.  Inputs up to kRadix * kBucketLarge keys take
-    // this path without looking at the data (nothing is read back, so the
-    // call stays stream-ordered and can be captured): buckets up to
-    // kBucketLds keys sort in LDS, a larger one streams through device
-    // memory inside its workgroup, which is slower but only meets meshes
-    // whose triangles crowd into a few of the top-level Morton cells.
-    int p0 = 0;  // first pass still to run
-    if (key_bits > 8 && first_bit == 0) {
-        const int top = key_bits - 8;
-        const Digit dtop{nullptr, 0, top};
-        const int nlow = (top + 7) / 8;
-        if (ntiles <= kFusedTiles) {
-            hipLaunchKernelGGL(k_hist<kItems>, dim3(ntiles), dim3(kThreads), 0, s, ka, va, n, dtop, sc.hist, ntiles,
-                               nullptr);
-            hipLaunchKernelGGL((k_scatter<true, kItems>), dim3(ntiles), dim3(kThreads), 0, s, ka, va, kb, vb, n,
-                               dtop, sc.hist, ntiles, dtop, nullptr, nullptr);
-            hipLaunchKernelGGL(k_bucket_sort, dim3(kRadix), dim3(kThreads), 0, s, kb, vb, ka, va, sc.hist, ntiles, n,
-                               0, nlow);
-            p0 = (key_bits + 7) / 8;
-        } else if (n <= (int64_t)kRadix * kBucketLarge) {  // else even the average bucket is too large
-            hipLaunchKernelGGL(k_hist<kItems>, dim3(ntiles), dim3(kThreads), 0, s, ka, va, n, dtop, sc.hist, ntiles,
-                               nullptr);
-            scan_table(sc.hist, hsz, s);
-            hipLaunchKernelGGL((k_scatter<false, kItems>), dim3(ntiles), dim3(kThreads), 0, s, ka, va, kb, vb, n,
-                               dtop, sc.hist, ntiles, dtop, nullptr, nullptr);
-            hipLaunchKernelGGL(k_bucket_sort, dim3(kRadix), dim3(kThreads), 0, s, kb, vb, ka, va, sc.hist, ntiles, n,
-                               1, nlow);
-            p0 = (key_bits + 7) / 8;
-        }
-    }
-    if (p0 == np) return hipGetLastError();
-    if (ntiles <= kFusedTiles) {
+    auto swap = [&]() {
+        uint64_t *tk = ka; ka = kb; kb = tk;
+        uint32_t *tv = va; va = vb; vb = tv;
+    };
+    // without kres the input is where sort_source said, so that the result
+    // ends in keys / vals
+    if (!kres && (p.moves & 1)) swap();
+    if (p.np > 0 && ntiles <= kFusedTiles) {
         // (smaller tiles, hence more workgroups, measured slower: each
         // workgroup then scans more histograms and the next-pass counters
         // see more atomic traffic)
-        fused_passes<kItems>(ka, va, kb, vb, n, passes + p0, np - p0, sc, s);
-        if ((np - p0) & 1) {
-            uint64_t *tk = ka; ka = kb; kb = tk;
-            uint32_t *tv = va; va = vb; vb = tv;
-        }
+        fused_passes<kItems>(ka, va, kb, vb, n, p.pass, p.np, sc, s);
+        if (p.np & 1) swap();
     } else {
-        for (int p = p0; p < np; ++p) {
-            const Digit dg = passes[p];
+        for (int q = 0; q < p.np; ++q) {
+            const Digit dg = p.pass[q];
             hipLaunchKernelGGL(k_hist<kItems>, dim3(ntiles), dim3(kThreads), 0, s, ka, va, n, dg, sc.hist, ntiles,
                                nullptr);
-            scan_table(sc.hist, hsz, s);
+            hipLaunchKernelGGL(k_scan, dim3(kRadix), dim3(kThreads), 0, s, sc.hist, ntiles,
+                               sc.hist + (int64_t)ntiles * kRadix);
             hipLaunchKernelGGL((k_scatter<false, kItems>), dim3(ntiles), dim3(kThreads), 0, s, ka, va, kb, vb, n, dg,
                                sc.hist, ntiles, dg, nullptr, nullptr);
-            uint64_t *tk = ka; ka = kb; kb = tk;
-            uint32_t *tv = va; va = vb; vb = tv;
+            swap();
         }
+    }
+    if (p.low) {
+        const int64_t *off = mesh_off && M > 1 ? mesh_off : nullptr;
+        auto finish = [&](auto kern, int tile) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)((n + tile - 1) / tile)), dim3(kThreads), 0, s, ka, va, kb, vb,
+                               n, p.low, off, M);
+        };
+        // small sorts: more workgroups
+        if (p.low > 52) finish(k_finish<256, 512, false>, 256);
+        else if (n <= 131072) finish(k_finish<256, 512, true>, 256);
+        else finish(k_finish<2048, 512, true>, 2048);
+        swap();
     }
     if (kres && vres) {  // the caller takes the result where it is
         *kres = ka;
         *vres = va;
-        return hipGetLastError();
-    }
-    if (ka != keys) {
-        const int blk = 256;
-        hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)((n + blk - 1) / blk)), dim3(blk), 0, s, ka, va, keys,
-                           vals, n);
     }
     return hipGetLastError();
 }

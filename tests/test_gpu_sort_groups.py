@@ -1,0 +1,82 @@
+"""The sort's last pass at the sizes where it can go wrong: groups of equal
+key prefixes around the window's halo (512 keys) and far past it,
+keys equal throughout (the order must stay stable), and totals around the
+changes of the number of digit passes.  Held bit for bit to a stable host
+sort of the same keys, through the segment order; the Morton order of a
+clustered batch is held to single builds."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2209_02878_amd import rsi
+from paper_2209_02878_amd import workloads as wl
+from tests.test_gpu_order import host_keys
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a, dtype=torch.float32):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype).contiguous()
+
+
+def _order(S, E):
+    V, T = wl.noisy_sphere(2, 5, 0.3)
+    mesh = rsi.Mesh(_t(V), _t(T, torch.int32))
+    order, _, _ = mesh.segment_order(_t(S), _t(E))
+    got = order.cpu().numpy()
+    mesh.close()
+    return got
+
+
+def _clusters(sizes, width, rng):
+    """Segments whose midpoints crowd into one small cube per entry of
+    `sizes` (shuffled), a few far ones setting the box."""
+    mids = [np.array([[0, 0, 0], [1, 1, 1]], np.float64)]
+    for s in sizes:
+        mids.append(rng.uniform(0.05, 0.95, 3) + width * rng.uniform(-1, 1, (s, 3)))
+    m = np.concatenate(mids)
+    m = m[rng.permutation(len(m))]
+    d = rng.uniform(0.001, 0.002, 3)
+    return (m - d).astype(np.float32), (m + d).astype(np.float32)
+
+
+@pytest.mark.parametrize("width", [0.0, 1e-3, 8e-3])
+@pytest.mark.parametrize("sizes", [
+    [511, 512, 513, 1023, 1025, 2500, 1, 7],                         # one pass
+    [511, 512, 513, 1025, 2047, 2049, 4097, 30_000, 1] + [600] * 20,  # two passes, tiles of 256
+    [511, 512, 513, 1025, 2047, 2049, 70_000, 3] + [515] * 200,       # two passes, tiles of 2,048
+])
+def test_clustered_segments(sizes, width):
+    rng = np.random.default_rng(len(sizes))
+    S, E = _clusters(sizes, width, rng)
+    assert np.array_equal(_order(S, E), np.argsort(host_keys(S, E), kind="stable"))
+
+
+@pytest.mark.parametrize("n", [2, 255, 256, 257, 1023, 1024, 1025, 16_384, 16_385, 32_768, 32_769, 131_072, 131_073, 1_048_577])
+def test_totals_around_the_plan_changes(n):
+    rng = np.random.default_rng(n)
+    S, E = wl.segments_in_box(rng, [0, 0, 0], [1, 1, 0.1], n)
+    assert np.array_equal(_order(S, E), np.argsort(host_keys(S, E), kind="stable"))
+
+
+def test_clustered_batch_matches_single_builds():
+    rng = np.random.default_rng(3)
+    meshes = []
+    for n_t, spread in ((1, 1.0), (900, 0.0), (3_000, 1e-4), (1_300, 1e-7), (70_000, 1e-3), (2, 1.0)):
+        c = rng.uniform(0, 1, (n_t, 1, 3)) * spread + rng.integers(0, 2, (n_t, 1, 3))
+        V = (c + 0.01 * rng.uniform(-1, 1, (n_t, 3, 3)) * (spread > 0)).reshape(-1, 3).astype(np.float32)
+        meshes.append((_t(V), _t(np.arange(3 * n_t).reshape(n_t, 3), torch.int32)))
+    batch = rsi.Batch(meshes)
+    tree, base = batch.tree(), 0
+    for V, T in meshes:
+        m = rsi.Mesh(V, T)
+        one, n = m.tree(), T.shape[0]
+        assert np.array_equal(tree["order"][base:base + n] - base, one["order"])
+        assert np.array_equal(tree["keys"][base:base + n], one["keys"])
+        assert np.array_equal(np.argsort(one["keys"], kind="stable"), np.arange(n))
+        same = one["keys"][1:] == one["keys"][:-1]
+        assert np.all(one["order"][1:][same] > one["order"][:-1][same])
+        base += n
+        m.close()
+    batch.close()
