@@ -105,12 +105,26 @@ struct QArgs {
     int32_t defer;       // test pending leaves once fewer lanes than this can step
     int32_t refill;      // fetch new segments once this many lanes are idle
     int32_t chunk;       // work items a wave claims per atomic on a range counter
+    int32_t own_max;     // four-way walk: items a wave walks at a time (64, or fewer when there are few items)
     // batched queries: work item k belongs to mesh m with bt.seg_off[m] <= k < bt.seg_off[m+1]
     int32_t M;
     const int32_t *mesh_entry;
     const float *mesh_scale;  // per mesh: the largest |coordinate| of its box
     BatchTables bt;
 };
+
+// The launch's arguments, for code that runs seldom (claims, segment starts
+// and ends, overflowed lists): fields read through this reference are loaded
+// where they are used, instead of living in scalar registers through the
+// walk's loops (the all-hits walks had 33 to 44 of those spilled).  Every
+// kernel of this file has QArgs as its only argument.
+__device__ inline const QArgs &seldom()
+{
+    typedef const __attribute__((address_space(4))) QArgs *ptr;
+    ptr p = (ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const QArgs *)p;
+}
 
 // Streaming accesses (segment ends in, results out).
 template <typename T>
@@ -236,6 +250,7 @@ struct Lane {
     int32_t mesh;      // batched queries: the segment's mesh
     int32_t hp0, hp1, hp2, hp3;  // all hits, capacity <= 4: the hit positions found so far
     bool found;
+    int32_t own;       // four-way walk: the lane whose segment this lane walks (itself, or the one it helps)
     bool retry;        // the stack outgrew the pass's stack: the deep pass walks this segment again
 };
 
@@ -324,13 +339,14 @@ __device__ inline void take_crossing(const QArgs &a, Lane &L, int32_t pos, volat
         } else {
             // past the slots: an arena record (entry, rank, position);
             // the segment's overflow-table entry is taken at its first
-            const int32_t e = wave_take<0>(a, wst, c == K);
+            const QArgs &b = seldom();
+            const int32_t e = wave_take<0>(b, wst, c == K);
             if (c == K) L.e = e;
-            const int32_t r = wave_take<1>(a, wst, true);
-            if (L.e < a.ovf_cap && r >= 0 && r < a.arena_cap)
-                a.arena[r] = make_int4(L.e, c, pos, 0);
+            const int32_t r = wave_take<1>(b, wst, true);
+            if (L.e < b.ovf_cap && r >= 0 && r < b.arena_cap)
+                b.arena[r] = make_int4(L.e, c, pos, 0);
             else
-                atomicOr(&a.scalars[kOvfFull], 1);
+                atomicOr(&b.scalars[kOvfFull], 1);
         }
     }
 }
@@ -378,11 +394,11 @@ __device__ inline void wave_lds_sync()
 // outcome of a leaf is the set of its triangles crossed (a bit mask) and,
 // for the first hit, its best crossing in (t, id) order: the owner's results
 // are the same as from testing its leaves itself, in any order.  The plain
-// boolean query needs one bit per lane (a flag in the queue entry of the
-// owner's number); the other modes get the outcome back through the queue
-// entry of the pair.
+// boolean query needs one bit per segment (a flag in the queue entry of the
+// lane that holds the segment, which also stops the lanes that help it); the
+// other modes get the outcome back through the queue entry of the pair.
 template <uint32_t MODE>
-using LeafEnt = typename std::conditional<MODE == M_BOOL, int2, int4>::type;
+using LeafEnt = typename std::conditional<MODE == M_BOOL || (MODE & M_ALL) != 0, int2, int4>::type;
 
 template <uint32_t MODE, bool COUNT, typename Pop>
 __device__ inline void leaf_phase4(const QArgs &a, Lane &L, int32_t &cur, Pop pop, uint32_t &tests,
@@ -461,9 +477,10 @@ __device__ inline void leaf_phase4(const QArgs &a, Lane &L, int32_t &cur, Pop po
     }
     // outcomes back to the owners
     if constexpr (MODE == M_BOOL) {
-        if (mask) q[own].x = 1;
+        const int32_t seg_lane = __shfl(L.own, own, 64);
+        if (mask) q[seg_lane].x = 1;
         wave_lds_sync();
-        if (q[lane].x) {
+        if (q[L.own].x) {
             L.found = true;
             cur = kDone;
         }
@@ -562,18 +579,227 @@ __device__ inline void finish(const QArgs &a, const Lane &L)
     }
 }
 
+// ------------------------------------------------- walks shared in a wave --
+//
+// When a wave has lanes without a segment (no items are left, or there were
+// fewer than lanes from the start), those lanes take over parts of the
+// other lanes' walks: an idle lane takes the lowest entry of a walking lane's
+// stack, its largest untouched subtree, with a copy of the segment, and
+// walks it on its own stack.  The time of a launch with few segments, and the
+// end of every other one, is the longest walks' (up to a hundred dependent
+// node visits); shared, such a walk takes little more than the tree's depth.
+// The segment's results stay with the lane that holds it (`own`).
+
+// Idle, finished or helping lanes that a sharing wave waits for before it
+// spends a round on them (a round costs as much as a node step).
+constexpr int kShareMin = 8;
+
+// An idle lane's share of a walk: pairs of idle lanes and lanes with an
+// entry to give, matched in lane order, one entry per round.
+template <bool BATCH, typename Ent>
+__device__ inline void share_walks(Lane &L, int32_t &item, int32_t &cur, int32_t &col, int32_t *&sp, int32_t *&bot,
+                                   int32_t *stk, Ent *q, int32_t &vis)
+{
+    const bool idle = item == -1 || item == -2;
+    const bool gives = !idle && cur != kDone && sp > bot;
+    const uint64_t I = ballot(idle), D = ballot(gives);
+    const int32_t n = (int32_t)min(__popcll(I), __popcll(D));
+    if (n == 0) return;
+    const int32_t di = (int32_t)lanes_below(D), ii = (int32_t)lanes_below(I);
+    if (gives && di < n) {
+        bot += 64;
+        Ent e = {};
+        e.x = *bot;
+        e.y = (int32_t)__lane_id();
+        q[di] = e;
+        *bot = kDone;
+    }
+    wave_lds_sync();
+    const bool takes = idle && ii < n;
+    int32_t ref = kDone, from = (int32_t)__lane_id();
+    if (takes) {
+        const Ent e = q[ii];
+        ref = e.x;
+        from = e.y;
+    }
+    wave_lds_sync();
+    const Seg s = {__shfl(L.seg.ox, from, 64), __shfl(L.seg.oy, from, 64), __shfl(L.seg.oz, from, 64),
+                   __shfl(L.seg.dx, from, 64), __shfl(L.seg.dy, from, 64), __shfl(L.seg.dz, from, 64),
+                   __shfl(L.seg.ix, from, 64), __shfl(L.seg.iy, from, 64), __shfl(L.seg.iz, from, 64)};
+    const float tlim = __shfl(L.tlim, from, 64), tiny = __shfl(L.tiny, from, 64);
+    const int32_t own = __shfl(L.own, from, 64);
+    if (takes) {
+        L.seg = s;
+        L.tlim = tlim;
+        L.tiny = tiny;
+        L.own = own;
+        L.best_t = INFINITY;
+        L.best_id = 0x7FFFFFFF;
+        L.best_pos = -1;
+        L.count = 0;
+        L.found = false;
+        L.retry = false;
+        item = -3;
+        cur = ref;
+        sp = bot = stk;
+        *stk = kDone;
+        col &= ~1023;
+        vis = 0;
+    }
+}
+
+// Helping lanes whose part is walked hand their results to the lane that
+// holds the segment and are idle again; returns, for a lane that holds a
+// segment, whether a helper is still walking.  All-hits crossings and
+// boolean hits reach their lane in the leaf phase already.
+template <uint32_t MODE, typename Ent>
+__device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_t col, Ent *q)
+{
+    const int32_t lane = (int32_t)__lane_id();
+    constexpr bool FIRST = (MODE & M_FIRST) && !(MODE & M_ALL);
+    const bool ends = item == -3 && cur == kDone && (col & 511) == 0;
+    // the flags' word: 1 a helper walks, 2 a helper found no column; counts above
+    int32_t *const flags = reinterpret_cast<int32_t *>(q + lane) + (sizeof(Ent) / 4 - 1);
+    *flags = 0;
+    if constexpr (FIRST) *reinterpret_cast<unsigned long long *>(q + lane) = ~0ull;
+    wave_lds_sync();
+    unsigned long long key = ~0ull;
+    if (item == -3) {
+        int32_t *const f = reinterpret_cast<int32_t *>(q + L.own) + (sizeof(Ent) / 4 - 1);
+        const int32_t bits = ends ? (L.retry ? 2 : 0) : 1;
+        if (bits) atomicOr(f, bits);
+        if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) {
+            if (ends && L.count) atomicAdd(f, L.count << 2);
+        }
+        if constexpr (FIRST) {
+            if (ends && L.best_pos >= 0) {
+                // t >= 0, so its bits order like the number (+ 0 makes -0 into 0)
+                key = ((unsigned long long)(uint32_t)__float_as_int(L.best_t + 0.0f) << 32) | (uint32_t)L.best_id;
+                atomicMin(reinterpret_cast<unsigned long long *>(q + L.own), key);
+            }
+        }
+    }
+    wave_lds_sync();
+    if constexpr (FIRST) {
+        // (t, id) names one triangle of one part, so one lane writes
+        if (key != ~0ull && *reinterpret_cast<unsigned long long *>(q + L.own) == key) q[L.own].z = L.best_pos;
+        wave_lds_sync();
+    }
+    bool helped = false;
+    if (item >= 0) {
+        const int32_t f = *flags;
+        helped = (f & 1) != 0;
+        if (f & 2) L.retry = true;
+        if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) {
+            L.count += f >> 2;
+            if (f >> 2) L.found = true;
+        }
+        if constexpr (FIRST) {
+            const unsigned long long k = *reinterpret_cast<unsigned long long *>(q + lane);
+            if (k != ~0ull) {
+                L.found = true;
+                take_first<MODE>(L, __int_as_float((int32_t)(k >> 32)), (int32_t)(uint32_t)k, q[lane].z);
+            }
+        }
+    }
+    wave_lds_sync();
+    if (ends) {
+        item = -1;
+        L.own = lane;  // its limit must not reach the next segment of the lane it helped
+    }
+    return helped;
+}
+
+// First hit: every lane on a segment takes the smallest t limit of them.
+template <typename Ent>
+__device__ inline void share_tlim(Lane &L, Ent *q)
+{
+    const int32_t lane = (int32_t)__lane_id();
+    q[lane].x = 0x7FFFFFFF;
+    wave_lds_sync();
+    atomicMin(&q[L.own].x, __float_as_int(L.tlim));  // tlim >= 0: its bits order like the number
+    wave_lds_sync();
+    L.tlim = __int_as_float(q[L.own].x);
+    wave_lds_sync();
+}
+
+// All hits, the leaf phase: the top leaf of each lane per round, one triangle
+// at a time.  A crossing is recorded by the lane that found it, or in shared
+// walks, crossing by crossing, by the lane that holds the segment (one copy
+// of the recording code: two cost the all-hits variants 9 to 20 spilled
+// registers).  Gathered like the other modes' leaves, the 29,768-triangle
+// mesh's query was 3% faster and the 499,280-triangle sphere's 10% slower
+// (3.30 against 2.97 ms).
+template <uint32_t MODE, bool BATCH, bool COUNT, typename Pop>
+__device__ inline void leaf_rounds_all(const QArgs &a, Lane &L, int32_t &cur, Pop pop, bool share, uint32_t &tests,
+                                       volatile int32_t *wst, uint32_t &w_rounds, unsigned long long &w_lanes)
+{
+    const int32_t lane = (int32_t)__lane_id();
+    uint64_t m;
+    while ((m = ballot(cur < 0)) != 0) {
+        if (COUNT) {
+            ++w_rounds;
+            w_lanes += (unsigned long long)__popcll(m);
+        }
+        const bool has = cur < 0;
+        int32_t pos = leaf_first(cur);
+        const int32_t end = has ? pos + leaf_count(cur) : pos;
+        if (has) cur = pop();
+        for (; ballot(pos < end) != 0; ++pos) {
+            bool hit = false;
+            float t = 0.0f;
+            int32_t id = 0;
+            if (pos < end) {
+                float v[9];
+                tri_load(a.tris, pos, v, id);
+                if (COUNT) ++tests;
+                const MTHit h = mt_test(L.seg, v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], 1.0f);
+                hit = h.hit;
+                if (MODE & M_FIRST) t = h.tn / h.det;
+            }
+            uint64_t hits = ballot(hit);
+            while (hits != 0) {
+                bool mine = hit;
+                int32_t p = pos, ih = id;
+                float th = t;
+                if (share) {
+                    const int src = __builtin_ctzll(hits);
+                    hits &= hits - 1;
+                    mine = lane == __builtin_amdgcn_readlane(L.own, src);
+                    p = __builtin_amdgcn_readlane(pos, src);
+                    if (MODE & M_FIRST) {
+                        th = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), src));
+                        ih = __builtin_amdgcn_readlane(id, src);
+                    }
+                } else {
+                    hits = 0;
+                }
+                if (mine) {
+                    L.found = true;
+                    if (MODE & M_FIRST) take_first<MODE>(L, th, ih, p);
+                    take_crossing<MODE, BATCH>(a, L, p, wst);
+                }
+            }
+        }
+    }
+}
+
 // Work claiming, shared by both walks.  The main pass's items are cut into
 // eight contiguous ranges, one per XCD, each with its own counter on its own
 // 128-byte line; a wave takes chunks from its XCD's range first, then from
 // the others in turn.  A single counter line shared by all XCDs serialises
 // the claims in the memory fabric (measured: 0.83 against 0.69 ms for the
 // 10M-segment boolean query); with the ranges each XCD also walks its own
-// part of spatially ordered items.  The deep pass has one range.  Every
-// field is wave-uniform; items number below 2^30 (checked at the boundary),
-// so the arithmetic is 32-bit.
+// part of spatially ordered items.  A wave learns from one word (kRangeDone)
+// which ranges are used up: finding out by a failing atomic on each of the
+// eight counters, every wave at the end of every launch did that, cost about
+// 45 us per launch (400k segments against 1,922 triangles: 119 -> 76 us).
+// The deep pass has one range.  Every field is wave-uniform; items number
+// below 2^30 (checked at the boundary), so the arithmetic is 32-bit.
 struct Claim {
     int32_t n_items;
-    int32_t range, ranges_left;
+    int32_t range;
+    uint32_t dead;      // ranges known to be used up, a bit each
     int32_t next, end;  // the wave's claimed, not yet handed out items
     bool exhausted;     // every range's counter has passed its last item
 };
@@ -588,50 +814,64 @@ __device__ inline Claim claim_init(const QArgs &a)
         c.n_items = q < (int32_t)a.retry_cap ? q : (int32_t)a.retry_cap;
     }
     c.range = RETRY ? 0 : xcd_id();
-    c.ranges_left = RETRY ? 1 : kXcds;
+    c.dead = 0;
     c.next = c.end = 0;
     c.exhausted = false;
     return c;
 }
 
-// Hand each lane with `idle` the next unclaimed item (-1: none); a new chunk
-// is claimed from a range counter with one atomic.
+// Hand up to `most` of the lanes with `idle_lane` the next unclaimed items
+// (-1: none); a new chunk is claimed from a range counter with one atomic.
 template <bool RETRY>
-__device__ inline int32_t claim_items(const QArgs &a, Claim &c, bool idle_lane)
+__device__ inline int32_t claim_items(const QArgs &a, Claim &c, bool idle_lane, int32_t most = 64)
 {
     constexpr int kRanges = RETRY ? 1 : kXcds;
     int32_t *const work = &a.scalars[RETRY ? kWorkRetry : kWorkXcd];
     const uint64_t idle = ballot(idle_lane);
     const int32_t n_idle = (int32_t)__popcll(idle);
+    const int32_t want = n_idle < most ? n_idle : most;
     const int32_t rank = (int32_t)lanes_below(idle);
     int32_t k = -1;
     const int32_t avail = c.end - c.next;
-    const int32_t used = avail < n_idle ? avail : n_idle;
+    const int32_t used = avail < want ? avail : want;
     if (rank < used) k = c.next + rank;
     c.next += used;
-    if (used < n_idle && !c.exhausted) {
-        const int leader = __builtin_ctzll(idle);
-        for (;;) {
-            const int32_t lo = (int32_t)((int64_t)c.n_items * c.range / kRanges);
-            const int32_t hi = (int32_t)((int64_t)c.n_items * (c.range + 1) / kRanges);
-            int32_t base = 0;
-            if ((int)__lane_id() == leader) base = atomicAdd(work + kWorkStride * c.range, a.chunk);
-            base = __builtin_amdgcn_readfirstlane(__shfl(base, leader, 64));
-            if (base < hi - lo) {
-                c.next = lo + base;
-                c.end = hi - c.next > a.chunk ? c.next + a.chunk : hi;
-                const int32_t room = c.end - c.next;
-                const int32_t more = n_idle - used < room ? n_idle - used : room;
-                if (rank >= used && rank - used < more) k = c.next + (rank - used);
-                c.next += more;
-                break;
+    const int leader = __builtin_ctzll(idle);
+    int32_t served = used;
+    while (served < want && !c.exhausted) {
+        const int32_t lo = (int32_t)((int64_t)c.n_items * c.range / kRanges);
+        const int32_t hi = (int32_t)((int64_t)c.n_items * (c.range + 1) / kRanges);
+        int32_t base = 0;
+        if ((int)__lane_id() == leader) base = atomicAdd(work + kWorkStride * c.range, a.chunk);
+        base = __builtin_amdgcn_readfirstlane(__shfl(base, leader, 64));
+        if (base < hi - lo) {
+            c.next = lo + base;
+            c.end = hi - c.next > a.chunk ? c.next + a.chunk : hi;
+            const int32_t room = c.end - c.next;
+            const int32_t more = want - served < room ? want - served : room;
+            if (rank >= served && rank - served < more) k = c.next + (rank - served);
+            c.next += more;
+            served += more;
+        } else {
+            // this range is used up: leave word of it, see which others
+            // are, and go on with one that is not
+            int32_t *const done = &a.scalars[kRangeDone];
+            uint32_t m = 0;
+            if ((int)__lane_id() == leader) {
+                m = (uint32_t)__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!RETRY && !(m >> c.range & 1)) atomicOr(done, 1 << c.range);
             }
-            // this range is used up: the next one
-            if (--c.ranges_left == 0) {
+            m = (uint32_t)__builtin_amdgcn_readfirstlane(__shfl((int32_t)m, leader, 64));
+            c.dead |= (RETRY ? 0u : m) | 1u << c.range;
+            if (c.dead == (1u << kRanges) - 1) {
                 c.exhausted = true;
-                break;
+            } else {
+                // waves of one XCD spread over the ranges that are left
+                const int32_t from = (c.range + 1 + (int32_t)(blockIdx.x >> 3)) & (kRanges - 1);
+                const uint32_t alive = ~c.dead & ((1u << kRanges) - 1);
+                const uint32_t turned = (alive >> from | alive << (kRanges - from)) & ((1u << kRanges) - 1);
+                c.range = (from + __builtin_ctz(turned)) & (kRanges - 1);
             }
-            c.range = c.range + 1 == kRanges ? 0 : c.range + 1;
         }
     }
     return idle_lane ? k : -1;
@@ -737,8 +977,11 @@ __device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
 // column taken still leaves its segment to that pass (RETRY: work items come
 // from the retry queue, whose length is read on the device, and every lane
 // has a column).
+// Registers: six waves per SIMD for all hits (80 VGPRs), seven for the others
+// (72; the LDS parts allow no more).
 template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_ALL) ? 6 : 1))) void k_query(QArgs a)
+__global__ __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu((MODE & M_ALL) ? 6 : 7))) void k_query(QArgs a)
 {
     // the deep pass is launched after every main pass; with nothing queued
     // (the usual case) every workgroup leaves before touching memory
@@ -751,7 +994,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
         if (threadIdx.x < 64) load_top(a.nodes4, a.entry, top4, threadIdx.x);
         __syncthreads();
     }
-    // each wave's stack slots [lds_depth + 1][64], then (all hits aside) each wave's leaf queue
+    // each wave's stack slots [lds_depth + 1][64], then each wave's leaf queue
     const int wave = (int)(threadIdx.x >> 6);
     const int wave_ints = 64 * (a.lds_depth + 1);
     int32_t *const stk = lds_dyn + wave * wave_ints + (int)__lane_id();
@@ -777,8 +1020,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
     Lane L = {};
     L.tlim = 1.0f;
     L.e = -1;
-    int32_t item = -1;    // >= 0 owned work item; -1 idle; -2 no work left
+    L.own = (int32_t)__lane_id();
+    int32_t item = -1;    // >= 0 owned work item; -1 idle; -2 idle, no work left; -3 helps another lane
     int32_t cur = kDone;  // next entry: >= 0 a node, < 0 a leaf, kDone none
+    int32_t *bot = stk;   // the slot below the lowest entry (holds kDone)
+    bool helped = false;  // another lane walks a part of this lane's segment
     // bound on a walk (a damaged tree can give wrong answers, never a hang):
     // each lane counts the node records it visits for its current segment; a
     // walk of a valid tree visits every record at most once, so a count past
@@ -798,22 +1044,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
     };
     // make room in a full window; false when no column is left
     auto spill = [&]() -> bool {
+        int32_t n = (int32_t)(sp - bot) >> 6;
+        if (bot != stk) {  // slots whose entries were given away
+            for (int32_t i = 1; i <= n; ++i) stk[64 * i] = bot[64 * i];
+            bot = stk;
+            sp = stk + 64 * n;
+            return true;
+        }
+        const QArgs &b = seldom();
         if (col < 1024) {
-            const int32_t c = atomicAdd(&a.scalars[kStackCol], 1);
-            if (c >= a.n_cols) return false;
+            const int32_t c = atomicAdd(&b.scalars[kStackCol], 1);
+            if (c >= b.n_cols) return false;
             col = (c + 1) << 10;
         }
         if (!(col & 512)) {
             col |= 512;
-            if (!RETRY) atomicAdd(&a.scalars[kSpilled], 1);
+            if (!RETRY) atomicAdd(&b.scalars[kSpilled], 1);
         }
-        const int32_t n = (int32_t)(sp - stk) >> 6, k = (n + 1) >> 1;
-        const int32_t have = col & 511;
-        int32_t *g = a.gstack + ((col >> 10) - 1);
-        if (have + k > a.depth) {  // deeper than any valid tree: the entries are dropped and flagged
-            atomicOr(&a.scalars[kStackDropped], 1);
+        const int32_t k = (n + 1) >> 1, have = col & 511;
+        int32_t *g = b.gstack + ((col >> 10) - 1);
+        if (have + k > b.depth) {  // deeper than any valid tree: the entries are dropped and flagged
+            atomicOr(&b.scalars[kStackDropped], 1);
         } else {
-            for (int32_t i = 0; i < k; ++i) g[(int64_t)(have + i) * a.n_cols] = stk[64 * (1 + i)];
+            for (int32_t i = 0; i < k; ++i) g[(int64_t)(have + i) * b.n_cols] = stk[64 * (1 + i)];
             col += k;
         }
         for (int32_t i = 1; i <= n - k; ++i) stk[64 * i] = stk[64 * (i + k)];
@@ -831,35 +1084,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
             // lanes out of entries with some in their column: the newest
             // half window comes back
             if (cur == kDone && (col & 511) != 0) {
-                const int32_t have = col & 511, half = (a.lds_depth + 1) >> 1;
+                const QArgs &b = seldom();
+                const int32_t have = col & 511, half = (b.lds_depth + 1) >> 1;
                 const int32_t k = have < half ? have : half;
-                const int32_t *g = a.gstack + ((col >> 10) - 1);
-                for (int32_t i = 0; i < k; ++i) stk[64 * (1 + i)] = g[(int64_t)(have - k + i) * a.n_cols];
+                const int32_t *g = b.gstack + ((col >> 10) - 1);
+                for (int32_t i = 0; i < k; ++i) stk[64 * (1 + i)] = g[(int64_t)(have - k + i) * b.n_cols];
                 col -= k;
                 sp = stk + 64 * k;
+                bot = stk;
                 cur = pop();
             }
         }
-        const bool done = item >= 0 && cur == kDone;
+        const bool share = cl.exhausted || a.own_max < 64;
+        const bool over = item >= 0 && cur == kDone;
+        if (share && ballot(item == -3) != 0 &&
+            (ballot(over) != 0 || (int)__popcll(ballot(item == -3 && cur == kDone)) >= kShareMin))
+            helped = share_results<MODE>(L, item, cur, col, leafq);
+        const bool done = over && !helped;
         const uint64_t waiting = ballot(done || item == -1);
-        if (waiting != 0 && ((int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
+        // (a sharing wave: a few finished ones at a time, and with few items
+        // the next ones when it has none left)
+        if (waiting != 0 && (share ? (int)__popcll(ballot(done)) >= kShareMin || ballot(cur != kDone) == 0
+                                   : (int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
             if (COUNT) ++tl.w_refill;
             if (done) {
-                finish<MODE, RETRY, BATCH>(a, L);
+                finish<MODE, RETRY, BATCH>(seldom(), L);
                 item = -1;
             }
-            const int32_t k = claim_items<RETRY>(a, cl, item == -1);
+            const bool none = ballot(item >= 0) == 0;
+            const int32_t k =
+                a.own_max == 64 || none ? claim_items<RETRY>(seldom(), cl, item == -1, a.own_max) : -1;
             if (item == -1) {
                 if (k >= 0) {
                     item = k;
-                    const int32_t entry = start_item<RETRY, BATCH>(a, L, k);
+                    const int32_t entry = start_item<RETRY, BATCH>(seldom(), L, k);
                     // |coordinate| bound of the mesh's box: with the
                     // origin's it bounds every plane offset of this walk
-                    const float scale = a.mesh_scale[BATCH ? L.mesh : 0];
+                    const float scale = seldom().mesh_scale[BATCH ? L.mesh : 0];
                     L.tiny = box_tiny(L.seg, scale);
                     box_rcp(L.seg, 1.0f, L.tiny);
+                    L.own = (int32_t)__lane_id();
                     cur = entry < 0 ? kDone : (TOP ? kTopRef : entry);
-                    sp = stk;
+                    sp = bot = stk;
+                    *stk = kDone;
                     col &= ~1023;
                     vis = 0;
                     if (COUNT && !RETRY) ++tl.segs;
@@ -869,16 +1136,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
             }
         }
         if (ballot(item >= 0) == 0) break;
+        // ---- idle lanes take over parts of others' walks
+        if (share && (int)__popcll(ballot(item == -1 || item == -2)) >= kShareMin)
+            share_walks<BATCH>(L, item, cur, col, sp, bot, stk, leafq, vis);
 
         // ---- node steps for every lane with a node on top.  Steps repeat
         // without the refill and leaf-phase checks while at least `defer`
         // lanes step; pending leaves are tested after the first step made by
         // fewer lanes.
+        // With fewer lanes stepping from the start (a shared or nearly
+        // finished wave), steps repeat while half of them do.
         uint64_t w;
+        int32_t enough = 0;
         do {
             const bool want = (uint32_t)cur < (uint32_t)kDone;
             w = ballot(want);
             if (w == 0) break;
+            if (enough == 0) {
+                const int32_t n = (int32_t)__popcll(w);
+                enough = n < a.defer ? (n + 1) >> 1 : a.defer;
+            }
             if (COUNT) {
                 ++tl.w_steps;
                 const uint64_t leaf = ballot(cur < 0);
@@ -970,22 +1247,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
                     // a full window: the last touched child stays in a
                     // register, the others are pushed one by one
                     int32_t top = near;
-                    auto put = [&](bool h, int32_t child) {
-                        if (!h) return;
+                    uint32_t hit = (h0 ? 1u : 0u) | (h1 ? 2u : 0u) | (h2 ? 4u : 0u) | (h3 ? 8u : 0u);
+#pragma unroll 1
+                    for (; hit != 0; hit &= hit - 1) {
+                        const int32_t child = ref_at(C, (int)__builtin_ctz(hit));
                         const int32_t e = NEAREST ? child : top;
                         if (!NEAREST) top = child;
-                        if (e == kDone) return;
+                        if (e == kDone) continue;
                         if (sp == sp_last && !spill()) {
                             L.retry = true;
-                            return;
+                            break;
                         }
                         sp += 64;
                         *sp = e;
-                    };
-                    put(h0, C.x);
-                    put(h1, C.y);
-                    put(h2, C.z);
-                    put(h3, C.w);
+                    }
                     cur = top != kDone ? top : pop();
                     if (L.retry) {  // no column left: the deep pass walks this segment again
                         cur = kDone;
@@ -997,34 +1272,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
                 if (vis > a.max_steps) {
                     cur = kDone;
                     col &= ~511;
-                    atomicOr(&a.scalars[kWalkCut], 1);
+                    atomicOr(&seldom().scalars[kWalkCut], 1);
                 }
             }
-        } while ((int)__popcll(w) >= a.defer);
+        } while ((int)__popcll(w) >= enough);
 
         // ---- test pending leaves once few lanes can still step
         if (ballot(cur < 0) != 0) {
             if (COUNT) ++tl.w_leaf;
             const float before = L.tlim;
             if constexpr ((MODE & M_ALL) != 0) {
-                // all hits: the top leaf of each lane per round (gathered,
-                // the 29,768-triangle mesh's query is 3% faster and the
-                // 499,280-triangle sphere's 10% slower: 3.30 against 2.97 ms)
-                uint64_t m;
-                while ((m = ballot(cur < 0)) != 0) {
-                    if (COUNT) {
-                        ++tl.w_lrounds;
-                        tl.w_llanes += (unsigned long long)__popcll(m);
-                    }
-                    if (cur < 0) {
-                        visit_leaf<MODE, BATCH, COUNT>(a, L, cur, tl.tests, wst);
-                        cur = pop();
-                    }
-                }
+                leaf_rounds_all<MODE, BATCH, COUNT>(a, L, cur, pop, share, tl.tests, wst, tl.w_lrounds, tl.w_llanes);
             } else {
                 leaf_phase4<MODE, COUNT>(a, L, cur, pop, tl.tests, leafq, tl.w_lrounds, tl.w_llanes);
             }
             if (MODE == M_BOOL && L.found) col &= ~511;  // the walk is over
+            if (NEAREST && share) share_tlim(L, leafq);
             // a nearer hit shortens the segment for the boxes
             if (NEAREST && L.tlim != before) box_rcp(L.seg, L.tlim * (1.0f + 0x1p-20f), L.tiny);
         }
@@ -1083,14 +1346,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
         if (waiting != 0 && ((int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
             if (COUNT) ++tl.w_refill;
             if (done) {
-                finish<MODE, RETRY, BATCH>(a, L);
+                finish<MODE, RETRY, BATCH>(seldom(), L);
                 item = -1;
             }
-            const int32_t k = claim_items<RETRY>(a, cl, item == -1);
+            const int32_t k = claim_items<RETRY>(seldom(), cl, item == -1);
             if (item == -1) {
                 if (k >= 0) {
                     item = k;
-                    node = start_item<RETRY, BATCH>(a, L, k);  // < 0 for an empty mesh: the segment misses
+                    node = start_item<RETRY, BATCH>(seldom(), L, k);  // < 0 for an empty mesh: the segment misses
                     L.seg.ix = guarded_rcp(L.seg.dx);
                     L.seg.iy = guarded_rcp(L.seg.dy);
                     L.seg.iz = guarded_rcp(L.seg.dz);
@@ -1206,7 +1469,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
             if (__builtin_expect((++wround & 63) == 0, 0)) {
                 if (vis > a.max_steps) {
                     node = -1;
-                    atomicOr(&a.scalars[kWalkCut], 1);
+                    atomicOr(&seldom().scalars[kWalkCut], 1);
                 }
             }
         } while ((int)__popcll(w) >= a.defer);
@@ -1899,6 +2162,7 @@ __global__ void k_reset(int32_t *scalars, Counters *c, int keep)
     const int32_t zero[] = {kWorkRetry, kRetryN,  kStackCol, kSpilled, kOvfSegs, kOvfTotalLo, kOvfTotalHi,   kArenaLo, kArenaHi,
                             kOvfFull,   kOvfUsed, kArenaUsed, kRetryLost, kStackDropped, kWalkCut};
     for (int r = 0; r < kXcds; ++r) scalars[kWorkXcd + kWorkStride * r] = 0;
+    scalars[kRangeDone] = 0;
     const int n = (int)(sizeof(zero) / sizeof(zero[0])) - (keep ? 3 : 0);
     for (int k = 0; k < n; ++k) scalars[zero[k]] = 0;
     if (c && !keep) {
@@ -1998,6 +2262,9 @@ hipError_t launch_refine_first(const QArgs &a, hipStream_t s)
 // array room for a queue of 4.3 million segments.
 constexpr int kStackCols = 28672;
 
+// Waves per CU that few items are spread over.
+constexpr int kSpreadWaves = 6;
+
 int device_cus()
 {
     int dev = 0, n_cu = 0;
@@ -2012,6 +2279,7 @@ hipError_t launch_kernel(const QArgs &a, int block, size_t lds, hipStream_t s)
     auto kern = WIDE ? k_query<MODE, RETRY, COUNT, BATCH> : k_query_binary<MODE, RETRY, COUNT, BATCH>;
     int64_t grid;
     QArgs b = a;
+    b.own_max = 64;
     if (RETRY) {
         grid = device_cus();
         if (grid > kStackCols / block) grid = kStackCols / block;  // block <= 256: at least 112
@@ -2025,16 +2293,32 @@ hipError_t launch_kernel(const QArgs &a, int block, size_t lds, hipStream_t s)
         if (e != hipSuccess) return e;
         if (per_cu < 1) per_cu = 1;
         grid = (int64_t)per_cu * device_cus();
-        const int64_t need = (a.n_items + block - 1) / block;
+        const int64_t wpb = block / 64;
+        // the four-way walk shares a segment among a wave's lanes, so few
+        // items are spread over the waves, up to kSpreadWaves per CU (more
+        // waves than that cost more in idle lanes' instructions than the
+        // shorter walks give: 10k segments against 29,768 triangles, 4 waves
+        // per CU 44 us, 8 52 us, 16 67 us; 100k segments against the
+        // 499,280-triangle sphere 86, 81 and 100 us; unshared 92 and 204 us)
+        const int64_t spread = (a.n_items + kSpreadWaves * device_cus() - 1) / (kSpreadWaves * device_cus());
+        const int64_t own = WIDE && spread < 64 ? spread : 64;
+        const int64_t need = (a.n_items + own * wpb - 1) / (own * wpb);
         if (grid > need) grid = need;
         if (grid < 1) grid = 1;
-        if (b.chunk <= 0) {
+        const int64_t waves = grid * wpb;
+        const int64_t per_wave = (a.n_items + waves - 1) / waves;
+        if (own < 64) {
+            b.own_max = (int32_t)own;
+            b.chunk = (int32_t)own;
+        } else if (b.chunk <= 0) {
             // about eight chunks per resident wave keeps the tail short while the
             // range counters see one atomic per chunk
-            const int64_t waves = grid * (block / 64);
-            int64_t c = (a.n_items + 8 * waves - 1) / (8 * waves);
+            // (smaller chunks than 64 cost more atomics than they balance:
+            // 1M segments against 1,922 triangles, chunks of 32 130 us, of 64
+            // to 128 108 us, of 512 195 us)
+            int64_t c = (per_wave + 7) / 8;
             c = (c + 63) / 64 * 64;
-            b.chunk = (int32_t)(c < 64 ? 64 : (c > 4096 ? 4096 : c));
+            b.chunk = (int32_t)(c > 4096 ? 4096 : c);
         }
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(block), lds, s, b);
@@ -2078,12 +2362,12 @@ hipError_t dispatch(uint32_t mode, const QArgs &a, const QArgs &d, int block, si
 }
 
 // Dynamic LDS of a query launch: the stack's LDS part; in the four-way walk
-// with one more slot per lane (the end marker), then (all-hits modes aside)
-// each wave's leaf queue (64 entries).
+// with one more slot per lane (the end marker), then each wave's leaf queue
+// (64 entries).
 size_t query_lds(int block, int depth, int width, uint32_t mode)
 {
     if (width != 4) return (size_t)block * depth * sizeof(int32_t);
-    const size_t ent = (mode & M_ALL) ? 0 : mode == M_BOOL ? sizeof(int2) : sizeof(int4);
+    const size_t ent = mode == M_BOOL || (mode & M_ALL) ? sizeof(int2) : sizeof(int4);
     return (size_t)block * ((depth + 1) * sizeof(int32_t) + ent);
 }
 
@@ -2301,11 +2585,11 @@ hipError_t ensure_query_memory(rsi_bvh *h, int64_t n, bool all_hits)
     if (all_hits) {
         // waves that can hold a block of entries and one of records at
         // once: every resident wave of the main pass (at most 32 per CU,
-        // and no more than the segments fill) and of the deep pass (one
+        // and no more than there are segments) and of the deep pass (one
         // workgroup of at most 4 waves per CU); each may leave its blocks'
         // unused rest void
         const int64_t cus = device_cus();
-        const int64_t waves = ((n + 63) / 64 < 32 * cus ? (n + 63) / 64 : 32 * cus) + 4 * cus;
+        const int64_t waves = (n < 32 * cus ? n : 32 * cus) + 4 * cus;
         // one entry per segment, plus room for the entries that walks handed
         // to the deep pass leave void, plus the void block tails
         const int64_t want = n + n / 8 + (int64_t)(kEntBlock - 1) * waves + 1024;

@@ -38,7 +38,8 @@ enum Scalar {
     kOvfSegs = kWorkXcd + 8 * kWorkStride,  // overflow-table entries handed out (in blocks; unused ones are void)
     kArenaLo = kOvfSegs + kWorkStride,      // 64-bit count of arena records handed out during the walk, in
     kArenaHi = kArenaLo + 1,                // blocks (lo, hi words)
-    kNumScalars = kArenaLo + kWorkStride
+    kRangeDone = kArenaLo + kWorkStride,    // a bit per eighth of the items that is all claimed
+    kNumScalars = kRangeDone + kWorkStride
 };
 
 struct Counters {

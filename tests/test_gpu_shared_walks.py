@@ -1,0 +1,82 @@
+"""Walks shared among a wave's lanes (fewer segments than lanes, and the end
+of every launch): the answers must be those of many segments at once, whose
+walks are not shared, bit for bit, in every mode, at sizes around a wave and
+the changes of the items per wave; long stacked hits, so that helpers find
+most crossings; and single segments against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2209_02878_amd import rsi
+from paper_2209_02878_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+MODES = ("bool", "first", "count", "all", "first|bool", "first|count", "count|bool", "all|first", "all|first|bool")
+
+
+def _t(a, dtype=torch.float32):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype).contiguous()
+
+
+def _lists(sp):
+    if sp is None:
+        return {}
+    seg, off, cnt = (sp[k].cpu().numpy() for k in ("seg", "offset", "count"))
+    ids, ts = sp["ids"].cpu().numpy(), sp["ts"].cpu().numpy()
+    return {int(s): (ids[o:o + c].tolist(), ts[o:o + c].tolist()) for s, o, c in zip(seg, off, cnt)}
+
+
+def _layers(n_layers):
+    """Stacked square sheets, two triangles each, z = 0 .. 1."""
+    V, T = [], []
+    for k in range(n_layers):
+        z = k / max(1, n_layers - 1)
+        V += [[0, 0, z], [1, 0, z], [1, 1, z], [0, 1, z]]
+        T += [[4 * k, 4 * k + 1, 4 * k + 2], [4 * k, 4 * k + 2, 4 * k + 3]]
+    return np.array(V, np.float32), np.array(T, np.int32)
+
+
+@pytest.mark.parametrize("leaf_size", [1, 4])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1000, 8191, 70_001, 250_007, 600_001])
+def test_few_segments_match_many(n, leaf_size):
+    V, T = wl.noisy_sphere(24, 7, 0.3)
+    S, E = wl.segments_in_box(np.random.default_rng(11), V.min(0), V.max(0), 1_500_000, scale=1.5)
+    S, E = _t(S), _t(E)
+    mesh = rsi.Mesh(_t(V), _t(T, torch.int32), leaf_size=leaf_size)
+    for mode in MODES:
+        want, got = mesh.query(S, E, mode, capacity=2), mesh.query(S[:n].clone(), E[:n].clone(), mode, capacity=2)
+        for k in got:
+            if k != "spill":
+                assert torch.equal(got[k], want[k][:n]), (mode, k)
+        if "spill" in got or "spill" in want:
+            full = {s: v for s, v in _lists(want.get("spill")).items() if s < n}
+            assert _lists(got.get("spill")) == full, mode
+    mesh.close()
+
+
+@pytest.mark.parametrize("layers", [1, 3, 70, 500])
+def test_stacked_sheets(layers):
+    V, T = _layers(layers)
+    rng = np.random.default_rng(layers)
+    xy = rng.uniform(0.05, 0.95, (9, 2))
+    S = np.concatenate([xy, np.full((9, 1), -0.5)], 1).astype(np.float32)
+    E = np.concatenate([xy + rng.uniform(-0.02, 0.02, (9, 2)), np.full((9, 1), 1.5)], 1).astype(np.float32)
+    ref = parity.oracle_reference(V, T, S, E)
+    ok = ref["degenerate"] == 0
+    mesh = rsi.Mesh(_t(V), _t(T, torch.int32))
+    for mode in MODES:
+        out = mesh.query(_t(S), _t(E), mode, capacity=3)
+        if "count" in out:
+            assert np.array_equal(out["count"].cpu().numpy()[ok], ref["count"][ok]), mode
+        if "hit" in out:
+            assert np.array_equal(out["hit"].cpu().numpy()[ok].astype(bool), ref["count"][ok] > 0), mode
+        if "tri" in out:
+            assert np.array_equal(out["tri"].cpu().numpy()[ok], ref["first_tri"][ok]), mode
+        if "spill" in out:
+            for s, (ids, ts) in _lists(out["spill"]).items():
+                assert len(ids) == ref["count"][s] or not ok[s]
+                assert ts == sorted(ts)
+    assert ref["count"][ok].max() >= layers
+    mesh.close()
