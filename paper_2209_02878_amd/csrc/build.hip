@@ -125,18 +125,46 @@ __global__ void k_init(BuildArgs a)
 constexpr int kCentBlock = 256;
 constexpr int kCentMeshes = 4;  // meshes per block reduced in LDS; the rest go straight to global
 
+__device__ inline int32_t wave_min(int32_t v)
+{
+    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+// PER triangles per thread.  The bounds end in atomics on one or a few cache
+// lines, which the GPU serialises, so their number sets the time of a large
+// mesh: with one triangle per thread, 499,280 triangles took 11,700 of them
+// and 51 us.  PER = 8 (from 131,072 triangles on; fewer leave CUs idle at
+// eight per thread) and a reduction in the wave before the LDS one.
+template <int PER>
 __global__ __launch_bounds__(kCentBlock) void k_centroids(BuildArgs a)
 {
-    __shared__ int32_t lb[kCentMeshes][6];
+    __shared__ int32_t lb[kCentMeshes][6];  // per mesh: minima, then negated maxima (as minima)
     const int tid = threadIdx.x;
-    if (tid < kCentMeshes * 6) {
-        lb[tid / 6][tid % 6] = float_to_ordered((tid % 6) < 3 ? FLT_MAX : -FLT_MAX);
-    }
-    const int64_t j0 = (int64_t)blockIdx.x * kCentBlock;
+    if (tid < kCentMeshes * 6) lb[tid / 6][tid % 6] = 0x7FFFFFFF;
+    const int64_t j0 = (int64_t)blockIdx.x * (kCentBlock * PER);
     const int32_t m0 = mesh_of(a.off, a.M, j0 < a.n_t ? j0 : a.n_t - 1);
     __syncthreads();
-    const int64_t j = j0 + tid;
-    if (j < a.n_t) {
+    // this thread's bounds so far, all of mesh `at` (-1: none yet)
+    int32_t at = -1, b[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) b[k] = 0x7FFFFFFF;
+    auto flush = [&](int32_t m, const int32_t (&v)[6]) {
+        if (m - m0 < kCentMeshes) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) atomicMin(&lb[m - m0][k], v[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                atomicMin(&a.bounds[6 * m + k], v[k]);
+                atomicMax(&a.bounds[6 * m + 3 + k], ~v[3 + k]);
+            }
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int64_t j = j0 + r * kCentBlock + tid;
+        if (j >= a.n_t) break;
         int32_t va = a.T[3 * j], vb = a.T[3 * j + 1], vc = a.T[3 * j + 2];
         const bool ok = va >= 0 && va < a.n_v && vb >= 0 && vb < a.n_v && vc >= 0 && vc < a.n_v;
         if (!ok) {
@@ -149,28 +177,38 @@ __global__ __launch_bounds__(kCentBlock) void k_centroids(BuildArgs a)
         a.cent[j] = cx;
         a.cent[a.n_t + j] = cy;
         a.cent[2 * a.n_t + j] = cz;
-        const int32_t m = mesh_of(a.off, a.M, j);
+        const int32_t m = a.M > 1 ? mesh_of(a.off, a.M, j) : 0;
         const int32_t q[3] = {float_to_ordered(cx), float_to_ordered(cy), float_to_ordered(cz)};
-        if (m - m0 < kCentMeshes) {
-            int32_t *l = lb[m - m0];
-            for (int k = 0; k < 3; ++k) {
-                atomicMin(&l[k], q[k]);
-                atomicMax(&l[3 + k], q[k]);
-            }
-        } else {
-            for (int k = 0; k < 3; ++k) {
-                atomicMin(&a.bounds[6 * m + k], q[k]);
-                atomicMax(&a.bounds[6 * m + 3 + k], q[k]);
-            }
+        if (m != at && at >= 0) {
+            flush(at, b);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) b[k] = 0x7FFFFFFF;
         }
+        at = m;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            b[k] = min(b[k], q[k]);
+            b[3 + k] = min(b[3 + k], ~q[k]);  // ~ reverses the order of ints
+        }
+    }
+    // a wave whose threads all end in one mesh reduces first
+    const int32_t m_first = __builtin_amdgcn_readfirstlane(at);
+    if (__builtin_amdgcn_ballot_w64(at != m_first && at >= 0) == 0) {
+        if (m_first >= 0) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) b[k] = wave_min(b[k]);
+            if (__lane_id() == 0) flush(m_first, b);
+        }
+    } else if (at >= 0) {
+        flush(at, b);
     }
     __syncthreads();
     if (tid < kCentMeshes * 6) {
         const int32_t m = m0 + tid / 6, k = tid % 6;
         const int32_t v = lb[tid / 6][k];
-        if (m < a.M && v != float_to_ordered(k < 3 ? FLT_MAX : -FLT_MAX)) {
+        if (m < a.M && v != 0x7FFFFFFF) {
             if (k < 3) atomicMin(&a.bounds[6 * m + k], v);
-            else atomicMax(&a.bounds[6 * m + k], v);
+            else atomicMax(&a.bounds[6 * m + k], ~v);
         }
     }
 }
@@ -696,8 +734,12 @@ hipError_t launch_build(rsi_bvh *h, const float *V, hipStream_t s)
     if (n == 0) return hipSuccess;
     const BuildArgs a = make_build_args(h, V);
     hipLaunchKernelGGL(k_init, dim3(init_grid(a)), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_centroids, dim3((unsigned)((n + kCentBlock - 1) / kCentBlock)), dim3(kCentBlock), 0, s,
-                       a);
+    if (n >= 131072)
+        hipLaunchKernelGGL(k_centroids<8>, dim3((unsigned)((n + 8 * kCentBlock - 1) / (8 * kCentBlock))),
+                           dim3(kCentBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_centroids<1>, dim3((unsigned)((n + kCentBlock - 1) / kCentBlock)), dim3(kCentBlock), 0, s,
+                           a);
     const int64_t *mesh_off = h->M > 1 ? h->tri_off : nullptr;
     BuildArgs km = a;  // the codes go where the sort wants its input
     hipError_t e = sort_source(h->keys, h->order, n, kCodeBits, h->sort, mesh_off, h->M, &km.keys, &km.order);

@@ -22,39 +22,82 @@ __global__ void k_seg_bounds_init(int32_t *b)
     else if (threadIdx.x < 6) b[threadIdx.x] = (int32_t)0x80000000;  // ordered max
 }
 
-// Bounding box of the midpoints (block min/max in LDS, one ordered-int
-// atomic per block and bound).
-__global__ __launch_bounds__(256) void k_seg_bounds(const float *__restrict__ S, const float *__restrict__ E,
-                                                    int64_t n, int32_t *__restrict__ b)
+// Bounding box of the midpoints: one workgroup of 1,024 threads per CU,
+// reduced in registers, by wave and in LDS, then one ordered-int atomic per
+// workgroup and bound.  The atomics meet on one cache line and are
+// serialised: 1,024 workgroups took 25 us for them.  The arrays are read as
+// streams of floats, four at a time (VEC; both pointers 16-byte aligned) or
+// one; the number of threads is a multiple of 3, so every value of a thread's
+// at a place in its vector belongs to the same axis.
+constexpr int kBoundThreads = 960;
+
+template <bool VEC>
+__global__ __launch_bounds__(kBoundThreads) void k_seg_bounds(const float *__restrict__ S, const float *__restrict__ E,
+                                                              int64_t n, int32_t *__restrict__ b)
 {
-    __shared__ int32_t lb[6][256];
-    int32_t mn[3] = {0x7FFFFFFF, 0x7FFFFFFF, 0x7FFFFFFF};
-    int32_t mx[3] = {(int32_t)0x80000000, (int32_t)0x80000000, (int32_t)0x80000000};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        for (int k = 0; k < 3; ++k) {
-            const int32_t m = float_to_ordered(0.5f * (S[3 * i + k] + E[3 * i + k]));
-            mn[k] = m < mn[k] ? m : mn[k];
-            mx[k] = m > mx[k] ? m : mx[k];
+    constexpr int W = VEC ? 4 : 1;
+    __shared__ int32_t lb[6];
+    const int tid = threadIdx.x;
+    if (tid < 6) lb[tid] = 0x7FFFFFFF;
+    __syncthreads();
+    const int64_t total = 3 * n, threads = (int64_t)gridDim.x * kBoundThreads;
+    const int64_t me = (int64_t)blockIdx.x * kBoundThreads + tid;
+    int32_t mn[W], mx[W];  // minima, and minima of the reversed order (~)
+#pragma unroll
+    for (int k = 0; k < W; ++k) mn[k] = mx[k] = 0x7FFFFFFF;
+    const int64_t whole = total / W;
+#pragma unroll 4
+    for (int64_t i = me; i < whole; i += threads) {
+        float s[W], e[W];
+        if constexpr (VEC) {
+            *reinterpret_cast<float4 *>(s) = reinterpret_cast<const float4 *>(S)[i];
+            *reinterpret_cast<float4 *>(e) = reinterpret_cast<const float4 *>(E)[i];
+        } else {
+            s[0] = S[i];
+            e[0] = E[i];
+        }
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const int32_t m = float_to_ordered(0.5f * (s[k] + e[k]));
+            mn[k] = min(mn[k], m);
+            mx[k] = min(mx[k], ~m);
         }
     }
-    for (int k = 0; k < 3; ++k) {
-        lb[k][threadIdx.x] = mn[k];
-        lb[3 + k][threadIdx.x] = mx[k];
-    }
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            for (int k = 0; k < 3; ++k) {
-                const int32_t a = lb[k][threadIdx.x + h], c = lb[3 + k][threadIdx.x + h];
-                if (a < lb[k][threadIdx.x]) lb[k][threadIdx.x] = a;
-                if (c > lb[3 + k][threadIdx.x]) lb[3 + k][threadIdx.x] = c;
+    // by axis: the thread's value k is of axis (W me + k) mod 3
+    int32_t v[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = 0x7FFFFFFF;
+    const int first = (int)(W * me % 3);
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            if ((first + k) % 3 == x) {
+                v[x] = min(v[x], mn[k]);
+                v[3 + x] = min(v[3 + x], mx[k]);
             }
         }
-        __syncthreads();
     }
-    if (threadIdx.x < 3) atomicMin(&b[threadIdx.x], lb[threadIdx.x][0]);
-    else if (threadIdx.x < 6) atomicMax(&b[threadIdx.x], lb[threadIdx.x][0]);
+    if (VEC && me < total - 4 * whole) {  // the last one to three floats
+        const int64_t f = 4 * whole + me;
+        const int32_t m = float_to_ordered(0.5f * (S[f] + E[f]));
+        const int x = (int)(f % 3);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k == x) {
+                v[k] = min(v[k], m);
+                v[3 + k] = min(v[3 + k], ~m);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        for (int o = 32; o > 0; o >>= 1) v[k] = min(v[k], __shfl_xor(v[k], o, 64));
+        if (__lane_id() == 0) atomicMin(&lb[k], v[k]);
+    }
+    __syncthreads();
+    if (tid < 3) atomicMin(&b[tid], lb[tid]);
+    else if (tid < 6) atomicMax(&b[tid], ~lb[tid]);
 }
 
 __device__ inline uint32_t spread10(uint32_t v)
@@ -127,9 +170,11 @@ hipError_t launch_segment_order(rsi_bvh *h, const float *S, const float *E, int6
     int dev = 0, n_cu = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 4 * (int64_t)n_cu) blocks = 4 * (int64_t)n_cu;
-    hipLaunchKernelGGL(k_seg_bounds, dim3((unsigned)blocks), dim3(256), 0, s, S, E, n, b);
+    const bool vec = ((reinterpret_cast<uintptr_t>(S) | reinterpret_cast<uintptr_t>(E)) & 15) == 0;
+    int64_t blocks = (3 * n + (vec ? 4 : 1) * kBoundThreads - 1) / ((vec ? 4 : 1) * kBoundThreads);
+    if (blocks > n_cu) blocks = n_cu;
+    if (vec) hipLaunchKernelGGL(k_seg_bounds<true>, dim3((unsigned)blocks), dim3(kBoundThreads), 0, s, S, E, n, b);
+    else hipLaunchKernelGGL(k_seg_bounds<false>, dim3((unsigned)blocks), dim3(kBoundThreads), 0, s, S, E, n, b);
     hipLaunchKernelGGL(k_seg_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, E, n, b, ksrc,
                        vsrc);
     if ((e = hipGetLastError()) != hipSuccess) return e;
