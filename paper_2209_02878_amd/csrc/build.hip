@@ -57,6 +57,7 @@ struct BuildArgs {
     uint32_t *order;
     int32_t *rank;
     Node *nodes;
+    Node4 *nodes4;         // four-way records, null when the walk does not use them
     Tri *tris;
     int32_t *arrive;
     int32_t *heights;
@@ -327,6 +328,92 @@ __device__ inline void write_entry(const BuildArgs &a, int32_t m, int32_t lo, in
     a.mesh_scale[m] = s;
 }
 
+// Four-way view: record n lists the boxes and references of n's
+// grandchildren (a leaf child stands for itself), quantised inside their
+// union box.  Every node gets its record, also those no traversal reaches
+// (inside collapsed leaves).
+//
+// Grid step per axis: the smallest power of two 2^e with 254.5 * 2^e >= the
+// box extent.  Planes are placed in FP32: an offset from the corner is off by
+// at most 2^-24 of itself, 2^-16 steps, and the scaling by a power of two is
+// exact, so a plane moved outward by kQuantMargin (2^-10 steps) before it is
+// rounded outward lies outside the child's box by nearly that (the box test
+// needs half of it).
+__device__ inline int quant_exponent(float ext)
+{
+    // ext / 254.5, rounded up; the exponent of the next power of two from the bits
+    const float x = ext * (float)((1.0 + 0x1p-20) / 254.5);
+    const uint32_t u = (uint32_t)__float_as_int(x);
+    const int e = (int)(u >> 23) - 127 + ((u & 0x7FFFFFu) ? 1 : 0);
+    return e < -126 ? -126 : (e > 127 ? 127 : e);
+}
+
+struct Wide {
+    float box[4][6];
+    int32_t ref[4];
+    int k = 0;
+    __device__ inline void add(const float *b, int32_t r)
+    {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s == k) {
+#pragma unroll
+                for (int q = 0; q < 6; ++q) box[s][q] = b[q];
+                ref[s] = r;
+            }
+        }
+        ++k;
+    }
+    __device__ inline void store(Node4 *out, int64_t n) const
+    {
+        Node4 w;
+        float lo[3], step[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float l = FLT_MAX, h = -FLT_MAX;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (s < k) {
+                    l = fminf(l, box[s][a]);
+                    h = fmaxf(h, box[s][3 + a]);
+                }
+            }
+            const int e = quant_exponent(h - l);
+            const float inv = ldexpf(1.0f, -e);
+            lo[a] = l;
+            step[a] = ldexpf(1.0f, e);  // a normal float for e in [-126, 127]
+            uint32_t ql = 0, qh = 0;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                uint32_t x = 255u, y = 0u;  // unused slot: an empty box
+                if (s < k) {
+                    x = (uint32_t)fminf(fmaxf(floorf((box[s][a] - l) * inv - kQuantMargin), 0.0f), 255.0f);
+                    y = (uint32_t)fminf(fmaxf(ceilf((box[s][3 + a] - l) * inv + kQuantMargin), 0.0f), 255.0f);
+                }
+                ql |= x << (8 * s);
+                qh |= y << (8 * s);
+            }
+            w.lo[a] = ql;
+            w.hi[a] = qh;
+        }
+        w.ox = lo[0];
+        w.oy = lo[1];
+        w.oz = lo[2];
+        w.sx = step[0];
+        w.sy = step[1];
+        w.sz = step[2];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) w.ref[s] = s < k ? ref[s] : leaf_ref((int32_t)n, 1);
+        const uint4 *src = reinterpret_cast<const uint4 *>(&w);
+        uint4 *dst = reinterpret_cast<uint4 *>(out);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dst[q] = src[q];
+    }
+};
+
+// Arrival count of a node whose four-way record the local pass has written.
+constexpr int32_t kWidened = 4;
+
 constexpr int kClimbWords = 11;
 
 // Local pass: each workgroup owns kLocal consecutive sorted leaves (2048 with
@@ -485,7 +572,27 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
         q->aux[1] = lbound[tid][1];
         a.heights[2 * p] = lh[tid][0];
         a.heights[2 * p + 1] = lh[tid][1];
-        a.arrive[p] = lflag[tid];
+        int32_t arrived = lflag[tid];
+        if (a.nodes4 && arrived == 2) {
+            // both children's subtrees lie in the block, so the four-way
+            // record's boxes are here (a later pass over the node records
+            // would read them all again: 45 us at 499,280 triangles)
+            Wide w;
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const int32_t c = lref[tid][side];
+                if (c >= 0) {
+                    const int slot = c - B0;
+                    w.add(lbox[slot], lref[slot][0]);
+                    w.add(lbox[slot] + 6, lref[slot][1]);
+                } else {
+                    w.add(lbox[tid] + 6 * side, c);
+                }
+            }
+            w.store(a.nodes4 + p, n);
+            arrived = kWidened;
+        }
+        a.arrive[p] = arrived;
     }
     }
 }
@@ -549,103 +656,37 @@ __global__ __launch_bounds__(256) void k_lbvh_global(BuildArgs a)
     write_entry(a, m, lo, hi, c);
 }
 
-// Four-way view: record n lists the boxes and references of n's
-// grandchildren (a leaf child stands for itself), read from n's record and
-// its internal children's records, quantised inside their union box.
-// Every record is rewritten, including ones no traversal reaches (inside
-// collapsed leaves), so references are range-checked before use.
-//
-// Grid step per axis: the smallest power of two 2^e with 254.5 * 2^e >= the
-// box extent; planes are placed in FP64, where the offset from the corner
-// carries at most 2^-45 steps of rounding error, and rounded outward with a
-// margin of kQuantMargin steps (the box test relies on it), so corner +
-// q * step bounds the exact plane on the safe side.
-__device__ inline int quant_exponent(double ext)
-{
-    const double x = ext * (1.0 + 0x1p-40) / 254.5;
-    if (!(x > 0x1p-126)) return -126;
-    int k = 0;
-    const double m = frexp(x, &k);  // x = m 2^k, m in [0.5, 1)
-    const int e = (m == 0.5) ? k - 1 : k;
-    return e > 127 ? 127 : e;
-}
-
-// `inv_step` is 1 / step, a power of two, so the scaling is exact
-__device__ inline uint32_t quant_down(double off, double inv_step)
-{
-    const double q = floor(off * inv_step - kQuantMargin);
-    return (uint32_t)fmin(fmax(q, 0.0), 255.0);
-}
-
-__device__ inline uint32_t quant_up(double off, double inv_step)
-{
-    const double q = ceil(off * inv_step + kQuantMargin);
-    return (uint32_t)fmin(fmax(q, 0.0), 255.0);
-}
-
-__global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, int64_t n, Node4 *__restrict__ out)
+// The records the local pass has not laid out: nodes whose subtrees cross its
+// blocks, the entry nodes, and every record of a tree built without the
+// four-way view.
+__global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, const int32_t *__restrict__ arrive,
+                                               int64_t n, Node4 *__restrict__ out)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
+    if (j >= n || arrive[j] == kWidened) return;
     const Node nd = nodes[j];
-    float box[4][6];
-    int32_t ref[4];
-    int k = 0;
+    Wide w;
     for (int side = 0; side < 2; ++side) {
         const int32_t c = nd.ref[side];
         if (c >= 0 && c < n) {
             const Node ch = nodes[c];
-            for (int g = 0; g < 2; ++g) {
-                for (int q = 0; q < 6; ++q) box[k][q] = ch.f[6 * g + q];
-                ref[k++] = ch.ref[g];
-            }
+            for (int g = 0; g < 2; ++g) w.add(ch.f + 6 * g, ch.ref[g]);
         } else {
             // the entry record's far box (all FLT_MAX) is no child: the slot
             // stays empty
             bool far = true;
             for (int q = 0; q < 6; ++q) far = far && nd.f[6 * side + q] == FLT_MAX;
-            if (far) continue;
-            for (int q = 0; q < 6; ++q) box[k][q] = nd.f[6 * side + q];
-            ref[k++] = c < 0 ? c : leaf_ref(0, 1);
+            if (!far) w.add(nd.f + 6 * side, c < 0 ? c : leaf_ref(0, 1));
         }
     }
-    // union box of the used slots
-    float lo[3] = {FLT_MAX, FLT_MAX, FLT_MAX}, hi[3] = {-FLT_MAX, -FLT_MAX, -FLT_MAX};
-    for (int s = 0; s < k; ++s)
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = fminf(lo[a], box[s][a]);
-            hi[a] = fmaxf(hi[a], box[s][3 + a]);
-        }
-    Node4 w;
-    double inv_step[3];
-    float step[3];
-    for (int a = 0; a < 3; ++a) {
-        const int e = quant_exponent((double)hi[a] - (double)lo[a]);
-        inv_step[a] = ldexp(1.0, -e);
-        step[a] = ldexpf(1.0f, e);  // a normal float for e in [-126, 127]
-    }
-    w.ox = lo[0];
-    w.oy = lo[1];
-    w.oz = lo[2];
-    w.sx = step[0];
-    w.sy = step[1];
-    w.sz = step[2];
-    for (int a = 0; a < 3; ++a) {
-        uint32_t ql = 0, qh = 0;
-        for (int s = 0; s < 4; ++s) {
-            uint32_t l = 255u, h = 0u;  // unused slot: an empty box
-            if (s < k) {
-                l = quant_down((double)box[s][a] - (double)lo[a], inv_step[a]);
-                h = quant_up((double)box[s][3 + a] - (double)lo[a], inv_step[a]);
-            }
-            ql |= l << (8 * s);
-            qh |= h << (8 * s);
-        }
-        w.lo[a] = ql;
-        w.hi[a] = qh;
-    }
-    for (int s = 0; s < 4; ++s) w.ref[s] = s < k ? ref[s] : leaf_ref((int32_t)n, 1);
-    out[j] = w;
+    w.store(out + j, n);
+}
+
+// Whether the handle's tree gets the four-way view (whose walk addresses
+// records by 32-bit byte offsets: 2^26 of them).
+bool wide_view(const rsi_bvh *h)
+{
+    return h->width == 4 && h->n_t > 0 && h->n_t <= (int64_t(1) << 26) && h->nodes4;
 }
 
 BuildArgs make_build_args(rsi_bvh *h, const float *V)
@@ -662,6 +703,7 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     a.order = h->order;
     a.rank = h->rank;
     a.nodes = h->nodes;
+    a.nodes4 = wide_view(h) ? h->nodes4 : nullptr;
     a.tris = h->tris;
     a.arrive = h->arrive;
     a.heights = h->heights;
@@ -717,13 +759,12 @@ hipError_t launch_gather(rsi_bvh *h, hipStream_t s)
 
 hipError_t launch_widen(rsi_bvh *h, hipStream_t s)
 {
-    // (the four-way walk addresses records by 32-bit byte offsets: 2^26 of them)
-    if (h->width != 4 || h->n_t == 0 || h->n_t > (int64_t(1) << 26) || !h->nodes4) {
+    if (!wide_view(h)) {
         h->width_built = 2;
         return hipSuccess;
     }
-    hipLaunchKernelGGL(k_widen, dim3((unsigned)((h->n_t + 255) / 256)), dim3(256), 0, s, h->nodes, h->n_t,
-                       h->nodes4);
+    hipLaunchKernelGGL(k_widen, dim3((unsigned)((h->n_t + 255) / 256)), dim3(256), 0, s, h->nodes,
+                       h->arrive, h->n_t, h->nodes4);
     h->width_built = 4;
     return hipGetLastError();
 }

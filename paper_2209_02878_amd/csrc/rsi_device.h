@@ -42,7 +42,7 @@ static_assert(sizeof(Node) == 64, "Node must be 64 bytes");
 //                steps spanning n's box on that axis
 //   lo[a]        byte c: child c's lower plane on axis a in grid steps,
 //                rounded down;  hi[a] likewise for the upper plane, rounded
-//                up, each at least kQuantMargin steps outside the child's
+//                up, each at least 2^-11 steps outside the child's
 //                box except a lower plane at 0, the exact corner
 //   ref[c]       child reference; an unused slot (planes 255 and 0, so its
 //                box is empty) names the leaf at position n_t, a record of
@@ -157,12 +157,12 @@ __device__ inline bool slab_hit(const Seg &s, float lx, float ly, float lz,
 // Why it never rejects a touched box.  id is within 1 ulp, step is a power
 // of two: the roundings of D, id, b, bn / bf and the fma add up to at most
 // 2^-21.4 |b| + 2^-22.4 q |a|.  The margin is 2^-19 |b|, and for every plane
-// with q > 0 also 2^-10 |a| (k_widen places planes at least 2^-10 steps
+// with q > 0 also 2^-11 |a| (Wide::store places planes at least 2^-11 steps
 // outside the child's box; a lower plane at q = 0 is the exact corner, and
 // its parameter has no term in q).  So each parameter is strictly on the
 // safe side of the exact one, by enough that (i) a box met at t <= 1 has
 // near < 1: there q |a| + |b| >= 1, hence a margin of at least 2^-19 (2^-19 |b|
-// + 2^-10 |a|, q <= 255) minus the shift 2^-21 and the roundings; (ii) a box
+// + 2^-11 |a|, q <= 255) minus the shift 2^-21 and the roundings; (ii) a box
 // left at t >= 0 has far >= 2^-21 minus roundings relative to it, so far > 0,
 // also when the start lies exactly on its face (b = 2^-21 then); (iii) in
 // between, near <= exact near <= exact far <= far with a strict step on each
@@ -170,7 +170,7 @@ __device__ inline bool slab_hit(const Seg &s, float lx, float ly, float lz,
 // box_rcp keeps every product finite, so no NaN arises from finite input.
 constexpr float kPlaneRel = 0x1p-19f;
 constexpr float kStartShift = 0x1p-21f;
-constexpr double kQuantMargin = 0x1p-10;  // grid steps between a child's box and its planes
+constexpr float kQuantMargin = 0x1p-10f;  // grid steps between a child's box and its planes, before FP32 rounding
 
 __device__ inline bool qslab_hit(float ax, float ay, float az, float bnx, float bny, float bnz, float bfx,
                                  float bfy, float bfz, float qnx, float qny, float qnz, float qfx, float qfy,

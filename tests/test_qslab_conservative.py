@@ -1,8 +1,8 @@
 """The quantised box test of the four-way walk never rejects a box that the
 segment touches.
 
-Restates, in FP32 through numpy, the grid of a node (k_widen: corner,
-power-of-two steps, child planes at least 2^-10 steps outside the child's
+Restates, in FP32 through numpy, the grid of a node (Wide::store: corner,
+power-of-two steps, child planes at least 2^-11 steps outside the child's
 box except a lower plane at the corner), the guarded reciprocal (box_tiny,
 box_rcp; the hardware reciprocal taken as any value within 1 ulp) and the
 test itself (qslab_hit: planes at fma(q, a, b -+ |b| 2^-19), shifted by
@@ -10,7 +10,7 @@ test itself (qslab_hit: planes at fma(q, a, b -+ |b| 2^-19), shifted by
 slab test of test_slab_conservative.py.  fma is formed in FP64 and rounded
 once; the product of two FP32 numbers is exact there.
 """
-import math
+from fractions import Fraction
 
 import numpy as np
 import pytest
@@ -25,21 +25,31 @@ def fma(a, b, c):
 
 
 def grid(lo, hi):
-    """Steps of a node whose box is [lo, hi]."""
+    """Steps of a node whose box is [lo, hi]: the exponent of the next power
+    of two above extent / 254.5, from the bits of the FP32 value."""
     step = []
     for k in range(3):
-        x = (float(hi[k]) - float(lo[k])) * (1 + 2.0 ** -40) / 254.5
-        if not x > 2.0 ** -126:
-            step.append(2.0 ** -126)
-            continue
-        m, e = math.frexp(x)
-        step.append(2.0 ** (e - 1 if m == 0.5 else e))
+        x = F32(F32(hi[k] - lo[k]) * F32((1 + 2.0 ** -20) / 254.5))
+        u = int(x.view(np.uint32))
+        e = (u >> 23) - 127 + (1 if u & 0x7FFFFF else 0)
+        step.append(2.0 ** min(max(e, -126), 127))
     return step
 
 
 def planes(lo, step, clo, chi):
-    qlo = [min(max(math.floor((float(clo[k]) - float(lo[k])) / step[k] - 2.0 ** -10), 0), 255) for k in range(3)]
-    qhi = [min(max(math.ceil((float(chi[k]) - float(lo[k])) / step[k] + 2.0 ** -10), 0), 255) for k in range(3)]
+    qlo, qhi = [], []
+    for k in range(3):
+        inv, m = F32(1.0 / step[k]), F32(2.0 ** -10)
+        x = np.floor(F32(F32(F32(clo[k] - lo[k]) * inv) - m))
+        y = np.ceil(F32(F32(F32(chi[k] - lo[k]) * inv) + m))
+        qlo.append(int(min(max(x, 0), 255)))
+        qhi.append(int(min(max(y, 0), 255)))
+        # the quantised box holds the child's (exactly), and by the margin the
+        # box test needs wherever a plane is not the corner itself
+        assert Fraction(qhi[k]) * Fraction(step[k]) + Fraction(float(lo[k])) >= Fraction(float(chi[k])) + Fraction(
+            step[k]) / 2048
+        assert qlo[k] == 0 or Fraction(qlo[k]) * Fraction(step[k]) + Fraction(float(lo[k])) <= Fraction(
+            float(clo[k])) - Fraction(step[k]) / 2048
     return qlo, qhi
 
 
