@@ -65,15 +65,16 @@ enum {
 /* Build / query options; a zero field selects the default. */
 typedef struct {
     int32_t leaf_size;    /* max triangles per BVH leaf, 1..16 (default 1) */
-    int32_t block_size;   /* traversal workgroup size: 64, 128, 192 or 256 (default 128) */
+    int32_t block_size;   /* traversal workgroup size: 64, 128, 192 or 256 (default 128; left at the default,
+                             the four-way walk of a single mesh takes 256) */
     int32_t defer_lanes;  /* a wave tests its lanes' pending triangles once fewer than this many
                              of its lanes can still visit a node, 1..64 (default 32) */
     int32_t refill_lanes; /* a wave writes finished segments and takes new ones once this many
                              of its lanes are done, 1..64 (default 32) */
     int32_t chunk;        /* segments a wave claims per global atomic, 64..2^20
                              (default: about eight chunks per resident wave, 64..4096) */
-    int32_t stack_depth;  /* traversal-stack entries per lane kept in LDS (default 18 on the four-way
-                             walk, 17 for its boolean and counting walks, 32 on the binary walk); a
+    int32_t stack_depth;  /* traversal-stack entries per lane kept in LDS (default 12 on the four-way
+                             walk, 32 on the binary walk); a
                              walk that needs more continues in device memory (four-way: its older
                              entries move there; binary: the deep pass walks it again).  A smaller
                              value raises occupancy. 1..255 */

@@ -12,18 +12,17 @@
 // avoids.
 //
 // A lane walks the tree from the entry node with a stack laid out
-// [depth][lane] in LDS so a wave's pushes and pops hit distinct banks (18
-// entries per lane on the four-way walk, 17 when it holds the top copy
-// below; 32 on the binary walk).  On the four-way walk the LDS part is a
+// [depth][lane] in LDS so a wave's pushes and pops hit distinct banks (12
+// entries per lane on the four-way walk, 32 on the binary walk).  On the four-way walk the LDS part is a
 // window on the stack's top whose older entries move to device memory when
 // it is full.  On the binary walk a push past it stops the walk and queues
 // its segment, and a deep pass (a small grid whose stacks continue in device
 // memory up to a bound on the tree height) walks those segments again from
 // the root.  No tree height is needed on the host, so builds, rebuilds and
 // queries are enqueued without waiting for the device.
-// Each node step loads one 64-byte record; the boolean and counting walks of
-// a single mesh read the records of the top three four-way levels from a
-// per-workgroup copy in LDS instead.
+// Each node step loads one 64-byte record; the four-way walk of a single mesh
+// reads the records of the top four levels from a per-workgroup copy in LDS
+// instead.
 // The default four-way walk (Node4) tests the segment against the four
 // quantised boxes of the node's grandchildren and pushes the touched
 // children, nodes and leaves alike; the binary walk (Node, branching 2)
@@ -159,60 +158,55 @@ __device__ inline uint32_t lanes_below(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// The four-way walk of a single mesh (boolean and counting modes) reads
-// the records of the top three levels (the entry record, its internal
-// children and theirs: at most 21) from a copy in LDS.  Every walk starts
-// there, so these are the most visited records; served by LDS they leave
-// the vector-memory path, which the walk keeps busy.  References at or above kTopRef name a record of the
-// copy (internal references stay below 2^27).
-constexpr int kTopNodes = 21;
+// The four-way walk of a single mesh reads the records of the top four
+// levels (the entry record and three levels below: at most 85) from a copy
+// in LDS.  Every walk starts there, so these are the most visited records;
+// served by LDS they leave the vector-memory path, which the walk keeps
+// busy.  A workgroup of 256 threads shares the copy: with the 12-entry stack
+// window 7 workgroups fit a CU.  Against three levels, boolean and counting
+// walks only, 128 threads and 17 entries: 10M boolean queries of the
+// 29,768-triangle mesh 537 -> 486 us, all hits 1,123 -> 1,084 us.  References at or above kTopRef are kTopRef plus the byte offset of a
+// record in the copy (internal references stay below 2^27).  Records lie 80
+// bytes apart, so lanes that read the same words of different records use
+// all banks.
+constexpr int kTopLevels = 4;
+constexpr int kTopNodes = 85;
+constexpr int kTopStride = 80;
 constexpr int32_t kTopRef = 0x40000000;
 
-// Modes that walk with the top copy: the boolean and counting walks.  The
-// first-hit and all-hits walks go deeper on large meshes, and there the
-// LDS entries the copy takes from the stack cost more than it saves.
-constexpr bool top_copy(uint32_t mode) { return !(mode & (M_ALL | M_FIRST)); }
-
-__device__ inline bool inner_ref(int32_t r) { return r >= 0; }
 __device__ inline int32_t ref_at(const int4 &c, int k) { return k == 0 ? c.x : (k == 1 ? c.y : (k == 2 ? c.z : c.w)); }
 
-// Lane l < kTopNodes of the block's first wave fills slot l of the copy:
-// slot 0 the entry record, slots 1..4 its children, slot 5 + 4k + j child j
-// of slot 1 + k.  A slot whose record does not exist stays unused: no
-// reference names it.  References between copied records are rewritten to
-// kTopRef + slot.
-__device__ inline void load_top(const Node4 *__restrict__ nodes4, int32_t entry, uint4 *top, int l)
+// The whole block fills the copy level by level: slot 0 the entry record,
+// slot 4 p + 1 + c child c of slot p.  The thread that copies a child turns
+// its parent's reference to it into one to the copy; a slot without a record
+// gets leaf references, so nothing is copied below it.
+__device__ inline void load_top(const Node4 *__restrict__ nodes4, int32_t entry, uint4 *top)
 {
-    if (l >= kTopNodes || entry < 0) return;
-    const int4 *rec = reinterpret_cast<const int4 *>(nodes4);
-    const int4 c0 = rec[4 * (int64_t)entry + 3];
-    int32_t id = -1;
-    if (l == 0) {
-        id = entry;
-    } else if (l < 5) {
-        const int32_t r = ref_at(c0, l - 1);
-        id = inner_ref(r) ? r : -1;
-    } else {
-        const int32_t p = ref_at(c0, (l - 5) >> 2);
-        if (inner_ref(p)) {
-            const int32_t r = ref_at(rec[4 * (int64_t)p + 3], (l - 5) & 3);
-            id = inner_ref(r) ? r : -1;
+    int first = 0, count = 1;
+    for (int level = 0; level < kTopLevels; ++level) {
+        for (int l = first + (int)threadIdx.x; l < first + count; l += blockDim.x) {
+            int32_t id = entry;
+            if (l > 0) {
+                int32_t *const r = reinterpret_cast<int32_t *>(top) + ((l - 1) >> 2) * (kTopStride / 4) + 12 + ((l - 1) & 3);
+                id = *r;
+                if (id >= 0) *r = kTopRef + l * kTopStride;
+            }
+            uint4 *const t = top + l * (kTopStride / 16);
+            if (id >= 0) {
+                const uint4 *q = reinterpret_cast<const uint4 *>(nodes4 + id);
+                const uint4 r0 = q[0], r1 = q[1], r2 = q[2], r3 = q[3];
+                t[0] = r0;
+                t[1] = r1;
+                t[2] = r2;
+                t[3] = r3;
+            } else {
+                t[3] = make_uint4(~0u, ~0u, ~0u, ~0u);
+            }
         }
+        __syncthreads();
+        first = 4 * first + 1;
+        count *= 4;
     }
-    if (id < 0) return;
-    const uint4 *q = reinterpret_cast<const uint4 *>(nodes4 + id);
-    int4 c = rec[4 * (int64_t)id + 3];
-    if (l < 5) {
-        const int32_t base = kTopRef + (l == 0 ? 1 : 5 + 4 * (l - 1));
-        c.x = inner_ref(c.x) ? base : c.x;
-        c.y = inner_ref(c.y) ? base + 1 : c.y;
-        c.z = inner_ref(c.z) ? base + 2 : c.z;
-        c.w = inner_ref(c.w) ? base + 3 : c.w;
-    }
-    top[4 * l] = q[0];
-    top[4 * l + 1] = q[1];
-    top[4 * l + 2] = q[2];
-    top[4 * l + 3] = make_uint4((uint32_t)c.x, (uint32_t)c.y, (uint32_t)c.z, (uint32_t)c.w);
 }
 
 // All hits: overflow-table entries and arena records are handed out in
@@ -987,13 +981,12 @@ __global__ __launch_bounds__(256)
     // (the usual case) every workgroup leaves before touching memory
     if (RETRY && a.scalars[kRetryN] == 0) return;
     extern __shared__ int32_t lds_dyn[];
-    constexpr bool TOP = !BATCH && top_copy(MODE);
+    constexpr bool TOP = !BATCH && !RETRY;
     constexpr bool NEAREST = (MODE & M_FIRST) && !(MODE & M_FULL);
-    __shared__ uint4 top4[TOP ? 4 * kTopNodes : 4];
-    if constexpr (TOP) {
-        if (threadIdx.x < 64) load_top(a.nodes4, a.entry, top4, threadIdx.x);
-        __syncthreads();
-    }
+    __shared__ uint4 top4[TOP ? kTopNodes * kTopStride / 16 : 1];
+    // (a launch of few items ends sooner without the copy)
+    const bool top = TOP && a.own_max == 64 && a.entry >= 0;
+    if (top) load_top(a.nodes4, a.entry, top4);
     // each wave's stack slots [lds_depth + 1][64], then each wave's leaf queue
     const int wave = (int)(threadIdx.x >> 6);
     const int wave_ints = 64 * (a.lds_depth + 1);
@@ -1124,7 +1117,7 @@ __global__ __launch_bounds__(256)
                     L.tiny = box_tiny(L.seg, scale);
                     box_rcp(L.seg, 1.0f, L.tiny);
                     L.own = (int32_t)__lane_id();
-                    cur = entry < 0 ? kDone : (TOP ? kTopRef : entry);
+                    cur = entry < 0 ? kDone : (top ? kTopRef : entry);
                     sp = bot = stk;
                     *stk = kDone;
                     col &= ~1023;
@@ -1167,7 +1160,8 @@ __global__ __launch_bounds__(256)
                 uint4 P, Q, R;
                 int4 C;
                 if (TOP && cur >= kTopRef) {
-                    const uint4 *t = top4 + 4 * (cur - kTopRef);
+                    const uint4 *t =
+                        reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(top4) + (cur - kTopRef));
                     P = t[0];
                     Q = t[1];
                     R = t[2];
@@ -2390,15 +2384,24 @@ int stack_need(int height, int width)
 }
 
 // LDS stack entries per lane of the main pass: the `stack_depth` option, or
-// 18 on the four-way walk (17 when the walk also holds the 1,344-byte copy
-// of the top records), 32 on the binary walk; never more than the bound.
-int lds_part(const rsi_bvh *h, bool top)
+// 12 on the four-way walk (a fuller stack continues in device memory; 8
+// entries made that common on the 499,280-triangle sphere, 2,952 -> 7,463 us,
+// 10 cost 16%, 12 to 24 measure alike), 32 on the binary walk; never more
+// than the bound.
+int lds_part(const rsi_bvh *h)
 {
     const int width = h->width_built;
     const int bound = stack_need(h->height_bound, width);
     int cap = h->stack_cap;
-    if (cap <= 0) cap = width == 4 ? (top ? 17 : 18) : 32;
+    if (cap <= 0) cap = width == 4 ? 12 : 32;
     return cap < bound ? cap : bound;
+}
+
+// Workgroup size: the `block_size` option when one was chosen, or 256 where
+// the waves share the copy of the top records, else 128.
+int want_block(const rsi_bvh *h)
+{
+    return !h->block_chosen && h->width_built == 4 && h->M == 1 ? 256 : h->block_size;
 }
 
 QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, const QueryOut &o)
@@ -2488,7 +2491,7 @@ hipError_t launch_all_hits_tail(const QArgs &a, bool batch, hipStream_t s)
 
 int64_t deep_stack_entries(const rsi_bvh *h, uint32_t mode)
 {
-    const int ld = lds_part(h, h->width_built == 4 && top_copy(mode));
+    const int ld = lds_part(h);
     const int need = stack_need(h->height_bound, h->width_built);
     return (int64_t)kStackCols * (need > ld ? need : ld);
 }
@@ -2504,8 +2507,8 @@ hipError_t launch_query_scratch(rsi_bvh *h, const float *S, const float *E, int6
                                 const QueryOut &o, const QueryScratch &sc, bool keep_flags, hipStream_t s)
 {
     if (n_r == 0) return hipSuccess;
-    const int ld = lds_part(h, h->width_built == 4 && top_copy(mode));
-    const int block = fit_block(h->block_size, ld, h->width_built, mode);
+    const int ld = lds_part(h);
+    const int block = fit_block(want_block(h), ld, h->width_built, mode);
     const size_t lds = query_lds(block, ld, h->width_built, mode);
     QArgs a = make_args(h, S, E, n_r, o), d;
     a.retry_q = sc.retry_q;
@@ -2526,8 +2529,8 @@ hipError_t launch_batch_query(rsi_bvh *h, const BatchTables &bt, int64_t n_total
                               hipStream_t s)
 {
     if (n_total == 0) return hipSuccess;
-    const int ld = lds_part(h, false);
-    const int block = fit_block(h->block_size, ld, h->width_built, mode);
+    const int ld = lds_part(h);
+    const int block = fit_block(want_block(h), ld, h->width_built, mode);
     const size_t lds = query_lds(block, ld, h->width_built, mode);
     QueryOut o = {};
     o.cap = cap;

@@ -87,6 +87,7 @@ struct rsi_bvh {
     int64_t n_v = 0, n_t = 0;      // totals over all meshes
     int32_t leaf_size = 1;
     int32_t block_size = 128;
+    bool block_chosen = false;     // block_size was set by the caller
     int32_t defer_lanes = 32;
     int32_t refill_lanes = 32;
     int32_t chunk = 0;             // 0: sized per launch
