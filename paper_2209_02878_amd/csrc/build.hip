@@ -328,9 +328,9 @@ __device__ inline void write_entry(const BuildArgs &a, int32_t m, int32_t lo, in
     a.mesh_scale[m] = s;
 }
 
-// Four-way view: record n lists the boxes and references of n's
-// grandchildren (a leaf child stands for itself), quantised inside their
-// union box.  Every node gets its record, also those no traversal reaches
+// Four-way view: record n lists the boxes and references of up to four of
+// n's descendants whose subtrees make up n's, quantised inside their union
+// box.  Every node gets its record, also those no traversal reaches
 // (inside collapsed leaves).
 //
 // Grid step per axis: the smallest power of two 2^e with 254.5 * 2^e >= the
@@ -348,21 +348,65 @@ __device__ inline int quant_exponent(float ext)
     return e < -126 ? -126 : (e > 127 ? 127 : e);
 }
 
+// The children of a record, from the node's two: the internal one with the
+// larger box surface gives way to its own two, twice.
 struct Wide {
     float box[4][6];
     int32_t ref[4];
     int k = 0;
     __device__ inline void add(const float *b, int32_t r)
     {
+        put(k, b, r);
+        ++k;
+    }
+    __device__ inline void put(int at, const float *b, int32_t r)
+    {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            if (s == k) {
+            if (s == at) {
 #pragma unroll
                 for (int q = 0; q < 6; ++q) box[s][q] = b[q];
                 ref[s] = r;
             }
         }
-        ++k;
+    }
+    // `child(c, side, box)` reads node c's child: its box, and its reference
+    template <typename Child>
+    __device__ inline void open(Child child)
+    {
+#pragma unroll
+        for (int turn = 0; turn < 2; ++turn) {
+            int at = -1;
+            int32_t c = -1;
+            float most = -1.0f;
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                if (s >= k || ref[s] < 0) continue;
+                const float x = box[s][3] - box[s][0], y = box[s][4] - box[s][1], z = box[s][5] - box[s][2];
+                const float area = x * y + y * z + z * x;
+                if (at < 0 || area > most) {
+                    at = s;
+                    c = ref[s];
+                    most = area;
+                }
+            }
+            if (at < 0) break;
+            // in place, so the children stay in Morton order
+#pragma unroll
+            for (int s = 3; s > 0; --s) {
+                if (s > at + 1) {
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) box[s][q] = box[s - 1][q];
+                    ref[s] = ref[s - 1];
+                }
+            }
+            float b[6];
+            int32_t r = child(c, 0, b);
+            put(at, b, r);
+            r = child(c, 1, b);
+            put(at + 1, b, r);
+            ++k;
+        }
     }
     __device__ inline void store(Node4 *out, int64_t n) const
     {
@@ -578,17 +622,14 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
             // record's boxes are here (a later pass over the node records
             // would read them all again: 45 us at 499,280 triangles)
             Wide w;
+            w.add(lbox[tid], lref[tid][0]);
+            w.add(lbox[tid] + 6, lref[tid][1]);
+            w.open([&](int32_t c, int side, float *b) -> int32_t {
+                const int slot = c - B0;
 #pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                const int32_t c = lref[tid][side];
-                if (c >= 0) {
-                    const int slot = c - B0;
-                    w.add(lbox[slot], lref[slot][0]);
-                    w.add(lbox[slot] + 6, lref[slot][1]);
-                } else {
-                    w.add(lbox[tid] + 6 * side, c);
-                }
-            }
+                for (int q = 0; q < 6; ++q) b[q] = lbox[slot][6 * side + q];
+                return lref[slot][side];
+            });
             w.store(a.nodes4 + p, n);
             arrived = kWidened;
         }
@@ -664,21 +705,25 @@ __global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, c
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n || arrive[j] == kWidened) return;
-    const Node nd = nodes[j];
+    // a node no climb reached (inside a collapsed leaf) may hold anything:
+    // its references are checked before use
+    const auto read = [&](int64_t c, int side, float *b) -> int32_t {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) b[q] = nodes[c].f[6 * side + q];
+        const int32_t r = nodes[c].ref[side];
+        return r < n ? r : leaf_ref(0, 1);
+    };
     Wide w;
     for (int side = 0; side < 2; ++side) {
-        const int32_t c = nd.ref[side];
-        if (c >= 0 && c < n) {
-            const Node ch = nodes[c];
-            for (int g = 0; g < 2; ++g) w.add(ch.f + 6 * g, ch.ref[g]);
-        } else {
-            // the entry record's far box (all FLT_MAX) is no child: the slot
-            // stays empty
-            bool far = true;
-            for (int q = 0; q < 6; ++q) far = far && nd.f[6 * side + q] == FLT_MAX;
-            if (!far) w.add(nd.f + 6 * side, c < 0 ? c : leaf_ref(0, 1));
-        }
+        float b[6];
+        const int32_t r = read(j, side, b);
+        // the entry record's far box (all FLT_MAX) is no child: the slot
+        // stays empty
+        bool far = true;
+        for (int q = 0; q < 6; ++q) far = far && b[q] == FLT_MAX;
+        if (!far) w.add(b, r);
     }
+    w.open(read);
     w.store(out + j, n);
 }
 

@@ -2252,9 +2252,9 @@ hipError_t launch_refine_first(const QArgs &a, hipStream_t s)
 
 // Columns of the stacks' device-memory part, and with it the most threads of
 // the deep pass (about one workgroup per CU: the queue is short).  At the
-// deepest stack bound they take 16 MB, which leaves rsi_query_noalloc's fixed
+// deepest stack bound (274 entries) they take 16 MB, which leaves rsi_query_noalloc's fixed
 // array room for a queue of 4.3 million segments.
-constexpr int kStackCols = 28672;
+constexpr int kStackCols = 14848;
 
 // Waves per CU that few items are spread over.
 constexpr int kSpreadWaves = 6;
@@ -2276,7 +2276,7 @@ hipError_t launch_kernel(const QArgs &a, int block, size_t lds, hipStream_t s)
     b.own_max = 64;
     if (RETRY) {
         grid = device_cus();
-        if (grid > kStackCols / block) grid = kStackCols / block;  // block <= 256: at least 112
+        if (grid > kStackCols / block) grid = kStackCols / block;  // block <= 256: at least 58
         if (a.lds_depth < a.depth &&
             (a.gstack == nullptr || grid * block * (int64_t)(a.depth - a.lds_depth) > a.gstack_cap))
             return hipErrorInvalidValue;
@@ -2376,10 +2376,11 @@ int fit_block(int want, int depth, int width, uint32_t mode)
 
 // Traversal-stack entries a lane can need for a tree of the given height:
 // one pushed sibling per binary level (height + 1); in the four-way walk up
-// to three per four-way level, of which there are at most (height + 2) / 2 + 1.
+// to three per four-way level, each of which goes down at least one binary
+// level (below 512 in all, the bits of the walk's entry count).
 int stack_need(int height, int width)
 {
-    if (width == 4) return 3 * ((height + 2) / 2 + 1) + 1;
+    if (width == 4) return 3 * (height + 1) + 1;
     return height + 1;
 }
 

@@ -31,11 +31,12 @@ struct alignas(64) Node {
 static_assert(sizeof(Node) == 64, "Node must be 64 bytes");
 
 // Node4 (64 bytes, four 16-byte loads like a binary step): the four-way
-// view of binary node n, whose children are n's grandchildren (a child that
-// is a leaf stands for itself), with the child boxes quantised to 8 bits per
+// view of binary node n, whose children are descendants of n (its two
+// children, the internal one with the larger box surface replaced by its own
+// two, twice), with the child boxes quantised to 8 bits per
 // plane on a grid anchored at the lower corner of n's box.  Record n of the
 // Node4 array belongs to binary node n, so a child reference (an internal
-// grandchild's index, or a leaf) is valid in both arrays.
+// node's index, or a leaf) is valid in both arrays.
 //
 //   ox, oy, oz   lower corner of n's box (exact)
 //   sx, sy, sz   grid steps, powers of two (2^-126 .. 2^122) with 255
