@@ -108,8 +108,9 @@ __global__ __launch_bounds__(256) void k_adj_solve(AdjArgs a)
     if (pos >= 0 && pos < a.n_t) {
         const float4 ta = a.tris[pos].a, tb4 = a.tris[pos].b, tc = a.tris[pos].c;
         if (tc.w == 0.0f) {
-            const d3 s = mk(a.S[3 * i], a.S[3 * i + 1], a.S[3 * i + 2]);
-            const d3 e = mk(a.E[3 * i], a.E[3 * i + 1], a.E[3 * i + 2]);
+            const row3 fs = ld3(a.S + 3 * i), fe = ld3(a.E + 3 * i);
+            const d3 s = mk(fs.x, fs.y, fs.z);
+            const d3 e = mk(fe.x, fe.y, fe.z);
             const d3 v0 = mk(ta.x, ta.y, ta.z);
             const d3 v1 = mk(ta.w, tb4.x, tb4.y);
             const d3 v2 = mk(tb4.z, tb4.w, tc.x);
@@ -123,7 +124,11 @@ __global__ __launch_bounds__(256) void k_adj_solve(AdjArgs a)
                 const double t = dot(q, c12) * inv;
                 const double u = dot(md, cross(q, e2)) * inv;
                 const double v = dot(md, cross(e1, q)) * inv;
-                const d3 pb = a.g_p ? mk(a.g_p[3 * i], a.g_p[3 * i + 1], a.g_p[3 * i + 2]) : mk(0, 0, 0);
+                d3 pb = mk(0, 0, 0);
+                if (a.g_p) {
+                    const row3 g = ld3(a.g_p + 3 * i);
+                    pb = mk(g.x, g.y, g.z);
+                }
                 const double tb = (a.g_t ? (double)a.g_t[i] : 0.0) + dot(pb, d);
                 const double ub = a.g_uv ? (double)a.g_uv[2 * i] : 0.0;
                 const double vb = a.g_uv ? (double)a.g_uv[2 * i + 1] : 0.0;
@@ -149,16 +154,8 @@ __global__ __launch_bounds__(256) void k_adj_solve(AdjArgs a)
             }
         }
     }
-    if (a.dS) {
-        a.dS[3 * i] = (float)gs[0];
-        a.dS[3 * i + 1] = (float)gs[1];
-        a.dS[3 * i + 2] = (float)gs[2];
-    }
-    if (a.dE) {
-        a.dE[3 * i] = (float)ge[0];
-        a.dE[3 * i + 1] = (float)ge[1];
-        a.dE[3 * i + 2] = (float)ge[2];
-    }
+    if (a.dS) st3(a.dS + 3 * i, (float)gs[0], (float)gs[1], (float)gs[2]);
+    if (a.dE) st3(a.dE + 3 * i, (float)ge[0], (float)ge[1], (float)ge[2]);
     a.rec[i] = r;
     a.rec_v[i] = rv;
     a.keys[i] = key;

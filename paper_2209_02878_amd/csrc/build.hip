@@ -81,9 +81,8 @@ __global__ void k_gather(int32_t M, const float *const *__restrict__ Vp, const i
         if (k < nv) {
             const int32_t m = mesh_of(voff, M, k);
             const int64_t loc = k - voff[m];
-            V[3 * k] = Vp[m][3 * loc];
-            V[3 * k + 1] = Vp[m][3 * loc + 1];
-            V[3 * k + 2] = Vp[m][3 * loc + 2];
+            const row3 v = ld3(Vp[m] + 3 * loc);
+            st3(V + 3 * k, v.x, v.y, v.z);
         } else {
             const int64_t j = k - nv;
             const int32_t m = mesh_of(toff, M, j);
@@ -172,9 +171,10 @@ __global__ __launch_bounds__(kCentBlock) void k_centroids(BuildArgs a)
             atomicOr(&a.scalars[kBadIndex], 1);
             va = vb = vc = 0;
         }
-        const float cx = (a.V[3 * va] + a.V[3 * vb] + a.V[3 * vc]) * (1.0f / 3.0f);
-        const float cy = (a.V[3 * va + 1] + a.V[3 * vb + 1] + a.V[3 * vc + 1]) * (1.0f / 3.0f);
-        const float cz = (a.V[3 * va + 2] + a.V[3 * vb + 2] + a.V[3 * vc + 2]) * (1.0f / 3.0f);
+        const row3 pa = ld3(a.V + 3 * (int64_t)va), pb = ld3(a.V + 3 * (int64_t)vb), pc = ld3(a.V + 3 * (int64_t)vc);
+        const float cx = (pa.x + pb.x + pc.x) * (1.0f / 3.0f);
+        const float cy = (pa.y + pb.y + pc.y) * (1.0f / 3.0f);
+        const float cz = (pa.z + pb.z + pc.z) * (1.0f / 3.0f);
         a.cent[j] = cx;
         a.cent[a.n_t + j] = cy;
         a.cent[2 * a.n_t + j] = cz;
@@ -526,9 +526,10 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
         if (va < 0 || va >= a.n_v) va = 0;
         if (vb < 0 || vb >= a.n_v) vb = 0;
         if (vd < 0 || vd >= a.n_v) vd = 0;
-        const float v0x = a.V[3 * va], v0y = a.V[3 * va + 1], v0z = a.V[3 * va + 2];
-        const float v1x = a.V[3 * vb], v1y = a.V[3 * vb + 1], v1z = a.V[3 * vb + 2];
-        const float v2x = a.V[3 * vd], v2y = a.V[3 * vd + 1], v2z = a.V[3 * vd + 2];
+        const row3 p0 = ld3(a.V + 3 * (int64_t)va), p1 = ld3(a.V + 3 * (int64_t)vb), p2 = ld3(a.V + 3 * (int64_t)vd);
+        const float v0x = p0.x, v0y = p0.y, v0z = p0.z;
+        const float v1x = p1.x, v1y = p1.y, v1z = p1.z;
+        const float v2x = p2.x, v2y = p2.y, v2z = p2.z;
         Tri tr;
         tr.a = make_float4(v0x, v0y, v0z, v1x);
         tr.b = make_float4(v1y, v1z, v2x, v2y);

@@ -118,14 +118,16 @@ __global__ __launch_bounds__(256) void k_seg_keys(const float *__restrict__ S, c
     if (i >= n) return;
     uint32_t q[3];
     uint32_t oct = 0;
+    const row3 s = ld3(S + 3 * i), e = ld3(E + 3 * i);
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
         const float lo = ordered_to_float(b[k]), hi = ordered_to_float(b[3 + k]);
-        const float m = 0.5f * (S[3 * i + k] + E[3 * i + k]);
+        const float m = 0.5f * (s[k] + e[k]);
         const float ext = hi - lo;
         float x = ext > 0.0f ? (m - lo) / ext * 1024.0f : 0.0f;
         x = fminf(fmaxf(x, 0.0f), 1023.0f);
         q[k] = (uint32_t)x;
-        oct |= (E[3 * i + k] < S[3 * i + k] ? 1u : 0u) << k;
+        oct |= (e[k] < s[k] ? 1u : 0u) << k;
     }
     const uint32_t code = spread10(q[0]) | (spread10(q[1]) << 1) | (spread10(q[2]) << 2);
     keys[i] = ((uint64_t)oct << 30) | code;
@@ -140,10 +142,9 @@ __global__ __launch_bounds__(256) void k_gather_segments(const float *__restrict
     if (k >= n) return;
     int64_t i = order[k];
     if (i < 0 || i >= n) i = 0;  // every read stays inside S and E
-    for (int c = 0; c < 3; ++c) {
-        So[3 * k + c] = S[3 * i + c];
-        Eo[3 * k + c] = E[3 * i + c];
-    }
+    const row3 s = ld3(S + 3 * i), e = ld3(E + 3 * i);
+    st3(So + 3 * k, s.x, s.y, s.z);
+    st3(Eo + 3 * k, e.x, e.y, e.z);
 }
 
 }  // namespace

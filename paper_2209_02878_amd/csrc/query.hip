@@ -895,12 +895,13 @@ __device__ inline int32_t start_item(const QArgs &a, Lane &L, int32_t k)
     }
     L.item = it;
     L.seg_i = i;
-    L.seg.ox = ld_nt(sp);
-    L.seg.oy = ld_nt(sp + 1);
-    L.seg.oz = ld_nt(sp + 2);
-    L.seg.dx = ld_nt(ep) - L.seg.ox;
-    L.seg.dy = ld_nt(ep + 1) - L.seg.oy;
-    L.seg.dz = ld_nt(ep + 2) - L.seg.oz;
+    const row3 o = ld3_nt(sp), e = ld3_nt(ep);
+    L.seg.ox = o.x;
+    L.seg.oy = o.y;
+    L.seg.oz = o.z;
+    L.seg.dx = e.x - o.x;
+    L.seg.dy = e.y - o.y;
+    L.seg.dz = e.z - o.z;
     L.tlim = 1.0f;
     L.best_t = INFINITY;
     L.best_id = 0x7FFFFFFF;
@@ -1709,11 +1710,11 @@ __global__ __launch_bounds__(256) void k_spill_place(QArgs a)
                 float t = INFINITY;
                 if (pos >= 0 && pos < a.n_tris) {
                     const ItemView<BATCH> v = item_view<BATCH>(a, a.ovf_seg[e]);
+                    const row3 p = ld3(v.S + 3 * v.i), q = ld3(v.E + 3 * v.i);
                     float w[9];
                     tri_load(a.tris, pos, w, id);
                     double td, u, vv;
-                    mt_refine64(v.S[3 * v.i], v.S[3 * v.i + 1], v.S[3 * v.i + 2], v.E[3 * v.i], v.E[3 * v.i + 1],
-                                v.E[3 * v.i + 2], w, td, u, vv);
+                    mt_refine64(p.x, p.y, p.z, q.x, q.y, q.z, w, td, u, vv);
                     t = (float)td;
                 }
                 a.o.pool_ids[off + c] = id;
@@ -1892,12 +1893,13 @@ __device__ inline void item_ends(const QArgs &a, int64_t k, float &sx, float &sy
                                  float &ez)
 {
     const ItemView<BATCH> v = item_view<BATCH>(a, k);
-    sx = ld_nt(v.S + 3 * v.i);
-    sy = ld_nt(v.S + 3 * v.i + 1);
-    sz = ld_nt(v.S + 3 * v.i + 2);
-    ex = ld_nt(v.E + 3 * v.i);
-    ey = ld_nt(v.E + 3 * v.i + 1);
-    ez = ld_nt(v.E + 3 * v.i + 2);
+    const row3 s = ld3_nt(v.S + 3 * v.i), e = ld3_nt(v.E + 3 * v.i);
+    sx = s.x;
+    sy = s.y;
+    sz = s.z;
+    ex = e.x;
+    ey = e.y;
+    ez = e.z;
 }
 
 // All hits, after the walk: every segment with 1..K crossings has their
@@ -2132,12 +2134,11 @@ __global__ void k_inside_ends(const float *__restrict__ P, int64_t n, const Node
     const float cx = 0.5f * (b[0] + b[3]), cy = 0.5f * (b[1] + b[4]), cz = 0.5f * (b[2] + b[5]);
     const float hx = 0.5f * (b[3] - b[0]), hy = 0.5f * (b[4] - b[1]), hz = 0.5f * (b[5] - b[2]);
     const float R = sqrtf(hx * hx + hy * hy + hz * hz);
-    const float px = P[3 * i], py = P[3 * i + 1], pz = P[3 * i + 2];
+    const row3 p = ld3(P + 3 * i);
+    const float px = p.x, py = p.y, pz = p.z;
     const float qx = px - cx, qy = py - cy, qz = pz - cz;
     const float L = sqrtf(qx * qx + qy * qy + qz * qz) + 2.0f * R + 1.0f;
-    E[3 * i] = px + L * kInsideDir[0];
-    E[3 * i + 1] = py + L * kInsideDir[1];
-    E[3 * i + 2] = pz + L * kInsideDir[2];
+    st3(E + 3 * i, px + L * kInsideDir[0], py + L * kInsideDir[1], pz + L * kInsideDir[2]);
 }
 
 __global__ void k_parity(const int32_t *__restrict__ count, int64_t n, uint8_t *__restrict__ inside)
@@ -2232,11 +2233,9 @@ __global__ __launch_bounds__(256) void k_refine_first(QArgs a)
         if (k < a.n_items) {
             st_nt(tri + i, hit ? r_id[tid] : -1);
             st_nt(tt + i, hit ? r_f[tid] : INFINITY);
-            st_nt(uv + 2 * i, hit ? r_f[256 + tid] : 0.0f);
-            st_nt(uv + 2 * i + 1, hit ? r_f[512 + tid] : 0.0f);
-            st_nt(pt + 3 * i, hit ? r_f[768 + tid] : 0.0f);
-            st_nt(pt + 3 * i + 1, hit ? r_f[1024 + tid] : 0.0f);
-            st_nt(pt + 3 * i + 2, hit ? r_f[1280 + tid] : 0.0f);
+            st2_nt(uv + 2 * i, hit ? r_f[256 + tid] : 0.0f, hit ? r_f[512 + tid] : 0.0f);
+            st3_nt(pt + 3 * i, hit ? r_f[768 + tid] : 0.0f, hit ? r_f[1024 + tid] : 0.0f,
+                   hit ? r_f[1280 + tid] : 0.0f);
         }
         __syncthreads();
     }

@@ -85,6 +85,29 @@ __host__ __device__ inline bool ref_is_leaf(int32_t r) { return r < 0; }
 __host__ __device__ inline int32_t leaf_first(int32_t r) { return r & kLeafFirstMask; }
 __host__ __device__ inline int32_t leaf_count(int32_t r) { return ((r >> kLeafFirstBits) & 15) + 1; }
 
+// Rows of two and three floats, aligned like a float, read or written by one
+// access.  (Three one-float accesses per row, 12 bytes apart across the
+// lanes, visit every cache line three times.)
+typedef float row2 __attribute__((ext_vector_type(2), aligned(4), may_alias));
+typedef float row3 __attribute__((ext_vector_type(3), aligned(4), may_alias));
+__device__ inline row3 ld3(const float *p) { return *reinterpret_cast<const row3 *>(p); }
+__device__ inline row3 ld3_nt(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const row3 *>(p)); }
+__device__ inline void st3(float *p, float x, float y, float z)
+{
+    const row3 v = {x, y, z};
+    *reinterpret_cast<row3 *>(p) = v;
+}
+__device__ inline void st3_nt(float *p, float x, float y, float z)
+{
+    const row3 v = {x, y, z};
+    __builtin_nontemporal_store(v, reinterpret_cast<row3 *>(p));
+}
+__device__ inline void st2_nt(float *p, float x, float y)
+{
+    const row2 v = {x, y};
+    __builtin_nontemporal_store(v, reinterpret_cast<row2 *>(p));
+}
+
 // ---------------------------------------------------------------- segment --
 //
 // Per-lane segment state: origin o = S, direction d = E - S (t in [0, 1]
