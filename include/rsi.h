@@ -68,9 +68,11 @@ typedef struct {
     int32_t block_size;   /* traversal workgroup size: 64, 128, 192 or 256 (default 128; left at the default,
                              the four-way walk of a single mesh takes 256) */
     int32_t defer_lanes;  /* a wave tests its lanes' pending triangles once fewer than this many
-                             of its lanes can still visit a node, 1..64 (default 32) */
+                             of its lanes can still visit a node, 1..64 (default 32; left at the
+                             default, the four-way all-hits walk takes 24) */
     int32_t refill_lanes; /* a wave writes finished segments and takes new ones once this many
-                             of its lanes are done, 1..64 (default 32) */
+                             of its lanes are done, 1..64 (default 32; left at the default, the
+                             four-way walk takes 24 for first hits and counts, 28 for all hits) */
     int32_t chunk;        /* segments a wave claims per global atomic, 64..2^20
                              (default: about eight chunks per resident wave, 64..4096) */
     int32_t stack_depth;  /* traversal-stack entries per lane kept in LDS (default 12 on the four-way

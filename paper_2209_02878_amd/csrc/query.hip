@@ -2404,7 +2404,27 @@ int want_block(const rsi_bvh *h)
     return !h->block_chosen && h->width_built == 4 && h->M == 1 ? 256 : h->block_size;
 }
 
-QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, const QueryOut &o)
+// Lanes that must be done before a wave refills, and lanes that must still
+// step before it tests leaves: the options when chosen, else 32 and 32 for
+// the boolean walk, whose lanes end close together.  The other walks of the
+// four-way view leave lanes waiting longer and refill sooner: at 24, the
+// first hits of 4M segments on 199,712 triangles take 377 us against 393 and
+// 4M counts on 29,768 triangles 305 us against 317 (16 and 20 measure
+// alike, and the boolean walk of 1M segments takes 119 us against 114).  All
+// hits: 28 and 24.  10M segments on 29,768 triangles take 1,043 us at 32 and
+// 32, 1,010 at 24 and 24, 1,033 at 32 and 24; on the 499,280-triangle sphere,
+// whose waves share fewer records the sooner they refill, 2,801, 2,815 and
+// 2,771 us.
+void lane_rule(const rsi_bvh *h, uint32_t mode, QArgs &a)
+{
+    a.defer = h->defer_lanes;
+    a.refill = h->refill_lanes;
+    if (h->width_built != 4 || mode == M_BOOL) return;
+    if (!h->refill_chosen) a.refill = (mode & M_ALL) ? 28 : 24;
+    if (!h->defer_chosen && (mode & M_ALL)) a.defer = 24;
+}
+
+QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, uint32_t mode, const QueryOut &o)
 {
     QArgs a;
     a.nodes = h->nodes;
@@ -2434,8 +2454,7 @@ QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, con
     a.retry_q = h->retry_q;
     a.retry_cap = h->retry_cap;
     a.max_steps = (int32_t)(h->n_t > 0 ? h->n_t : 1);
-    a.defer = h->defer_lanes;
-    a.refill = h->refill_lanes;
+    lane_rule(h, mode, a);
     a.chunk = h->chunk;
     a.M = h->M;
     a.mesh_entry = h->mesh_entry;
@@ -2510,7 +2529,7 @@ hipError_t launch_query_scratch(rsi_bvh *h, const float *S, const float *E, int6
     const int ld = lds_part(h);
     const int block = fit_block(want_block(h), ld, h->width_built, mode);
     const size_t lds = query_lds(block, ld, h->width_built, mode);
-    QArgs a = make_args(h, S, E, n_r, o), d;
+    QArgs a = make_args(h, S, E, n_r, mode, o), d;
     a.retry_q = sc.retry_q;
     a.retry_cap = sc.retry_cap;
     a.gstack = sc.gstack;
@@ -2537,7 +2556,7 @@ hipError_t launch_batch_query(rsi_bvh *h, const BatchTables &bt, int64_t n_total
     o.pool_ids = h->pool_ids;
     o.pool_ts = h->pool_ts;
     o.pool_cap = h->pool_cap;
-    QArgs a = make_args(h, nullptr, nullptr, n_total, o), d;
+    QArgs a = make_args(h, nullptr, nullptr, n_total, mode, o), d;
     a.bt = bt;
     pass_args(h, a, d, ld);
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(1), 0, s, h->scalars, nullptr, 0);

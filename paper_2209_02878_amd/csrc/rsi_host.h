@@ -90,6 +90,8 @@ struct rsi_bvh {
     bool block_chosen = false;     // block_size was set by the caller
     int32_t defer_lanes = 32;
     int32_t refill_lanes = 32;
+    bool defer_chosen = false;     // defer_lanes / refill_lanes were set by the caller
+    bool refill_chosen = false;
     int32_t chunk = 0;             // 0: sized per launch
     int32_t stack_cap = 0;         // LDS stack entries per lane of the main pass (0: default)
     bool counting = false;
