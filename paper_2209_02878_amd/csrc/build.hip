@@ -25,12 +25,11 @@
 //                reference into its parent, and the parent's arrival counter
 //                lets only the second child continue -- so the parent's box
 //                is formed exactly once, from both children.  Ranges with at
-//                most `leaf_size` triangles become leaves.  The climb runs in
-//                two passes: subtrees inside a block of 2048 sorted leaves
-//                finish in LDS (k_lbvh_local), the few that cross block
-//                boundaries finish in k_lbvh_global, which exchanges the
-//                climb data through memory past the per-XCD caches, so only
-//                those pay for cross-XCD ordering.
+//                most `leaf_size` triangles become leaves.  Subtrees inside
+//                a block of 2048 (or 512) sorted leaves finish in LDS
+//                (k_lbvh_local), and the few that cross block boundaries are
+//                joined in LDS too, by a workgroup per 64 blocks and one for
+//                the rest (k_lbvh_join).
 //
 // The entry node of mesh m is its last record off[m+1] - 1 (unused by its
 // n - 1 internal nodes): its left child is the root and its right child an
@@ -60,9 +59,7 @@ struct BuildArgs {
     Node4 *nodes4;         // four-way records, null when the walk does not use them
     Tri *tris;
     int32_t *arrive;
-    int32_t *heights;
-    int32_t *climb;
-    uint8_t *prefix;       // [n_t] common-prefix length at sorted split k
+    int32_t *joins;        // lists of the local blocks' subtrees (kListWords each)
     int32_t *bounds;       // [6M] ordered-int centroid bounds per mesh
     int32_t *mesh_height;  // [M]
     int32_t *mesh_root;    // [M]
@@ -458,15 +455,146 @@ struct Wide {
 // Arrival count of a node whose four-way record the local pass has written.
 constexpr int32_t kWidened = 4;
 
-constexpr int kClimbWords = 11;
+// The subtrees a workgroup has completed but cannot join to their siblings,
+// which lie in other workgroups' leaves: a list per local block, in leaf
+// order.  Each side of a block's range cuts a path from a mesh's root, and the
+// subtrees hang off it, at most 90 per side (prefix lengths grow along a
+// path).  An item: leaf range l, r, reference, height, box, and the prefix
+// lengths at splits l - 1 and r.
+constexpr int kListItems = 192;
+constexpr int kItemWords = 12;
+constexpr int kListWords = 4 + kListItems * kItemWords;  // word 0: items in use
+
+struct Item {
+    Climb c;
+    int32_t pre_l, pre_r;
+};
+
+__device__ inline void put_item(const BuildArgs &a, int32_t *list, int32_t at, const Item &x)
+{
+    if (at >= kListItems) {  // cannot happen in a tree of at most 90 levels; never written past the list
+        atomicOr(&a.scalars[kBadIndex], 2);
+        return;
+    }
+    int4 *w = reinterpret_cast<int4 *>(list + 4 + kItemWords * at);
+    w[0] = make_int4(x.c.l, x.c.r, x.c.ref, x.c.h);
+    w[1] = make_int4(__float_as_int(x.c.box[0]), __float_as_int(x.c.box[1]), __float_as_int(x.c.box[2]),
+                     __float_as_int(x.c.box[3]));
+    w[2] = make_int4(__float_as_int(x.c.box[4]), __float_as_int(x.c.box[5]), x.pre_l, x.pre_r);
+}
+
+__device__ inline Item get_item(const int32_t *list, int32_t at)
+{
+    const int4 *w = reinterpret_cast<const int4 *>(list + 4 + kItemWords * at);
+    const int4 u = w[0], v = w[1], t = w[2];
+    Item x;
+    x.c.l = u.x;
+    x.c.r = u.y;
+    x.c.ref = u.z;
+    x.c.h = u.w;
+    x.c.box[0] = __int_as_float(v.x);
+    x.c.box[1] = __int_as_float(v.y);
+    x.c.box[2] = __int_as_float(v.z);
+    x.c.box[3] = __int_as_float(v.w);
+    x.c.box[4] = __int_as_float(t.x);
+    x.c.box[5] = __int_as_float(t.y);
+    x.pre_l = t.z;
+    x.pre_r = t.w;
+    return x;
+}
+
+// Places of set bits in order: the first wave counts the bits below each of
+// W <= 64 words (and all of them: the return value, in that wave).
+template <int W>
+__device__ inline int32_t count_below(const uint32_t *bits, int32_t *below)
+{
+    const int t = (int)threadIdx.x;
+    const int32_t n = t < W ? __popc(bits[t]) : 0;
+    int32_t x = n;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(x, o, 64);
+        if (t >= o) x += y;
+    }
+    if (t < W) below[t] = x - n;
+    return __shfl(x, 63, 64);
+}
+
+__device__ inline int32_t place_of(const uint32_t *bits, const int32_t *below, int32_t k)
+{
+    return below[k >> 5] + __popc(bits[k >> 5] & ((1u << (k & 31)) - 1u));
+}
+
+// One node's two children in LDS: a climb writes its side, then counts itself
+// in (bit `side` of the node's flag).
+//
+// A wave's LDS operations are performed in the order it issues them, so the
+// child data is in place before the flag moves, and the sibling's data read
+// right after the update (before its result is known; unused if we arrive
+// first) is complete whenever the flag shows that the sibling arrived.  The
+// signal fences keep the compiler from moving LDS accesses across the update;
+// one wait then covers the update and the reads.
+struct Slots {
+    int32_t *flag;
+    float (*box)[12];
+    int32_t (*ref)[2], (*bound)[2], (*h)[2];
+};
+
+// Returns false when the sibling has not arrived (it goes on); else fills
+// in the sibling's box, far bound and height.
+__device__ inline bool arrive_at(const Slots &s, int32_t slot, int side, const Climb &c, float *g, int32_t &ob,
+                                 int32_t &oh)
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s.box[slot][6 * side + k] = c.box[k];
+    s.ref[slot][side] = c.ref;
+    s.bound[slot][side] = side ? c.r : c.l;
+    s.h[slot][side] = c.h;
+    const int other = 1 - side;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    const int32_t prev =
+        __hip_atomic_fetch_or(&s.flag[slot], 1 << side, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) g[k] = s.box[slot][6 * other + k];
+    ob = s.bound[slot][other];
+    oh = s.h[slot][other];
+    // an empty statement that uses the loaded values keeps the compiler
+    // from sinking the reads below the branch (it emits no instruction)
+    asm volatile("" : : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(g[4]), "v"(g[5]), "v"(ob), "v"(oh));
+    return prev != 0;
+}
+
+__device__ inline void store_node(const Slots &s, int32_t slot, Node *q)
+{
+#pragma unroll
+    for (int k = 0; k < 12; ++k) q->f[k] = s.box[slot][k];
+    q->ref[0] = s.ref[slot][0];
+    q->ref[1] = s.ref[slot][1];
+    q->aux[0] = s.bound[slot][0];
+    q->aux[1] = s.bound[slot][1];
+}
+
+// The one child that has arrived at a node (flag f: 1 the left one, 2 the
+// right one) whose split is p.
+__device__ inline Climb half_of(const Slots &s, int32_t slot, int32_t f, int32_t p)
+{
+    const int side = f == 1 ? 0 : 1;
+    Climb c;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) c.box[k] = s.box[slot][6 * side + k];
+    c.ref = s.ref[slot][side];
+    c.h = s.h[slot][side];
+    c.l = side == 0 ? s.bound[slot][0] : p + 1;
+    c.r = side == 0 ? p : s.bound[slot][1];
+    return c;
+}
 
 // Local pass: each workgroup owns kLocal consecutive sorted leaves (2048 with
-// 1024 threads, whose 152 KiB of LDS node slots fit gfx950's 160 KiB; or 512
-// with 256 threads).  A node whose leaf range lies inside that block has its
-// whole subtree inside it, so these subtrees are completed here with the
-// arrival counters and child records in LDS.  A climb that reaches a split
-// outside the block (its parent range crosses the block boundary) is saved
-// for the global pass.
+// 1024 threads, whose LDS node slots fit gfx950's 160 KiB; or 512 with 256
+// threads).  A node whose leaf range lies inside that block has its whole
+// subtree inside it, so these subtrees are completed here with the arrival
+// flags and child records in LDS.  The largest of them go to the block's list
+// for the joining pass.
 template <int kLocal, int kLocalThreads>
 __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
 {
@@ -477,19 +605,18 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
     __shared__ int32_t lbound[kLocal][2];
     __shared__ int32_t lh[kLocal][2];
     __shared__ uint8_t lpre[kLocal + 1];  // prefix length at split k, k = B0-1 .. B1
+    __shared__ uint32_t bits[kLocal / 32];  // first leaves of the subtrees to hand over
+    __shared__ int32_t below[kLocal / 32];
+    const Slots slots = {lflag, lbox, lref, lbound, lh};
     const int32_t n = (int32_t)a.n_t;
     const int32_t B0 = (int32_t)blockIdx.x * kLocal;
     const int32_t B1 = (B0 + kLocal < n ? B0 + kLocal : n) - 1;  // last leaf of this block
-    // split prefixes of the block (and the split before it) into LDS; each
-    // split is also stored once for the global pass
+    // split prefixes of the block (and the split before it) into LDS
     for (int t = threadIdx.x; t <= kLocal; t += kLocalThreads) {
         const int32_t k = B0 - 1 + t;
-        if (k >= 0 && k <= B1 && k < n - 1) {
-            const uint8_t p = split_prefix(a.keys, k);
-            lpre[t] = p;
-            if (t > 0) a.prefix[k] = p;
-        }
+        lpre[t] = k >= 0 && k <= B1 && k < n - 1 ? split_prefix(a.keys, k) : 0;
         if (t < kLocal) lflag[t] = 0;
+        if (t < kLocal / 32) bits[t] = 0;
     }
     __syncthreads();
     const auto prefix = [&](int32_t k) { return (int32_t)lpre[k - B0 + 1]; };
@@ -544,81 +671,49 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
         c.l = c.r = i;
         c.ref = leaf_ref(i, 1);
         c.h = 0;
-        a.climb[kClimbWords * (int64_t)i] = 0;  // no saved climb for this leaf unless set below
     }
 
     // each thread climbs from its leaves one after the other; a climb that
     // arrives first at a node stops, so no thread ever waits
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-    const int32_t i = B0 + (int32_t)threadIdx.x + q * kLocalThreads;
-    Climb &c = cl[q];
-    const int32_t m = m_[q], lo = lo_[q], hi = hi_[q];
-    // a climb inside the block takes fewer than kLocal steps
-    for (int step = 0; act[q]; ++step) {
-        if (c.l == lo && c.r == hi) {  // the whole mesh fits in this block
-            write_entry(a, m, lo, hi, c);
-            break;
+        Climb &c = cl[q];
+        const int32_t m = m_[q], lo = lo_[q], hi = hi_[q];
+        bool up = act[q];
+        act[q] = false;  // from here on: handed over
+        // a climb inside the block takes fewer than kLocal steps
+        for (int step = 0; up; ++step) {
+            if (c.l == lo && c.r == hi) {  // the whole mesh fits in this block
+                write_entry(a, m, lo, hi, c);
+                break;
+            }
+            int side;
+            // inside the block [l, r] lies in [B0, B1], so both splits are in lpre
+            const int32_t parent = choose_parent(prefix, lo, hi, c.l, c.r, side);
+            if (parent < B0 || parent >= B1 || step >= kLocal) {
+                // the sibling lies outside the block
+                atomicOr(&bits[(c.l - B0) >> 5], 1u << ((c.l - B0) & 31));
+                act[q] = true;
+                break;
+            }
+            float g[6];
+            int32_t ob, oh;
+            if (!arrive_at(slots, parent - B0, side, c, g, ob, oh)) break;
+            merge(c, g, ob, oh, side, parent, a.leaf_size);
         }
-        int side;
-        // inside the block [l, r] lies in [B0, B1], so both splits are in lpre
-        const int32_t parent = choose_parent(prefix, lo, hi, c.l, c.r, side);
-        if (parent < B0 || parent >= B1 || step >= kLocal) {
-            // the parent's range crosses the block boundary: hand over
-            int32_t *st = a.climb + kClimbWords * (int64_t)i;
-            st[0] = 1;
-            st[1] = c.l;
-            st[2] = c.r;
-            st[3] = c.ref;
-            st[4] = c.h;
-#pragma unroll
-            for (int k = 0; k < 6; ++k) st[5 + k] = __float_as_int(c.box[k]);
-            break;
-        }
-        const int slot = parent - B0;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) lbox[slot][6 * side + k] = c.box[k];
-        lref[slot][side] = c.ref;
-        lbound[slot][side] = side ? c.r : c.l;
-        lh[slot][side] = c.h;
-        // A wave's LDS operations are performed in the order it issues them,
-        // so the child data above is in place before the counter moves, and
-        // the sibling's data read right after the counter update (before its
-        // result is known; unused if we arrive first) is complete whenever
-        // the counter shows that the sibling arrived.  The signal fences
-        // keep the compiler from moving LDS accesses across the update; one
-        // wait then covers the update and the reads.
-        const int other = 1 - side;
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const int32_t prev = __hip_atomic_fetch_add(&lflag[slot], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        float g[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) g[k] = lbox[slot][6 * other + k];
-        const int32_t ob = lbound[slot][other], oh = lh[slot][other];
-        // an empty statement that uses the loaded values keeps the compiler
-        // from sinking the reads below the branch (it emits no instruction)
-        asm volatile("" : : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(g[4]), "v"(g[5]), "v"(ob), "v"(oh));
-        if (prev == 0) break;  // the sibling finishes this parent
-        merge(c, g, ob, oh, side, parent, a.leaf_size);
-    }
     }
     __syncthreads();
-    // publish the block's internal node records (splits B0 .. B1-1)
-    for (int tid = threadIdx.x; tid < kLocal; tid += kLocalThreads) {
-    if (tid < B1 - B0 && lflag[tid] > 0) {
-        const int32_t p = B0 + tid;
-        Node *q = a.nodes + p;
-#pragma unroll
-        for (int k = 0; k < 12; ++k) q->f[k] = lbox[tid][k];
-        q->ref[0] = lref[tid][0];
-        q->ref[1] = lref[tid][1];
-        q->aux[0] = lbound[tid][0];
-        q->aux[1] = lbound[tid][1];
-        a.heights[2 * p] = lh[tid][0];
-        a.heights[2 * p + 1] = lh[tid][1];
-        int32_t arrived = lflag[tid];
-        if (a.nodes4 && arrived == 2) {
+    // publish the block's completed nodes (splits B0 .. B1-1); a node with one
+    // child hands that over
+    for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
+        const int32_t p = B0 + tid, f = lflag[tid];
+        if (f == 1 || f == 2) {
+            const int32_t l = (f == 1 ? lbound[tid][0] : p + 1) - B0;
+            atomicOr(&bits[l >> 5], 1u << (l & 31));
+        }
+        if (f != 3) continue;
+        store_node(slots, tid, a.nodes + p);
+        if (a.nodes4) {
             // both children's subtrees lie in the block, so the four-way
             // record's boxes are here (a later pass over the node records
             // would read them all again: 45 us at 499,280 triangles)
@@ -632,70 +727,148 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
                 return lref[slot][side];
             });
             w.store(a.nodes4 + p, n);
-            arrived = kWidened;
+            a.arrive[p] = kWidened;
         }
-        a.arrive[p] = arrived;
     }
+    // the block's list, in leaf order
+    if (gridDim.x == 1) return;  // one block: every mesh is complete
+    int32_t *const list = a.joins + (int64_t)kListWords * blockIdx.x;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int32_t total = count_below<kLocal / 32>(bits, below);
+        if (threadIdx.x == 0) list[0] = total < kListItems ? total : kListItems;
+    }
+    __syncthreads();
+    const auto hand = [&](const Climb &c) {
+        put_item(a, list, place_of(bits, below, c.l - B0), {c, prefix(c.l - 1), prefix(c.r)});
+    };
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        if (act[q]) hand(cl[q]);
+    }
+    for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
+        const int32_t f = lflag[tid];
+        if (f == 1 || f == 2) hand(half_of(slots, tid, f, B0 + tid));
     }
 }
 
-// Global pass: continue the climbs saved by the local pass.  Their parents
-// are shared between workgroups on different XCDs, whose L2 caches are not
-// coherent with each other.  Release/acquire ordering at device scope would
-// write back and invalidate a whole L2 at every level of every climb;
-// instead the few words a sibling needs are written and read with
-// system-coherent accesses (past the per-XCD caches), the writes complete
-// before the arrival counter moves, and the counter is a system-coherent
-// atomic.  Only the subtrees that cross block boundaries remain.
-__global__ __launch_bounds__(256) void k_lbvh_global(BuildArgs a)
+// Joining pass: the subtrees of the local blocks' lists, in leaf order, climb
+// on in LDS, one workgroup for `per` consecutive lists.  It takes as many
+// lists as make kJoin items (at least five), replaces them by the list of
+// what they leave, and goes on with that and the next ones until one list is
+// left; with the last workgroup every mesh is complete.  Bound by the chain of
+// LDS updates of the longest climb.  When the climbs met in memory, past the
+// per-XCD caches, they cost about 2 us a level, and each leaf had a word that
+// said whether its climb went on: 46 us at 499,280 triangles (both launches
+// here: 37), 29 us at 29,768 (20) and 111 us for the 64 meshes of 1,000 to
+// 200,000 triangles (45).
+//
+// List i of the pass is block min(stride i + stride - 1, nb - 1)'s: a
+// workgroup leaves its result in the place of its last list.
+constexpr int kJoin = 1024;
+
+__global__ __launch_bounds__(kJoin) void k_lbvh_join(BuildArgs a, int32_t nb, int32_t stride, int32_t per)
 {
-    const int32_t n = (int32_t)a.n_t;
-    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= n) return;
-    const int32_t *st = a.climb + kClimbWords * (int64_t)i;
-    if (st[0] == 0) return;
-    const int32_t m = mesh_of(a.off, a.M, i);
-    const int32_t lo = (int32_t)a.off[m], hi = (int32_t)a.off[m + 1] - 1;
-    Climb c;
-    c.l = st[1];
-    c.r = st[2];
-    c.ref = st[3];
-    c.h = st[4];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) c.box[k] = __int_as_float(st[5 + k]);
-    // every step strictly widens [l, r], so at most n - 1 steps are needed
-    for (int32_t step = 0; !(c.l == lo && c.r == hi); ++step) {
-        if (step >= n || c.l < lo || c.r > hi || c.l > c.r) {  // inconsistent: report, do not wander
-            atomicOr(&a.scalars[kBadIndex], 2);
-            return;
+    __shared__ int32_t lflag[kJoin];
+    __shared__ float lbox[kJoin][12];
+    __shared__ int32_t lref[kJoin][2];
+    __shared__ int32_t lbound[kJoin][2];
+    __shared__ int32_t lend[kJoin][2];  // bounds as item numbers
+    __shared__ int32_t lh[kJoin][2];
+    __shared__ uint8_t lpre[kJoin + 1];  // prefix length before item k
+    __shared__ uint32_t bits[kJoin / 32];
+    __shared__ int32_t below[kJoin / 32];
+    __shared__ int32_t first[65];  // first item of each list taken
+    __shared__ int32_t taken;
+    const Slots slots = {lflag, lbox, lref, lbound, lh};
+    const int tid = (int)threadIdx.x;
+    const int32_t lists = (nb + stride - 1) / stride;
+    int32_t at = (int32_t)blockIdx.x * per;
+    const int32_t end = at + per < lists ? at + per : lists;
+    const auto list_of = [&](int32_t i) {
+        const int64_t b = (int64_t)stride * i + stride - 1;
+        return a.joins + kListWords * (b < nb ? b : nb - 1);
+    };
+    // at least one list goes with each turn
+    while (at < end - 1) {
+        if (tid < 64) {
+            int32_t c = at + tid < end ? list_of(at + tid)[0] : 0;
+            if (c < 0 || c > kListItems) c = 0;
+            int32_t x = c;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int32_t y = __shfl_up(x, o, 64);
+                if (tid >= o) x += y;
+            }
+            first[tid + 1] = x;
+            if (tid == 0) first[0] = 0;
+            const uint64_t fit = __builtin_amdgcn_ballot_w64(at + tid < end && x <= kJoin);
+            if (tid == 0) taken = __popcll(fit);
         }
-        int side;
-        const int32_t parent =
-            choose_parent([&](int32_t k) { return a.prefix[k]; }, lo, hi, c.l, c.r, side);
-        Node *p = a.nodes + parent;
-        // child data with system-coherent stores (they bypass the per-XCD
-        // caches), completed before the counter moves; the sibling reads
-        // them back with system-coherent loads, so no cache-wide write-back
-        // or invalidation is needed at any level
-        for (int k = 0; k < 6; ++k)
-            __hip_atomic_store(&p->f[6 * side + k], c.box[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&p->ref[side], c.ref, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&p->aux[side], side ? c.r : c.l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&a.heights[2 * parent + side], c.h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __builtin_amdgcn_s_waitcnt(0);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const int32_t prev = __hip_atomic_fetch_add(&a.arrive[parent], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (prev == 0) return;  // the sibling finishes this parent
-        const int other = 1 - side;
-        float g[6];
-        for (int k = 0; k < 6; ++k)
-            g[k] = __hip_atomic_load(&p->f[6 * other + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        const int32_t ob = __hip_atomic_load(&p->aux[other], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        const int32_t oh = __hip_atomic_load(&a.heights[2 * parent + other], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        merge(c, g, ob, oh, side, parent, a.leaf_size);
+        if (tid < kJoin / 32) bits[tid] = 0;
+        lflag[tid] = 0;
+        __syncthreads();
+        const int32_t t = taken, K = first[t];
+        Item x = {};
+        int32_t m = 0, lo = 0, hi = -1;
+        const bool has = tid < K;
+        if (has) {
+            int32_t q = 0, e = t;  // first[q] <= tid < first[e]
+            while (e - q > 1) {
+                const int32_t mid = (q + e) >> 1;
+                if (first[mid] <= tid) q = mid;
+                else e = mid;
+            }
+            x = get_item(list_of(at + q), tid - first[q]);
+            m = mesh_of(a.off, a.M, x.c.l);
+            lo = (int32_t)a.off[m];
+            hi = (int32_t)a.off[m + 1] - 1;
+            lpre[tid + 1] = (uint8_t)x.pre_r;
+            if (tid == 0) lpre[0] = (uint8_t)x.pre_l;
+        }
+        const int32_t split = x.c.r;  // between this item and the next
+        __syncthreads();
+        Climb &c = x.c;
+        int32_t il = tid, ir = tid;  // the climb's items
+        bool handed = false;
+        for (int step = 0; has; ++step) {
+            if (c.l == lo && c.r == hi) {
+                write_entry(a, m, lo, hi, c);
+                break;
+            }
+            const int side = c.l == lo || (c.r != hi && lpre[ir + 1] > lpre[il]) ? 0 : 1;
+            const int32_t slot = side == 0 ? ir : il - 1;
+            if (slot < 0 || slot >= K - 1 || step >= kJoin) {
+                atomicOr(&bits[il >> 5], 1u << (il & 31));
+                handed = true;
+                break;
+            }
+            lend[slot][side] = side ? ir : il;
+            float g[6];
+            int32_t ob, oh;
+            if (!arrive_at(slots, slot, side, c, g, ob, oh)) break;
+            const int32_t oe = lend[slot][1 - side];
+            merge(c, g, ob, oh, side, side == 0 ? c.r : c.l - 1, a.leaf_size);
+            if (side == 0) ir = oe;
+            else il = oe;
+        }
+        __syncthreads();
+        const int32_t f = tid < K - 1 ? lflag[tid] : 0;
+        if (f == 3) store_node(slots, tid, a.nodes + split);
+        const int32_t hl = f == 1 ? lend[tid][0] : tid + 1, hr = f == 1 ? tid : lend[tid][1];
+        if (f == 1 || f == 2) atomicOr(&bits[hl >> 5], 1u << (hl & 31));
+        __syncthreads();
+        int32_t *const out = list_of(at + t - 1);
+        if (tid < 64) {
+            const int32_t total = count_below<kJoin / 32>(bits, below);
+            if (tid == 0) out[0] = total < kListItems ? total : kListItems;
+        }
+        __syncthreads();
+        if (handed) put_item(a, out, place_of(bits, below, il), {c, lpre[il], lpre[ir + 1]});
+        if (f == 1 || f == 2)
+            put_item(a, out, place_of(bits, below, hl), {half_of(slots, tid, f, split), lpre[hl], lpre[hr + 1]});
+        at += t - 1;
+        __syncthreads();
     }
-    write_entry(a, m, lo, hi, c);
 }
 
 // The records the local pass has not laid out: nodes whose subtrees cross its
@@ -752,9 +925,7 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     a.nodes4 = wide_view(h) ? h->nodes4 : nullptr;
     a.tris = h->tris;
     a.arrive = h->arrive;
-    a.heights = h->heights;
-    a.climb = h->climb;
-    a.prefix = h->split_prefix;
+    a.joins = h->joins;
     a.bounds = h->mesh_bounds;
     a.mesh_height = h->mesh_height;
     a.mesh_root = h->mesh_root;
@@ -764,22 +935,32 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     return a;
 }
 
+// Leaves per local block.  Blocks of 2048: one block holds a small mesh whole
+// (nothing to join), and a large one leaves few subtrees to join.  Between
+// the two, blocks of 512 spread the local pass over four times as many CUs
+// (the 29,768-triangle rebuild: 0.119 -> 0.109 ms; the trees are the same).
+int64_t local_leaves(int64_t n) { return n > 2048 && n <= 131072 ? 512 : 2048; }
+
+int64_t local_blocks(int64_t n) { return (n + local_leaves(n) - 1) / local_leaves(n); }
+
 hipError_t run_hierarchy(const BuildArgs &a, hipStream_t s)
 {
     const int32_t n = (int32_t)a.n_t;
-    // Blocks of 2048 leaves: one block holds a small mesh whole (no global
-    // pass), and a large one needs few device-wide climbs.  Between the two,
-    // blocks of 512 spread the local pass over four times as many CUs (the
-    // 29,768-triangle rebuild: 0.119 -> 0.109 ms; the trees are the same).
-    unsigned nb;
-    if (n > 2048 && n <= 131072) {
-        nb = (unsigned)((n + 511) / 512);
+    const unsigned nb = (unsigned)local_blocks(n);
+    if (local_leaves(n) == 512) {
         hipLaunchKernelGGL((k_lbvh_local<512, 256>), dim3(nb), dim3(256), 0, s, a);
     } else {
-        nb = (unsigned)((n + 2047) / 2048);
         hipLaunchKernelGGL((k_lbvh_local<2048, 1024>), dim3(nb), dim3(1024), 0, s, a);
     }
-    if (nb > 1) hipLaunchKernelGGL(k_lbvh_global, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+    // up to 64 lists (some 13 items each) by one workgroup, more by one per 64
+    // and one for what those leave
+    const int32_t lists = (int32_t)nb, groups = (lists + 63) / 64;
+    if (groups > 1) {
+        hipLaunchKernelGGL(k_lbvh_join, dim3((unsigned)groups), dim3(kJoin), 0, s, a, lists, 1, 64);
+        hipLaunchKernelGGL(k_lbvh_join, dim3(1), dim3(kJoin), 0, s, a, lists, 64, groups);
+    } else if (lists > 1) {
+        hipLaunchKernelGGL(k_lbvh_join, dim3(1), dim3(kJoin), 0, s, a, lists, 1, lists);
+    }
     return hipGetLastError();
 }
 
@@ -790,6 +971,8 @@ unsigned init_grid(const BuildArgs &a)
 }
 
 }  // namespace
+
+int64_t join_words(int64_t n) { return n > 0 ? kListWords * local_blocks(n) : 0; }
 
 hipError_t launch_gather(rsi_bvh *h, hipStream_t s)
 {

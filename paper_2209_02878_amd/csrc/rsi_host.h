@@ -118,9 +118,7 @@ struct rsi_bvh {
     rsi::Node *nodes = nullptr;    // [max(n_t, 1)]; each mesh's last record is its entry node
     rsi::Tri *tris = nullptr;      // [n_t + 1] in sorted order, then a record of zeros (unused four-way slots name it)
     int32_t *arrive = nullptr;     // arrival counters [n_t]
-    int32_t *heights = nullptr;    // child heights [2*n_t]
-    int32_t *climb = nullptr;      // climbs handed from the local to the global build pass [11*n_t]
-    uint8_t *split_prefix = nullptr;  // common-prefix length at each sorted split [n_t]
+    int32_t *joins = nullptr;      // subtree lists handed from the local build pass to the joining one
     int32_t *scalars = nullptr;    // rsi::Scalar
     rsi::Counters *counters = nullptr;
     rsi::SortScratch sort;
@@ -215,6 +213,8 @@ void set_error(const std::string &msg);
 
 // build.hip
 hipError_t launch_gather(rsi_bvh *h, hipStream_t s);
+// Words of the lists that the joining pass of a build reads.
+int64_t join_words(int64_t n_t);
 hipError_t launch_build(rsi_bvh *h, const float *V, hipStream_t s);
 hipError_t launch_refit(rsi_bvh *h, const float *V, hipStream_t s);
 
