@@ -35,3 +35,28 @@ def test_window_sizes_keep_answers(depth, n):
                 assert torch.equal(want[k], got[k]), (mode, k)
     base.close()
     small.close()
+
+
+@pytest.mark.parametrize("n", [1, 232, 233])
+@pytest.mark.parametrize("depth", [1, 9])
+def test_launch_with_a_column_for_each_lane(depth, n):
+    """Up to 232 segments every lane has a stack column in device memory and no
+    deep pass follows; the answers are those of the same segments in a larger
+    launch with the default window."""
+    V, T = wl.noisy_sphere(30, 4, 0.3)
+    S, E = wl.segments_in_box(np.random.default_rng(10), V.min(0), V.max(0), n, scale=1.5)
+    V, T, S, E = _t(V), _t(T, torch.int32), _t(S), _t(E)
+    many = rsi.Mesh(V, T)
+    small = rsi.Mesh(V, T, stack_depth=depth)
+    reps = 4000 // n + 1
+    for mode in ("bool", "first", "count", "all"):
+        # the same segments among so many that the deep pass is launched
+        want = many.query(S.repeat(reps, 1), E.repeat(reps, 1), mode, capacity=2)
+        got = small.query(S, E, mode, capacity=2)
+        st = small.stats()
+        assert st["stack_dropped"] == 0 and st["walk_cut"] == 0
+        for k in got:
+            if k not in ("spill", "spill_off"):
+                assert torch.equal(want[k][: got[k].shape[0]], got[k]), (mode, k)
+    many.close()
+    small.close()
