@@ -26,7 +26,7 @@
 //                lets only the second child continue -- so the parent's box
 //                is formed exactly once, from both children.  Ranges with at
 //                most `leaf_size` triangles become leaves.  Subtrees inside
-//                a block of 2048 (or 512) sorted leaves finish in LDS
+//                a block of 512 (or 2048) sorted leaves finish in LDS
 //                (k_lbvh_local), and the few that cross block boundaries are
 //                joined in LDS too, by a workgroup per 64 blocks and one for
 //                the rest (k_lbvh_join).
@@ -589,9 +589,9 @@ __device__ inline Climb half_of(const Slots &s, int32_t slot, int32_t f, int32_t
     return c;
 }
 
-// Local pass: each workgroup owns kLocal consecutive sorted leaves (2048 with
-// 1024 threads, whose LDS node slots fit gfx950's 160 KiB; or 512 with 256
-// threads).  A node whose leaf range lies inside that block has its whole
+// Local pass: each workgroup owns kLocal consecutive sorted leaves (512 with
+// 512 threads, four workgroups to a CU; or 2048 with 1024 threads, whose LDS
+// node slots fit gfx950's 160 KiB).  A node whose leaf range lies inside that block has its whole
 // subtree inside it, so these subtrees are completed here with the arrival
 // flags and child records in LDS.  The largest of them go to the block's list
 // for the joining pass.
@@ -759,9 +759,9 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
 // left; with the last workgroup every mesh is complete.  Bound by the chain of
 // LDS updates of the longest climb.  When the climbs met in memory, past the
 // per-XCD caches, they cost about 2 us a level, and each leaf had a word that
-// said whether its climb went on: 46 us at 499,280 triangles (both launches
-// here: 37), 29 us at 29,768 (20) and 111 us for the 64 meshes of 1,000 to
-// 200,000 triangles (45).
+// said whether its climb went on: 46 us at 499,280 triangles in blocks of
+// 2048 (both launches here: 37, in blocks of 512 41), 29 us at 29,768 (20) and
+// 111 us for the 64 meshes of 1,000 to 200,000 triangles (45, and 59).
 //
 // List i of the pass is block min(stride i + stride - 1, nb - 1)'s: a
 // workgroup leaves its result in the place of its last list.
@@ -935,11 +935,15 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     return a;
 }
 
-// Leaves per local block.  Blocks of 2048: one block holds a small mesh whole
-// (nothing to join), and a large one leaves few subtrees to join.  Between
-// the two, blocks of 512 spread the local pass over four times as many CUs
-// (the 29,768-triangle rebuild: 0.119 -> 0.109 ms; the trees are the same).
-int64_t local_leaves(int64_t n) { return n > 2048 && n <= 131072 ? 512 : 2048; }
+// Leaves per local block.  Up to 2048 one block holds the mesh whole and
+// nothing is left to join.  Above that 512: four workgroups share a CU, so one
+// loads or stores while another climbs, which the subtrees left to the joining
+// pass (four times as many blocks' worth) cost less than.  Local pass, 2048
+// leaves and 1024 threads -> 512 and 512: 499,280 triangles 53 -> 42 us, 199,712
+// 42 -> 24, the 64-mesh batch 244 -> 174; with 256 threads for 512 leaves 43,
+// 30 and 199.  Blocks of 256 lose as much in the joining pass as they gain
+// (rebuild of 1.5M triangles 342 -> 362 us).
+int64_t local_leaves(int64_t n) { return n > 2048 ? 512 : 2048; }
 
 int64_t local_blocks(int64_t n) { return (n + local_leaves(n) - 1) / local_leaves(n); }
 
@@ -948,7 +952,7 @@ hipError_t run_hierarchy(const BuildArgs &a, hipStream_t s)
     const int32_t n = (int32_t)a.n_t;
     const unsigned nb = (unsigned)local_blocks(n);
     if (local_leaves(n) == 512) {
-        hipLaunchKernelGGL((k_lbvh_local<512, 256>), dim3(nb), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_lbvh_local<512, 512>), dim3(nb), dim3(512), 0, s, a);
     } else {
         hipLaunchKernelGGL((k_lbvh_local<2048, 1024>), dim3(nb), dim3(1024), 0, s, a);
     }

@@ -1,9 +1,9 @@
 """Subtrees that cross the local build blocks, joined in LDS.
 
-The local pass completes subtrees inside blocks of 512 (to 131,072 triangles)
-or 2,048 sorted leaves; one workgroup joins what up to 64 blocks leave, and a
-further one what those leave.  Sizes here lie on either side of a block, of 64
-blocks and of the change of block size; the chain's centroids halve from one
+The local pass completes subtrees inside blocks of 512 sorted leaves (2,048
+where one block holds the mesh); one workgroup joins what up to 64 blocks
+leave, and a further one what those leave.  Sizes here lie on either side of a
+block, of 64 blocks, of 256 and of the change of block size; the chain's centroids halve from one
 triangle to the next (the deepest paths a key allows), with enough copies of
 each that the path crosses blocks.  The trees are held to the exact validator
 of test_gpu_tree.py, after a build and after a refit.
