@@ -165,10 +165,16 @@ __device__ inline uint32_t lanes_below(uint64_t mask)
 // busy.  A workgroup of 256 threads shares the copy: with the 12-entry stack
 // window 7 workgroups fit a CU.  Against three levels, boolean and counting
 // walks only, 128 threads and 17 entries: 10M boolean queries of the
-// 29,768-triangle mesh 537 -> 486 us, all hits 1,123 -> 1,084 us.  References at or above kTopRef are kTopRef plus the byte offset of a
+// 29,768-triangle mesh 537 -> 486 us, all hits 1,123 -> 1,084 us.  Per CU, 64
+// lanes read 64 different records in 177 clocks through the vector L1 (44 per
+// load, whatever its width) and in 46 from here.  A fifth level (341 records)
+// fits only with larger workgroups and six waves per SIMD instead of seven:
+// boolean 466 -> 484 us, first hit alike, all hits 1,044 -> 1,033.
+//
+// References at or above kTopRef are kTopRef plus the byte offset of a
 // record in the copy (internal references stay below 2^27).  Records lie 80
 // bytes apart, so lanes that read the same words of different records use
-// all banks.
+// all banks (64 bytes apart: 130 clocks).
 constexpr int kTopLevels = 4;
 constexpr int kTopNodes = 85;
 constexpr int kTopStride = 80;
@@ -954,13 +960,18 @@ __device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
 // every child whose box the segment touches and takes the top entry as the
 // next one (`cur`), an internal node or a leaf; a lane with a leaf on top
 // waits for the wave's leaf phase.  Slot 0 of every stack holds kDone, so a
-// pop needs no check for the end.  The step is what bounds the walk (VALU
-// issue 0.99 on the 29,768-triangle mesh with 10M segments), so it is kept
-// short: about 100 VALU instructions per step, against 148 when leaves were
-// kept in registers, the nearest child was picked in every mode and the
-// plane margins were formed per plane.  Only the first-hit walk still picks
-// the nearest child (pruning pays for it); for the other modes the build
-// orders the children.
+// pop needs no check for the end.  The step bounds the walk (10M boolean
+// queries of the 29,768-triangle mesh: the texture-data unit busy 0.97 of the
+// time, a VALU instruction active 0.99 of it), so it is kept short: about 100
+// VALU instructions, against 148 when leaves were kept in registers, the
+// nearest child was picked in every mode and the plane margins were formed
+// per plane.  Only the first-hit walk still picks the nearest child (pruning
+// pays for it); for the other modes the build orders the children.  On
+// gfx950 an FP32 fma, mul or add, an integer add, and, or, xor and a right
+// shift issue in two clocks per wave, everything else here in four: byte
+// conversions (24 a step) cost twice what the fmas they feed cost, and
+// replacing them by byte pairs as FP16 with v_perm and v_fma_mix, nine
+// instructions fewer but of four clocks, changed nothing.
 //
 // The stack's LDS part is a window on its top.  A push that finds it full
 // moves the older half of the window to a column in device memory (claimed
