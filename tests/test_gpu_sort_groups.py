@@ -12,6 +12,7 @@ torch = pytest.importorskip("torch")
 from paper_2209_02878_amd import rsi
 from paper_2209_02878_amd import workloads as wl
 from tests.test_gpu_order import host_keys
+from tests.test_gpu_tree import _morton_reference
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +81,26 @@ def test_clustered_batch_matches_single_builds():
         base += n
         m.close()
     batch.close()
+
+
+@pytest.mark.parametrize("meshes,each", [(2, 8000), (9, 1800), (70, 400), (3, 10_900)])
+def test_few_and_many_mesh_ids(meshes, each):
+    """Tables of at most 16 tiles count the mesh id's digits in the pass before:
+    lanes that agree add together, down to groups of eight."""
+    rng = np.random.default_rng(meshes)
+    parts = []
+    for m in range(meshes):
+        c = rng.uniform(0, 1, (each + 7 * m, 1, 3)) + rng.uniform(-0.01, 0.01, (each + 7 * m, 3, 3))
+        V = c.astype(np.float32).reshape(-1, 3)
+        parts.append((V, np.arange(len(V), dtype=np.int32).reshape(-1, 3)))
+    b = rsi.Batch([(torch.from_numpy(V).cuda(), torch.from_numpy(T).cuda()) for V, T in parts])
+    tree = b.tree()
+    at = 0
+    for V, T in parts:
+        ref = _morton_reference(V, T)
+        want = np.argsort(ref, kind="stable")
+        n = len(T)
+        assert np.array_equal(tree["keys"][at:at + n], ref[want])
+        assert np.array_equal(tree["order"][at:at + n] - at, want)
+        at += n
+    b.close()
