@@ -22,13 +22,14 @@
 //   (sort.hip)    one stable pass per 8 bits of the cell index (position >>
 //                 10): the pairs of each cell of 1,024 consecutive
 //                 triangles become contiguous, in input order within a cell
-//   k_adj_tri     four workgroups per cell, each taking a quarter of the
+//   k_adj_tri     four workgroups per cell (up to 128 where cells are few),
+//                 each taking an equal part of the
 //                 cell's pairs in order: tiles of 512 pairs are ranked
 //                 stably by (cell triangle mod 256) in LDS, and thread t adds
 //                 the records of its four triangles (t + 256 j) in that order,
 //                 in FP64, to nine running sums per triangle (three corners x
-//                 three axes); each quarter's sums are stored
-//   k_adj_combine one lane per triangle: the four quarters' sums, in order
+//                 three axes); each part's sums are stored
+//   k_adj_combine one lane per triangle and sum: the parts', in order
 //   k_adj_vertex  one lane per vertex: the sums of the (triangle, corner)
 //                 pairs incident to it (a table sorted by vertex, built once
 //                 per topology), added to dV
@@ -50,7 +51,7 @@ using rank::kRadix;
 constexpr int kCellBits = 10;                    // triangles per cell: 1,024
 constexpr int kCellTris = 1 << kCellBits;
 constexpr int kTriPerThread = kCellTris / kThreads;  // 4: thread t owns cell triangles t + 256 j
-constexpr int kChunks = 4;                       // k_adj_tri workgroups per cell (each a quarter of its pairs)
+constexpr int kChunks = 4;                       // k_adj_tri workgroups per cell, at least (see chunks_of)
 constexpr int kTriItems = 2;                     // pairs per thread per tile of k_adj_tri
 constexpr int kTriTile = kThreads * kTriItems;
 
@@ -77,6 +78,7 @@ struct AdjArgs {
     uint32_t *vals;       // per segment: its index
     double *tri_sum;      // per sorted triangle: 3 corners x 3 axes
     double *part;         // per (cell, chunk, cell triangle): the chunk's 9 sums
+    int32_t chunks;       // per cell
 };
 
 struct d3 {
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(256) void k_bucket_starts(const uint64_t *__restric
     for (int64_t b = prev + 1; b <= cur && b <= nb; ++b) first[b] = k;
 }
 
-// One workgroup per (cell g, chunk c): the c-th quarter of the cell's pairs
+// One workgroup per (cell g, chunk c): the c-th part of the cell's pairs
 // (in order).  keys/vals: the pairs ordered by cell (stable, so input order
 // within a cell).  Thread t owns the cell's triangles t + 256 j (j < 4); the
 // tile's pairs are ranked stably by (cell triangle mod 256), so thread t
@@ -205,14 +207,14 @@ __global__ __launch_bounds__(kThreads) void k_adj_tri(AdjArgs a, const uint64_t 
     __shared__ uint8_t sj[kTriTile];
     __shared__ int64_t range[2];
     const int tid = threadIdx.x;
-    const int64_t g = blockIdx.x / kChunks;
-    const int chunk = (int)(blockIdx.x % kChunks);
+    const int64_t g = blockIdx.x / a.chunks;
+    const int chunk = (int)(blockIdx.x % a.chunks);
     if (tid == 0) {
         const int64_t clo = cell_first[g];
         const int64_t chi = cell_first[g + 1];
         const int64_t len = chi - clo;
-        range[0] = clo + len * chunk / kChunks;
-        range[1] = clo + len * (chunk + 1) / kChunks;
+        range[0] = clo + len * chunk / a.chunks;
+        range[1] = clo + len * (chunk + 1) / a.chunks;
     }
     __syncthreads();
     const int64_t lo = range[0], hi = range[1];
@@ -263,30 +265,42 @@ __global__ __launch_bounds__(kThreads) void k_adj_tri(AdjArgs a, const uint64_t 
         }
         __syncthreads();
     }
-    double *o = a.part + ((g * kChunks + chunk) * kCellTris) * 9;
+    double *o = a.part + ((g * a.chunks + chunk) * kCellTris) * 9;
 #pragma unroll
     for (int j = 0; j < kTriPerThread; ++j)
 #pragma unroll
         for (int q = 0; q < 9; ++q) o[(j * kThreads + tid) * 9 + q] = acc[j][q];
 }
 
-// Per sorted triangle: its chunks' sums, added in chunk order.
+// Per sorted triangle and component: its chunks' sums, added in chunk order.
 __global__ __launch_bounds__(256) void k_adj_combine(AdjArgs a)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= a.n_t) return;
-    const int64_t g = t >> kCellBits, local = t & (kCellTris - 1);
-    double s[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) s[q] = 0.0;
-    for (int c = 0; c < kChunks; ++c) {
-        const double *p = a.part + ((g * kChunks + c) * kCellTris + local) * 9;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) s[q] += p[q];
-    }
-    double *o = a.tri_sum + 9 * t;
-#pragma unroll
-    for (int q = 0; q < 9; ++q) o[q] = s[q];
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= 9 * a.n_t) return;
+    const int64_t t = k / 9;
+    const double *p = a.part + ((t >> kCellBits) * a.chunks * kCellTris + (t & (kCellTris - 1))) * 9 + (k - 9 * t);
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < a.chunks; ++c) s += p[(int64_t)c * (9 * kCellTris)];
+    a.tri_sum[k] = s;
+}
+
+// k_adj_tri workgroups per cell.  Four where cells are many; a small mesh has
+// few, and four workgroups walked all its pairs (gradient step of 938,671
+// segments on 54 triangles 4.06 ms, 0.30 now; of 1M on 3,000 1.51 and 0.31).
+// So up to 512 workgroups in all, 128 per cell, while each still has four
+// tiles of pairs.  The number follows from the sizes alone, so the order of
+// the sums is the same from call to call.
+int64_t most_chunks(int64_t n_cells)
+{
+    const int64_t c = 512 / (n_cells > 0 ? n_cells : 1);
+    return c < kChunks ? kChunks : (c > 128 ? 128 : c);
+}
+
+int32_t chunks_of(int64_t n_cells, int64_t n_r)
+{
+    const int64_t c = n_r / (4 * kTriTile * (n_cells > 0 ? n_cells : 1)), most = most_chunks(n_cells);
+    return (int32_t)(c < kChunks ? kChunks : (c > most ? most : c));
 }
 
 // Incidence table of a topology: pairs (vertex, 3 * sorted position + corner).
@@ -381,7 +395,7 @@ hipError_t launch_first_hit_adjoint(rsi_bvh *h, const float *V, const float *S, 
     if ((e = grow(&h->adj_rec_v, h->adj_rec_v_cap, n_r)) != hipSuccess) return e;
     const int64_t n_cells = (h->n_t + kCellTris - 1) >> kCellBits;
     if ((e = grow(&h->tri_sum, h->tri_sum_cap, 9 * h->n_t)) != hipSuccess) return e;
-    if ((e = grow(&h->adj_part, h->adj_part_cap, 9 * n_cells * kChunks * kCellTris)) != hipSuccess) return e;
+    if ((e = grow(&h->adj_part, h->adj_part_cap, 9 * n_cells * most_chunks(n_cells) * kCellTris)) != hipSuccess) return e;
     // incidence table of the current topology (kept until a build changes it)
     if (!h->inc_valid) {
         const int64_t n_inc = 3 * h->n_t;
@@ -416,6 +430,7 @@ hipError_t launch_first_hit_adjoint(rsi_bvh *h, const float *V, const float *S, 
     a.vals = h->adj_vals;
     a.tri_sum = h->tri_sum;
     a.part = h->adj_part;
+    a.chunks = chunks_of(n_cells, n_r);
     const unsigned grid = (unsigned)((n_r + 255) / 256);
     hipLaunchKernelGGL(k_adj_solve, dim3(grid), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -430,10 +445,10 @@ hipError_t launch_first_hit_adjoint(rsi_bvh *h, const float *V, const float *S, 
     hipLaunchKernelGGL(k_bucket_starts, dim3((unsigned)((n_r + 1 + 255) / 256)), dim3(256), 0, s, ks, n_r, kCellBits,
                        n_cells, h->adj_cell_first);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adj_tri, dim3((unsigned)(n_cells * kChunks)), dim3(kThreads), 0, s, a, ks, vs,
+    hipLaunchKernelGGL(k_adj_tri, dim3((unsigned)(n_cells * a.chunks)), dim3(kThreads), 0, s, a, ks, vs,
                        h->adj_cell_first);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adj_combine, dim3((unsigned)((h->n_t + 255) / 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_adj_combine, dim3((unsigned)((9 * h->n_t + 255) / 256)), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (dV) {
         hipLaunchKernelGGL(k_adj_vertex, dim3((unsigned)((h->n_v + 255) / 256)), dim3(256), 0, s, a, h->inc_keys,
