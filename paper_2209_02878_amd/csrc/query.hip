@@ -628,6 +628,7 @@ __device__ inline void share_walks(Lane &L, int32_t &item, int32_t &cur, int32_t
                    __shfl(L.seg.ix, from, 64), __shfl(L.seg.iy, from, 64), __shfl(L.seg.iz, from, 64)};
     const float tlim = __shfl(L.tlim, from, 64), tiny = __shfl(L.tiny, from, 64);
     const int32_t own = __shfl(L.own, from, 64);
+    const int32_t seen = __shfl(vis, from, 64);  // the records visited on the way here
     if (takes) {
         L.seg = s;
         L.tlim = tlim;
@@ -644,7 +645,7 @@ __device__ inline void share_walks(Lane &L, int32_t &item, int32_t &cur, int32_t
         sp = bot = stk;
         *stk = kDone;
         col &= ~1023;
-        vis = 0;
+        vis = seen;
     }
 }
 
@@ -1031,11 +1032,15 @@ __global__ __launch_bounds__(256)
     int32_t *bot = stk;   // the slot below the lowest entry (holds kDone)
     bool helped = false;  // another lane walks a part of this lane's segment
     // bound on a walk (a damaged tree can give wrong answers, never a hang):
-    // each lane counts the node records it visits for its current segment; a
-    // walk of a valid tree visits every record at most once, so a count past
-    // the number of records can only come from a damaged tree.  Lanes check
-    // their count every 64 node-step rounds of the wave (behind a
-    // wave-uniform branch); a lane past the bound stops its walk and flags it.
+    // each lane counts the node records visited on its line of descent: its
+    // own since it took the segment, or the giver's count when it took the
+    // entry and its own since then.  A walk of a valid tree visits every
+    // record at most once, on whatever lanes, so a count past the number of
+    // records can only come from a damaged tree.  (Helpers that started from
+    // zero could hand the entries of a cycle to each other for ever.)  Lanes
+    // check their counts every 64 node-step rounds of the wave (behind a
+    // wave-uniform branch); a segment with a lane past the bound ends on all
+    // its lanes, flagged.
     int32_t wround = 0;  // wave-uniform
     int32_t vis = 0;
     Tally tl = {};
@@ -1275,10 +1280,14 @@ __global__ __launch_bounds__(256)
                 }
             }
             if (__builtin_expect((++wround & 63) == 0, 0)) {
-                if (vis > a.max_steps) {
-                    cur = kDone;
-                    col &= ~511;
-                    atomicOr(&seldom().scalars[kWalkCut], 1);
+                // the segment of a lane past the bound ends on every lane
+                // that walks a part of it
+                for (uint64_t past = ballot(vis > a.max_steps); past != 0; past &= past - 1) {
+                    if (L.own == __builtin_amdgcn_readlane(L.own, __builtin_ctzll(past))) {
+                        cur = kDone;
+                        col &= ~511;
+                        atomicOr(&seldom().scalars[kWalkCut], 1);
+                    }
                 }
             }
         } while ((int)__popcll(w) >= enough);
