@@ -658,8 +658,11 @@ __device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_
 {
     const int32_t lane = (int32_t)__lane_id();
     constexpr bool FIRST = (MODE & M_FIRST) && !(MODE & M_ALL);
+    constexpr bool FOUND = MODE != M_BOOL && !(MODE & M_ALL);
     const bool ends = item == -3 && cur == kDone && (col & 511) == 0;
-    // the flags' word: 1 a helper walks, 2 a helper found no column; counts above
+    // the flags' word: 1 a helper walks, 2 a helper found no column, 4 a
+    // helper found a crossing (whose t may be NaN where products overflow, and
+    // then no candidate says so); counts above
     int32_t *const flags = reinterpret_cast<int32_t *>(q + lane) + (sizeof(Ent) / 4 - 1);
     *flags = 0;
     if constexpr (FIRST) *reinterpret_cast<unsigned long long *>(q + lane) = ~0ull;
@@ -667,10 +670,10 @@ __device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_
     unsigned long long key = ~0ull;
     if (item == -3) {
         int32_t *const f = reinterpret_cast<int32_t *>(q + L.own) + (sizeof(Ent) / 4 - 1);
-        const int32_t bits = ends ? (L.retry ? 2 : 0) : 1;
+        const int32_t bits = ends ? (L.retry ? 2 : 0) | (FOUND && L.found ? 4 : 0) : 1;
         if (bits) atomicOr(f, bits);
         if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) {
-            if (ends && L.count) atomicAdd(f, L.count << 2);
+            if (ends && L.count) atomicAdd(f, L.count << 3);
         }
         if constexpr (FIRST) {
             if (ends && L.best_pos >= 0) {
@@ -691,16 +694,12 @@ __device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_
         const int32_t f = *flags;
         helped = (f & 1) != 0;
         if (f & 2) L.retry = true;
-        if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) {
-            L.count += f >> 2;
-            if (f >> 2) L.found = true;
-        }
+        if (FOUND && (f & 4)) L.found = true;
+        if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) L.count += f >> 3;
         if constexpr (FIRST) {
             const unsigned long long k = *reinterpret_cast<unsigned long long *>(q + lane);
-            if (k != ~0ull) {
-                L.found = true;
+            if (k != ~0ull)
                 take_first<MODE>(L, __int_as_float((int32_t)(k >> 32)), (int32_t)(uint32_t)k, q[lane].z);
-            }
         }
     }
     wave_lds_sync();

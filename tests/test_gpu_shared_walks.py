@@ -80,3 +80,20 @@ def test_stacked_sheets(layers):
                 assert ts == sorted(ts)
     assert ref["count"][ok].max() >= layers
     mesh.close()
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e14, 1e18])
+@pytest.mark.parametrize("n", [64, 3_000])
+def test_found_where_products_overflow(n, scale):
+    """At 1e14 the triangle test's products leave FP32: a crossing's t can be
+    NaN, which no first-hit candidate carries.  The segment is crossed all the
+    same, in every mode alike, whichever lane found it."""
+    V, T = wl.noisy_sphere(30, 4, 0.3)
+    S, E = wl.segments_in_box(np.random.default_rng(9), V.min(0), V.max(0), n, scale=1.5)
+    mesh = rsi.Mesh(_t(V * scale), _t(T, torch.int32))
+    S, E = _t(S * scale), _t(E * scale)
+    hit = mesh.query(S, E, "bool")["hit"]
+    assert hit.any()
+    for mode in ("first|bool", "count|bool", "all|first|bool"):
+        assert torch.equal(mesh.query(S, E, mode)["hit"], hit), mode
+    mesh.close()
