@@ -114,31 +114,14 @@ __global__ __launch_bounds__(kThreads) void k_scan(uint32_t *__restrict__ hist, 
     if (tid == 0) total[blockIdx.x] = base;
 }
 
-// Add one at h[at] for each active lane.  Lanes of a wave that agree add
-// together: a digit of few values (the mesh id of a small batch, keys of a
-// cluster) puts a whole table's atomics on a few addresses, which take them
-// one at a time (6 meshes, 10,000 triangles: 82 us for the pass before the
-// mesh id's, 15 now).  A group of fewer than eight lanes ends the search: the
-// values are many, and the rest add for themselves.
-__device__ inline void count_at(uint32_t *h, int32_t at)
-{
-    const int lane = (int)__lane_id();
-    uint64_t left = __ballot(true);
-    while (left) {
-        const int lead = __builtin_ctzll(left);
-        const uint64_t m = __ballot(at == __builtin_amdgcn_readlane(at, lead)) & left;
-        const uint32_t n = (uint32_t)__popcll(m);
-        if (lane == lead) atomicAdd(&h[at], n);
-        left &= ~m;
-        if (n < 8) break;
-    }
-    if ((left >> lane) & 1) atomicAdd(&h[at], 1u);
-}
-
 // FUSED: `offs` holds the raw per-tile histograms and each workgroup forms
 // its own global digit offsets (few tiles: this saves the separate scan
 // launch); it then also adds the next pass's digit counts of the elements it
-// writes into `hnext` (per destination tile) and clears `hclear`.  Otherwise
+// writes into `hnext` (per destination tile) and clears `hclear`.  They are
+// counted in LDS first: a digit of few values (the mesh id of a small batch,
+// keys of a cluster) puts a whole table's atomics on a few addresses, which
+// take them one at a time (6 meshes, 22,000 triangles: the pass before the
+// mesh id's 75 us when lanes that agree added together, @@ now).  Otherwise
 // `offs` holds each digit's counts scanned over the tiles, and the digits'
 // sums behind them.
 template <bool FUSED, int IPT>
@@ -248,6 +231,12 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict
 
     const int64_t rem = n - base;
     const int cnt = rem < (kThreads * IPT) ? (int)rem : (kThreads * IPT);
+    static_assert(kFusedTiles <= IPT * kWaves, "the next pass's counts fit in wcnt");
+    uint32_t *const next = &wcnt[0][0][0];  // the next pass's digits, [digit][tile], as hnext
+    if (FUSED && hnext) {
+        for (int i = tid; i < ntiles * kRadix; i += kThreads) next[i] = 0;
+        __syncthreads();
+    }
     for (int p = tid; p < cnt; p += kThreads) {
         const uint64_t k = skey[p];
         const uint32_t v = sval[p];
@@ -255,7 +244,12 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict
         const int64_t dst = (int64_t)gbase[d] + (p - start[d]);
         kout[dst] = k;
         vout[dst] = v;
-        if (FUSED && hnext) count_at(hnext, (int32_t)(dnext(k, v) * ntiles + dst / (kThreads * IPT)));
+        if (FUSED && hnext) atomicAdd(&next[dnext(k, v) * ntiles + dst / (kThreads * IPT)], 1u);
+    }
+    if (FUSED && hnext) {
+        __syncthreads();
+        for (int i = tid; i < ntiles * kRadix; i += kThreads)
+            if (next[i]) atomicAdd(&hnext[i], next[i]);
     }
 }
 
