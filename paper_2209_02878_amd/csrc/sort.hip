@@ -34,7 +34,6 @@ using rank::kRadix;
 using rank::kWaves;
 using rank::lanemask_lt;
 using rank::scan256;
-using rank::rank_tile;
 constexpr int kItems = 8;                // elements per thread in large sorts
 constexpr int kTile = kThreads * kItems;
 constexpr int kFusedTiles = 16;  // up to this many tiles each workgroup scans the histograms itself
@@ -253,55 +252,184 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict
     }
 }
 
-// A group too large for the window below: the stable passes over its `low`
-// low key bits in device memory by one workgroup, one histogram sweep and
-// one tile-by-tile scatter sweep per pass, alternating between the range in
-// kin and in kout (the result ends in kout).
-constexpr int kLargeItems = 4;
+// Groups too large for the window below are sorted by one workgroup with
+// stable passes over their low key bits, tile by tile.  Item r of lane l in
+// wave w is element (w IPT + r) 64 + l of a tile.
 
-__device__ inline void sort_group_global(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
-                                         uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t b0,
-                                         int64_t bn, int low, uint32_t *wcnt, uint32_t *run, uint32_t *start,
-                                         uint32_t *gcount, uint32_t *gbase)
+// The digit of `low` low key bits that starts at bit `shift`.
+__device__ inline uint32_t low_digit(uint64_t key, int shift, int low)
 {
-    const int tid = threadIdx.x;
+    return (uint32_t)(key >> shift) & (low - shift < 8 ? (1u << (low - shift)) - 1u : kRadix - 1u);
+}
+
+struct GroupRank {
+    uint32_t wcnt[kWaves][kRadix];  // per wave and digit: first its items, then those of earlier waves
+    uint32_t run[kRadix];           // the tile's count of each digit
+    uint32_t start[kRadix];         // exclusive scan of run
+};
+
+// Places of a tile's items in stable order of their digits.  A wave counts on
+// through its rounds, so the counts take 4 KB of LDS whatever IPT (a row for
+// every round and wave, as k_scatter's, takes 4 KB a round; a row for a
+// quarter of the rounds, a shorter chain of LDS accesses, was no faster).
+template <int IPT>
+__device__ __forceinline__ void rank_group(const uint32_t (&dig)[IPT], const bool (&valid)[IPT], uint32_t (&pos)[IPT],
+                                  GroupRank &g)
+{
+    const int tid = threadIdx.x, wave = tid >> 6;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) g.wcnt[w][tid] = 0;
+    __syncthreads();
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        uint64_t peers = __ballot(valid[r]);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const bool bit = (dig[r] >> b) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t below = (uint32_t)__popcll(peers & lt);
+        const uint32_t before = g.wcnt[wave][dig[r]];
+        __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations run in order)
+        if (valid[r] && below == 0) g.wcnt[wave][dig[r]] = before + (uint32_t)__popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+        pos[r] = before + below;
+    }
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = g.wcnt[w][tid];
+        g.wcnt[w][tid] = sum;
+        sum += c;
+    }
+    g.run[tid] = sum;
+    __syncthreads();
+    scan256(g.run, g.start);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) pos[r] += g.start[dig[r]] + g.wcnt[wave][dig[r]];
+}
+
+template <int IPT>
+struct GroupWork {
+    union {  // keys and values change places one after the other
+        uint64_t key[IPT * kThreads];
+        uint32_t val[IPT * kThreads];
+    };
+    GroupRank rank;
+};
+
+// A group of at most IPT * kThreads keys, from kin/vin to kout/vout: its
+// passes in registers and LDS, over the bits in which its keys differ.  (The
+// 4,000 keys of a mesh with one far vertex: 43 us; 90 by the passes in device
+// memory.)  Inlined: behind a call the LDS accesses would be flat ones, 71 us.
+template <int IPT, int MOST>
+__device__ __forceinline__ void sort_group_lds(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
+                                      uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t b0, int bn,
+                                      GroupWork<MOST> &g)
+{
+    const int tid = threadIdx.x, first = (tid >> 6) * (64 * IPT) + (int)__lane_id();
+    uint64_t key[IPT];
+    uint32_t val[IPT], dig[IPT], pos[IPT];
+    bool valid[IPT];
+    const uint64_t key0 = kin[b0];
+    uint64_t differ = 0;
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const int i = first + 64 * r;
+        valid[r] = i < bn;
+        key[r] = kin[b0 + (valid[r] ? i : 0)];
+        val[r] = vin[b0 + (valid[r] ? i : 0)];
+    }
+    // (a use right behind each load would wait for them one by one)
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) differ |= key[r] ^ key0;
+    for (int o = 32; o > 0; o >>= 1) differ |= (uint64_t)__shfl_xor((unsigned long long)differ, o, 64);
+    if (__lane_id() == 0) g.key[tid >> 6] = differ;
+    __syncthreads();
+    differ = g.key[0] | g.key[1] | g.key[2] | g.key[3];
+    static_assert(kWaves == 4, "the waves' words above");
+    __syncthreads();
+    const int low = 64 - (differ ? __clzll((long long)differ) : 64);
+    for (int shift = differ ? __builtin_ctzll(differ) : 0; shift < low; shift += 8) {
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) dig[r] = low_digit(key[r], shift, low);
+        rank_group<IPT>(dig, valid, pos, g.rank);
+#pragma unroll
+        for (int r = 0; r < IPT; ++r)
+            if (valid[r]) g.key[pos[r]] = key[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r)
+            if (valid[r]) key[r] = g.key[first + 64 * r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r)
+            if (valid[r]) g.val[pos[r]] = val[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r)
+            if (valid[r]) val[r] = g.val[first + 64 * r];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < IPT; ++r)
+        if (valid[r]) {
+            kout[b0 + first + 64 * r] = key[r];
+            vout[b0 + first + 64 * r] = val[r];
+        }
+}
+
+// A larger one: the passes over its `low` low key bits in device memory, one
+// histogram sweep and one tile-by-tile scatter sweep per pass, alternating
+// between the range in kin and in kout (the result ends in kout).
+constexpr int kPassItems = 8;
+
+__device__ __forceinline__ void sort_group_global(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
+                                         uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t b0,
+                                         int64_t bn, int low, GroupRank &g, uint32_t *gcount, uint32_t *gbase)
+{
+    const int tid = threadIdx.x, first = (tid >> 6) * (64 * kPassItems) + (int)__lane_id();
     uint64_t *ks = kin + b0, *kd = kout + b0;
     uint32_t *vs = vin + b0, *vd = vout + b0;
     for (int shift = 0; shift < low; shift += 8) {
-        const uint32_t mask = low - shift < 8 ? (1u << (low - shift)) - 1u : kRadix - 1u;
         gcount[tid] = 0;
         __syncthreads();
-        for (int64_t i = tid; i < bn; i += kThreads) atomicAdd(&gcount[(uint32_t)(ks[i] >> shift) & mask], 1u);
+        for (int64_t i = tid; i < bn; i += kThreads) atomicAdd(&gcount[low_digit(ks[i], shift, low)], 1u);
         __syncthreads();
         // a digit that every element of the group shares changes no order
-        if (gcount[(uint32_t)(ks[0] >> shift) & mask] == (uint32_t)bn) {
+        if (gcount[low_digit(ks[0], shift, low)] == (uint32_t)bn) {
             __syncthreads();
             continue;
         }
         scan256(gcount, gbase);
         __syncthreads();
-        for (int64_t c0 = 0; c0 < bn; c0 += kThreads * kLargeItems) {
-            uint64_t key[kLargeItems];
-            uint32_t val[kLargeItems], dig[kLargeItems], pos[kLargeItems];
-            bool valid[kLargeItems];
+        for (int64_t c0 = first; c0 - first < bn; c0 += kThreads * kPassItems) {
+            uint64_t key[kPassItems];
+            uint32_t val[kPassItems], dig[kPassItems], pos[kPassItems];
+            bool valid[kPassItems];
 #pragma unroll
-            for (int r = 0; r < kLargeItems; ++r) {
-                const int64_t i = c0 + r * kThreads + tid;
+            for (int r = 0; r < kPassItems; ++r) {
+                const int64_t i = c0 + 64 * r;
                 valid[r] = i < bn;
-                key[r] = valid[r] ? ks[i] : 0ull;
-                val[r] = valid[r] ? vs[i] : 0u;
-                dig[r] = valid[r] ? (uint32_t)(key[r] >> shift) & mask : 0u;
+                key[r] = ks[valid[r] ? i : 0];
+                val[r] = vs[valid[r] ? i : 0];
             }
-            rank_tile<kLargeItems>(dig, valid, pos, wcnt, run, start);
 #pragma unroll
-            for (int r = 0; r < kLargeItems; ++r)
+            for (int r = 0; r < kPassItems; ++r) dig[r] = low_digit(key[r], shift, low);
+            rank_group<kPassItems>(dig, valid, pos, g);
+#pragma unroll
+            for (int r = 0; r < kPassItems; ++r)
                 if (valid[r]) {
-                    const int64_t dst = (int64_t)gbase[dig[r]] + (pos[r] - start[dig[r]]);
+                    const int64_t dst = (int64_t)gbase[dig[r]] + (pos[r] - g.start[dig[r]]);
                     kd[dst] = key[r];
                     vd[dst] = val[r];
                 }
             __syncthreads();
-            gbase[tid] += run[tid];
+            gbase[tid] += g.run[tid];
             __syncthreads();
         }
         uint64_t *tk = ks; ks = kd; kd = tk;
@@ -338,25 +466,39 @@ __device__ inline void sort_group_global(uint64_t *__restrict__ kin, uint32_t *_
 // false (low > 52) compares key and position.  The first keys of the groups
 // are one bit each.
 template <int TILE, int HALO, bool PACKED>
-__global__ __launch_bounds__(kThreads) void k_finish(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
-                                                     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
-                                                     int64_t n, int low, const int64_t *__restrict__ off, int32_t M)
+__global__ __launch_bounds__(kThreads)
+    __attribute__((amdgpu_waves_per_eu(TILE == 256 ? 2 : 4))) void k_finish(uint64_t *__restrict__ kin,
+                                                                            uint32_t *__restrict__ vin,
+                                                                            uint64_t *__restrict__ kout,
+                                                                            uint32_t *__restrict__ vout, int64_t n,
+                                                                            int low, const int64_t *__restrict__ off,
+                                                                            int32_t M)
 {
     constexpr int kWin = TILE + 2 * HALO;
     static_assert(kWin <= 4096 && kWin % 64 == 0, "window positions take 12 bits, group starts whole words");
-    constexpr int kWork = kLargeItems * kWaves * kRadix + 4 * kRadix;  // words of the large-group passes
+    // items per thread of the largest group sorted in LDS: small sorts have
+    // LDS and registers to spare
+    constexpr int kMostItems = TILE == 256 ? 16 : 8;
+    constexpr int kMost = TILE / HALO + 1;  // first keys of large groups lie more than HALO keys apart
     __shared__ union {
-        uint64_t key[kWin];
-        uint32_t work[kWork];
+        struct {
+            uint64_t key[kWin];
+            uint64_t head[kWin / 64];  // bit j of word w: window position 64 w + j starts a group
+            int64_t large[kMost];      // first keys of large groups
+            int n_large;
+        };
+        GroupWork<kMostItems> work;
+        struct {
+            GroupRank rank;
+            uint32_t gcount[kRadix], gbase[kRadix];
+        };
     } sh;
-    __shared__ uint64_t head[kWin / 64];        // bit j of word w: window position 64 w + j starts a group
-    __shared__ int64_t large[TILE / HALO + 1];  // first keys of large groups: more than HALO keys apart
-    __shared__ int n_large;
+    static_assert(sizeof(sh) <= 163840 / (TILE == 256 ? 4 : 6), "four or six workgroups on a CU");
     const int tid = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * TILE;
     const int64_t w0 = t0 - HALO > 0 ? t0 - HALO : 0;
     const int nw = (int)((t0 + TILE + HALO < n ? t0 + TILE + HALO : n) - w0);
-    if (tid == 0) n_large = 0;
+    if (tid == 0) sh.n_large = 0;
     // all loads first: one memory latency for the whole window
     constexpr int kPer = kWin / kThreads;
     static_assert(kWin % kThreads == 0, "whole rounds");
@@ -379,7 +521,7 @@ __global__ __launch_bounds__(kThreads) void k_finish(uint64_t *__restrict__ kin,
         if (off && !first) first = off[mesh_of(off, M, w0 + p)] == w0 + p;
         sh.key[p] = PACKED ? (k << 12) | (uint64_t)p : k;
         const uint64_t m = __ballot(first);
-        if (__lane_id() == 0) head[p >> 6] = m;
+        if (__lane_id() == 0) sh.head[p >> 6] = m;
     }
     __syncthreads();
     for (int q = tid; q < TILE; q += kThreads) {
@@ -389,16 +531,16 @@ __global__ __launch_bounds__(kThreads) void k_finish(uint64_t *__restrict__ kin,
         // the group's visible extent [b, e): the last start up to me, the
         // first one after it (or the window's end)
         int w = me >> 6;
-        uint64_t m = head[w] & (~0ull >> (63 - (me & 63)));
-        while (m == 0) m = head[--w];  // bit 0 of word 0 is set
+        uint64_t m = sh.head[w] & (~0ull >> (63 - (me & 63)));
+        while (m == 0) m = sh.head[--w];  // bit 0 of word 0 is set
         const int b = 64 * w + 63 - __clzll((long long)m);
         w = (me + 1) >> 6;
-        m = w < kWin / 64 ? head[w] & (~0ull << ((me + 1) & 63)) : 0;
-        while (m == 0 && ++w < kWin / 64) m = head[w];
+        m = w < kWin / 64 ? sh.head[w] & (~0ull << ((me + 1) & 63)) : 0;
+        while (m == 0 && ++w < kWin / 64) m = sh.head[w];
         const int e = m ? 64 * w + __builtin_ctzll(m) : kWin;
         if (e - b > HALO) {
             // (an extent cut by the window starts before the tile)
-            if (me == b) large[atomicAdd(&n_large, 1)] = i;
+            if (me == b) sh.large[atomicAdd(&sh.n_large, 1)] = i;
             continue;
         }
         const uint64_t k = sh.key[me];
@@ -413,9 +555,15 @@ __global__ __launch_bounds__(kThreads) void k_finish(uint64_t *__restrict__ kin,
         vout[dst] = vin[i];
     }
     __syncthreads();
-    const int nl = n_large;
+    const int nl = sh.n_large;
+    int64_t first[kMost];
+#pragma unroll
+    for (int g = 0; g < kMost; ++g) first[g] = g < nl ? sh.large[g] : 0;
+    __syncthreads();  // their space is the sorts' now
     for (int g = 0; g < nl; ++g) {
-        const int64_t b0 = large[g];
+        int64_t b0 = first[0];
+#pragma unroll
+        for (int k = 1; k < kMost; ++k) b0 = g == k ? first[k] : b0;
         // the group's end: the first later key with another prefix, or its mesh's last
         int64_t lo = b0 + 1, hi = n;
         if (off) hi = off[mesh_of(off, M, b0) + 1];
@@ -425,10 +573,15 @@ __global__ __launch_bounds__(kThreads) void k_finish(uint64_t *__restrict__ kin,
             if ((kin[mid] >> low) <= pre) lo = mid + 1;
             else hi = mid;
         }
-        uint32_t *w = sh.work;
-        sort_group_global(kin, vin, kout, vout, b0, lo - b0, low, w, w + kLargeItems * kWaves * kRadix,
-                          w + kLargeItems * kWaves * kRadix + kRadix, w + kLargeItems * kWaves * kRadix + 2 * kRadix,
-                          w + kLargeItems * kWaves * kRadix + 3 * kRadix);
+        const int64_t bn = lo - b0;
+        if (bn <= 4 * kThreads)
+            sort_group_lds<4, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
+        else if (bn <= 8 * kThreads)
+            sort_group_lds<8, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
+        else if (bn <= kMostItems * kThreads)
+            sort_group_lds<kMostItems, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
+        else
+            sort_group_global(kin, vin, kout, vout, b0, bn, low, sh.rank, sh.gcount, sh.gbase);
         __syncthreads();
     }
 }

@@ -104,3 +104,24 @@ def test_few_and_many_mesh_ids(meshes, each):
         assert np.array_equal(tree["order"][at:at + n] - at, want)
         at += n
     b.close()
+
+
+@pytest.mark.parametrize("size", [513, 1024, 1025, 2048, 2049, 4096, 4097])
+@pytest.mark.parametrize("spread", [0.0, 1e-6, 1e-3])
+def test_far_triangle(size, spread):
+    """One far triangle puts all others in one group of equal top bits: sizes
+    around those sorted in LDS by 4, 8 and 16 keys a thread, or past it, with
+    63-bit keys; beside small groups in tables of other tiles."""
+    rng = np.random.default_rng(size)
+    for rest in (0, 150_000):  # far more triangles: the large tiles
+        c = np.concatenate([0.3 + spread * rng.uniform(-1, 1, (size, 1, 3)), [[[9.0, 9.0, 9.0]]],
+                            rng.uniform(4, 8, (rest, 1, 3))])
+        V = (c + 1e-3 * spread * rng.uniform(-1, 1, (len(c), 3, 3))).astype(np.float32).reshape(-1, 3)
+        T = rng.permutation(len(c)).astype(np.int32)[:, None] * 3 + np.arange(3, dtype=np.int32)
+        mesh = rsi.Mesh(_t(V), _t(T, torch.int32))
+        tree = mesh.tree()
+        ref = _morton_reference(V, T)
+        want = np.argsort(ref, kind="stable")
+        assert np.array_equal(tree["keys"], ref[want])
+        assert np.array_equal(tree["order"], want)
+        mesh.close()
