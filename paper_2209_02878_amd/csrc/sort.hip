@@ -38,48 +38,61 @@ constexpr int kItems = 8;                // elements per thread in large sorts
 constexpr int kTile = kThreads * kItems;
 constexpr int kFusedTiles = 16;  // up to this many tiles each workgroup scans the histograms itself
 
-// Digit of an element for one pass: 8 bits of the key, or (for batches)
-// 8 bits of the mesh that the element's value (a triangle index) belongs to.
+// Digit of an element for one pass: up to 8 bits of the key, or (for batches)
+// of the mesh that the element's value (a triangle index) belongs to.
 struct Digit {
     const int64_t *off;  // null: key digits
     int32_t M;
     int shift;
+    uint32_t mask = kRadix - 1;
     __device__ inline uint32_t operator()(uint64_t key, uint32_t val) const
     {
-        if (off) return ((uint32_t)mesh_of(off, M, (int64_t)val) >> shift) & (kRadix - 1);
-        return (uint32_t)(key >> shift) & (kRadix - 1);
+        if (off) return ((uint32_t)mesh_of(off, M, (int64_t)val) >> shift) & mask;
+        return (uint32_t)(key >> shift) & mask;
     }
 };
 
-template <int IPT>
+// GATED, here and in the next two kernels: a pass that only runs when the word
+// at `gate` is set; few workgroups then take all the tiles, so that it costs
+// little when it is not.
+template <int IPT, bool GATED = false>
 __global__ __launch_bounds__(kThreads) void k_hist(const uint64_t *__restrict__ keys,
                                                    const uint32_t *__restrict__ vals, int64_t n, Digit dg,
                                                    uint32_t *__restrict__ hist, int ntiles,
-                                                   uint32_t *__restrict__ clear)
+                                                   uint32_t *__restrict__ clear, const uint32_t *__restrict__ gate)
 {
+    if (GATED && *gate == 0) return;
     __shared__ uint32_t h[kRadix];
     const int tid = threadIdx.x;
-    // `clear` (may be null): a histogram buffer the next scatter adds into
-    if (clear) clear[(int64_t)tid * ntiles + blockIdx.x] = 0;
-    h[tid] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * (kThreads * IPT);
+    int tile = (int)blockIdx.x;
+    do {
+        // `clear` (may be null): a histogram buffer the next scatter adds into
+        if (clear) clear[(int64_t)tid * ntiles + tile] = 0;
+        h[tid] = 0;
+        __syncthreads();
+        const int64_t base = (int64_t)tile * (kThreads * IPT);
 #pragma unroll
-    for (int r = 0; r < IPT; ++r) {
-        int64_t i = base + r * kThreads + tid;
-        if (i < n) atomicAdd(&h[dg(keys[i], dg.off ? vals[i] : 0u)], 1u);
-    }
-    __syncthreads();
-    hist[(int64_t)tid * ntiles + blockIdx.x] = h[tid];
+        for (int r = 0; r < IPT; ++r) {
+            int64_t i = base + r * kThreads + tid;
+            if (i < n) atomicAdd(&h[dg(keys[i], dg.off ? vals[i] : 0u)], 1u);
+        }
+        __syncthreads();
+        hist[(int64_t)tid * ntiles + tile] = h[tid];
+        tile += (int)gridDim.x;
+    } while (GATED && tile < ntiles);
 }
 
 // Exclusive scan of every digit's counts over the tiles, in place, one
 // workgroup per digit; total[d] gets the digit's sum (k_scatter turns the
 // sums into the digits' offsets).  One launch; a scan of the whole table
 // (block sums, their scan, a second sweep) took three, 16 us a pass.
+template <bool GATED = false>
 __global__ __launch_bounds__(kThreads) void k_scan(uint32_t *__restrict__ hist, int ntiles,
-                                                   uint32_t *__restrict__ total)
+                                                   uint32_t *__restrict__ total, uint32_t *__restrict__ gate)
 {
+    if (GATED && *gate == 0) return;
+    // `gate` (may be null) is cleared by an ungated pass
+    if (!GATED && gate && blockIdx.x == 0 && threadIdx.x == 0) *gate = 0;
     __shared__ uint32_t ws[kWaves];
     const int tid = threadIdx.x, wave = tid >> 6;
     uint32_t *const row = hist + (int64_t)blockIdx.x * ntiles;
@@ -123,14 +136,16 @@ __global__ __launch_bounds__(kThreads) void k_scan(uint32_t *__restrict__ hist, 
 // mesh id's 75 us when lanes that agree added together, @@ now).  Otherwise
 // `offs` holds each digit's counts scanned over the tiles, and the digits'
 // sums behind them.
-template <bool FUSED, int IPT>
+template <bool FUSED, int IPT, bool GATED = false>
 __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict__ kin,
                                                       const uint32_t *__restrict__ vin,
                                                       uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
                                                       int64_t n, Digit dg, const uint32_t *__restrict__ offs,
                                                       int ntiles, Digit dnext, uint32_t *__restrict__ hnext,
-                                                      uint32_t *__restrict__ hclear)
+                                                      uint32_t *__restrict__ hclear,
+                                                      const uint32_t *__restrict__ gate)
 {
+    if (GATED && *gate == 0) return;
     // wcnt[r][w][d]: elements with digit d held by wave w in round r; after
     // the scan, the number of elements with digit d before (r, w) in the tile
     __shared__ uint32_t wcnt[IPT][kWaves][kRadix];
@@ -142,114 +157,119 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint64_t *__restrict
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
-    const int64_t base = (int64_t)blockIdx.x * (kThreads * IPT);
+    int tile = (int)blockIdx.x;
+    do {
+        const int64_t base = (int64_t)tile * (kThreads * IPT);
 
-    // all loads first: one memory latency for the whole tile
-    uint64_t key[IPT];
-    uint32_t val[IPT];
+        // all loads first: one memory latency for the whole tile
+        uint64_t key[IPT];
+        uint32_t val[IPT];
 #pragma unroll
-    for (int r = 0; r < IPT; ++r) {
-        const int64_t i = base + r * kThreads + tid;
-        key[r] = i < n ? kin[i] : 0ull;
-        val[r] = i < n ? vin[i] : 0u;
-    }
-    if (FUSED && hclear) hclear[(int64_t)tid * ntiles + blockIdx.x] = 0;
-#pragma unroll
-    for (int r = 0; r < IPT; ++r)
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) wcnt[r][w][tid] = 0;
-    if (FUSED) {
-        // digit tid: elements in earlier tiles and in all tiles
-        uint32_t before = 0, total = 0;
-        for (int b = 0; b < ntiles; ++b) {
-            const uint32_t c = offs[(int64_t)tid * ntiles + b];
-            before += b < (int)blockIdx.x ? c : 0u;
-            total += c;
+        for (int r = 0; r < IPT; ++r) {
+            const int64_t i = base + r * kThreads + tid;
+            key[r] = i < n ? kin[i] : 0ull;
+            val[r] = i < n ? vin[i] : 0u;
         }
-        start[tid] = total;
-        __syncthreads();
-        scan256(start, gbase);
-        __syncthreads();
-        gbase[tid] += before;
-    } else {
-        const uint32_t before = offs[(int64_t)tid * ntiles + blockIdx.x];
-        start[tid] = offs[(int64_t)kRadix * ntiles + tid];
-        __syncthreads();
-        scan256(start, gbase);
-        __syncthreads();
-        gbase[tid] += before;
-    }
-
-    // per round: the lanes of this wave holding the same digit (8 ballots);
-    // the lowest of them records the group size
-    uint32_t dig[IPT];
-    uint32_t below[IPT];
-    const uint64_t lt = lanemask_lt();
-#pragma unroll
-    for (int r = 0; r < IPT; ++r) {
-        const bool valid = base + r * kThreads + tid < n;
-        const uint32_t d = valid ? dg(key[r], val[r]) : 0u;
-        dig[r] = d;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        below[r] = (uint32_t)__popcll(peers & lt);
-        if (valid && below[r] == 0) wcnt[r][wave][d] = (uint32_t)__popcll(peers);
-    }
-    __syncthreads();
-    // digit tid: exclusive prefix over (round, wave) in the tile's stable order
-    {
-        uint32_t acc = 0;
+        if (FUSED && hclear) hclear[(int64_t)tid * ntiles + tile] = 0;
 #pragma unroll
         for (int r = 0; r < IPT; ++r)
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t c = wcnt[r][w][tid];
-                wcnt[r][w][tid] = acc;
-                acc += c;
+            for (int w = 0; w < kWaves; ++w) wcnt[r][w][tid] = 0;
+        if (FUSED) {
+            // digit tid: elements in earlier tiles and in all tiles
+            uint32_t before = 0, total = 0;
+            for (int b = 0; b < ntiles; ++b) {
+                const uint32_t c = offs[(int64_t)tid * ntiles + b];
+                before += b < tile ? c : 0u;
+                total += c;
             }
-        run[tid] = acc;
-    }
-    __syncthreads();
-    scan256(run, start);
-    __syncthreads();
+            start[tid] = total;
+            __syncthreads();
+            scan256(start, gbase);
+            __syncthreads();
+            gbase[tid] += before;
+        } else {
+            const uint32_t before = offs[(int64_t)tid * ntiles + tile];
+            start[tid] = offs[(int64_t)kRadix * ntiles + tid];
+            __syncthreads();
+            scan256(start, gbase);
+            __syncthreads();
+            gbase[tid] += before;
+        }
+
+        // per round: the lanes of this wave holding the same digit (8 ballots);
+        // the lowest of them records the group size
+        uint32_t dig[IPT];
+        uint32_t below[IPT];
+        const uint64_t lt = lanemask_lt();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            const bool valid = base + r * kThreads + tid < n;
+            const uint32_t d = valid ? dg(key[r], val[r]) : 0u;
+            dig[r] = d;
+            uint64_t peers = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            below[r] = (uint32_t)__popcll(peers & lt);
+            if (valid && below[r] == 0) wcnt[r][wave][d] = (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        // digit tid: exclusive prefix over (round, wave) in the tile's stable order
+        {
+            uint32_t acc = 0;
+#pragma unroll
+            for (int r = 0; r < IPT; ++r)
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) {
+                    const uint32_t c = wcnt[r][w][tid];
+                    wcnt[r][w][tid] = acc;
+                    acc += c;
+                }
+            run[tid] = acc;
+        }
+        __syncthreads();
+        scan256(run, start);
+        __syncthreads();
 
 #pragma unroll
-    for (int r = 0; r < IPT; ++r) {
-        if (base + r * kThreads + tid < n) {
-            const uint32_t p = start[dig[r]] + wcnt[r][wave][dig[r]] + below[r];
-            skey[p] = key[r];
-            sval[p] = val[r];
+        for (int r = 0; r < IPT; ++r) {
+            if (base + r * kThreads + tid < n) {
+                const uint32_t p = start[dig[r]] + wcnt[r][wave][dig[r]] + below[r];
+                skey[p] = key[r];
+                sval[p] = val[r];
+            }
         }
-    }
-    __syncthreads();
+        __syncthreads();
 
-    const int64_t rem = n - base;
-    const int cnt = rem < (kThreads * IPT) ? (int)rem : (kThreads * IPT);
-    static_assert(kFusedTiles <= IPT * kWaves, "the next pass's counts fit in wcnt");
-    uint32_t *const next = &wcnt[0][0][0];  // the next pass's digits, [digit][tile], as hnext
-    if (FUSED && hnext) {
-        for (int i = tid; i < ntiles * kRadix; i += kThreads) next[i] = 0;
-        __syncthreads();
-    }
-    for (int p = tid; p < cnt; p += kThreads) {
-        const uint64_t k = skey[p];
-        const uint32_t v = sval[p];
-        const uint32_t d = dg(k, v);
-        const int64_t dst = (int64_t)gbase[d] + (p - start[d]);
-        kout[dst] = k;
-        vout[dst] = v;
-        if (FUSED && hnext) atomicAdd(&next[dnext(k, v) * ntiles + dst / (kThreads * IPT)], 1u);
-    }
-    if (FUSED && hnext) {
-        __syncthreads();
-        for (int i = tid; i < ntiles * kRadix; i += kThreads)
-            if (next[i]) atomicAdd(&hnext[i], next[i]);
-    }
+        const int64_t rem = n - base;
+        const int cnt = rem < (kThreads * IPT) ? (int)rem : (kThreads * IPT);
+        static_assert(kFusedTiles <= IPT * kWaves, "the next pass's counts fit in wcnt");
+        uint32_t *const next = &wcnt[0][0][0];  // the next pass's digits, [digit][tile], as hnext
+        if (FUSED && hnext) {
+            for (int i = tid; i < ntiles * kRadix; i += kThreads) next[i] = 0;
+            __syncthreads();
+        }
+        for (int p = tid; p < cnt; p += kThreads) {
+            const uint64_t k = skey[p];
+            const uint32_t v = sval[p];
+            const uint32_t d = dg(k, v);
+            const int64_t dst = (int64_t)gbase[d] + (p - start[d]);
+            kout[dst] = k;
+            vout[dst] = v;
+            if (FUSED && hnext) atomicAdd(&next[dnext(k, v) * ntiles + dst / (kThreads * IPT)], 1u);
+        }
+        if (FUSED && hnext) {
+            __syncthreads();
+            for (int i = tid; i < ntiles * kRadix; i += kThreads)
+                if (next[i]) atomicAdd(&hnext[i], next[i]);
+        }
+        if (GATED) __syncthreads();
+        tile += (int)gridDim.x;
+    } while (GATED && tile < ntiles);
 }
 
 // Groups too large for the window below are sorted by one workgroup with
@@ -460,11 +480,16 @@ __device__ __forceinline__ void sort_group_global(uint64_t *__restrict__ kin, ui
 // 499,280 keys took 189 us and at 4M 1,187 us (a 16,000-key bucket streamed
 // through one workgroup).
 //
+// With `redo`, a group of more than kAlone keys is left as it is and *redo set:
+// gated passes over all the digits follow (redo_passes).
+//
 // The window's keys lie in LDS shifted up by 12 bits (their prefixes, equal
 // within a group, may fall off) with their window position below, so keys
 // are distinct and one 64-bit compare counts equal keys by position; PACKED
 // false (low > 52) compares key and position.  The first keys of the groups
 // are one bit each.
+constexpr int64_t kAlone = 16384;
+
 template <int TILE, int HALO, bool PACKED>
 __global__ __launch_bounds__(kThreads)
     __attribute__((amdgpu_waves_per_eu(TILE == 256 ? 2 : 4))) void k_finish(uint64_t *__restrict__ kin,
@@ -472,7 +497,7 @@ __global__ __launch_bounds__(kThreads)
                                                                             uint64_t *__restrict__ kout,
                                                                             uint32_t *__restrict__ vout, int64_t n,
                                                                             int low, const int64_t *__restrict__ off,
-                                                                            int32_t M)
+                                                                            int32_t M, uint32_t *__restrict__ redo)
 {
     constexpr int kWin = TILE + 2 * HALO;
     static_assert(kWin <= 4096 && kWin % 64 == 0, "window positions take 12 bits, group starts whole words");
@@ -574,6 +599,10 @@ __global__ __launch_bounds__(kThreads)
             else hi = mid;
         }
         const int64_t bn = lo - b0;
+        if (redo && bn > kAlone) {
+            if (tid == 0) *redo = 1;
+            continue;
+        }
         if (bn <= 4 * kThreads)
             sort_group_lds<4, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
         else if (bn <= 8 * kThreads)
@@ -602,8 +631,8 @@ hipError_t ensure_sort_scratch(SortScratch &sc, int64_t n)
         sc.cap = n;
     }
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    // fused path: three rotating histograms; else one table and the digits' sums
-    const int64_t hn = ntiles <= kFusedTiles ? 3 * kFusedTiles * kRadix : (ntiles + 1) * kRadix;
+    // fused path: three rotating histograms; else one table, the digits' sums and redo_passes' word
+    const int64_t hn = ntiles <= kFusedTiles ? 3 * kFusedTiles * kRadix : (ntiles + 1) * kRadix + 1;
     if (hn > sc.hist_cap) {
         if (sc.hist) (void)hipFree(sc.hist);
         sc.hist = nullptr;
@@ -632,14 +661,52 @@ void fused_passes(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_
     const int64_t hsz = (int64_t)ntiles * kRadix;
     uint32_t *H[3] = {sc.hist, sc.hist + hsz, sc.hist + 2 * hsz};
     hipLaunchKernelGGL(k_hist<IPT>, dim3(ntiles), dim3(kThreads), 0, s, ka, va, n, passes[0], H[0], ntiles,
-                       np > 1 ? H[1] : nullptr);
+                       np > 1 ? H[1] : nullptr, nullptr);
     for (int p = 0; p < np; ++p) {
         const Digit dn = p + 1 < np ? passes[p + 1] : passes[p];
         hipLaunchKernelGGL((k_scatter<true, IPT>), dim3(ntiles), dim3(kThreads), 0, s, ka, va, kb, vb, n, passes[p],
                            H[p % 3], ntiles, dn, p + 1 < np ? H[(p + 1) % 3] : nullptr,
-                           p + 2 < np ? H[(p + 2) % 3] : nullptr);
+                           p + 2 < np ? H[(p + 2) % 3] : nullptr, nullptr);
         uint64_t *tk = ka; ka = kb; kb = tk;
         uint32_t *tv = va; va = vb; vb = tv;
+    }
+}
+
+// Above this many keys no workgroup is left alone with a group of more than
+// kAlone: one far segment or vertex puts nearly every key in a few groups.
+// 10M segments with one far: 4,760 us, 1,470 with the passes over the whole
+// table, whose launches cost 26 us where they do not run (930 -> 955).  Up to
+// this many keys the bucket sort that this one replaced left such groups to
+// one workgroup as well, and took longer: 4M segments with one far 2,960 us,
+// 1,970 now.
+constexpr int64_t kAloneTotal = int64_t(1) << 22;
+
+// The whole sort once more, from kin/vin to kout/vout, for a table with a group
+// above kAlone (the word at `gate`): stable passes over all digits, an odd
+// number of them so that the result ends in kout.  kin is in stable order of
+// prefixes, so keys that are equal keep their input order.
+void redo_passes(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout, int64_t n, int key_bits,
+                 const int64_t *mesh_off, int32_t M, uint32_t *hist, int ntiles, uint32_t *gate, hipStream_t s)
+{
+    Digit pass[16];
+    int np = 0;
+    const int meshes = !mesh_off || M <= 1 ? 0 : M > 256 ? 2 : 1;
+    int keys = (key_bits + 7) / 8;
+    if ((keys + meshes) % 2 == 0) ++keys;
+    const int width = (key_bits + keys - 1) / keys;
+    for (int k = 0; k < keys; ++k) pass[np++] = Digit{nullptr, 0, k * width, (1u << width) - 1};
+    for (int k = 0; k < meshes; ++k) pass[np++] = Digit{mesh_off, M, 8 * k};
+    const unsigned grid = (unsigned)(ntiles < 512 ? ntiles : 512);
+    uint32_t *const total = hist + (int64_t)ntiles * kRadix;
+    for (int p = 0; p < np; ++p) {
+        hipLaunchKernelGGL((k_hist<kItems, true>), dim3(grid), dim3(kThreads), 0, s, kin, vin, n, pass[p], hist, ntiles,
+                           nullptr, gate);
+        hipLaunchKernelGGL(k_scan<true>, dim3(kRadix), dim3(kThreads), 0, s, hist, ntiles, total,
+                           gate);
+        hipLaunchKernelGGL((k_scatter<false, kItems, true>), dim3(grid), dim3(kThreads), 0, s, kin, vin, kout, vout, n,
+                           pass[p], hist, ntiles, pass[p], nullptr, nullptr, gate);
+        uint64_t *tk = kin; kin = kout; kout = tk;
+        uint32_t *tv = vin; vin = vout; vout = tv;
     }
 }
 
@@ -711,6 +778,7 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
     hipError_t e = ensure_sort_scratch(sc, n);
     if (e != hipSuccess) return e;
     const int ntiles = (int)((n + kTile - 1) / kTile);
+    uint32_t *const redo = n > kAloneTotal ? sc.hist + (int64_t)(ntiles + 1) * kRadix : nullptr;
     const SortPlan p = plan_sort(n, key_bits, first_bit, mesh_off, M);
     uint64_t *ka = keys, *kb = sc.keys_alt;
     uint32_t *va = vals, *vb = sc.vals_alt;
@@ -731,11 +799,11 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
         for (int q = 0; q < p.np; ++q) {
             const Digit dg = p.pass[q];
             hipLaunchKernelGGL(k_hist<kItems>, dim3(ntiles), dim3(kThreads), 0, s, ka, va, n, dg, sc.hist, ntiles,
-                               nullptr);
-            hipLaunchKernelGGL(k_scan, dim3(kRadix), dim3(kThreads), 0, s, sc.hist, ntiles,
-                               sc.hist + (int64_t)ntiles * kRadix);
+                               nullptr, nullptr);
+            hipLaunchKernelGGL(k_scan<>, dim3(kRadix), dim3(kThreads), 0, s, sc.hist, ntiles,
+                               sc.hist + (int64_t)ntiles * kRadix, redo);
             hipLaunchKernelGGL((k_scatter<false, kItems>), dim3(ntiles), dim3(kThreads), 0, s, ka, va, kb, vb, n, dg,
-                               sc.hist, ntiles, dg, nullptr, nullptr);
+                               sc.hist, ntiles, dg, nullptr, nullptr, nullptr);
             swap();
         }
     }
@@ -743,12 +811,13 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
         const int64_t *off = mesh_off && M > 1 ? mesh_off : nullptr;
         auto finish = [&](auto kern, int tile) {
             hipLaunchKernelGGL(kern, dim3((unsigned)((n + tile - 1) / tile)), dim3(kThreads), 0, s, ka, va, kb, vb,
-                               n, p.low, off, M);
+                               n, p.low, off, M, redo);
         };
         // small sorts: more workgroups
         if (p.low > 52) finish(k_finish<256, 512, false>, 256);
         else if (n <= 131072) finish(k_finish<256, 512, true>, 256);
         else finish(k_finish<2048, 512, true>, 2048);
+        if (redo) redo_passes(ka, va, kb, vb, n, key_bits, off, M, sc.hist, ntiles, redo, s);
         swap();
     }
     if (kres && vres) {  // the caller takes the result where it is

@@ -125,3 +125,61 @@ def test_far_triangle(size, spread):
         assert np.array_equal(tree["keys"], ref[want])
         assert np.array_equal(tree["order"], want)
         mesh.close()
+
+
+@pytest.mark.parametrize("n", [4_194_304, 4_194_305, 5_000_011])
+@pytest.mark.parametrize("width", [0.0, 1e-6, 1e-3])
+def test_far_segment_in_a_large_table(n, width):
+    """Above 2^22 keys a group of more than 16,384 equal prefixes is sorted by
+    passes over the whole table."""
+    rng = np.random.default_rng(n)
+    S, E = _clusters([n - 20_000, 10_000, 9_998], width, rng)
+    assert len(S) == n
+    assert np.array_equal(_order(S, E), np.argsort(host_keys(S, E), kind="stable"))
+
+
+@pytest.mark.parametrize("meshes", [1, 2, 300])
+def test_far_triangle_in_a_large_table(meshes):
+    """The same with 63-bit keys, alone and under one or two mesh-id digits."""
+    rng = np.random.default_rng(meshes)
+    sizes = [4_300_000] + [50 + k for k in range(meshes - 1)]
+    parts = []
+    for n in sizes:
+        c = (0.3 + 1e-4 * rng.uniform(-1, 1, (n, 1, 3))).astype(np.float32)
+        c[0] = 9
+        V = (c + 1e-5 * rng.uniform(-1, 1, (n, 3, 3))).astype(np.float32).reshape(-1, 3)
+        parts.append((_t(V), _t(np.arange(3 * n).reshape(n, 3), torch.int32)))
+    mesh = rsi.Batch(parts) if meshes > 1 else rsi.Mesh(*parts[0])
+    tree, at = mesh.tree(), 0
+    for (V, T), n in zip(parts, sizes):
+        ref = _morton_reference(V.cpu().numpy(), T.cpu().numpy())
+        want = np.argsort(ref, kind="stable")
+        assert np.array_equal(tree["keys"][at:at + n], ref[want])
+        assert np.array_equal(tree["order"][at:at + n] - at, want)
+        at += n
+    mesh.close()
+
+
+def test_time_of_a_large_table_with_one_far_segment():
+    """Not left to a few workgroups: 4.8 times the time without the far segment
+    when it was, about twice with the passes over the whole table."""
+    n = 5_000_000
+    S = torch.rand(n, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    E = S + 0.01
+    far = S * 1e-3
+    far[0] = 5
+    V, T = wl.noisy_sphere(2, 5, 0.3)
+    mesh = rsi.Mesh(_t(V), _t(T, torch.int32))
+    times = []
+    for s, e in ((S, E), (far, far + 1e-5)):
+        ms = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            mesh.segment_order(s, e)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        times.append(min(ms))
+    mesh.close()
+    assert times[1] < 3.5 * times[0], times
