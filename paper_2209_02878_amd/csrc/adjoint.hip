@@ -410,7 +410,7 @@ hipError_t launch_first_hit_adjoint(rsi_bvh *h, const float *V, const float *S, 
         uint64_t *ksrc = nullptr;
         uint32_t *vsrc = nullptr;
         const int bits = bits_for(h->n_v);
-        e = sort_source(h->inc_keys, h->inc_vals, n_inc, bits, h->seg_sort, nullptr, 1, &ksrc, &vsrc);
+        e = sort_source(h->inc_keys, h->inc_vals, n_inc, bits, h->seg_sort, nullptr, 1, 0, &ksrc, &vsrc);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_adj_incidence, dim3((unsigned)((n_inc + 255) / 256)), dim3(256), 0, s, h->T, h->n_t,
                            h->rank, h->n_v, ksrc, vsrc);
@@ -437,7 +437,7 @@ hipError_t launch_first_hit_adjoint(rsi_bvh *h, const float *V, const float *S, 
     // group the pairs by cell (keys in [0, n_t]; cell = key >> kCellBits)
     uint64_t *ks = h->seg_keys;
     uint32_t *vs = h->adj_vals;
-    e = radix_sort_pairs(h->seg_keys, h->adj_vals, n_r, bits_for(h->n_t), h->seg_sort, s, nullptr, 1, kCellBits, &ks,
+    e = radix_sort_pairs(h->seg_keys, h->adj_vals, n_r, bits_for(h->n_t), h->seg_sort, s, nullptr, 1, 0, kCellBits, &ks,
                          &vs);
     if (e != hipSuccess) return e;
     // pairs of cell g: [cell_first[g], cell_first[g + 1]); misses (key n_t) sort last

@@ -164,7 +164,7 @@ hipError_t launch_segment_order(rsi_bvh *h, const float *S, const float *E, int6
     }
     uint32_t *vals = reinterpret_cast<uint32_t *>(order), *vsrc = nullptr;
     uint64_t *ksrc = nullptr;
-    if ((e = sort_source(h->seg_keys, vals, n, kSegKeyBits, h->seg_sort, nullptr, 1, &ksrc, &vsrc)) != hipSuccess)
+    if ((e = sort_source(h->seg_keys, vals, n, kSegKeyBits, h->seg_sort, nullptr, 1, 0, &ksrc, &vsrc)) != hipSuccess)
         return e;
     int32_t *b = h->scalars + kSegBounds;
     hipLaunchKernelGGL(k_seg_bounds_init, dim3(1), dim3(64), 0, s, b);

@@ -220,15 +220,16 @@ hipError_t launch_refit(rsi_bvh *h, const float *V, hipStream_t s);
 
 // sort.hip: stable radix sort of (key, value) pairs by key bits [first_bit,
 // key_bits) into keys / vals; with mesh_off (M > 1) the mesh of each value is
-// the most significant digit.  The pairs change buffers in every pass, so
+// the most significant digit, and `most` is the largest mesh's number of
+// pairs.  The pairs change buffers in every pass, so
 // the caller puts the input where sort_source says (keys / vals or the
 // scratch).  With kres and vres the input is in keys / vals and the result
 // may be left in the scratch: *kres, *vres then name the arrays that hold it.
 hipError_t sort_source(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, SortScratch &scratch,
-                       const int64_t *mesh_off, int32_t M, uint64_t **ksrc, uint32_t **vsrc);
+                       const int64_t *mesh_off, int32_t M, int64_t most, uint64_t **ksrc, uint32_t **vsrc);
 hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, SortScratch &scratch,
-                            hipStream_t s, const int64_t *mesh_off = nullptr, int32_t M = 1, int first_bit = 0,
-                            uint64_t **kres = nullptr, uint32_t **vres = nullptr);
+                            hipStream_t s, const int64_t *mesh_off = nullptr, int32_t M = 1, int64_t most = 0,
+                            int first_bit = 0, uint64_t **kres = nullptr, uint32_t **vres = nullptr);
 hipError_t ensure_sort_scratch(SortScratch &scratch, int64_t n);
 void free_sort_scratch(SortScratch &scratch);
 

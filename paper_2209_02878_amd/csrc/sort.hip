@@ -713,7 +713,7 @@ void redo_passes(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout, i
 // The passes of a sort.  Key sorts (first_bit 0): `prefix` stable passes on
 // the top 8-bit digits, so that the groups of equal prefixes hold tens of
 // keys, then k_finish over the `low` other bits, however many they are.  The
-// number of passes goes by n (by n per mesh in a batch, whose groups lie
+// number of passes goes by n (by the largest mesh in a batch, whose groups lie
 // inside a mesh) alone: none while one group may hold every key (k_finish
 // alone), one while 256 groups keep the count loop short, two up to 2^20
 // keys, else three.  Measured: 29,768 triangles, k_finish 18 us after one
@@ -734,14 +734,14 @@ constexpr int64_t kOneGroup = 256;
 constexpr int64_t kOnePass = 16384;
 constexpr int64_t kTwoPasses = int64_t(1) << 20;
 
-static SortPlan plan_sort(int64_t n, int key_bits, int first_bit, const int64_t *mesh_off, int32_t M)
+// `most`: keys of the largest mesh (n without meshes).
+static SortPlan plan_sort(int64_t n, int64_t most, int key_bits, int first_bit, const int64_t *mesh_off, int32_t M)
 {
     SortPlan p;
     int from = first_bit;
     const bool batch = mesh_off && M > 1;
     if (first_bit == 0) {
-        const int64_t per = batch ? n / M : n;
-        const int prefix = n <= kOneGroup ? 0 : n <= kOnePass ? 1 : per <= kTwoPasses ? 2 : 3;
+        const int prefix = n <= kOneGroup ? 0 : n <= kOnePass ? 1 : most <= kTwoPasses ? 2 : 3;
         if (8 * prefix < key_bits) p.low = from = key_bits - 8 * prefix;
     }
     for (int b = from; b < key_bits; b += 8) p.pass[p.np++] = Digit{nullptr, 0, b};
@@ -754,14 +754,14 @@ static SortPlan plan_sort(int64_t n, int key_bits, int first_bit, const int64_t 
 }
 
 hipError_t sort_source(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, SortScratch &sc,
-                       const int64_t *mesh_off, int32_t M, uint64_t **ksrc, uint32_t **vsrc)
+                       const int64_t *mesh_off, int32_t M, int64_t most, uint64_t **ksrc, uint32_t **vsrc)
 {
     *ksrc = keys;
     *vsrc = vals;
     if (n <= 1 || key_bits <= 0) return hipSuccess;
     const hipError_t e = ensure_sort_scratch(sc, n);
     if (e != hipSuccess) return e;
-    if (plan_sort(n, key_bits, 0, mesh_off, M).moves & 1) {
+    if (plan_sort(n, mesh_off && M > 1 ? most : n, key_bits, 0, mesh_off, M).moves & 1) {
         *ksrc = sc.keys_alt;
         *vsrc = sc.vals_alt;
     }
@@ -769,7 +769,7 @@ hipError_t sort_source(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, 
 }
 
 hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_bits, SortScratch &sc,
-                            hipStream_t s, const int64_t *mesh_off, int32_t M, int first_bit, uint64_t **kres,
+                            hipStream_t s, const int64_t *mesh_off, int32_t M, int64_t most, int first_bit, uint64_t **kres,
                             uint32_t **vres)
 {
     if (kres) *kres = keys;
@@ -779,7 +779,7 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
     if (e != hipSuccess) return e;
     const int ntiles = (int)((n + kTile - 1) / kTile);
     uint32_t *const redo = n > kAloneTotal ? sc.hist + (int64_t)(ntiles + 1) * kRadix : nullptr;
-    const SortPlan p = plan_sort(n, key_bits, first_bit, mesh_off, M);
+    const SortPlan p = plan_sort(n, mesh_off && M > 1 ? most : n, key_bits, first_bit, mesh_off, M);
     uint64_t *ka = keys, *kb = sc.keys_alt;
     uint32_t *va = vals, *vb = sc.vals_alt;
     auto swap = [&]() {
