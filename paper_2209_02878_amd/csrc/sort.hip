@@ -714,11 +714,17 @@ void redo_passes(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout, i
 // the top 8-bit digits, so that the groups of equal prefixes hold tens of
 // keys, then k_finish over the `low` other bits, however many they are.  The
 // number of passes goes by n (by the largest mesh in a batch, whose groups lie
-// inside a mesh) alone: none while one group may hold every key (k_finish
-// alone), one while 256 groups keep the count loop short, two up to 2^20
-// keys, else three.  Measured: 29,768 triangles, k_finish 18 us after one
-// pass and 6 us after two (a pass: 9 us); 4M segments, 189 us after two (the
-// densest groups pass 512 keys) and 32 us after three (a pass: 55 us).  Keys
+// inside a mesh) and the length of the keys alone: none while one group may
+// hold every key (k_finish alone), one while 256 groups keep the count loop
+// short, two up to kTwoPasses, else three.  Measured, k_finish and a pass: 29,768
+// triangles 18 us after one pass, 5 after two, a pass 10; 499,280 triangles
+// 45 us after two, 13 after three, a pass 19; 4M segments 189 us after two
+// (the densest groups pass 512 keys), 32 after three, a pass 54.  Rebuilds
+// after two and three passes: terrain of 200,000 triangles 140 and 144 us,
+// 300,000 156 and 156, 500,000 192 and 182, 1M 293 and 238; sphere 139 and 143,
+// 159 and 153, 197 and 182, 312 and 248.  Segments spread over a volume make
+// smaller groups: 400,000 ordered in 82 us and 92, 1M on the terrain in 149 and
+// 133 (upright ones on a plane 94 after three, 141 after two).  Keys
 // of no more bits than that, and passes that start above bit 0 (which leave
 // the lower bits unsorted), run as digit passes only.  With mesh_off (M > 1)
 // the mesh id's digits follow the key's, so each mesh's elements end up
@@ -732,7 +738,8 @@ struct SortPlan {
 
 constexpr int64_t kOneGroup = 256;
 constexpr int64_t kOnePass = 16384;
-constexpr int64_t kTwoPasses = int64_t(1) << 20;
+constexpr int64_t kTwoPasses = int64_t(1) << 18;       // 63-bit codes of triangles
+constexpr int64_t kTwoPassesShort = int64_t(1) << 20;  // keys of at most 40 bits: segments, vertices
 
 // `most`: keys of the largest mesh (n without meshes).
 static SortPlan plan_sort(int64_t n, int64_t most, int key_bits, int first_bit, const int64_t *mesh_off, int32_t M)
@@ -741,7 +748,8 @@ static SortPlan plan_sort(int64_t n, int64_t most, int key_bits, int first_bit, 
     int from = first_bit;
     const bool batch = mesh_off && M > 1;
     if (first_bit == 0) {
-        const int prefix = n <= kOneGroup ? 0 : n <= kOnePass ? 1 : most <= kTwoPasses ? 2 : 3;
+        const int64_t two = key_bits > 40 ? kTwoPasses : kTwoPassesShort;
+        const int prefix = n <= kOneGroup ? 0 : n <= kOnePass ? 1 : most <= two ? 2 : 3;
         if (8 * prefix < key_bits) p.low = from = key_bits - 8 * prefix;
     }
     for (int b = from; b < key_bits; b += 8) p.pass[p.np++] = Digit{nullptr, 0, b};
