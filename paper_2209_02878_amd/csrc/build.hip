@@ -120,7 +120,6 @@ __global__ void k_init(BuildArgs a)
 }
 
 constexpr int kCentBlock = 256;
-constexpr int kCentMeshes = 4;  // meshes per block reduced in LDS; the rest go straight to global
 
 __device__ inline int32_t wave_min(int32_t v)
 {
@@ -132,10 +131,16 @@ __device__ inline int32_t wave_min(int32_t v)
 // lines, which the GPU serialises, so their number sets the time of a large
 // mesh: with one triangle per thread, 499,280 triangles took 11,700 of them
 // and 51 us.  PER = 8 (from 131,072 triangles on; fewer leave CUs idle at
-// eight per thread) and a reduction in the wave before the LDS one.
+// eight per thread) and a reduction in the wave before the LDS one.  A block
+// reduces its first 4 PER meshes in LDS, one for 64 of its triangles; the
+// rest go straight to device memory.  (Four with PER = 8: a batch of 1,500 meshes
+// of 180 triangles, eleven to a block, took 289 us to rebuild with one triangle
+// per thread, 334 with eight, 228 now.)
 template <int PER>
 __global__ __launch_bounds__(kCentBlock) void k_centroids(BuildArgs a)
 {
+    constexpr int kCentMeshes = 4 * PER;
+    static_assert(kCentMeshes * 6 <= kCentBlock, "one thread per bound");
     __shared__ int32_t lb[kCentMeshes][6];  // per mesh: minima, then negated maxima (as minima)
     const int tid = threadIdx.x;
     if (tid < kCentMeshes * 6) lb[tid / 6][tid % 6] = 0x7FFFFFFF;

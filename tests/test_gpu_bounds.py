@@ -73,3 +73,21 @@ def test_segment_bounds_alignment(n, shift):
     assert np.array_equal(order.cpu().numpy(), np.argsort(host_keys(S, E), kind="stable"))
     assert torch.equal(So, St[order.long()]) and torch.equal(Eo, Et[order.long()])
     mesh.close()
+
+
+@pytest.mark.parametrize("each", [7, 63, 64, 65, 190])
+def test_centroid_bounds_of_many_small_meshes(each):
+    """A workgroup of the eight-per-thread pass spans 2,048 triangles and keeps
+    32 meshes in LDS: borders below, at and above that, meshes of one triangle
+    and larger ones among them."""
+    rng = np.random.default_rng(each)
+    sizes = [each + (k % 3) for k in range(135_000 // each)]
+    sizes[10:10] = [1] * 40
+    sizes[90:90] = [5_000]
+    parts = [_soup(n, rng) for n in sizes]
+    batch = rsi.Batch([(_t(V), _t(T, torch.int32)) for V, T in parts])
+    keys, at = batch.tree()["keys"], 0
+    for (V, T), n in zip(parts, sizes):
+        assert np.array_equal(keys[at:at + n], np.sort(_codes(V, T))), n
+        at += n
+    batch.close()
