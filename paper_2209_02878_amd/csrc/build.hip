@@ -940,15 +940,20 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     return a;
 }
 
-// Leaves per local block.  Up to 2048 one block holds the mesh whole and
+// Leaves per local block.  Up to kOneBlock one block holds the mesh whole and
 // nothing is left to join.  Above that 512: four workgroups share a CU, so one
 // loads or stores while another climbs, which the subtrees left to the joining
 // pass (four times as many blocks' worth) cost less than.  Local pass, 2048
 // leaves and 1024 threads -> 512 and 512: 499,280 triangles 53 -> 42 us, 199,712
 // 42 -> 24, the 64-mesh batch 244 -> 174; with 256 threads for 512 leaves 43,
 // 30 and 199.  Blocks of 256 lose as much in the joining pass as they gain
-// (rebuild of 1.5M triangles 342 -> 362 us).
-int64_t local_leaves(int64_t n) { return n > 2048 ? 512 : 2048; }
+// (rebuild of 1.5M triangles 342 -> 362 us).  Rebuilds in one block and in
+// blocks of 512 with a join: 1,250 triangles 53.8 and 56.4 us, 1,568 60.4 and
+// 57.2, 2,048 66.8 and 52.1 (the block's four-way records take 5 us more from one
+// workgroup than from the grid of a pass of their own).
+constexpr int64_t kOneBlock = 1400;
+
+int64_t local_leaves(int64_t n) { return n > kOneBlock ? 512 : 2048; }
 
 int64_t local_blocks(int64_t n) { return (n + local_leaves(n) - 1) / local_leaves(n); }
 

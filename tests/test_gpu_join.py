@@ -66,3 +66,18 @@ def test_meshes_across_blocks():
             assert torch.equal(x[key], y[key]), key
         m.close()
     b.close()
+
+
+@pytest.mark.parametrize("n,leaf", [(511, 1), (512, 3), (1399, 1), (1400, 1), (1401, 1), (1536, 2), (1537, 1),
+                                    (2047, 1), (2048, 16)])
+def test_one_block_or_blocks_of_512(n, leaf):
+    """Up to 1,400 triangles one block holds the mesh."""
+    rng = np.random.default_rng(n)
+    V, T = _soup(rng.uniform(0, 1, (n, 3)) ** 2, 1e-3)
+    m = _mesh(V, T, leaf_size=leaf)
+    inner = _validate(m.tree(), V, T, leaf)
+    assert leaf > 1 or inner == n - 1
+    W = (V * np.float32(1.5)).astype(np.float32)
+    m.refit(torch.from_numpy(W).cuda())
+    _validate(m.tree(), W, T, leaf)
+    m.close()
