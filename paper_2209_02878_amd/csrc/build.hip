@@ -335,19 +335,30 @@ __device__ inline void write_entry(const BuildArgs &a, int32_t m, int32_t lo, in
 // box.  Every node gets its record, also those no traversal reaches
 // (inside collapsed leaves).
 //
-// Grid step per axis: the smallest power of two 2^e with 254.5 * 2^e >= the
-// box extent.  Planes are placed in FP32: an offset from the corner is off by
-// at most 2^-24 of itself, 2^-16 steps, and the scaling by a power of two is
-// exact, so a plane moved outward by kQuantMargin (2^-10 steps) before it is
-// rounded outward lies outside the child's box by nearly that (the box test
-// needs half of it).
-__device__ inline int quant_exponent(float ext)
+// Grid step per axis: the smallest power of two 2^e with (255 - 2^-10) 2^e >=
+// the box extent, formed in FP64 (the extent of a box of finite FP32 numbers
+// can exceed the FP32 range).  Planes are placed in FP64 too: an offset from the
+// corner is off by at most 2^-53 of itself, 2^-45 steps, and the scaling by a
+// power of two is exact, so a plane moved outward by kQuantMargin before it is
+// rounded outward (quant_plane) lies outside the child's box by 2^-11 steps at least, which
+// the box test needs.
+__device__ inline int quant_exponent(double ext)
 {
-    // ext / 254.5, rounded up; the exponent of the next power of two from the bits
-    const float x = ext * (float)((1.0 + 0x1p-20) / 254.5);
-    const uint32_t u = (uint32_t)__float_as_int(x);
-    const int e = (int)(u >> 23) - 127 + ((u & 0x7FFFFFu) ? 1 : 0);
-    return e < -126 ? -126 : (e > 127 ? 127 : e);
+    const double x = ext * ((1.0 + 0x1p-40) / (255.0 - 0x1p-10));
+    if (!(x > 0x1p-126)) return -126;
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const int e = (int)(u >> 52) - 1023 + ((u & 0xFFFFFFFFFFFFFull) ? 1 : 0);
+    return e > 127 ? 127 : e;
+}
+
+// The plane nearest to v, moved by `out` (half a step and the margin) so that
+// rounding to nearest rounds outward: adding 1.5 2^52 leaves the integer in the
+// low word.
+__device__ inline uint32_t quant_plane(float v, float corner, double inv, double out)
+{
+    const double at = fma((double)v - (double)corner, inv, out) + 0x1.8p52;
+    const int32_t q = (int32_t)__double_as_longlong(at);
+    return (uint32_t)min(max(q, 0), 255);
 }
 
 // The children of a record, from the node's two: the internal one with the
@@ -424,8 +435,9 @@ struct Wide {
                     h = fmaxf(h, box[s][3 + a]);
                 }
             }
-            const int e = quant_exponent(h - l);
-            const float inv = ldexpf(1.0f, -e);
+            l = fmaxf(l, -FLT_MAX);  // an infinite box is cut at the finite numbers
+            const int e = quant_exponent((double)fminf(h, FLT_MAX) - (double)l);
+            const double inv = __longlong_as_double((long long)(1023 - e) << 52);
             lo[a] = l;
             step[a] = ldexpf(1.0f, e);  // a normal float for e in [-126, 127]
             uint32_t ql = 0, qh = 0;
@@ -433,8 +445,8 @@ struct Wide {
             for (int s = 0; s < 4; ++s) {
                 uint32_t x = 255u, y = 0u;  // unused slot: an empty box
                 if (s < k) {
-                    x = (uint32_t)fminf(fmaxf(floorf((box[s][a] - l) * inv - kQuantMargin), 0.0f), 255.0f);
-                    y = (uint32_t)fminf(fmaxf(ceilf((box[s][3 + a] - l) * inv + kQuantMargin), 0.0f), 255.0f);
+                    x = quant_plane(box[s][a], l, inv, -0.5 - kQuantMargin);
+                    y = quant_plane(fminf(box[s][3 + a], FLT_MAX), l, inv, 0.5 + kQuantMargin);
                 }
                 ql |= x << (8 * s);
                 qh |= y << (8 * s);
@@ -708,15 +720,41 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
         }
     }
     __syncthreads();
-    // publish the block's completed nodes (splits B0 .. B1-1); a node with one
-    // child hands that over
-    for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
-        const int32_t p = B0 + tid, f = lflag[tid];
-        if (f == 1 || f == 2) {
-            const int32_t l = (f == 1 ? lbound[tid][0] : p + 1) - B0;
-            atomicOr(&bits[l >> 5], 1u << (l & 31));
+    // the subtrees to hand over: of the climbs that left the block and of the
+    // nodes with one child
+    if (gridDim.x > 1) {  // (one block: every mesh is complete)
+        for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
+            const int32_t p = B0 + tid, f = lflag[tid];
+            if (f == 1 || f == 2) {
+                const int32_t l = (f == 1 ? lbound[tid][0] : p + 1) - B0;
+                atomicOr(&bits[l >> 5], 1u << (l & 31));
+            }
         }
-        if (f != 3) continue;
+        // the block's list, in leaf order
+        int32_t *const list = a.joins + (int64_t)kListWords * blockIdx.x;
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            const int32_t total = count_below<kLocal / 32>(bits, below);
+            if (threadIdx.x == 0) list[0] = total < kListItems ? total : kListItems;
+        }
+        __syncthreads();
+        const auto hand = [&](const Climb &c) {
+            put_item(a, list, place_of(bits, below, c.l - B0), {c, prefix(c.l - 1), prefix(c.r)});
+        };
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            if (act[q]) hand(cl[q]);
+        }
+        for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
+            const int32_t f = lflag[tid];
+            if (f == 1 || f == 2) hand(half_of(slots, tid, f, B0 + tid));
+        }
+    }
+    // publish the block's completed nodes (splits B0 .. B1-1), last: the records
+    // take the registers of the climbs
+    for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
+        const int32_t p = B0 + tid;
+        if (lflag[tid] != 3) continue;
         store_node(slots, tid, a.nodes + p);
         if (a.nodes4) {
             // both children's subtrees lie in the block, so the four-way
@@ -734,26 +772,6 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
             w.store(a.nodes4 + p, n);
             a.arrive[p] = kWidened;
         }
-    }
-    // the block's list, in leaf order
-    if (gridDim.x == 1) return;  // one block: every mesh is complete
-    int32_t *const list = a.joins + (int64_t)kListWords * blockIdx.x;
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const int32_t total = count_below<kLocal / 32>(bits, below);
-        if (threadIdx.x == 0) list[0] = total < kListItems ? total : kListItems;
-    }
-    __syncthreads();
-    const auto hand = [&](const Climb &c) {
-        put_item(a, list, place_of(bits, below, c.l - B0), {c, prefix(c.l - 1), prefix(c.r)});
-    };
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        if (act[q]) hand(cl[q]);
-    }
-    for (int tid = threadIdx.x; tid < B1 - B0; tid += kLocalThreads) {
-        const int32_t f = lflag[tid];
-        if (f == 1 || f == 2) hand(half_of(slots, tid, f, B0 + tid));
     }
 }
 

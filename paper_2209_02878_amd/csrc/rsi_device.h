@@ -194,7 +194,7 @@ __device__ inline bool slab_hit(const Seg &s, float lx, float ly, float lz,
 // box_rcp keeps every product finite, so no NaN arises from finite input.
 constexpr float kPlaneRel = 0x1p-19f;
 constexpr float kStartShift = 0x1p-21f;
-constexpr float kQuantMargin = 0x1p-10f;  // grid steps between a child's box and its planes, before FP32 rounding
+constexpr double kQuantMargin = 0x1p-11 + 0x1p-40;  // grid steps between a child's box and its planes, before FP64 rounding
 
 __device__ inline bool qslab_hit(float ax, float ay, float az, float bnx, float bny, float bnz, float bfx,
                                  float bfy, float bfz, float qnx, float qny, float qnz, float qfx, float qfy,
