@@ -406,13 +406,13 @@ __device__ __forceinline__ void sort_group_lds(const uint64_t *__restrict__ kin,
 // A larger one: the passes over its `low` low key bits in device memory, one
 // histogram sweep and one tile-by-tile scatter sweep per pass, alternating
 // between the range in kin and in kout (the result ends in kout).
-constexpr int kPassItems = 8;
-
+// ITEMS keys per thread and tile.
+template <int ITEMS>
 __device__ __forceinline__ void sort_group_global(uint64_t *__restrict__ kin, uint32_t *__restrict__ vin,
                                          uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t b0,
                                          int64_t bn, int low, GroupRank &g, uint32_t *gcount, uint32_t *gbase)
 {
-    const int tid = threadIdx.x, first = (tid >> 6) * (64 * kPassItems) + (int)__lane_id();
+    const int tid = threadIdx.x, first = (tid >> 6) * (64 * ITEMS) + (int)__lane_id();
     uint64_t *ks = kin + b0, *kd = kout + b0;
     uint32_t *vs = vin + b0, *vd = vout + b0;
     for (int shift = 0; shift < low; shift += 8) {
@@ -427,22 +427,22 @@ __device__ __forceinline__ void sort_group_global(uint64_t *__restrict__ kin, ui
         }
         scan256(gcount, gbase);
         __syncthreads();
-        for (int64_t c0 = first; c0 - first < bn; c0 += kThreads * kPassItems) {
-            uint64_t key[kPassItems];
-            uint32_t val[kPassItems], dig[kPassItems], pos[kPassItems];
-            bool valid[kPassItems];
+        for (int64_t c0 = first; c0 - first < bn; c0 += kThreads * ITEMS) {
+            uint64_t key[ITEMS];
+            uint32_t val[ITEMS], dig[ITEMS], pos[ITEMS];
+            bool valid[ITEMS];
 #pragma unroll
-            for (int r = 0; r < kPassItems; ++r) {
+            for (int r = 0; r < ITEMS; ++r) {
                 const int64_t i = c0 + 64 * r;
                 valid[r] = i < bn;
                 key[r] = ks[valid[r] ? i : 0];
                 val[r] = vs[valid[r] ? i : 0];
             }
 #pragma unroll
-            for (int r = 0; r < kPassItems; ++r) dig[r] = low_digit(key[r], shift, low);
-            rank_group<kPassItems>(dig, valid, pos, g);
+            for (int r = 0; r < ITEMS; ++r) dig[r] = low_digit(key[r], shift, low);
+            rank_group<ITEMS>(dig, valid, pos, g);
 #pragma unroll
-            for (int r = 0; r < kPassItems; ++r)
+            for (int r = 0; r < ITEMS; ++r)
                 if (valid[r]) {
                     const int64_t dst = (int64_t)gbase[dig[r]] + (pos[r] - g.start[dig[r]]);
                     kd[dst] = key[r];
@@ -492,7 +492,7 @@ constexpr int64_t kAlone = 16384;
 
 template <int TILE, int HALO, bool PACKED>
 __global__ __launch_bounds__(kThreads)
-    __attribute__((amdgpu_waves_per_eu(TILE == 256 ? 2 : 4))) void k_finish(uint64_t *__restrict__ kin,
+    __attribute__((amdgpu_waves_per_eu(TILE == 256 ? 2 : 5))) void k_finish(uint64_t *__restrict__ kin,
                                                                             uint32_t *__restrict__ vin,
                                                                             uint64_t *__restrict__ kout,
                                                                             uint32_t *__restrict__ vout, int64_t n,
@@ -501,9 +501,11 @@ __global__ __launch_bounds__(kThreads)
 {
     constexpr int kWin = TILE + 2 * HALO;
     static_assert(kWin <= 4096 && kWin % 64 == 0, "window positions take 12 bits, group starts whole words");
-    // items per thread of the largest group sorted in LDS: small sorts have
-    // LDS and registers to spare
-    constexpr int kMostItems = TILE == 256 ? 16 : 8;
+    // items per thread of the largest group sorted in LDS: small sorts, of at
+    // most two workgroups per CU, have LDS and registers to spare; with 8 in the
+    // large ones (128 VGPRs, 96 now) the 64-mesh batch's k_finish took 54 us, 40
+    // with 4
+    constexpr int kMostItems = TILE == 256 ? 16 : 4;
     constexpr int kMost = TILE / HALO + 1;  // first keys of large groups lie more than HALO keys apart
     __shared__ union {
         struct {
@@ -603,14 +605,14 @@ __global__ __launch_bounds__(kThreads)
             if (tid == 0) *redo = 1;
             continue;
         }
-        if (bn <= 4 * kThreads)
+        if (bn <= 4 * kThreads) {
             sort_group_lds<4, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
-        else if (bn <= 8 * kThreads)
-            sort_group_lds<8, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
-        else if (bn <= kMostItems * kThreads)
-            sort_group_lds<kMostItems, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
-        else
-            sort_group_global(kin, vin, kout, vout, b0, bn, low, sh.rank, sh.gcount, sh.gbase);
+        } else if (bn > kMostItems * kThreads) {
+            sort_group_global<TILE == 256 ? 8 : 4>(kin, vin, kout, vout, b0, bn, low, sh.rank, sh.gcount, sh.gbase);
+        } else if constexpr (kMostItems == 16) {
+            if (bn <= 8 * kThreads) sort_group_lds<8, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
+            else sort_group_lds<16, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
+        }
         __syncthreads();
     }
 }
