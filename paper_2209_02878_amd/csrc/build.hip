@@ -924,12 +924,8 @@ __global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, c
     w.store(out + j, n);
 }
 
-// Whether the handle's tree gets the four-way view (whose walk addresses
-// records by 32-bit byte offsets: 2^26 of them).
-bool wide_view(const rsi_bvh *h)
-{
-    return h->width == 4 && h->n_t > 0 && h->n_t <= (int64_t(1) << 26) && h->nodes4;
-}
+// Whether the handle's tree gets the four-way view.
+bool wide_view(const rsi_bvh *h) { return h->width == 4 && h->n_t > 0 && h->nodes4; }
 
 BuildArgs make_build_args(rsi_bvh *h, const float *V)
 {

@@ -181,6 +181,12 @@ constexpr int kTopNodes = 85;
 constexpr int kTopStride = 80;
 constexpr int32_t kTopRef = 0x40000000;
 
+// Records of up to this many triangles are addressed by 32-bit byte offsets
+// from the array's start (BIG: by 64-bit ones, also in the counting variants
+// and the deep pass).  Telling the two apart in the walk cost the 64-mesh
+// batch's boolean query 1,381 -> 1,407 us.
+constexpr int32_t kTris32 = 1 << 26;
+
 __device__ inline int32_t ref_at(const int4 &c, int k) { return k == 0 ? c.x : (k == 1 ? c.y : (k == 2 ? c.z : c.w)); }
 
 // The whole block fills the copy level by level: slot 0 the entry record,
@@ -1005,7 +1011,7 @@ __device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
 // has a column).
 // Registers: six waves per SIMD for all hits (80 VGPRs), seven for the others
 // (72; the LDS parts allow no more).
-template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH>
+template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH, bool BIG>
 __global__ __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu((MODE & M_ALL) ? 6 : 7))) void k_query(QArgs a)
 {
@@ -1204,8 +1210,8 @@ __global__ __launch_bounds__(256)
                     const uint4 c = t[3];
                     C = make_int4((int32_t)c.x, (int32_t)c.y, (int32_t)c.z, (int32_t)c.w);
                 } else {
-                    // n_t <= 2^26 in this walk, so a record's offset fits 32 bits
-                    const char *rec = reinterpret_cast<const char *>(a.nodes4) + ((uint32_t)cur << 6);
+                    const char *rec = reinterpret_cast<const char *>(a.nodes4) +
+                                      (BIG ? (uint64_t)(uint32_t)cur << 6 : (uint64_t)((uint32_t)cur << 6));
                     const uint4 *q = reinterpret_cast<const uint4 *>(rec);
                     P = q[0];
                     Q = q[1];
@@ -1330,8 +1336,7 @@ __global__ __launch_bounds__(256)
     if (COUNT) tally_out(a, tl);
 }
 
-// The walk of the binary tree itself (branching 2, and meshes past 2^26
-// triangles).  RETRY as for k_query.  The all-hits variants are held to six
+// The walk of the binary tree itself (branching 2).  RETRY as for k_query.  The all-hits variants are held to six
 // waves per SIMD (80 VGPRs): without the bound the compiler gives them 94
 // and five waves.
 template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH>
@@ -2308,7 +2313,10 @@ int device_cus()
 template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH, bool WIDE>
 hipError_t launch_kernel(const QArgs &a, int block, size_t lds, hipStream_t s, int64_t &threads)
 {
-    auto kern = WIDE ? k_query<MODE, RETRY, COUNT, BATCH> : k_query_binary<MODE, RETRY, COUNT, BATCH>;
+    auto kern = WIDE ? k_query<MODE, RETRY, COUNT, BATCH, true> : k_query_binary<MODE, RETRY, COUNT, BATCH>;
+    if constexpr (WIDE && !RETRY && !COUNT) {
+        if (a.n_tris <= kTris32) kern = k_query<MODE, RETRY, COUNT, BATCH, false>;
+    }
     int64_t grid;
     QArgs b = a;
     b.own_max = 64;
