@@ -65,24 +65,27 @@ enum {
 /* Build / query options; a zero field selects the default. */
 typedef struct {
     int32_t leaf_size;    /* max triangles per BVH leaf, 1..16 (default 1) */
-    int32_t block_size;   /* traversal workgroup size: 64, 128, 192 or 256 (default 128; left at the default,
-                             the four-way walk of a single mesh takes 256) */
+    int32_t block_size;   /* traversal workgroup size: 64, 128, 192 or 256.  128, the default, leaves it to
+                             the library: 256 for the four-way walk of a single mesh, else 128 */
     int32_t defer_lanes;  /* a wave tests its lanes' pending triangles once fewer than this many
-                             of its lanes can still visit a node, 1..64 (default 32; left at the
-                             default, the four-way all-hits walk takes 24) */
+                             of its lanes can still visit a node, 1..64.  32, the default, leaves
+                             it to the library: 24 for all hits on the four-way walk, else 32 */
     int32_t refill_lanes; /* a wave writes finished segments and takes new ones once this many
-                             of its lanes are done, 1..64 (default 32; left at the default, the
-                             four-way walk takes 24 for first hits and counts, 28 for all hits) */
-    int32_t chunk;        /* segments a wave claims per global atomic, 64..2^20
-                             (default: about eight chunks per resident wave, 64..4096) */
+                             of its lanes are done, 1..64.  32, the default, leaves it to the
+                             library: on the four-way walk 24 for first hits and counts, 28 for all
+                             hits, else 32 */
+    int32_t chunk;        /* segments a wave claims per global atomic, 64..2^20 (default: about eight
+                             chunks per resident wave, 64..4096).  Not used by a four-way launch of
+                             fewer than 384 segments per CU, whose segments are spread over the waves */
     int32_t stack_depth;  /* traversal-stack entries per lane kept in LDS (default 12 on the four-way
                              walk, 32 on the binary walk); a
                              walk that needs more continues in device memory (four-way: its older
                              entries move there; binary: the deep pass walks it again).  A smaller
                              value raises occupancy. 1..255 */
     int32_t branching;    /* 4 (default): traverse the four-way view of the binary tree of
-                             Section 3.1 (every node with its grandchildren as children, child
-                             boxes quantised outward to 8 bits per plane, one 64-byte record
+                             Section 3.1 (every node with up to four descendants as children: its
+                             own two, of which the internal one with the larger box surface gives
+                             way to its own two, twice; child boxes quantised outward to 8 bits per plane, one 64-byte record
                              per node, laid out after each build, rebuild and refit); 2:
                              traverse the binary tree itself.  Both cull conservatively and
                              decide with the same FP32 triangle test, so their answers agree

@@ -79,22 +79,12 @@ rsi_status read_opts(const rsi_opts *opts, rsi_bvh *h)
 {
     int leaf = h->leaf_size, block = h->block_size, defer = h->defer_lanes, refill = h->refill_lanes;
     int chunk = h->chunk, stack = h->stack_cap, width = h->width;
-    bool chosen = h->block_chosen, defer_chosen = h->defer_chosen, refill_chosen = h->refill_chosen;
     if (opts) {
         if (opts->branching) width = opts->branching;
         if (opts->leaf_size) leaf = opts->leaf_size;
-        if (opts->block_size) {
-            block = opts->block_size;
-            chosen = true;
-        }
-        if (opts->defer_lanes) {
-            defer = opts->defer_lanes;
-            defer_chosen = true;
-        }
-        if (opts->refill_lanes) {
-            refill = opts->refill_lanes;
-            refill_chosen = true;
-        }
+        if (opts->block_size) block = opts->block_size;
+        if (opts->defer_lanes) defer = opts->defer_lanes;
+        if (opts->refill_lanes) refill = opts->refill_lanes;
         if (opts->chunk) chunk = opts->chunk;
         if (opts->stack_depth) stack = opts->stack_depth;
     }
@@ -107,11 +97,8 @@ rsi_status read_opts(const rsi_opts *opts, rsi_bvh *h)
     if (width != 2 && width != 4) return invalid("branching must be 2 or 4");
     h->leaf_size = leaf;
     h->block_size = block;
-    h->block_chosen = chosen;
     h->defer_lanes = defer;
     h->refill_lanes = refill;
-    h->defer_chosen = defer_chosen;
-    h->refill_chosen = refill_chosen;
     h->chunk = chunk;
     h->stack_cap = stack;
     h->width = width;
@@ -843,16 +830,12 @@ rsi_status rsi_tune(rsi_handle h, const rsi_tune_job *job, const rsi_opts *cand,
     // options before tuning (set directly: a zero field in rsi_opts means "keep")
     const int32_t o_leaf = h->leaf_size, o_block = h->block_size, o_defer = h->defer_lanes;
     const int32_t o_refill = h->refill_lanes, o_chunk = h->chunk, o_stack = h->stack_cap, o_width = h->width;
-    const bool o_chosen = h->block_chosen, o_dchosen = h->defer_chosen, o_rchosen = h->refill_chosen;
     auto restore = [&]() {
         h->width = o_width;
         h->leaf_size = o_leaf;
         h->block_size = o_block;
-        h->block_chosen = o_chosen;
         h->defer_lanes = o_defer;
         h->refill_lanes = o_refill;
-        h->defer_chosen = o_dchosen;
-        h->refill_chosen = o_rchosen;
         h->chunk = o_chunk;
         h->stack_cap = o_stack;
     };

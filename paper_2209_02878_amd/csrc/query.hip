@@ -2452,15 +2452,15 @@ int lds_part(const rsi_bvh *h)
     return cap < bound ? cap : bound;
 }
 
-// Workgroup size: the `block_size` option when one was chosen, or 256 where
-// the waves share the copy of the top records, else 128.
+// Workgroup size: the `block_size` option; its default is 256 where the waves
+// share the copy of the top records, else 128.
 int want_block(const rsi_bvh *h)
 {
-    return !h->block_chosen && h->width_built == 4 && h->M == 1 ? 256 : h->block_size;
+    return h->block_size == kAutoBlock && h->width_built == 4 && h->M == 1 ? 256 : h->block_size;
 }
 
 // Lanes that must be done before a wave refills, and lanes that must still
-// step before it tests leaves: the options when chosen, else 32 and 32 for
+// step before it tests leaves: the options, whose default is 32 and 32 for
 // the boolean walk, whose lanes end close together.  The other walks of the
 // four-way view leave lanes waiting longer and refill sooner: at 24, the
 // first hits of 4M segments on 199,712 triangles take 377 us against 393 and
@@ -2475,8 +2475,8 @@ void lane_rule(const rsi_bvh *h, uint32_t mode, QArgs &a)
     a.defer = h->defer_lanes;
     a.refill = h->refill_lanes;
     if (h->width_built != 4 || mode == M_BOOL) return;
-    if (!h->refill_chosen) a.refill = (mode & M_ALL) ? 28 : 24;
-    if (!h->defer_chosen && (mode & M_ALL)) a.defer = 24;
+    if (a.refill == kAutoLanes) a.refill = (mode & M_ALL) ? 28 : 24;
+    if (a.defer == kAutoLanes && (mode & M_ALL)) a.defer = 24;
 }
 
 QArgs make_args(rsi_bvh *h, const float *S, const float *E, int64_t n_items, uint32_t mode, const QueryOut &o)

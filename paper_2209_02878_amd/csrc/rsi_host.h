@@ -42,6 +42,13 @@ enum Scalar {
     kNumScalars = kRangeDone + kWorkStride
 };
 
+// Defaults of the block_size, defer_lanes and refill_lanes options, reported
+// by rsi_get_opts.  They stand for a rule by walk and mode (want_block,
+// lane_rule), also when a caller sets them: what rsi_get_opts gave can be set
+// again, and the default is back.
+constexpr int32_t kAutoBlock = 128;
+constexpr int32_t kAutoLanes = 32;
+
 struct Counters {
     unsigned long long node_visits, box_tests, tri_tests, segments;
     // per wave: loop iterations, iterations with a node step, with a leaf
@@ -86,12 +93,9 @@ struct rsi_bvh {
     int32_t M = 1;
     int64_t n_v = 0, n_t = 0;      // totals over all meshes
     int32_t leaf_size = 1;
-    int32_t block_size = 128;
-    bool block_chosen = false;     // block_size was set by the caller
-    int32_t defer_lanes = 32;
-    int32_t refill_lanes = 32;
-    bool defer_chosen = false;     // defer_lanes / refill_lanes were set by the caller
-    bool refill_chosen = false;
+    int32_t block_size = rsi::kAutoBlock;
+    int32_t defer_lanes = rsi::kAutoLanes;
+    int32_t refill_lanes = rsi::kAutoLanes;
     int32_t chunk = 0;             // 0: sized per launch
     int32_t stack_cap = 0;         // LDS stack entries per lane of the main pass (0: default)
     bool counting = false;
