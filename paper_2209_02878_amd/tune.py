@@ -20,10 +20,16 @@ from . import rsi
 
 DEFAULT_CACHE = os.environ.get("RSI_TUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "rsi_tune.json"))
 
-# staged search: each stage varies some options on top of the best so far
+# Which walk the cached options were found on: an entry of another one is
+# searched again.
+WALK = 2
+
+# Staged search: each stage varies some options on top of the best so far.
+# Every stage holds the library's defaults (block size 128 and 32 lanes leave
+# the choice to its rules by walk and mode), so a search never ends slower.
 STAGES = [
     [{"branching": w, "block_size": b} for w in (2, 4) for b in (64, 128, 256)],
-    # LDS stack entries per lane of the main pass (deeper walks go to the deep pass)
+    # LDS stack entries per lane (the rest of a stack lies in device memory)
     [{"stack_depth": s} for s in (8, 12, 16, 20, 24, 32)],
     [{"defer_lanes": d, "refill_lanes": r} for d in (16, 32, 48) for r in (16, 24, 32, 48)],
     [{"leaf_size": leaf} for leaf in (1, 2, 4)],
@@ -84,13 +90,13 @@ def autotune(target, *args, mode="bool", kind="mesh", n_t=0, n_r=0, cache_path: 
     chosen options are applied to the target and returned."""
     key = cache_key(device_name(), kind, mode, n_t, n_r)
     cache = load_cache(cache_path) if cache_path else {}
-    if key in cache:
+    if cache.get(key, {}).get("walk") == WALK:
         opts = cache[key]["opts"]
         # a one-candidate run applies the options (rebuilding for a new leaf size)
         target.tune(*args, mode, [opts], reps=1)
         return opts
     best, log = staged_search(lambda c: target.tune(*args, mode, c, reps=reps))
     if cache_path:
-        cache[key] = {"opts": best, "ms": min(ms for _, ms in log)}
+        cache[key] = {"opts": best, "ms": min(ms for _, ms in log), "walk": WALK}
         save_cache(cache, cache_path)
     return best

@@ -44,3 +44,35 @@ def test_staged_search_keeps_best_of_each_stage():
     # later stages carry the earlier winners
     assert all(c["block_size"] == 64 for c in seen[1])
     assert len(log) == sum(len(s) for s in tune.STAGES)
+
+
+def test_defaults_are_candidates():
+    """The options a handle starts with (128 threads and 32 lanes stand for the
+    library's rules) are among every stage's candidates."""
+    defaults = {"block_size": 128, "defer_lanes": 32, "refill_lanes": 32, "leaf_size": 1, "branching": 4,
+                "stack_depth": 12}
+    for stage in tune.STAGES:
+        assert any(all(defaults[k] == v for k, v in c.items()) for c in stage)
+
+
+def test_entries_of_another_walk_are_searched_again(tmp_path, monkeypatch):
+    monkeypatch.setattr(tune, "device_name", lambda: "gfx950")
+    path = str(tmp_path / "cache.json")
+    key = tune.cache_key("gfx950", "mesh", "bool", 100, 1000)
+    tune.save_cache({key: {"opts": {"stack_depth": 24}, "ms": 1.0}}, path)
+
+    class Target:
+        def __init__(self):
+            self.calls = []
+
+        def tune(self, *args, reps=3):
+            cands = args[-1]
+            self.calls.append(cands)
+            ms = [abs(c.get("stack_depth", 12) - 16) + 1.0 for c in cands]
+            return ms.index(min(ms)), ms
+
+    first, again = Target(), Target()
+    best = tune.autotune(first, None, None, mode="bool", n_t=100, n_r=1000, cache_path=path)
+    assert len(first.calls) == len(tune.STAGES) and best["stack_depth"] == 16
+    assert tune.autotune(again, None, None, mode="bool", n_t=100, n_r=1000, cache_path=path) == best
+    assert again.calls == [[best]]
