@@ -512,8 +512,9 @@ __device__ inline void leaf_phase4(const QArgs &a, Lane &L, int32_t &cur, Pop po
 }
 
 // Write the results of a finished segment (or queue it for the deep pass).
+// `spilled`: its stack continued in device memory.
 template <uint32_t MODE, bool RETRY, bool BATCH>
-__device__ inline void finish(const QArgs &a, const Lane &L)
+__device__ inline void finish(const QArgs &a, const Lane &L, bool spilled)
 {
     if (!RETRY && L.retry) {
         const int32_t r = atomicAdd(&a.scalars[kRetryN], 1);
@@ -524,6 +525,7 @@ __device__ inline void finish(const QArgs &a, const Lane &L)
         if ((MODE & M_ALL) && L.e >= 0 && L.e < a.ovf_cap) a.ovf_cnt[L.e] = -1;
         return;
     }
+    if (!RETRY && spilled) atomicAdd(&a.scalars[kSpilled], 1);
     const int64_t i = L.seg_i;
     if (MODE & M_BOOL) {
         uint8_t *hit = BATCH ? a.bt.hit[L.mesh] : a.o.hit;
@@ -661,7 +663,7 @@ __device__ inline void share_walks(Lane &L, int32_t &item, int32_t &cur, int32_t
 // segment, whether a helper is still walking.  All-hits crossings and
 // boolean hits reach their lane in the leaf phase already.
 template <uint32_t MODE, typename Ent>
-__device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_t col, Ent *q)
+__device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_t &col, Ent *q)
 {
     const int32_t lane = (int32_t)__lane_id();
     constexpr bool FIRST = (MODE & M_FIRST) && !(MODE & M_ALL);
@@ -669,7 +671,7 @@ __device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_
     const bool ends = item == -3 && cur == kDone && (col & 511) == 0;
     // the flags' word: 1 a helper walks, 2 a helper found no column, 4 a
     // helper found a crossing (whose t may be NaN where products overflow, and
-    // then no candidate says so); counts above
+    // then no candidate says so), 8 a helper used a column; counts above
     int32_t *const flags = reinterpret_cast<int32_t *>(q + lane) + (sizeof(Ent) / 4 - 1);
     *flags = 0;
     if constexpr (FIRST) *reinterpret_cast<unsigned long long *>(q + lane) = ~0ull;
@@ -677,10 +679,10 @@ __device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_
     unsigned long long key = ~0ull;
     if (item == -3) {
         int32_t *const f = reinterpret_cast<int32_t *>(q + L.own) + (sizeof(Ent) / 4 - 1);
-        const int32_t bits = ends ? (L.retry ? 2 : 0) | (FOUND && L.found ? 4 : 0) : 1;
+        const int32_t bits = ends ? (L.retry ? 2 : 0) | (FOUND && L.found ? 4 : 0) | (col & 512) >> 6 : 1;
         if (bits) atomicOr(f, bits);
         if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) {
-            if (ends && L.count) atomicAdd(f, L.count << 3);
+            if (ends && L.count) atomicAdd(f, L.count << 4);  // below 2^27 in all
         }
         if constexpr (FIRST) {
             if (ends && L.best_pos >= 0) {
@@ -702,7 +704,8 @@ __device__ inline bool share_results(Lane &L, int32_t &item, int32_t cur, int32_
         helped = (f & 1) != 0;
         if (f & 2) L.retry = true;
         if (FOUND && (f & 4)) L.found = true;
-        if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) L.count += f >> 3;
+        col |= (f & 8) << 6;
+        if constexpr ((MODE & M_COUNT) && !(MODE & M_ALL)) L.count += f >> 4;
         if constexpr (FIRST) {
             const unsigned long long k = *reinterpret_cast<unsigned long long *>(q + lane);
             if (k != ~0ull)
@@ -1092,10 +1095,7 @@ __global__ __launch_bounds__(256)
             if (c >= b.n_cols) return false;
             col = (c + 1) << 10;
         }
-        if (!(col & 512)) {
-            col |= 512;
-            if (!RETRY) atomicAdd(&b.scalars[kSpilled], 1);
-        }
+        col |= 512;
         const int32_t k = (n + 1) >> 1, have = col & 511;
         int32_t *g = b.gstack + ((col >> 10) - 1);
         if (have + k > b.depth) {  // deeper than any valid tree: the entries are dropped and flagged
@@ -1143,7 +1143,7 @@ __global__ __launch_bounds__(256)
                                    : (int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
             if (COUNT) ++tl.w_refill;
             if (done) {
-                finish<MODE, RETRY, BATCH>(seldom(), L);
+                finish<MODE, RETRY, BATCH>(seldom(), L, (col & 512) != 0);
                 item = -1;
             }
             const bool none = ballot(item >= 0) == 0;
@@ -1385,7 +1385,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((MODE & M_A
         if (waiting != 0 && ((int)__popcll(waiting) >= a.refill || ballot(item >= 0 && !done) == 0)) {
             if (COUNT) ++tl.w_refill;
             if (done) {
-                finish<MODE, RETRY, BATCH>(seldom(), L);
+                finish<MODE, RETRY, BATCH>(seldom(), L, false);
                 item = -1;
             }
             const int32_t k = claim_items<RETRY>(seldom(), cl, item == -1);

@@ -60,3 +60,22 @@ def test_launch_with_a_column_for_each_lane(depth, n):
                 assert torch.equal(want[k][: got[k].shape[0]], got[k]), (mode, k)
     many.close()
     small.close()
+
+
+@pytest.mark.parametrize("n", [1, 3, 70, 2_000])
+def test_overflowed_segments_are_counted_once(n):
+    """deep_segments counts segments, however many lanes walked parts of one and
+    whichever of them overflowed: upright segments through 2,000 sheets."""
+    k = np.arange(2_000, dtype=np.float32)[:, None, None] / 2_000
+    quad = np.array([[0, 0, 0], [1, 0, 0], [1, 1, 0], [0, 1, 0]], np.float32)
+    V = (quad + k * np.array([0, 0, 1], np.float32)).reshape(-1, 3)
+    T = (4 * np.arange(2_000)[:, None, None] + np.array([[0, 1, 2], [0, 2, 3]])).reshape(-1, 3)
+    xy = np.random.default_rng(12).uniform(0.1, 0.9, (n, 2)).astype(np.float32)
+    S, E = (_t(np.concatenate([xy, np.full((n, 1), z, np.float32)], 1)) for z in (-1.0, 2.0))
+    small = rsi.Mesh(_t(V), _t(T, torch.int32), stack_depth=3)
+    for mode in ("count", "all", "first|count"):
+        got = small.query(S, E, mode, capacity=2)
+        assert torch.all(got["count"] >= 2_000)
+        st = small.stats()
+        assert st["deep_segments"] == n, (mode, st)
+    small.close()
