@@ -165,8 +165,8 @@ rsi_status rsi_refit(rsi_handle h, const float *V, int64_t n_v, void *stream);
  * Always asynchronous on `stream`.  Reported t, u, v and P are re-solved in
  * FP64 from the FP32 inputs; the crossing decisions are the FP32 test.
  * Memory kept with the handle, allocated on first use and grown with n_r:
- * a retry queue (4 bytes per segment) and the deep pass's stack (a fixed
- * grid); for RSI_ALL_HITS also 16 bytes per segment of overflow table, the
+ * a retry queue (4 bytes per segment) and the stacks' device-memory part (a
+ * fixed size, at most 16 MB); for RSI_ALL_HITS also 16 bytes per segment of overflow table, the
  * arena and the library pool.
  * n_r == 0 is a no-op (output pointers are then not inspected).
  * Errors: RSI_E_INVALID (n_r < 0 or >= 2^30, mode 0 or unknown bits, missing output
@@ -177,7 +177,7 @@ rsi_status rsi_query(rsi_handle h, const float *S, const float *E, int64_t n_r,
 /* rsi_query for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
  * handle, inputs and outputs are the caller's, as for rsi_query; the
- * library's own scratch (the deep pass's queue and stack) comes from one
+ * library's own scratch (the deep pass's queue, the stacks) comes from one
  * fixed 32 MiB device array per GPU, held from the first call on that GPU
  * until the process ends.  No allocation of any kind is made, and nothing
  * is waited for.
@@ -221,7 +221,8 @@ rsi_status rsi_query_noalloc(rsi_handle h, const float *S, const float *E, int64
  * (per triangle in FP64, then per vertex), so repeated calls give the same
  * bits.  Memory kept with the handle and released by rsi_destroy (allocated
  * on first use, grown for a larger batch): about 64 bytes per segment
- * (records, sort pairs and the sort's scratch), 72 bytes per triangle and a
+ * (records, sort pairs and the sort's scratch), 72 bytes per triangle, their
+ * part sums (288 bytes per triangle, or up to 38 MB on a small mesh) and a
  * vertex incidence table of 36 bytes per triangle (rebuilt after
  * rsi_build / rsi_rebuild, kept across rsi_refit).
  * Asynchronous on `stream`.  Errors: RSI_E_INVALID (NULL pointers, n_r out

@@ -50,7 +50,7 @@ void free_handle_memory(rsi_bvh *h)
     void *ptrs[] = {h->rank, h->adj_vals, h->seg_keys, h->adj_rec, h->adj_rec_v, h->tri_sum, h->adj_part, h->adj_cell_first, h->inc_first, h->inc_keys,
                     h->inc_vals, h->compact_counts, h->nodes4, h->aux_E, h->aux_count,
                     h->retry_q, h->retry_stack, h->arena, h->T, h->V_all, h->src_V, h->src_T, h->cent, h->keys,
-                    h->order, h->nodes, h->tris, h->arrive, h->joins, h->scalars,
+                    h->order, h->nodes, h->tris, h->laid_out, h->joins, h->scalars,
                     h->counters, h->ovf_seg, h->ovf_cnt, h->ovf_list, h->ovf_off, h->ovf_part, h->pool_ids, h->pool_ts, h->tri_off,
                     h->vert_off, h->mesh_bounds, h->mesh_height, h->mesh_root, h->mesh_entry,
                     h->mesh_scale};
@@ -170,7 +170,7 @@ rsi_status alloc_handle(int32_t M, const int64_t *n_v, const int64_t *n_t, const
     if (e == hipSuccess) e = dalloc(&h->nodes, n);
     if (e == hipSuccess && h->width == 4) e = dalloc(&h->nodes4, n);
     if (e == hipSuccess) e = dalloc(&h->tris, n + 1);
-    if (e == hipSuccess) e = dalloc(&h->arrive, n);
+    if (e == hipSuccess) e = dalloc(&h->laid_out, n);
     if (e == hipSuccess) e = dalloc(&h->joins, rsi::join_words(n));
     if (e == hipSuccess) e = dalloc(&h->scalars, rsi::kNumScalars);
     if (e == hipSuccess) e = dalloc(&h->counters, 1);

@@ -8,7 +8,7 @@
 //
 //   k_gather     (batches) copy every mesh's vertices and triangles into the
 //                concatenated arrays, offsetting the vertex indices
-//   k_init       reset per-mesh bounds, heights, roots and arrival counters
+//   k_init       reset per-mesh bounds, heights, roots and record flags
 //   k_centroids  c_j = (v_a + v_b + v_c) / 3 per triangle, index validation,
 //                and the support interval of each mesh's centroids (block
 //                min/max in LDS, then one ordered-int atomic per block, mesh
@@ -22,11 +22,11 @@
 //                keys (Apetrei's scheme, as the paper follows): every leaf
 //                climbs; at each step the node joins the neighbour across the
 //                split whose key distance is smaller, writes its box and
-//                reference into its parent, and the parent's arrival counter
+//                reference into its parent, and the parent's arrival flag
 //                lets only the second child continue -- so the parent's box
 //                is formed exactly once, from both children.  Ranges with at
 //                most `leaf_size` triangles become leaves.  Subtrees inside
-//                a block of 512 (or 2048) sorted leaves finish in LDS
+//                a block of 512 sorted leaves (or a small mesh) finish in LDS
 //                (k_lbvh_local), and the few that cross block boundaries are
 //                joined in LDS too, by a workgroup per 64 blocks and one for
 //                the rest (k_lbvh_join).
@@ -58,7 +58,7 @@ struct BuildArgs {
     Node *nodes;
     Node4 *nodes4;         // four-way records, null when the walk does not use them
     Tri *tris;
-    int32_t *arrive;
+    uint8_t *laid_out;
     int32_t *joins;        // lists of the local blocks' subtrees (kListWords each)
     int32_t *bounds;       // [6M] ordered-int centroid bounds per mesh
     int32_t *mesh_height;  // [M]
@@ -116,7 +116,7 @@ __global__ void k_init(BuildArgs a)
         a.tris[a.n_t].a = a.tris[a.n_t].b = a.tris[a.n_t].c = z;
     }
     if (i == 0) a.scalars[kBadIndex] = 0;
-    if (i < a.n_t) a.arrive[i] = 0;
+    if (i < a.n_t) a.laid_out[i] = 0;
 }
 
 constexpr int kCentBlock = 256;
@@ -469,9 +469,6 @@ struct Wide {
     }
 };
 
-// Arrival count of a node whose four-way record the local pass has written.
-constexpr int32_t kWidened = 4;
-
 // The subtrees a workgroup has completed but cannot join to their siblings,
 // which lie in other workgroups' leaves: a list per local block, in leaf
 // order.  Each side of a block's range cuts a path from a mesh's root, and the
@@ -770,7 +767,7 @@ __global__ __launch_bounds__(kLocalThreads) void k_lbvh_local(BuildArgs a)
                 return lref[slot][side];
             });
             w.store(a.nodes4 + p, n);
-            a.arrive[p] = kWidened;
+            a.laid_out[p] = 1;
         }
     }
 }
@@ -897,11 +894,11 @@ __global__ __launch_bounds__(kJoin) void k_lbvh_join(BuildArgs a, int32_t nb, in
 // The records the local pass has not laid out: nodes whose subtrees cross its
 // blocks, the entry nodes, and every record of a tree built without the
 // four-way view.
-__global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, const int32_t *__restrict__ arrive,
+__global__ __launch_bounds__(256) void k_widen(const Node *__restrict__ nodes, const uint8_t *__restrict__ laid_out,
                                                int64_t n, Node4 *__restrict__ out)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n || arrive[j] == kWidened) return;
+    if (j >= n || laid_out[j]) return;
     // a node no climb reached (inside a collapsed leaf) may hold anything:
     // its references are checked before use
     const auto read = [&](int64_t c, int side, float *b) -> int32_t {
@@ -943,7 +940,7 @@ BuildArgs make_build_args(rsi_bvh *h, const float *V)
     a.nodes = h->nodes;
     a.nodes4 = wide_view(h) ? h->nodes4 : nullptr;
     a.tris = h->tris;
-    a.arrive = h->arrive;
+    a.laid_out = h->laid_out;
     a.joins = h->joins;
     a.bounds = h->mesh_bounds;
     a.mesh_height = h->mesh_height;
@@ -1021,7 +1018,7 @@ hipError_t launch_widen(rsi_bvh *h, hipStream_t s)
         return hipSuccess;
     }
     hipLaunchKernelGGL(k_widen, dim3((unsigned)((h->n_t + 255) / 256)), dim3(256), 0, s, h->nodes,
-                       h->arrive, h->n_t, h->nodes4);
+                       h->laid_out, h->n_t, h->nodes4);
     h->width_built = 4;
     return hipGetLastError();
 }

@@ -4,8 +4,8 @@
 //
 // rsi_query keeps two scratch buffers with the handle, allocated on first use
 // and grown with the number of segments: the deep pass's queue (one int32 per
-// segment whose stack outgrew its LDS part) and its device-memory stack (one
-// column per thread of the deep pass's fixed grid).  Here both live in one
+// segment) and the stacks' device-memory part (a fixed number of columns,
+// claimed by the lanes whose stack outgrows its LDS part).  Here both live in one
 // file-scope device array of fixed size instead, and a query with more
 // segments than the array's queue part can hold runs as consecutive parts on
 // the same stream, each a complete query of a contiguous range of segments.
@@ -97,15 +97,11 @@ rsi_status rsi_query_noalloc(rsi_handle h, const float *S, const float *E, int64
                                : fail(RSI_E_HIP, std::string("rsi_query_noalloc: ") + hipGetErrorString(e));
     }
 
-    // the deep pass's stack takes the front of the array (64-entry aligned),
-    // the queue the rest; the queue sets how many segments one part holds
-    const int64_t stack_ints = (rsi::deep_stack_entries(h, mode) + 63) / 64 * 64;
+    // the stacks' device-memory part takes the front of the array (64-entry
+    // aligned; at most 14,848 columns of 274 entries, half of it), the queue the
+    // rest; the queue sets how many segments one part holds
+    const int64_t stack_ints = (rsi::deep_stack_entries(h) + 63) / 64 * 64;
     const int64_t part = kScratchInts - stack_ints;
-    if (part < 4096)
-        return fail(RSI_E_INVALID,
-                    "rsi_query_noalloc: the deep pass's stack for these options (" + std::to_string(stack_ints) +
-                        " entries) leaves no room in the 32 MiB scratch array; use a smaller block_size or "
-                        "rsi_query");
     const rsi::QueryScratch sc = {base + stack_ints, part, stack_ints > 0 ? base : nullptr, stack_ints};
     for (int64_t off = 0; off < n_r; off += part) {
         const int64_t n = n_r - off < part ? n_r - off : part;

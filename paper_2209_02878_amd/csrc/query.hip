@@ -24,7 +24,7 @@
 // reads the records of the top four levels from a per-workgroup copy in LDS
 // instead.
 // The default four-way walk (Node4) tests the segment against the four
-// quantised boxes of the node's grandchildren and pushes the touched
+// quantised boxes of up to four of the node's descendants and pushes the touched
 // children, nodes and leaves alike; the binary walk (Node, branching 2)
 // tests the two exact child boxes, keeps walking past one pending leaf and
 // descends into the nearer touched child.  Leaves are tested once few lanes
@@ -2565,7 +2565,7 @@ hipError_t launch_all_hits_tail(const QArgs &a, bool batch, hipStream_t s)
 
 }  // namespace
 
-int64_t deep_stack_entries(const rsi_bvh *h, uint32_t mode)
+int64_t deep_stack_entries(const rsi_bvh *h)
 {
     const int ld = lds_part(h);
     const int need = stack_need(h->height_bound, h->width_built);

@@ -121,7 +121,7 @@ struct rsi_bvh {
     int32_t *rank = nullptr;       // sorted position of each triangle (inverse of order) [n_t]
     rsi::Node *nodes = nullptr;    // [max(n_t, 1)]; each mesh's last record is its entry node
     rsi::Tri *tris = nullptr;      // [n_t + 1] in sorted order, then a record of zeros (unused four-way slots name it)
-    int32_t *arrive = nullptr;     // arrival counters [n_t]
+    uint8_t *laid_out = nullptr;   // 1 where the local build pass wrote the node's four-way record [n_t]
     int32_t *joins = nullptr;      // subtree lists handed from the local build pass to the joining one
     int32_t *scalars = nullptr;    // rsi::Scalar
     rsi::Counters *counters = nullptr;
@@ -265,7 +265,7 @@ struct QueryScratch {
 hipError_t launch_query_scratch(rsi_bvh *h, const float *S, const float *E, int64_t n_r, uint32_t mode,
                                 const QueryOut &o, const QueryScratch &sc, bool keep_flags, hipStream_t s);
 // stack entries (int32) the deep pass of a query in `mode` needs
-int64_t deep_stack_entries(const rsi_bvh *h, uint32_t mode);
+int64_t deep_stack_entries(const rsi_bvh *h);
 hipError_t launch_fill_miss(int64_t n_r, uint32_t mode, const QueryOut &o, hipStream_t s);
 // zero the per-query device scalars (a query that launches no walk)
 hipError_t launch_clear_query(rsi_bvh *h, hipStream_t s);
