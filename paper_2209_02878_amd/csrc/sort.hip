@@ -718,15 +718,18 @@ void redo_passes(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout, i
 // number of passes goes by n (by the largest mesh in a batch, whose groups lie
 // inside a mesh) and the length of the keys alone: none while one group may
 // hold every key (k_finish alone), one while 256 groups keep the count loop
-// short, two up to kTwoPasses, else three.  Measured, k_finish and a pass: 29,768
-// triangles 18 us after one pass, 5 after two, a pass 10; 499,280 triangles
-// 45 us after two, 13 after three, a pass 19; 4M segments 189 us after two
-// (the densest groups pass 512 keys), 32 after three, a pass 54.  Rebuilds
-// after two and three passes: terrain of 200,000 triangles 140 and 144 us,
-// 300,000 156 and 156, 500,000 192 and 182, 1M 293 and 238; sphere 139 and 143,
-// 159 and 153, 197 and 182, 312 and 248.  Segments spread over a volume make
-// smaller groups: 400,000 ordered in 82 us and 92, 1M on the terrain in 149 and
-// 133 (upright ones on a plane 94 after three, 141 after two).  Keys
+// short (kOnePass), two up to kTwoPasses, else three.  Measured, k_finish and a
+// pass: 29,768 triangles 18 us after one pass, 5 after two, a pass 10; 499,280
+// triangles 45 us after two, 13 after three, a pass 19; 4M segments 189 us
+// after two (the densest groups pass 512 keys), 32 after three, a pass 54.
+// Rebuilds after one and two passes: sphere of 20,000 triangles 85 us and 81,
+// 30,000 95 and 84.  After two and three: terrain of 200,000 triangles 140 and
+// 144, 300,000 156 and 156, 500,000 192 and 182, 1M 293 and 238; sphere 139 and
+// 143, 159 and 153, 197 and 182, 312 and 248.  Segments spread over a volume
+// make smaller groups.  After one and two passes: 19,000 ordered in 36 to 39 us
+// and 41, 32,000 in 38 to 53 and 44 (17,000 upright ones on a plane 51 and 41);
+// after two and three 400,000 in 82 and 92, 1M on the terrain in 149 and 133
+// (400,000 upright ones 141 and 94).  Keys
 // of no more bits than that, and passes that start above bit 0 (which leave
 // the lower bits unsorted), run as digit passes only.  With mesh_off (M > 1)
 // the mesh id's digits follow the key's, so each mesh's elements end up
@@ -739,9 +742,9 @@ struct SortPlan {
 };
 
 constexpr int64_t kOneGroup = 256;
-constexpr int64_t kOnePass = 16384;
-constexpr int64_t kTwoPasses = int64_t(1) << 18;       // 63-bit codes of triangles
-constexpr int64_t kTwoPassesShort = int64_t(1) << 20;  // keys of at most 40 bits: segments, vertices
+// 63-bit codes of triangles, and keys of at most 40 bits: segments, vertices
+constexpr int64_t kOnePass = 16384, kOnePassShort = 20480;
+constexpr int64_t kTwoPasses = int64_t(1) << 18, kTwoPassesShort = int64_t(1) << 20;
 
 // `most`: keys of the largest mesh (n without meshes).
 static SortPlan plan_sort(int64_t n, int64_t most, int key_bits, int first_bit, const int64_t *mesh_off, int32_t M)
@@ -750,8 +753,11 @@ static SortPlan plan_sort(int64_t n, int64_t most, int key_bits, int first_bit, 
     int from = first_bit;
     const bool batch = mesh_off && M > 1;
     if (first_bit == 0) {
-        const int64_t two = key_bits > 40 ? kTwoPasses : kTwoPassesShort;
-        const int prefix = n <= kOneGroup ? 0 : n <= kOnePass ? 1 : most <= two ? 2 : 3;
+        const bool wide = key_bits > 40;
+        const int prefix = n <= kOneGroup                            ? 0
+                           : n <= (wide ? kOnePass : kOnePassShort)  ? 1
+                           : most <= (wide ? kTwoPasses : kTwoPassesShort) ? 2
+                                                                     : 3;
         if (8 * prefix < key_bits) p.low = from = key_bits - 8 * prefix;
     }
     for (int b = from; b < key_bits; b += 8) p.pass[p.np++] = Digit{nullptr, 0, b};

@@ -183,3 +183,30 @@ def test_time_of_a_large_table_with_one_far_segment():
         times.append(min(ms))
     mesh.close()
     assert times[1] < 3.5 * times[0], times
+
+
+@pytest.mark.parametrize("n", [20_480, 20_481])
+@pytest.mark.parametrize("flat", [False, True])
+def test_totals_around_the_short_keys_limit(n, flat):
+    """Segments' 33-bit keys: one pass up to 20,480, then two; spread over a
+    volume, and with every midpoint on a plane (groups of over 512 keys)."""
+    rng = np.random.default_rng(n)
+    S, E = wl.segments_in_box(rng, [0, 0, 0], [1, 1, 0.1], n)
+    if flat:
+        S[:, 2], E[:, 2] = 1.0, -1.0
+    assert np.array_equal(_order(S, E), np.argsort(host_keys(S, E), kind="stable"))
+
+
+def test_totals_around_the_triangles_limits():
+    """63-bit codes: one pass up to 16,384 triangles, two up to 262,144."""
+    rng = np.random.default_rng(7)
+    for n in (16_384, 16_385, 262_144, 262_145):
+        c = rng.uniform(0, 1, (n, 1, 3)) * np.array([1, 1, 0.05])
+        V = (c + 1e-4 * rng.uniform(-1, 1, (n, 3, 3))).astype(np.float32).reshape(-1, 3)
+        T = np.arange(3 * n, dtype=np.int32).reshape(n, 3)
+        mesh = rsi.Mesh(_t(V), _t(T, torch.int32))
+        ref = _morton_reference(V, T)
+        want = np.argsort(ref, kind="stable")
+        tree = mesh.tree()
+        assert np.array_equal(tree["keys"], ref[want]) and np.array_equal(tree["order"], want), n
+        mesh.close()
