@@ -5,7 +5,8 @@
 // keeps resident; every lane owns one segment at a time and, when it is done,
 // takes the next unprocessed segment from its wave's chunk; a wave claims a
 // new chunk of segments with one atomic on the counter of its XCD's range of
-// the segments (the other ranges once its own is used up).  The paper's
+// the segments (the other ranges once its own is used up; where one chunk a
+// wave covers all, the chunks are fixed).  The paper's
 // kernel strides each thread over the rays instead (Section 3.3); with
 // segments whose traversal lengths vary by an order of magnitude, a wave that
 // waits for its slowest lane leaves most of its lanes idle, which the refill
@@ -989,10 +990,11 @@ __device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
 // every child whose box the segment touches and takes the top entry as the
 // next one (`cur`), an internal node or a leaf; a lane with a leaf on top
 // waits for the wave's leaf phase.  Slot 0 of every stack holds kDone, so a
-// pop needs no check for the end.  The step bounds the walk (10M boolean
-// queries of the 29,768-triangle mesh: the texture-data unit busy 0.97 of the
-// time, a VALU instruction active 0.99 of it), so it is kept short: about 100
-// VALU instructions, against 148 when leaves were kept in registers, the
+// pop needs no check for the end.  The step bounds the walk: in 10M boolean
+// queries of the 29,768-triangle mesh the texture-data unit is busy 0.92 of the
+// time, and the VALU instructions would fill 0.93 of it at four clocks each, an
+// upper limit, since many issue in two.  So it is kept short: about 100 VALU
+// instructions, against 148 when leaves were kept in registers, the
 // nearest child was picked in every mode and the plane margins were formed
 // per plane.  Only the first-hit walk still picks the nearest child (pruning
 // pays for it); for the other modes the build orders the children.  On
@@ -1006,14 +1008,18 @@ __device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
 // moves the older half of the window to a column in device memory (claimed
 // at the lane's first such push, kept for the launch) and a lane that runs
 // out of entries takes the newest ones back.  Walks that outgrow the LDS
-// part are few (2 to 6 segments of 4M to 10M on the 499,280-triangle sphere),
-// but finishing them in a pass of their own cost 150 to 275 us per query: a
-// few lanes walking alone from the root.  Only a lane that finds every
+// part are few (325 of the 10M boolean segments above, 5,596 of 10M all-hits
+// ones on the 499,280-triangle sphere), but finishing even 2 to 6 of them, as
+// with 20 entries, in a pass of their own cost 150 to 275 us per query: a few
+// lanes walking alone from the root.  Only a lane that finds every
 // column taken still leaves its segment to that pass (RETRY: work items come
 // from the retry queue, whose length is read on the device, and every lane
 // has a column).
-// Registers: six waves per SIMD for all hits (80 VGPRs), seven for the others
-// (72; the LDS parts allow no more).
+// Registers: six waves per SIMD for all hits (80 VGPRs; with a first hit as
+// well three of them live in scratch), seven for the others (up to 72, none in
+// scratch; the LDS parts allow no more).  First hits measure alike at six:
+// 3M on 29,768 triangles 357 us and 359 at seven, the gradient step of 4M on
+// 199,712 1,034 and 1,033, rebuild and 307,200 on 499,280 299 and 299.
 template <uint32_t MODE, bool RETRY, bool COUNT, bool BATCH, bool BIG>
 __global__ __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu((MODE & M_ALL) ? 6 : 7))) void k_query(QArgs a)
@@ -2336,11 +2342,13 @@ hipError_t launch_kernel(const QArgs &a, int block, size_t lds, hipStream_t s, i
         grid = (int64_t)per_cu * device_cus();
         const int64_t wpb = block / 64;
         // the four-way walk shares a segment among a wave's lanes, so few
-        // items are spread over the waves, up to kSpreadWaves per CU (more
-        // waves than that cost more in idle lanes' instructions than the
-        // shorter walks give: 10k segments against 29,768 triangles, 4 waves
-        // per CU 44 us, 8 52 us, 16 67 us; 100k segments against the
-        // 499,280-triangle sphere 86, 81 and 100 us; unshared 92 and 204 us)
+        // items are spread over the waves, up to kSpreadWaves per CU.  More
+        // waves cost more in idle lanes' instructions than the shorter walks
+        // give until the walks are long: counts of 10k segments on 29,768
+        // triangles take 43, 45, 44 and 48 us with 4, 6, 8 and 16 waves per
+        // CU, of 30k on the 499,280-triangle sphere 66, 85, 83 and 90, of 100k
+        // there 91, 91, 86 and 80; first hits of 100k on 29,768 triangles 58,
+        // 58, 56 and 61.  (Unshared, 10k and 100k take 92 and 204 us.)
         const int64_t spread = (a.n_items + kSpreadWaves * device_cus() - 1) / (kSpreadWaves * device_cus());
         const int64_t own = WIDE && spread < 64 ? spread : 64;
         const int64_t need = (a.n_items + own * wpb - 1) / (own * wpb);

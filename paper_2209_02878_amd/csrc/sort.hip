@@ -2,7 +2,9 @@
 // Morton-code sorting step timed in the paper's Table 2, which there ran on
 // the host): stable passes on the top 8-bit digits until the groups of equal
 // prefixes are small, then one pass that orders each group by counting
-// (k_finish; plan_sort says how many passes).
+// (k_finish; plan_sort says how many passes).  Groups that stay large are
+// sorted by a workgroup each, in LDS or device memory, and in a large table by
+// passes over all of it (redo_passes).
 //
 // One digit pass:
 //   k_hist     per-tile digit histogram in LDS -> hist[digit][tile]
