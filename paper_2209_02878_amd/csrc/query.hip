@@ -992,7 +992,7 @@ __device__ inline void void_blocks(const QArgs &a, volatile int32_t *wst)
 // waits for the wave's leaf phase.  Slot 0 of every stack holds kDone, so a
 // pop needs no check for the end.  The step bounds the walk: in 10M boolean
 // queries of the 29,768-triangle mesh the texture-data unit is busy 0.92 of the
-// time, and the VALU instructions would fill 0.93 of it at four clocks each, an
+// time, and the VALU instructions would fill as much at four clocks each, an
 // upper limit, since many issue in two.  So it is kept short: about 100 VALU
 // instructions, against 148 when leaves were kept in registers, the
 // nearest child was picked in every mode and the plane margins were formed
