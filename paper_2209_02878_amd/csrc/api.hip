@@ -149,6 +149,7 @@ rsi_status alloc_handle(int32_t M, const int64_t *n_v, const int64_t *n_t, const
     for (int32_t m = 0; m < M; ++m) {
         const int64_t hb = n_t[m] - 1 < 90 ? n_t[m] - 1 : 90;
         if (hb > h->height_bound) h->height_bound = (int32_t)hb;
+        if (n_t[m] > h->most_t) h->most_t = n_t[m];
     }
     if (h->n_t >= (int64_t(1) << rsi::kLeafFirstBits)) {
         delete h;

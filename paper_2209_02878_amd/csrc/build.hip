@@ -1036,17 +1036,12 @@ hipError_t launch_build(rsi_bvh *h, const float *V, hipStream_t s)
         hipLaunchKernelGGL(k_centroids<1>, dim3((unsigned)((n + kCentBlock - 1) / kCentBlock)), dim3(kCentBlock), 0, s,
                            a);
     const int64_t *mesh_off = h->M > 1 ? h->tri_off : nullptr;
-    int64_t most = 0;
-    for (int32_t m = 0; m < h->M; ++m) {
-        const int64_t k = h->h_tri_off[m + 1] - h->h_tri_off[m];
-        most = k > most ? k : most;
-    }
     BuildArgs km = a;  // the codes go where the sort wants its input
-    hipError_t e = sort_source(h->keys, h->order, n, kCodeBits, h->sort, mesh_off, h->M, most, &km.keys, &km.order);
+    hipError_t e = sort_source(h->keys, h->order, n, kCodeBits, h->sort, mesh_off, h->M, h->most_t, &km.keys, &km.order);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_morton, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, km);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = radix_sort_pairs(h->keys, h->order, n, kCodeBits, h->sort, s, mesh_off, h->M, most);
+    e = radix_sort_pairs(h->keys, h->order, n, kCodeBits, h->sort, s, mesh_off, h->M, h->most_t);
     if (e != hipSuccess) return e;
     e = run_hierarchy(a, s);
     if (e != hipSuccess) return e;

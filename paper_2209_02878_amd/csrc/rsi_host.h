@@ -92,6 +92,7 @@ struct rsi_bvh {
     int device = 0;
     int32_t M = 1;
     int64_t n_v = 0, n_t = 0;      // totals over all meshes
+    int64_t most_t = 0;            // triangles of the largest mesh
     int32_t leaf_size = 1;
     int32_t block_size = rsi::kAutoBlock;
     int32_t defer_lanes = rsi::kAutoLanes;
