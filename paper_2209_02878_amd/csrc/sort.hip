@@ -3,8 +3,8 @@
 // the host): stable passes on the top 8-bit digits until the groups of equal
 // prefixes are small, then one pass that orders each group by counting
 // (k_finish; plan_sort says how many passes).  Groups that stay large are
-// sorted by a workgroup each, in LDS or device memory, and in a large table by
-// passes over all of it (redo_passes).
+// sorted by a workgroup each, in LDS or device memory; a large table in which a
+// sample finds such groups gets passes on its low digits first (k_sample).
 //
 // One digit pass:
 //   k_hist     per-tile digit histogram in LDS -> hist[digit][tile]
@@ -90,11 +90,9 @@ __global__ __launch_bounds__(kThreads) void k_hist(const uint64_t *__restrict__ 
 // (block sums, their scan, a second sweep) took three, 16 us a pass.
 template <bool GATED = false>
 __global__ __launch_bounds__(kThreads) void k_scan(uint32_t *__restrict__ hist, int ntiles,
-                                                   uint32_t *__restrict__ total, uint32_t *__restrict__ gate)
+                                                   uint32_t *__restrict__ total, const uint32_t *__restrict__ gate)
 {
     if (GATED && *gate == 0) return;
-    // `gate` (may be null) is cleared by an ungated pass
-    if (!GATED && gate && blockIdx.x == 0 && threadIdx.x == 0) *gate = 0;
     __shared__ uint32_t ws[kWaves];
     const int tid = threadIdx.x, wave = tid >> 6;
     uint32_t *const row = hist + (int64_t)blockIdx.x * ntiles;
@@ -482,16 +480,13 @@ __device__ __forceinline__ void sort_group_global(uint64_t *__restrict__ kin, ui
 // 499,280 keys took 189 us and at 4M 1,187 us (a 16,000-key bucket streamed
 // through one workgroup).
 //
-// With `redo`, a group of more than kAlone keys is left as it is and *redo set:
-// gated passes over all the digits follow (redo_passes).
+// With *sorted set the passes before have put the whole table in order.
 //
 // The window's keys lie in LDS shifted up by 12 bits (their prefixes, equal
 // within a group, may fall off) with their window position below, so keys
 // are distinct and one 64-bit compare counts equal keys by position; PACKED
 // false (low > 52) compares key and position.  The first keys of the groups
 // are one bit each.
-constexpr int64_t kAlone = 16384;
-
 template <int TILE, int HALO, bool PACKED>
 __global__ __launch_bounds__(kThreads)
     __attribute__((amdgpu_waves_per_eu(TILE == 256 ? 2 : 5))) void k_finish(uint64_t *__restrict__ kin,
@@ -499,7 +494,8 @@ __global__ __launch_bounds__(kThreads)
                                                                             uint64_t *__restrict__ kout,
                                                                             uint32_t *__restrict__ vout, int64_t n,
                                                                             int low, const int64_t *__restrict__ off,
-                                                                            int32_t M, uint32_t *__restrict__ redo)
+                                                                            int32_t M,
+                                                                            const uint32_t *__restrict__ sorted)
 {
     constexpr int kWin = TILE + 2 * HALO;
     static_assert(kWin <= 4096 && kWin % 64 == 0, "window positions take 12 bits, group starts whole words");
@@ -525,6 +521,13 @@ __global__ __launch_bounds__(kThreads)
     static_assert(sizeof(sh) <= 163840 / (TILE == 256 ? 4 : 6), "four or six workgroups on a CU");
     const int tid = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * TILE;
+    if (sorted && *sorted) {
+        for (int64_t i = t0 + tid; i < n && i < t0 + TILE; i += kThreads) {
+            kout[i] = kin[i];
+            vout[i] = vin[i];
+        }
+        return;
+    }
     const int64_t w0 = t0 - HALO > 0 ? t0 - HALO : 0;
     const int nw = (int)((t0 + TILE + HALO < n ? t0 + TILE + HALO : n) - w0);
     if (tid == 0) sh.n_large = 0;
@@ -603,10 +606,6 @@ __global__ __launch_bounds__(kThreads)
             else hi = mid;
         }
         const int64_t bn = lo - b0;
-        if (redo && bn > kAlone) {
-            if (tid == 0) *redo = 1;
-            continue;
-        }
         if (bn <= 4 * kThreads) {
             sort_group_lds<4, kMostItems>(kin, vin, kout, vout, b0, (int)bn, sh.work);
         } else if (bn > kMostItems * kThreads) {
@@ -617,6 +616,49 @@ __global__ __launch_bounds__(kThreads)
         }
         __syncthreads();
     }
+}
+
+// Whether a table has large groups of equal prefixes: every 64th key (jittered
+// within its 64) is counted by a hash of its prefix, and *word set when an
+// entry of the counts (a power of two of them, 2^bits) reaches kSampleHits: a
+// group of 16,384 keys is met 256 times.  Entries are at least four times the
+// samples, so chance meetings stay far below.
+constexpr int kSampleStep = 64;
+constexpr uint32_t kSampleHits = 128;
+
+__global__ __launch_bounds__(kThreads) void k_sample_clear(uint32_t *__restrict__ count, int bits,
+                                                           uint32_t *__restrict__ word)
+{
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    if (i == 0) *word = 0;
+    if (i < (1u << bits)) count[i] = 0;
+}
+
+__global__ __launch_bounds__(kThreads) void k_sample(const uint64_t *__restrict__ keys,
+                                                     const uint32_t *__restrict__ vals, int64_t n, int low,
+                                                     const int64_t *__restrict__ off, int32_t M,
+                                                     uint32_t *__restrict__ count, int bits,
+                                                     uint32_t *__restrict__ word)
+{
+    const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t i = t * kSampleStep + (((uint32_t)t * 0x9E3779B1u) >> 26);
+    if (i >= n) return;
+    uint64_t h = keys[i] >> low;
+    if (off) h ^= (uint64_t)mesh_of(off, M, (int64_t)vals[i]) << 40;
+    h *= 0x9E3779B97F4A7C15ull;
+    h ^= h >> 32;
+    const uint32_t at = (uint32_t)((h * 0x9E3779B97F4A7C15ull) >> (64 - bits));
+    // lanes that agree add together, a few groups at most: a clustered table
+    // puts most of the samples on a few entries
+    uint64_t left = __ballot(true);
+    uint32_t add = 1;
+    for (int k = 0; k < 8 && left; ++k) {
+        const int lead = __builtin_ctzll(left);
+        const uint64_t m = __ballot(at == (uint32_t)__builtin_amdgcn_readlane((int)at, lead)) & left;
+        if ((m >> __lane_id()) & 1) add = (int)__lane_id() == lead ? (uint32_t)__popcll(m) : 0u;
+        left &= ~m;
+    }
+    if (add && atomicAdd(&count[at], add) + add >= kSampleHits) *word = 1;
 }
 
 }  // namespace
@@ -635,7 +677,7 @@ hipError_t ensure_sort_scratch(SortScratch &sc, int64_t n)
         sc.cap = n;
     }
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    // fused path: three rotating histograms; else one table, the digits' sums and redo_passes' word
+    // fused path: three rotating histograms; else one table, the digits' sums and k_sample's word
     const int64_t hn = ntiles <= kFusedTiles ? 3 * kFusedTiles * kRadix : (ntiles + 1) * kRadix + 1;
     if (hn > sc.hist_cap) {
         if (sc.hist) (void)hipFree(sc.hist);
@@ -676,41 +718,43 @@ void fused_passes(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_
     }
 }
 
-// Above this many keys no workgroup is left alone with a group of more than
-// kAlone: one far segment or vertex puts nearly every key in a few groups.
-// 10M segments with one far: 4,760 us, 1,470 with the passes over the whole
-// table, whose launches cost 26 us where they do not run (930 -> 955).  Up to
-// this many keys the bucket sort that this one replaced left such groups to
-// one workgroup as well, and took longer: 4M segments with one far 2,960 us,
-// 1,970 now.
+// Above this many keys large groups are looked for, so that no workgroup is
+// left alone with one: one far segment or vertex puts nearly every key in a few
+// groups.  10M segments with one far are ordered in 1,007 us (4,850 when their
+// groups were left to a workgroup each), 4.4M triangles with a far vertex rebuilt
+// in 1,152 (9,409); a table without large groups pays for the sample and for
+// launches that do not run: 932 -> 953 us for 10M segments, 795 -> 837 for the
+// rebuild of 4.4M triangles.  Up to this many keys the bucket sort that came
+// before left such groups to one workgroup as well, and took longer: 4M
+// segments with one far 2,945 us, 1,950 now.
 constexpr int64_t kAloneTotal = int64_t(1) << 22;
 
-// The whole sort once more, from kin/vin to kout/vout, for a table with a group
-// above kAlone (the word at `gate`): stable passes over all digits, an odd
-// number of them so that the result ends in kout.  kin is in stable order of
-// prefixes, so keys that are equal keep their input order.
-void redo_passes(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout, int64_t n, int key_bits,
-                 const int64_t *mesh_off, int32_t M, uint32_t *hist, int ntiles, uint32_t *gate, hipStream_t s)
+// Ahead of the passes on the top digits: sample the table, and when it has
+// large groups, stable passes on the `low` low bits, an even number of them, so
+// that the pairs are back in ka / va.  With the passes on the digits above
+// them they sort the whole key.
+void low_passes(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_t n, int low, const int64_t *mesh_off,
+                int32_t M, uint32_t *hist, int ntiles, uint32_t *word, hipStream_t s)
 {
-    Digit pass[16];
-    int np = 0;
-    const int meshes = !mesh_off || M <= 1 ? 0 : M > 256 ? 2 : 1;
-    int keys = (key_bits + 7) / 8;
-    if ((keys + meshes) % 2 == 0) ++keys;
-    const int width = (key_bits + keys - 1) / keys;
-    for (int k = 0; k < keys; ++k) pass[np++] = Digit{nullptr, 0, k * width, (1u << width) - 1};
-    for (int k = 0; k < meshes; ++k) pass[np++] = Digit{mesh_off, M, 8 * k};
+    int bits = 63 - __builtin_clzll((unsigned long long)(n / 16));  // the counts lie in the histograms' space
+    if (bits > 24) bits = 24;
+    const int64_t samples = (n + kSampleStep - 1) / kSampleStep;
+    hipLaunchKernelGGL(k_sample_clear, dim3((1u << bits) / kThreads), dim3(kThreads), 0, s, hist, bits, word);
+    hipLaunchKernelGGL(k_sample, dim3((unsigned)((samples + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, ka, va,
+                       n, low, mesh_off, M, hist, bits, word);
+    const int np = (low + 15) / 16 * 2, width = (low + np - 1) / np;
     const unsigned grid = (unsigned)(ntiles < 512 ? ntiles : 512);
-    uint32_t *const total = hist + (int64_t)ntiles * kRadix;
     for (int p = 0; p < np; ++p) {
-        hipLaunchKernelGGL((k_hist<kItems, true>), dim3(grid), dim3(kThreads), 0, s, kin, vin, n, pass[p], hist, ntiles,
-                           nullptr, gate);
-        hipLaunchKernelGGL(k_scan<true>, dim3(kRadix), dim3(kThreads), 0, s, hist, ntiles, total,
-                           gate);
-        hipLaunchKernelGGL((k_scatter<false, kItems, true>), dim3(grid), dim3(kThreads), 0, s, kin, vin, kout, vout, n,
-                           pass[p], hist, ntiles, pass[p], nullptr, nullptr, gate);
-        uint64_t *tk = kin; kin = kout; kout = tk;
-        uint32_t *tv = vin; vin = vout; vout = tv;
+        const int shift = p * width, left = low - shift;
+        const Digit dg{nullptr, 0, shift, left <= 0 ? 0u : (1u << (left < width ? left : width)) - 1};
+        hipLaunchKernelGGL((k_hist<kItems, true>), dim3(grid), dim3(kThreads), 0, s, ka, va, n, dg, hist, ntiles,
+                           nullptr, word);
+        hipLaunchKernelGGL(k_scan<true>, dim3(kRadix), dim3(kThreads), 0, s, hist, ntiles,
+                           hist + (int64_t)ntiles * kRadix, word);
+        hipLaunchKernelGGL((k_scatter<false, kItems, true>), dim3(grid), dim3(kThreads), 0, s, ka, va, kb, vb, n, dg,
+                           hist, ntiles, dg, nullptr, nullptr, word);
+        uint64_t *tk = ka; ka = kb; kb = tk;
+        uint32_t *tv = va; va = vb; vb = tv;
     }
 }
 
@@ -796,7 +840,6 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
     hipError_t e = ensure_sort_scratch(sc, n);
     if (e != hipSuccess) return e;
     const int ntiles = (int)((n + kTile - 1) / kTile);
-    uint32_t *const redo = n > kAloneTotal ? sc.hist + (int64_t)(ntiles + 1) * kRadix : nullptr;
     const SortPlan p = plan_sort(n, mesh_off && M > 1 ? most : n, key_bits, first_bit, mesh_off, M);
     uint64_t *ka = keys, *kb = sc.keys_alt;
     uint32_t *va = vals, *vb = sc.vals_alt;
@@ -807,6 +850,12 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
     // without kres the input is where sort_source said, so that the result
     // ends in keys / vals
     if (!kres && (p.moves & 1)) swap();
+    const int64_t *off = mesh_off && M > 1 ? mesh_off : nullptr;
+    uint32_t *word = nullptr;
+    if (p.low && n > kAloneTotal) {
+        word = sc.hist + (int64_t)(ntiles + 1) * kRadix;
+        low_passes(ka, va, kb, vb, n, p.low, off, M, sc.hist, ntiles, word, s);
+    }
     if (p.np > 0 && ntiles <= kFusedTiles) {
         // (smaller tiles, hence more workgroups, measured slower: each
         // workgroup then scans more histograms and the next-pass counters
@@ -819,23 +868,21 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int key_b
             hipLaunchKernelGGL(k_hist<kItems>, dim3(ntiles), dim3(kThreads), 0, s, ka, va, n, dg, sc.hist, ntiles,
                                nullptr, nullptr);
             hipLaunchKernelGGL(k_scan<>, dim3(kRadix), dim3(kThreads), 0, s, sc.hist, ntiles,
-                               sc.hist + (int64_t)ntiles * kRadix, redo);
+                               sc.hist + (int64_t)ntiles * kRadix, nullptr);
             hipLaunchKernelGGL((k_scatter<false, kItems>), dim3(ntiles), dim3(kThreads), 0, s, ka, va, kb, vb, n, dg,
                                sc.hist, ntiles, dg, nullptr, nullptr, nullptr);
             swap();
         }
     }
     if (p.low) {
-        const int64_t *off = mesh_off && M > 1 ? mesh_off : nullptr;
         auto finish = [&](auto kern, int tile) {
             hipLaunchKernelGGL(kern, dim3((unsigned)((n + tile - 1) / tile)), dim3(kThreads), 0, s, ka, va, kb, vb,
-                               n, p.low, off, M, redo);
+                               n, p.low, off, M, word);
         };
         // small sorts: more workgroups
         if (p.low > 52) finish(k_finish<256, 512, false>, 256);
         else if (n <= 131072) finish(k_finish<256, 512, true>, 256);
         else finish(k_finish<2048, 512, true>, 2048);
-        if (redo) redo_passes(ka, va, kb, vb, n, key_bits, off, M, sc.hist, ntiles, redo, s);
         swap();
     }
     if (kres && vres) {  // the caller takes the result where it is
