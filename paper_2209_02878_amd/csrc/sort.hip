@@ -621,8 +621,8 @@ __global__ __launch_bounds__(kThreads)
 // Whether a table has large groups of equal prefixes: every 64th key (jittered
 // within its 64) is counted by a hash of its prefix, and *word set when an
 // entry of the counts (a power of two of them, 2^bits) reaches kSampleHits: a
-// group of 16,384 keys is met 256 times.  There are four entries to a sample (at
-// least one past 2^28 keys), so chance meetings stay far below.
+// group of 16,384 keys is met 256 times.  There are two to four entries to a sample (one
+// at 2^30 keys), so chance meetings stay far below.
 constexpr int kSampleStep = 64;
 constexpr uint32_t kSampleHits = 128;
 
